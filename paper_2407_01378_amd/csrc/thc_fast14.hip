@@ -214,7 +214,10 @@ bool fast14_applicable(Mode mode, const ChunkArgs& a) {
     if (a.out_bf16 || mode == Mode::Plain || mode == Mode::PlainDecode) return false;
     // without the rotation: the range and the encoder on a given range have a tuned form
     if (a.no_rotate && !(mode == Mode::MinMax || (mode == Mode::Encode && a.range_in))) return false;
-    return k14::aligned16(a.in) && k14::aligned16(a.out);
+    // a range is one or two scalar stores per chunk: its place needs no more than the ABI's alignment
+    // (a worker's row of a W x chunks array starts anywhere)
+    const bool scalar_out = mode == Mode::Absmax || mode == Mode::MinMax;
+    return k14::aligned16(a.in) && (scalar_out || k14::aligned16(a.out));
 }
 
 hipError_t launch_fast14(Mode mode, const ChunkArgs& a, hipStream_t stream) {
