@@ -295,6 +295,10 @@ static int encode_all_impl(const void* const* grads, thc_dtype dt, uint32_t W, u
                 return THC_ERR_HIP;
             return finish(thc::launch_encode_all_fused(a, ptrs, dt == THC_BF16, bits, st));
         }
+        // smaller chunks: one launch too, without a workspace (a clear one stays clear)
+        if (thc::small_encode_all_applicable(a, ptrs, chunk_log2))
+            return finish(thc::launch_small_encode_all(a, ptrs, chunk_log2, base_args(n, chunk_log2, seed).inv_sqrt_c,
+                                                       dt == THC_BF16, bits, !cleared, st));
     }
     // Fallback: the unfused sequence, per-worker ranges kept in the workspace.
     if (!cleared && thc::launch_zero_words(words, 4, st) != hipSuccess) return THC_ERR_HIP;
@@ -564,6 +568,22 @@ int thc_aggregate_decode(const uint8_t* const* payloads, uint32_t W, const float
         return finish(thc::launch_aggregate_decode_fused(a, ptrs, bits, static_cast<hipStream_t>(stream)));
     }
     if (!sums) return THC_ERR_NULL;
+    if (thc::small_aggregate_decode_applicable(W, chunk_log2, bits, padded_coords(n, chunk_log2))) {
+        thc::FusedPayloadPtrs ptrs{};
+        for (uint32_t w = 0; w < W; ++w) ptrs.p[w] = payloads[w];
+        const ChunkArgs c = base_args(n, chunk_log2, seed);
+        thc::AggDecodeArgs a{};
+        a.n = n;
+        a.chunks = c.padded >> chunk_log2;
+        a.W = W;
+        a.key0 = c.key0;
+        a.key1 = c.key1;
+        a.scale = scale;
+        a.sums = sums;
+        a.out = out;
+        return finish(thc::launch_small_aggregate_decode(a, ptrs, chunk_log2, c.inv_sqrt_c, bits,
+                                                         static_cast<hipStream_t>(stream)));
+    }
     rc = thc_aggregate(payloads, W, n, chunk_log2, bits, sums, stream);
     if (rc != THC_OK) return rc;
     return thc_decode(sums, scale, W, n, chunk_log2, seed, bits, out, stream);

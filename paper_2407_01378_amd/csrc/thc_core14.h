@@ -149,11 +149,10 @@ __device__ __forceinline__ void raw_to_lds(Shared& sh, const Raw<UNITS>& raw, ui
 
 // The thread's 32 consecutive coordinates as UNITS 16-byte units -> fp32 registers
 // (layout L1): widens bf16 and applies the sign diagonal when SIGNED.
+// sx: the thread's sign bits, bf16: even bits in the low half, odd bits in the high half.
 template <int UNITS, bool SIGNED>
-__device__ __forceinline__ void units_to_l1(const SignTable& tab, const uint4 (&unit)[UNITS],
-                                            float (&v)[kRegs], uint32_t t) {
+__device__ __forceinline__ void units_to_l1(uint32_t sx, const uint4 (&unit)[UNITS], float (&v)[kRegs]) {
     if (UNITS == 4) {  // bf16: 8 coordinates per unit, two per dword
-        const uint32_t sx = SIGNED ? tab.sgx[t] : 0u;
 #pragma unroll
         for (int k = 0; k < UNITS; ++k) {
             const uint32_t w[4] = {unit[k].x, unit[k].y, unit[k].z, unit[k].w};
@@ -168,7 +167,6 @@ __device__ __forceinline__ void units_to_l1(const SignTable& tab, const uint4 (&
             }
         }
     } else {  // fp32: 4 coordinates per unit
-        const uint32_t sw = SIGNED ? tab.sgn[t] : 0u;
 #pragma unroll
         for (int k = 0; k < UNITS; ++k) {
             const uint32_t w[4] = {unit[k].x, unit[k].y, unit[k].z, unit[k].w};
@@ -176,11 +174,16 @@ __device__ __forceinline__ void units_to_l1(const SignTable& tab, const uint4 (&
             for (int d = 0; d < 4; ++d) {
                 const int r = 4 * k + d;
                 uint32_t x = w[d];
-                if (SIGNED) x = xor_masked(x, r == 31 ? sw : (sw << (31 - r)), 0x80000000u);
+                if (SIGNED) x = xor_masked(x, r == 31 ? sx : (sx << (31 - r)), 0x80000000u);
                 v[r] = __uint_as_float(x);
             }
         }
     }
+}
+template <int UNITS, bool SIGNED>
+__device__ __forceinline__ void units_to_l1(const SignTable& tab, const uint4 (&unit)[UNITS],
+                                            float (&v)[kRegs], uint32_t t) {
+    units_to_l1<UNITS, SIGNED>(SIGNED ? (UNITS == 4 ? tab.sgx[t] : tab.sgn[t]) : 0u, unit, v);
 }
 
 // Reads this thread's 32 consecutive coordinates back from the buffer (after raw_to_lds
@@ -434,38 +437,43 @@ __device__ __forceinline__ void cvt_into_byte(uint32_t& acc, float tt) {
     }
 }
 
-template <int BITS, bool CLAMP, bool FOLD, bool RANGED>
-__device__ __forceinline__ void quantize_pack(const float (&v)[kRegs], float sub, float mul, float base,
-                                              uint32_t L, uint64_t g, uint32_t worker, uint32_t key0,
-                                              uint32_t key1, uint32_t (&pk)[BITS]) {
+// One half of it: the 16 coordinates in registers 16 half .. 16 half + 15, which are those of
+// block `blk` of the rounding stream, into index bytes by[4 half .. 4 half + 3].
+//   norm     factor from v to y where it is not folded
+//   NEG      the lane holds the negated value where sgn = -1 (a lane exchange leaves it so): mul
+//            (FOLD) or norm carries the sign already, and sgn itself is used only where v meets sub
+template <int BITS, bool CLAMP, bool FOLD, bool RANGED, bool NEG = false>
+__device__ __forceinline__ void quantize_half(const float (&v)[kRegs], int half, uint64_t blk, float sub, float mul,
+                                              float base, uint32_t L, uint32_t worker, uint32_t key0, uint32_t key1,
+                                              uint32_t (&by)[8], float norm = kInvSqrtC, float sgn = 1.0f) {
     constexpr int kSub = 8 / BITS;        // coordinates per payload byte: 1, 2, 4
-    uint32_t by[8];                       // index bytes; by[m] serves payload word m / kSub
     const float Lf = (float)L;
+    const u32x4 rb = round_block(blk, worker, key0, key1);
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const u32x4 rb = round_block((g >> 4) + half, worker, key0, key1);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int r = 16 * half + e;
-            float y = FOLD ? v[r] : v[r] * kInvSqrtC;
-            if (RANGED) y = y - sub;
-            const uint32_t rnd = (rb.w[e >> 2] >> (8 * (e & 3))) & 0xFFu;
-            const float c = __builtin_fmaf((float)rnd, 0x1p-8f, base);
-            float tt = __builtin_fmaf(y, mul, c);            // tt >= 0: truncation = floor
-            if (CLAMP) tt = fminf(tt, Lf);                   // floor(min(t, L)) = min(floor(t), L)
-            // coordinate r sits in payload word d = r / (32 / BITS), at slot j = r % (32 / BITS);
-            // its index goes to byte j / kSub of register kSub * d + j % kSub
-            constexpr int kPerWord = 32 / BITS;
-            const int d = r / kPerWord, j = r % kPerWord;
-            const int m = kSub * d + j % kSub, byte = j / kSub;
-            switch (byte) {
-                case 0: cvt_into_byte<0, true>(by[m], tt); break;
-                case 1: cvt_into_byte<1, false>(by[m], tt); break;
-                case 2: cvt_into_byte<2, false>(by[m], tt); break;
-                default: cvt_into_byte<3, false>(by[m], tt); break;
-            }
+    for (int e = 0; e < 16; ++e) {
+        const int r = 16 * half + e;
+        float y = FOLD ? v[r] : v[r] * norm;
+        if (RANGED) y = FOLD && NEG ? __builtin_fmaf(v[r], sgn, -sub) : y - sub;   // (one rounding either way)
+        const uint32_t rnd = (rb.w[e >> 2] >> (8 * (e & 3))) & 0xFFu;
+        const float c = __builtin_fmaf((float)rnd, 0x1p-8f, base);
+        float tt = __builtin_fmaf(y, mul, c);            // tt >= 0: truncation = floor
+        if (CLAMP) tt = fminf(tt, Lf);                   // floor(min(t, L)) = min(floor(t), L)
+        // coordinate r sits in payload word d = r / (32 / BITS), at slot j = r % (32 / BITS);
+        // its index goes to byte j / kSub of register kSub * d + j % kSub
+        constexpr int kPerWord = 32 / BITS;
+        const int d = r / kPerWord, j = r % kPerWord;
+        const int m = kSub * d + j % kSub, byte = j / kSub;
+        switch (byte) {
+            case 0: cvt_into_byte<0, true>(by[m], tt); break;
+            case 1: cvt_into_byte<1, false>(by[m], tt); break;
+            case 2: cvt_into_byte<2, false>(by[m], tt); break;
+            default: cvt_into_byte<3, false>(by[m], tt); break;
         }
     }
+}
+// Index bytes -> payload words.
+template <int BITS>
+__device__ __forceinline__ void pack_bytes(const uint32_t (&by)[8], uint32_t (&pk)[BITS]) {
 #pragma unroll
     for (int d = 0; d < BITS; ++d) {
         if constexpr (BITS == 8) pk[d] = by[d];
@@ -473,6 +481,16 @@ __device__ __forceinline__ void quantize_pack(const float (&v)[kRegs], float sub
         if constexpr (BITS == 2)
             pk[d] = by[4 * d] | (by[4 * d + 1] << 2) | (by[4 * d + 2] << 4) | (by[4 * d + 3] << 6);
     }
+}
+template <int BITS, bool CLAMP, bool FOLD, bool RANGED>
+__device__ __forceinline__ void quantize_pack(const float (&v)[kRegs], float sub, float mul, float base,
+                                              uint32_t L, uint64_t g, uint32_t worker, uint32_t key0,
+                                              uint32_t key1, uint32_t (&pk)[BITS]) {
+    uint32_t by[8];                       // index bytes; by[m] serves payload word m / kSub
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+        quantize_half<BITS, CLAMP, FOLD, RANGED>(v, half, (g >> 4) + half, sub, mul, base, L, worker, key0, key1, by);
+    pack_bytes<BITS>(by, pk);
 }
 
 template <int BITS>

@@ -49,10 +49,15 @@ hipError_t launch_generic(Mode mode, const ChunkArgs& a, hipStream_t stream);
 bool fast14_applicable(Mode mode, const ChunkArgs& a);
 hipError_t launch_fast14(Mode mode, const ChunkArgs& a, hipStream_t stream);
 
+// Tuned path for chunk_log2 = 5 .. 13 (range, symmetric encode, decode of stored sums).
+bool small_applicable(Mode mode, const ChunkArgs& a);
+hipError_t launch_small(Mode mode, const ChunkArgs& a, hipStream_t stream);
+
 // Picks the tuned kernels when they apply, the generic ones otherwise.
 inline hipError_t launch_chunks(Mode mode, const ChunkArgs& a, hipStream_t stream) {
-    return fast14_applicable(mode, a) ? launch_fast14(mode, a, stream)
-                                      : launch_generic(mode, a, stream);
+    if (fast14_applicable(mode, a)) return launch_fast14(mode, a, stream);
+    if (small_applicable(mode, a)) return launch_small(mode, a, stream);
+    return launch_generic(mode, a, stream);
 }
 
 // ---- fused paths (chunk_log2 == 14) ------------------------------------------------
@@ -124,6 +129,14 @@ struct AggDecodeArgs {
 bool aggregate_decode_fused_applicable(uint32_t W, uint32_t chunk_log2, uint32_t bits);
 hipError_t launch_aggregate_decode_fused(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs,
                                          uint32_t bits, hipStream_t stream);
+// The same two steps for chunk_log2 = 5 .. 13 (thc_small.hip).  clear_error: the kernel also
+// zeroes the workspace's first four words.
+bool small_encode_all_applicable(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2);
+hipError_t launch_small_encode_all(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2, float norm,
+                                   bool bf16, uint32_t bits, bool clear_error, hipStream_t stream);
+bool small_aggregate_decode_applicable(uint32_t W, uint32_t chunk_log2, uint32_t bits, uint64_t padded);
+hipError_t launch_small_aggregate_decode(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs, uint32_t chunk_log2,
+                                         float norm, uint32_t bits, hipStream_t stream);
 // min/max grid: a.scale holds (lo, hi) pairs
 hipError_t launch_aggregate_decode_ranged(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs,
                                           uint32_t bits, hipStream_t stream);

@@ -1,0 +1,707 @@
+// Tuned kernels for chunks of 2^5 .. 2^13 coordinates, same results as the generic ones.
+//
+// Encode.  A chunk this small needs no agreement between workgroups: one workgroup holds the
+// same coordinates of ALL workers at once, a wave 2^11 coordinates of one worker (32 per
+// thread, in registers), so the shared range of a chunk is a maximum over a few words in LDS
+// behind one barrier.  Every gradient is read once.  The rotation stays inside the wave up to
+// chunks of 2^11: 5 stages between registers, 4 between lanes by data-parallel primitives and
+// 2 after a swap of a lane bit into the registers (thc_lanes.h).  Chunks of 2^12 and 2^13 span
+// two and four waves, which trade half of their registers through LDS before each further
+// stage.  Bound by vector-ALU issue (about 24 operations per worker-coordinate) for large
+// inputs, by the latency of the two launches for small ones.
+//   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 72 us
+//   (3.4 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 22 us.  Before: one range and one encode
+//   launch per worker of the generic kernels, which load element by element and take a
+//   barrier per stage above 2^4.
+//
+// Decode.  A workgroup of four waves owns 2^13 coordinates; a thread sums the workers' payload
+// words of its 32 coordinates, five stages run in registers, the wave re-shuffles through its
+// own 8 KB of LDS, the rest of the stages follow, and the result leaves in 128-byte lines.
+// Bound by memory.
+#include "thc_core14.h"
+#include "thc_internal.h"
+#include "thc_lanes.h"
+#include "thc_payload.h"
+
+#pragma clang fp contract(off)
+
+namespace thc {
+namespace k14 {
+namespace {
+
+constexpr uint32_t kWaveLog2 = 11;               // coordinates of a wave
+constexpr uint32_t kWaveCoords = 1u << kWaveLog2;
+constexpr uint32_t kMaxWaves = 16;
+constexpr uint32_t kPreferredWaves = 8;          // two workgroups of 8 waves fill a CU at 128 registers
+
+// What a launch does: encode all workers onto their common range; only the range of one
+// worker; encode one worker onto a range handed in.
+enum class SmallOp : int { EncodeAll = 0, Absmax = 1, EncodeOnto = 2 };
+
+struct SmallArgs {
+    uint64_t n, padded;
+    uint64_t items;           // workgroup-sized pieces of the gradient: `regions` units each
+    uint32_t l;               // chunk_log2
+    uint32_t W;
+    uint32_t worker0;         // number of the first worker in the random stream
+    uint32_t key0, key1;
+    uint32_t levels;
+    float norm;               // c^(-1/2)
+    float* scale_out;         // may be null
+    const float* scale_in;    // EncodeOnto
+    uint32_t* error;          // may be null: four words that a good run leaves zero
+    // shape of a workgroup: wave = (region * groups + group) * 2^wpw_log2 + part; a unit is the
+    // 2^max(11, l) coordinates of one worker that its 2^wpw_log2 waves hold, a group takes workers
+    // group, group + groups, ... (rounds of them)
+    uint32_t wpw_log2, groups, regions, rounds;
+};
+
+// Coordinate ranges by chunk size: CLASS 0: l <= 9, 1: l = 10, 11, 2: l = 12, 13.
+constexpr int class_of(uint32_t l) { return l <= 9 ? 0 : l <= 11 ? 1 : 2; }
+
+// The upper half of one wave's registers against the lower half of the other's (whose number
+// differs in bit PART of the wave's part): register bit 4 <-> that bit.  `upper`: this wave has
+// the bit set.  Ends with a barrier: the buffer may be rewritten.
+__device__ __forceinline__ void trade_halves(float (&v)[kRegs], float4* mine, const float4* theirs, bool upper,
+                                             uint32_t lane) {
+    // (the empty assembly statements differ, so the two branches are not merged into one that picks
+    // its registers by address, which would put v into memory)
+    if (upper) {
+        asm volatile("; upper wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mine[q * 64 + lane] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        asm volatile("; upper wave sent" ::: "memory");
+    } else {
+        asm volatile("; lower wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            mine[q * 64 + lane] = make_float4(v[16 + 4 * q], v[17 + 4 * q], v[18 + 4 * q], v[19 + 4 * q]);
+        asm volatile("; lower wave sent" ::: "memory");
+    }
+    __syncthreads();
+    if (upper) {
+        asm volatile("; upper wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = theirs[q * 64 + lane];
+            v[4 * q] = f.x;
+            v[4 * q + 1] = f.y;
+            v[4 * q + 2] = f.z;
+            v[4 * q + 3] = f.w;
+        }
+        asm volatile("; upper wave has" ::: "memory");
+    } else {
+        asm volatile("; lower wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = theirs[q * 64 + lane];
+            v[16 + 4 * q] = f.x;
+            v[17 + 4 * q] = f.y;
+            v[18 + 4 * q] = f.z;
+            v[19 + 4 * q] = f.w;
+        }
+        asm volatile("; lower wave has" ::: "memory");
+    }
+    __syncthreads();
+}
+
+template <bool BF16, int CLASS, int BITS, SmallOp OP>
+__global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const SmallArgs a, const FusedWorkerPtrs ptrs) {
+    constexpr int kUnits = BF16 ? 4 : 8;
+    constexpr int kElem = BF16 ? 2 : 4;
+    extern __shared__ uint4 dyn[];
+    const uint32_t t = threadIdx.x, lane = t & 63u;
+    // (the wave's number is the same for all lanes: kept in a scalar register, so are the
+    // addresses that follow from it)
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    const uint32_t waves = blockDim.x >> 6;
+    const uint32_t wpw = CLASS == 2 ? 1u << a.wpw_log2 : 1u;
+    const uint32_t part = wave & (wpw - 1u);
+    const uint32_t rg = CLASS == 2 ? wave >> a.wpw_log2 : wave;
+    const uint32_t region = rg / a.groups;
+    const uint32_t group = rg - region * a.groups;
+    const uint32_t block = lanes::block_of_lane(lane);
+    const uint32_t unit_log2 = CLASS == 2 ? a.l : kWaveLog2;
+
+    // LDS: staging of fp32 input / the traded registers, two sign tables, two range tables
+    constexpr uint32_t kStage = !BF16 ? 512u : (CLASS == 2 ? 256u : 0u);   // 16-byte units per wave
+    const uint32_t sign_words = a.regions * (1u << (unit_log2 - 5u));
+    uint4* stage = dyn + kStage * wave;
+    uint32_t* sign = reinterpret_cast<uint32_t*>(dyn + kStage * waves);
+    // chunks of a unit (one row of range words each), entries of a row: groups x waves of a chunk
+    const uint32_t rows_log2 = a.l < kWaveLog2 ? kWaveLog2 - a.l : 0u;
+    const uint32_t row = (a.groups * wpw + 3u) & ~3u;
+    float* red = reinterpret_cast<float*>(sign + 2u * sign_words);
+    const uint32_t red_words = (a.regions << rows_log2) * row;
+    if (OP == SmallOp::EncodeAll) {
+        for (uint32_t i = t; i < 2u * red_words; i += blockDim.x) red[i] = 0.0f;   // (the unused end of a row stays zero)
+    }
+    // this lane's chunk inside its unit
+    const uint32_t chunk = CLASS == 0 ? block >> (a.l - 5u) : (CLASS == 1 && a.l == 10u ? lane >> 5 : 0u);
+    float* red_row = red + ((region << rows_log2) + chunk) * row;
+
+    // where the two runs of 16 coordinates lie that the lane holds after the rotation
+    uint32_t run0, run1;
+    if (CLASS == 0) {
+        run0 = block << 5;
+        run1 = run0 + 16u;
+    } else {   // i4 = lane bit 4, i5..i8 as before, i9 and above as the swaps left them
+        const uint32_t mid = ((lane & 16u)) | ((block & 15u) << 5);
+        if (CLASS == 1 && a.l == 10u) {          // register bit 4 = i9, lane bit 5 = i10
+            run0 = mid | ((lane >> 5) << 10);
+            run1 = run0 + 512u;
+        } else if (CLASS == 1) {                 // register bit 4 = i10, lane bit 5 = i9
+            run0 = mid | ((lane >> 5) << 9);
+            run1 = run0 + 1024u;
+        } else {                                 // register bit 4 = i(l - 1), part = i10 (and i11)
+            run0 = mid | ((lane >> 5) << 9) | (part << 10);
+            run1 = run0 + (1u << (a.l - 1u));
+        }
+    }
+    const float sg0 = (block & 1u) ? -1.0f : 1.0f, sg1 = (block & 2u) ? -1.0f : 1.0f,
+                sg2 = (block & 4u) ? -1.0f : 1.0f, sg3 = (block & 8u) ? -1.0f : 1.0f;
+    const uint32_t lane_stages = CLASS == 0 ? a.l - 5u : 4u;   // how many of i5..i8 are rotated
+    const float neg = (__popc(block & ((1u << lane_stages) - 1u)) & 1) ? -1.0f : 1.0f;
+
+    // A step is one worker's unit: a round of an item.  Rounds 0 .. rounds-1 find the range; the
+    // last one is quantized where it stands, the earlier ones are rotated once more.
+    const uint32_t rounds = OP == SmallOp::EncodeAll ? a.rounds : 1u;
+    const uint32_t steps = 2u * rounds - 1u;
+    auto worker_of = [&](uint32_t step) { return group + a.groups * (step < rounds ? step : steps - 1u - step); };
+    auto coord0_of = [&](uint64_t item) { return (item * a.regions + region) << unit_log2; };
+
+    Raw<kUnits> raw;
+    uint32_t odd_tail = 0u;   // BF16: the last coordinate of an odd count, in the lane that owns it
+    auto load = [&](uint64_t item, uint32_t step) {
+        const uint32_t w = worker_of(step);
+        const uint64_t g0 = coord0_of(item) + part * kWaveCoords;
+        uint64_t left = (item < a.items && w < a.W && g0 < a.n) ? a.n - g0 : 0u;
+        if (left > (uint64_t)kWaveCoords) left = kWaveCoords;
+        uint64_t addr = reinterpret_cast<uint64_t>(ptrs.grad[w < a.W ? w : 0u]) + (left != 0u ? g0 * kElem : 0u);
+        addr = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)addr);
+        // reads past the range return zero; its check works on dwords, so the last coordinate
+        // of an odd count of bf16 is fetched by itself
+        const uint32_t bytes = BF16 ? ((uint32_t)left & ~1u) * 2u : (uint32_t)left * 4u;
+        __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(addr), 0, bytes, 0x00020000);
+        typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int j = 0; j < kUnits; ++j) {
+            // bf16: the lane's own 64 bytes; fp32: coalesced, dealt out through the wave's LDS
+            const uint32_t unit = BF16 ? 4u * block + j : (uint32_t)j * 64u + lane;
+            const u4v q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, unit * 16u, 0, 0);
+            raw.u[j] = make_uint4(q.x, q.y, q.z, q.w);
+        }
+        if (BF16 && (left & 1u)) {
+            odd_tail = 0u;
+            if (block == (uint32_t)left >> 5)
+                odd_tail = reinterpret_cast<const uint16_t*>(addr)[left - 1u];
+        }
+    };
+    // the coordinates of the step that exist (for the odd tail), as load() saw them
+    auto left_of = [&](uint64_t item, uint32_t step) -> uint32_t {
+        const uint64_t g0 = coord0_of(item) + part * kWaveCoords;
+        const uint64_t left = (item < a.items && worker_of(step) < a.W && g0 < a.n) ? a.n - g0 : 0u;
+        return left > (uint64_t)kWaveCoords ? kWaveCoords : (uint32_t)left;
+    };
+    auto fill_signs = [&](uint64_t item, uint32_t which) {
+        if (t < sign_words / 4u) {
+            const u32x4 s = sign_block(((item * a.regions) << (unit_log2 - 7u)) + t, a.key0, a.key1);
+            uint4 o = make_uint4(s.w[0], s.w[1], s.w[2], s.w[3]);
+            if (BF16) o = make_uint4(unshuffle_bits(s.w[0]), unshuffle_bits(s.w[1]), unshuffle_bits(s.w[2]), unshuffle_bits(s.w[3]));
+            reinterpret_cast<uint4*>(sign + which * sign_words)[t] = o;
+        }
+    };
+
+    uint64_t item = blockIdx.x;
+    load(item, 0u);
+    fill_signs(item, 0u);
+    __syncthreads();
+    uint32_t cur = 0u, step = 0u;
+    uint32_t most = 0u;   // largest magnitude of the lane's chunk over the rounds so far, as a word
+    float s = 0.0f;
+    while (item < a.items) {
+        const uint32_t w = worker_of(step);
+        const uint64_t u0 = coord0_of(item);
+        const uint32_t sx = sign[cur * sign_words + (region << (unit_log2 - 5u)) + part * 64u + block];
+        float v[kRegs];
+        if constexpr (BF16) {
+            if (a.n & 1u) {   // (uniform)
+                const uint32_t left = left_of(item, step);
+                if ((left & 1u) && block == left >> 5) {
+                    const uint32_t d = (left & 31u) >> 1;   // dword of the lane's 16 that holds it
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        raw.u[k].x = d == 4u * k ? odd_tail : raw.u[k].x;
+                        raw.u[k].y = d == 4u * k + 1u ? odd_tail : raw.u[k].y;
+                        raw.u[k].z = d == 4u * k + 2u ? odd_tail : raw.u[k].z;
+                        raw.u[k].w = d == 4u * k + 3u ? odd_tail : raw.u[k].w;
+                    }
+                }
+            }
+            units_to_l1<kUnits, true>(sx, raw.u, v);
+        } else {
+            // unit u of the wave at u ^ swz(u), swz = (u >> 4) & 7: 128-bit stores and loads both
+            // reach all columns (the readers that are served together differ in all of block's low bits)
+#pragma unroll
+            for (int j = 0; j < kUnits; ++j) {
+                const uint32_t u = (uint32_t)j * 64u + lane;
+                stage[u ^ ((u >> 4) & 7u)] = raw.u[j];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            uint4 unit[kUnits];
+#pragma unroll
+            for (int k = 0; k < kUnits; ++k) unit[k] = stage[8u * block + ((uint32_t)k ^ ((block >> 1) & 7u))];
+            units_to_l1<kUnits, true>(sx, unit, v);
+        }
+#pragma unroll
+        for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));   // converted before `raw` is loaded again
+        asm volatile("" ::: "memory");
+        const bool item_ends = step + 1u == steps;
+        load(item_ends ? item + gridDim.x : item, item_ends ? 0u : step + 1u);
+        if (step == 0u && item + gridDim.x < a.items) fill_signs(item + gridDim.x, cur ^ 1u);
+
+        butterflies<0, 5>(v);
+        if (CLASS != 0 || a.l > 5u) lanes::lane_stage<0>(v, sg0);
+        if (CLASS != 0 || a.l > 6u) lanes::lane_stage<1>(v, sg1);
+        if (CLASS != 0 || a.l > 7u) lanes::lane_stage<2>(v, sg2);
+        if (CLASS != 0 || a.l > 8u) lanes::lane_stage<3>(v, sg3);
+        if constexpr (CLASS != 0) {
+            lanes::swap_top_register_bit<16>(v);
+            butterflies<4, 5>(v);
+            if (CLASS == 2 || a.l > 10u) {
+                lanes::swap_top_register_bit<32>(v);
+                butterflies<4, 5>(v);
+            }
+        }
+        if constexpr (CLASS == 2) {
+            float4* buf = reinterpret_cast<float4*>(dyn);
+            trade_halves(v, buf + kStage * wave, buf + kStage * (wave ^ 1u), (part & 1u) != 0u, lane);
+            butterflies<4, 5>(v);
+            if (a.l > 12u) {
+                trade_halves(v, buf + kStage * wave, buf + kStage * (wave ^ 2u), (part & 2u) != 0u, lane);
+                butterflies<4, 5>(v);
+            }
+        }
+
+        if (OP != SmallOp::EncodeOnto && step < rounds) {
+            // the chunk's largest magnitude: registers, then the lanes that share the chunk
+            float m = 0.0f;
+#pragma unroll
+            for (int i = 0; i < kRegs; i += 2)
+                asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(v[i]), "v"(v[i + 1]));
+            uint32_t x = __float_as_uint(m * a.norm);   // non-negative floats order like their bit patterns
+            if (CLASS != 0 || a.l > 5u) x = lanes::umax_step<1>(x);
+            if (CLASS != 0 || a.l > 6u) x = lanes::umax_step<2>(x);
+            if (CLASS != 0 || a.l > 7u) x = lanes::umax_step<7>(x);
+            if (CLASS != 0 || a.l > 8u) x = lanes::umax_step<15>(x);
+            if constexpr (CLASS != 0) {
+                x = lanes::umax_step<16>(x);
+                if (CLASS == 2 || a.l > 10u) x = lanes::umax_step<32>(x);
+            }
+            most = step == 0u ? x : (x > most ? x : most);
+        }
+        const bool leader = CLASS == 0 ? (block & ((1u << (a.l - 5u)) - 1u)) == 0u
+                                       : (CLASS == 1 && a.l == 10u ? (lane & 31u) == 0u : lane == 0u);
+        const uint64_t p = (u0 >> a.l) + chunk;
+        const bool exists = (p << a.l) < a.padded;
+        if (OP == SmallOp::EncodeAll) {
+            if (step + 1u == rounds) {
+                // all workers' waves have published behind the barrier (which also orders the sign
+                // table of the next item); the two range tables take turns
+                float* at = red_row + cur * red_words;
+                if (leader) at[group * wpw + part] = __uint_as_float(most);
+                __syncthreads();
+                s = 0.0f;
+                for (uint32_t i = 0; i < row; i += 4u) {
+                    const float4 f = *reinterpret_cast<const float4*>(at + i);
+                    s = fmaxf(fmaxf(s, fmaxf(f.x, f.y)), fmaxf(f.z, f.w));
+                }
+                if (leader && group == 0u && part == 0u && exists && a.scale_out) a.scale_out[p] = s;
+            }
+        } else if (OP == SmallOp::Absmax) {
+            if (CLASS == 2) {
+                float* at = red_row + cur * red_words;
+                if (leader) at[part] = __uint_as_float(most);
+                __syncthreads();
+                s = 0.0f;
+                for (uint32_t i = 0; i < wpw; ++i) s = fmaxf(s, at[i]);
+                if (leader && part == 0u && exists) a.scale_out[p] = s;
+            } else {
+                if (leader && exists) a.scale_out[p] = __uint_as_float(most);
+                __syncthreads();   // the next item's sign table
+            }
+        } else {
+            s = exists ? a.scale_in[p] : 0.0f;
+            if (leader && part == 0u && exists && a.scale_out) a.scale_out[p] = s;
+            __syncthreads();       // the next item's sign table
+        }
+
+        if (OP != SmallOp::Absmax && step + 1u >= rounds && w < a.W) {
+            constexpr bool kClamp = OP == SmallOp::EncodeOnto;
+            constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;
+            const float two = s + s;
+            const bool ranged = two >= kMinRange;
+            const float inv = ranged ? (float)a.levels / two : 0.0f;
+            const float base = ((ranged ? !kOffset : (a.levels & 1u) == 0u) ? 0.5f * (float)a.levels : 0.0f) + 0x1p-9f;
+            const uint64_t b0 = (u0 + run0) >> 4, b1 = (u0 + run1) >> 4;
+            const uint32_t worker = a.worker0 + w;
+            uint32_t by[8], pk[BITS];
+            // even l: c^(-1/2) is a power of two and moves into the multiplier (see quantize_pack);
+            // the condition must hold for every lane, chunks of one wave differ in s
+            const bool fold = (a.l & 1u) == 0u && __all(!ranged || (s >= 0x1p-100f && s <= 0x1p100f));
+            if (fold) {
+                const float sub = -s * (1.0f / a.norm);
+                const float mul = inv * a.norm * (kOffset ? 1.0f : neg);
+                quantize_half<BITS, kClamp, true, kOffset, true>(v, 0, b0, sub, mul, base, a.levels, worker, a.key0, a.key1, by, 1.0f, neg);
+                quantize_half<BITS, kClamp, true, kOffset, true>(v, 1, b1, sub, mul, base, a.levels, worker, a.key0, a.key1, by, 1.0f, neg);
+            } else {
+                const float norm = a.norm * neg;
+                quantize_half<BITS, kClamp, false, kOffset, true>(v, 0, b0, -s, inv, base, a.levels, worker, a.key0, a.key1, by, norm, neg);
+                quantize_half<BITS, kClamp, false, kOffset, true>(v, 1, b1, -s, inv, base, a.levels, worker, a.key0, a.key1, by, norm, neg);
+            }
+            pack_bytes<BITS>(by, pk);
+            uint8_t* dst = ptrs.payload[w];
+            if constexpr (CLASS == 0) {   // 32 consecutive coordinates
+                if (exists) store_packed<BITS>(pk, dst + b0 * (2u * BITS));
+            } else if (exists) {
+                uint8_t* d0 = dst + b0 * (2u * BITS);
+                uint8_t* d1 = dst + b1 * (2u * BITS);
+                if constexpr (BITS == 8) {
+                    *reinterpret_cast<uint4*>(d0) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+                    *reinterpret_cast<uint4*>(d1) = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+                } else if constexpr (BITS == 4) {
+                    *reinterpret_cast<uint2*>(d0) = make_uint2(pk[0], pk[1]);
+                    *reinterpret_cast<uint2*>(d1) = make_uint2(pk[2], pk[3]);
+                } else {
+                    *reinterpret_cast<uint32_t*>(d0) = pk[0];
+                    *reinterpret_cast<uint32_t*>(d1) = pk[1];
+                }
+            }
+        }
+        if (item_ends) {
+            if (rounds > 1u) __syncthreads();   // the rounds behind the range's barrier read the sign table too
+            item += gridDim.x;
+            step = 0u;
+            cur ^= 1u;
+        } else {
+            ++step;
+        }
+    }
+    if (a.error && blockIdx.x == 0 && t < 4u) a.error[t] = 0u;
+}
+
+// ------------------------------------------------------------------------------ decode
+constexpr int kDecodeThreads = 256;
+constexpr uint32_t kDecodeLog2 = 13;   // coordinates of a workgroup
+
+struct SmallDecodeArgs {
+    uint64_t n, padded;
+    uint32_t l, W;
+    uint32_t key0, key1;
+    float norm;
+    const float* scale;
+    const void* in;     // stored sums (SRC u8 / u16)
+    void* sums;         // SRC payloads: where the integer sums go; may be null
+    float* out;
+};
+
+// SRC: 0 the workers' payloads, 1 stored u8 sums, 2 stored u16 sums.  WIDE: see PayloadSum.
+template <int SRC, int BITS, bool WIDE>
+__global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const SmallDecodeArgs a,
+                                                                      const FusedPayloadPtrs ptrs) {
+    __shared__ float4 xb4[4 * 512];
+    __shared__ alignas(16) uint32_t sign[1u << (kDecodeLog2 - 5u)];
+    const uint32_t t = threadIdx.x, lane = t & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    const uint64_t base = (uint64_t)blockIdx.x << kDecodeLog2;
+    const uint64_t g = base + 32u * t;
+    const bool exists = g < a.padded;   // (chunks are whole multiples of a thread's 32 coordinates)
+    const uint32_t l = a.l;
+    uint32_t S[kRegs];
+    float s = 0.0f;
+    if (exists) s = a.scale[g >> l];
+    if constexpr (SRC == 0) {
+        // up to 32 registers of payload in flight (nothing else is live yet)
+        PayloadSum<BITS, false, WIDE, BITS == 8 ? 4 : 8> sum{ptrs, nullptr, a.W};
+        sum.clear();
+        if (exists) {
+            const uint64_t byte0 = (g * BITS) / 8u;
+            for (uint32_t k = 0; k < sum.groups(); ++k) {
+                sum.issue(byte0, k);
+                sum.add(k);
+            }
+        }
+        if (wave == 0) *reinterpret_cast<u32x4*>(&sign[4 * lane]) = sign_block((base >> 7) + lane, a.key0, a.key1);
+        sum.unpack(S);
+        if (a.sums && exists) {
+            if (BITS == 8 || WIDE) store_sums16(S, static_cast<uint16_t*>(a.sums) + g);
+            else store_sums8(S, static_cast<uint8_t*>(a.sums) + g);
+        }
+    } else {
+        constexpr int kVecs = 2 * SRC;
+        uint4 q[kVecs];
+#pragma unroll
+        for (int k = 0; k < kVecs; ++k)
+            q[k] = exists ? load_last_use(reinterpret_cast<const uint4*>(static_cast<const uint8_t*>(a.in) + g * SRC) + k)
+                          : make_uint4(0u, 0u, 0u, 0u);
+        if (wave == 0) *reinterpret_cast<u32x4*>(&sign[4 * lane]) = sign_block((base >> 7) + lane, a.key0, a.key1);
+#pragma unroll
+        for (int k = 0; k < kVecs; ++k) {
+            const uint32_t x[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
+#pragma unroll
+            for (int e = 0; e < 16 / SRC; ++e) {
+                constexpr int per = 4 / SRC;
+                S[16 / SRC * k + e] = (x[e / per] >> (8 * SRC * (e % per))) & (SRC == 1 ? 0xFFu : 0xFFFFu);
+            }
+        }
+    }
+    const float qf = ((s + s) / (float)((1u << BITS) - 1u)) / (float)a.W;
+    float v[kRegs];
+#pragma unroll
+    for (int r = 0; r < kRegs; ++r) v[r] = (float)S[r] * qf - s;
+
+    butterflies<0, 5>(v);
+    float* reg = reinterpret_cast<float*>(xb4) + wave * 2048u;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        reinterpret_cast<float4*>(reg)[lay14::x1_store(lane, q) >> 2] =
+            make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int r = 0; r < kRegs; ++r) v[r] = reg[lay14::x1_load(lane, r)];
+    // now register = i5..i9, lane = i0..i4, i10
+    if (l > 5u) butterflies<0, 1>(v);
+    if (l > 6u) butterflies<1, 2>(v);
+    if (l > 7u) butterflies<2, 3>(v);
+    if (l > 8u) butterflies<3, 4>(v);
+    if (l > 9u) butterflies<4, 5>(v);
+    __syncthreads();   // the sign table; every wave has read its part of the buffer
+    // where register r's coordinate lies: (lane & 31) + 32 (r & 15) + at + (r >> 4) hi
+    uint32_t at = wave * kWaveCoords + ((lane >> 5) << 10), hi = 512u;
+    if (l > 10u) {
+        lanes::swap_top_register_bit<32>(v);   // register bit 4 = i10, lane bit 5 = i9
+        butterflies<4, 5>(v);
+        at = wave * kWaveCoords + ((lane >> 5) << 9);
+        hi = 1024u;
+    }
+    if (l > 11u) {
+        trade_halves(v, xb4 + 512u * wave, xb4 + 512u * (wave ^ 1u), (wave & 1u) != 0u, lane);
+        butterflies<4, 5>(v);
+        at = ((wave >> 1) << 12) + ((wave & 1u) << 10) + ((lane >> 5) << 9);
+        hi = 2048u;
+    }
+    if (l > 12u) {
+        trade_halves(v, xb4 + 512u * wave, xb4 + 512u * (wave ^ 2u), (wave & 2u) != 0u, lane);
+        butterflies<4, 5>(v);
+        at = (wave << 10) + ((lane >> 5) << 9);
+        hi = 4096u;
+    }
+    float* out = a.out + base + at + (lane & 31u);
+    const uint32_t* sw = sign + (at >> 5);
+    const uint32_t shift = 31u - (lane & 31u);
+    const uint64_t left = a.n - base;   // (the grid covers n: base < n)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint4 sq = *reinterpret_cast<const uint4*>(sw + (h * hi >> 5) + 4 * q);
+            const uint32_t wd[4] = {sq.x, sq.y, sq.z, sq.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 16 * h + 4 * q + e;
+                const uint32_t off = h * hi + 32u * (4 * q + e);
+                const uint32_t x = xor_masked(__float_as_uint(v[r] * a.norm), wd[e] << shift, 0x80000000u);
+                if (at + (lane & 31u) + off < left) __builtin_nontemporal_store(__uint_as_float(x), out + off);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------ launch
+int device_cus() {
+    static int cus = 0;
+    if (cus == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
+            cus = prop.multiProcessorCount;
+    }
+    return cus;
+}
+
+template <auto kernel>
+uint32_t resident_grid(uint32_t waves, uint32_t lds) {
+    static uint32_t cached[kMaxWaves + 1];   // by size of the workgroup (which fixes its LDS up to a few KB)
+    if (cached[waves] == 0) {
+        int occ = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, (int)(64u * waves), lds) != hipSuccess || occ < 1)
+            return 0;
+        cached[waves] = (uint32_t)(occ * device_cus());
+    }
+    return cached[waves];
+}
+
+template <bool BF16, int CLASS, int BITS, SmallOp OP>
+hipError_t launch_encode_t(const SmallArgs& a, const FusedWorkerPtrs& ptrs, hipStream_t stream) {
+    constexpr auto kernel = small_encode_kernel<BF16, CLASS, BITS, OP>;
+    const uint32_t wpw = 1u << a.wpw_log2, waves = a.regions * a.groups * wpw;
+    const uint32_t unit_log2 = a.l > kWaveLog2 ? a.l : kWaveLog2;
+    const uint32_t rows_log2 = a.l < kWaveLog2 ? kWaveLog2 - a.l : 0u;
+    const uint32_t lds = waves * (!BF16 ? 8192u : (CLASS == 2 ? 4096u : 0u)) +
+                         2u * 4u * (a.regions << (unit_log2 - 5u)) +
+                         2u * 4u * (a.regions << rows_log2) * ((a.groups * wpw + 3u) & ~3u);
+    if (lds > 65536u) {   // (idempotent; a launch with more than the default limit needs it)
+        static bool raised = false;
+        if (!raised) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    163840) != hipSuccess)
+                return hipErrorInvalidValue;
+            raised = true;
+        }
+    }
+    uint64_t G = resident_grid<kernel>(waves, lds);
+    if (G == 0) return hipErrorInvalidValue;
+    if (G > a.items) G = a.items;
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)G), dim3(64u * waves), lds, stream, a, ptrs);
+    return hipGetLastError();
+}
+
+template <bool BF16, int CLASS, SmallOp OP>
+hipError_t launch_encode_bits(const SmallArgs& a, const FusedWorkerPtrs& ptrs, uint32_t bits, hipStream_t stream) {
+    if (OP == SmallOp::Absmax) return launch_encode_t<BF16, CLASS, 4, SmallOp::Absmax>(a, ptrs, stream);
+    if (bits == 2) return launch_encode_t<BF16, CLASS, 2, OP>(a, ptrs, stream);
+    if (bits == 4) return launch_encode_t<BF16, CLASS, 4, OP>(a, ptrs, stream);
+    return launch_encode_t<BF16, CLASS, 8, OP>(a, ptrs, stream);
+}
+
+template <SmallOp OP>
+hipError_t launch_encode(SmallArgs& a, const FusedWorkerPtrs& ptrs, bool bf16, uint32_t bits, hipStream_t stream) {
+    // Shape of a workgroup.  All workers of a unit side by side where they fit 16 waves, and as
+    // many units as fill 8; more workers take rounds, evenly.
+    a.wpw_log2 = a.l > kWaveLog2 ? a.l - kWaveLog2 : 0u;
+    const uint32_t max_groups = kMaxWaves >> a.wpw_log2;
+    a.rounds = (a.W + max_groups - 1u) / max_groups;
+    a.groups = (a.W + a.rounds - 1u) / a.rounds;
+    const uint32_t per_region = a.groups << a.wpw_log2;
+    a.regions = per_region < kPreferredWaves ? kPreferredWaves / per_region : 1u;
+    const uint32_t unit_log2 = a.l > kWaveLog2 ? a.l : kWaveLog2;
+    const uint64_t units = (a.padded + (1ull << unit_log2) - 1u) >> unit_log2;
+    // (a few units: spread over the CUs before they share a workgroup)
+    while (a.regions > 1u && units <= (uint64_t)device_cus() * (a.regions >> 1)) a.regions >>= 1;
+    a.items = (units + a.regions - 1u) / a.regions;
+    const int cls = class_of(a.l);
+    if (bf16) {
+        if (cls == 0) return launch_encode_bits<true, 0, OP>(a, ptrs, bits, stream);
+        if (cls == 1) return launch_encode_bits<true, 1, OP>(a, ptrs, bits, stream);
+        return launch_encode_bits<true, 2, OP>(a, ptrs, bits, stream);
+    }
+    if (cls == 0) return launch_encode_bits<false, 0, OP>(a, ptrs, bits, stream);
+    if (cls == 1) return launch_encode_bits<false, 1, OP>(a, ptrs, bits, stream);
+    return launch_encode_bits<false, 2, OP>(a, ptrs, bits, stream);
+}
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+bool small_size(uint32_t chunk_log2) { return chunk_log2 >= 5u && chunk_log2 < 14u; }
+
+}  // namespace
+}  // namespace k14
+
+bool small_encode_all_applicable(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2) {
+    if (!k14::small_size(chunk_log2) || a.W > (uint32_t)kMaxFusedWorkers) return false;
+    for (uint32_t w = 0; w < a.W; ++w)
+        if (!k14::aligned16(ptrs.grad[w]) || !k14::aligned16(ptrs.payload[w])) return false;
+    return true;
+}
+
+hipError_t launch_small_encode_all(const EncodeAllArgs& e, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2, float norm,
+                                   bool bf16, uint32_t bits, bool clear_error, hipStream_t stream) {
+    k14::SmallArgs a{};
+    a.n = e.n;
+    a.padded = e.chunks << chunk_log2;
+    a.l = chunk_log2;
+    a.W = e.W;
+    a.key0 = e.key0;
+    a.key1 = e.key1;
+    a.levels = e.levels;
+    a.norm = norm;
+    a.scale_out = e.scale;
+    a.error = clear_error ? e.error : nullptr;
+    return k14::launch_encode<k14::SmallOp::EncodeAll>(a, ptrs, bf16, bits, stream);
+}
+
+bool small_applicable(Mode mode, const ChunkArgs& c) {
+    if (!k14::small_size(c.chunk_log2) || c.no_rotate || c.range_in || c.out_bf16) return false;
+    if (mode == Mode::Absmax) return k14::aligned16(c.in);
+    if (mode == Mode::Encode) return k14::aligned16(c.in) && k14::aligned16(c.out);
+    return mode == Mode::Decode && !c.sat && k14::aligned16(c.in) && (c.padded >> k14::kDecodeLog2) < 0x7FFFFFFFull;
+}
+
+static hipError_t small_decode(k14::SmallDecodeArgs& a, const FusedPayloadPtrs& ptrs, int src, uint32_t bits, bool wide,
+                               hipStream_t stream) {
+    using namespace k14;
+    const dim3 grid((uint32_t)((a.padded + (1ull << kDecodeLog2) - 1u) >> kDecodeLog2)), block(kDecodeThreads);
+    if (grid.x == 0) return hipSuccess;
+#define THC_SMALL_DECODE(S, B, WI) hipLaunchKernelGGL((small_decode_kernel<S, B, WI>), grid, block, 0, stream, a, ptrs)
+    if (src == 0) {
+        if (wide) THC_SMALL_DECODE(0, 4, true);
+        else if (bits == 2) THC_SMALL_DECODE(0, 2, false);
+        else if (bits == 4) THC_SMALL_DECODE(0, 4, false);
+        else THC_SMALL_DECODE(0, 8, false);
+    } else if (src == 1) {
+        if (bits == 2) THC_SMALL_DECODE(1, 2, false);
+        else if (bits == 4) THC_SMALL_DECODE(1, 4, false);
+        else THC_SMALL_DECODE(1, 8, false);
+    } else {
+        if (bits == 2) THC_SMALL_DECODE(2, 2, false);
+        else if (bits == 4) THC_SMALL_DECODE(2, 4, false);
+        else THC_SMALL_DECODE(2, 8, false);
+    }
+#undef THC_SMALL_DECODE
+    return hipGetLastError();
+}
+
+hipError_t launch_small(Mode mode, const ChunkArgs& c, hipStream_t stream) {
+    if (c.padded == 0) return hipSuccess;
+    if (mode == Mode::Decode) {
+        k14::SmallDecodeArgs d{c.n, c.padded, c.chunk_log2, c.W, c.key0, c.key1, c.inv_sqrt_c, c.scale_in, c.in, nullptr,
+                               static_cast<float*>(c.out)};
+        return small_decode(d, FusedPayloadPtrs{}, (int)c.sum_bytes, c.bits, false, stream);
+    }
+    k14::SmallArgs a{};
+    a.n = c.n;
+    a.padded = c.padded;
+    a.l = c.chunk_log2;
+    a.W = 1;
+    a.worker0 = c.worker;
+    a.key0 = c.key0;
+    a.key1 = c.key1;
+    a.levels = c.levels;
+    a.norm = c.inv_sqrt_c;
+    FusedWorkerPtrs ptrs{};
+    ptrs.grad[0] = c.in;
+    if (mode == Mode::Absmax) {
+        a.scale_out = static_cast<float*>(c.out);
+        return k14::launch_encode<k14::SmallOp::Absmax>(a, ptrs, c.in_bf16 != 0u, 4, stream);
+    }
+    ptrs.payload[0] = static_cast<uint8_t*>(c.out);
+    a.scale_in = c.scale_in;
+    a.scale_out = c.scale_out;
+    if (c.scale_in) return k14::launch_encode<k14::SmallOp::EncodeOnto>(a, ptrs, c.in_bf16 != 0u, c.bits, stream);
+    return k14::launch_encode<k14::SmallOp::EncodeAll>(a, ptrs, c.in_bf16 != 0u, c.bits, stream);
+}
+
+bool small_aggregate_decode_applicable(uint32_t W, uint32_t chunk_log2, uint32_t bits, uint64_t padded) {
+    return k14::small_size(chunk_log2) && aggregate_decode_fused_applicable(W, 14, bits) &&
+           (padded >> k14::kDecodeLog2) < 0x7FFFFFFFull;
+}
+
+hipError_t launch_small_aggregate_decode(const AggDecodeArgs& e, const FusedPayloadPtrs& ptrs, uint32_t chunk_log2,
+                                         float norm, uint32_t bits, hipStream_t stream) {
+    k14::SmallDecodeArgs d{e.n, e.chunks << chunk_log2, chunk_log2, e.W, e.key0, e.key1, norm, e.scale, nullptr, e.sums,
+                           e.out};
+    return small_decode(d, ptrs, 0, bits, bits == 4u && e.W * 15u > 255u, stream);
+}
+
+}  // namespace thc

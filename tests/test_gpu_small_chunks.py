@@ -1,0 +1,87 @@
+"""The tuned kernels for chunks of 2^5 .. 2^13 coordinates against the CPU oracle: every chunk
+size, worker counts around the edges of a workgroup (16 waves, rounds of workers beyond),
+odd and ragged sizes, one-pass and per-call forms, and the signed grid's centre rule."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_01378_amd as thc
+from oracle import thc as O
+from oracle import thc_sat as S
+from synth import to_numpy_bits
+
+from gpu_util import DEV, check_against_oracle, run_path, run_path_fused, run_path_timed
+
+pytestmark = pytest.mark.gpu
+
+
+def _grads(W, n, dtype, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    xs = []
+    for _ in range(W):
+        x = torch.randn(n, generator=g, device=DEV) / torch.sqrt((torch.randn(3, n, generator=g, device=DEV) ** 2).mean(dim=0))
+        x = x * torch.exp(torch.randn(n // 512 + 1, generator=g, device=DEV) * 3 - 6).repeat_interleave(512)[:n]
+        x[n // 3:n // 3 + n // 8] = 0.0   # whole chunks of zeros among the small sizes
+        xs.append(x.to(dtype))
+    return xs
+
+
+CASES = [  # (l, W, bits, n): a lone ragged chunk, edges of a wave's 2^11, rounds of workers, regions
+    (5, 8, 4, 33), (5, 3, 2, 40_001), (6, 1, 8, 70_000), (7, 16, 4, 10_243), (8, 17, 8, 5_001), (9, 2, 4, 131_072),
+    (9, 33, 2, 6_145), (10, 4, 4, 100_003), (10, 8, 8, 2_047), (10, 64, 4, 4_099), (11, 1, 4, 200_001), (11, 5, 2, 40_961),
+    (11, 18, 4, 8_191), (12, 8, 8, 60_001), (12, 3, 4, 4_097), (12, 9, 2, 12_289), (12, 1, 4, 300_001), (13, 4, 4, 90_003),
+    (13, 8, 2, 40_000), (13, 5, 8, 8_193), (13, 2, 4, 7),
+]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("l,W,bits,n", CASES)
+def test_small_chunks_match_the_oracle(l, W, bits, n, dtype):
+    print(f"small l={l} W={W} bits={bits} n={n} {dtype}", flush=True)
+    xs = _grads(W, n, dtype, 7 * l + W)
+    fused = run_path_fused(xs, l, 5, bits)
+    check_against_oracle(xs, fused, l, 5, bits)
+    per_call = run_path(xs, l, 5, bits)
+    check_against_oracle(xs, per_call, l, 5, bits)
+    timed = run_path_timed(xs, l, 5, bits)
+    assert torch.equal(timed["out"], fused["out"])
+    own = torch.empty_like(fused["payloads"][0])   # the worker's own range as the grid
+    scale = torch.empty_like(fused["scale"])
+    thc.thc_encode(xs[W - 1], l, 5, W - 1, bits, None, own, scale)
+    torch.cuda.synchronize()
+    bf = dtype == torch.bfloat16
+    y = O.rht_forward(to_numpy_bits(xs[W - 1]), l, 5, dtype=np.float32, bf16=bf)
+    s = O.chunk_absmax(y, l)
+    assert (scale.cpu().numpy() == s).all()
+    assert (own.cpu().numpy() == O.pack(O.quantize(y, s, l, W - 1, 5, bits, dtype=np.float32), bits)).all()
+
+
+@pytest.mark.parametrize("l,W,bits,dtype", [(5, 4, 4, torch.float32), (10, 8, 2, torch.bfloat16), (12, 9, 8, torch.bfloat16),
+                                            (13, 3, 4, torch.float32)])
+@pytest.mark.parametrize("magnitude", [1.0, 2.0 ** -118, 2.0 ** -112, 2.0 ** 104])
+def test_small_chunks_outside_the_folded_range(l, W, bits, dtype, magnitude):
+    n = 3 * (1 << l) + 77
+    print(f"small folded l={l} W={W} bits={bits} {dtype} {magnitude}", flush=True)
+    xs = [(x.float().clamp(-4, 4) * magnitude).to(dtype) for x in _grads(W, n, dtype, 3)]
+    check_against_oracle(xs, run_path_fused(xs, l, 9, bits), l, 9, bits)
+
+
+@pytest.mark.parametrize("l,W,bits", [(5, 2, 2), (11, 8, 4), (13, 7, 8)])
+def test_small_chunks_on_the_signed_grid(l, W, bits):
+    n = 2 * (1 << l) + 1001
+    xs = _grads(W, n, torch.bfloat16, 11)
+    xs = [torch.where(torch.arange(n, device=DEV) < (1 << l), torch.zeros_like(x), x) for x in xs]   # an empty chunk
+    P = thc.thc_num_chunks(n, l)
+    scale = torch.empty(P, device=DEV)
+    pay = [torch.empty(thc.thc_payload_bytes(n, l, bits), dtype=torch.uint8, device=DEV) for _ in range(W)]
+    ws = torch.empty(thc.thc_encode_all_workspace_bytes(W, n, l), dtype=torch.uint8, device=DEV)
+    thc.thc_sat_encode_all(xs, l, 5, bits, pay, scale, ws)
+    ref = [torch.empty_like(pay[0]) for _ in range(W)]
+    for w in range(W):
+        thc.thc_sat_encode(xs[w], l, 5, w, bits, scale, ref[w])
+    torch.cuda.synchronize()
+    want = S.sat_pipeline([to_numpy_bits(x) for x in xs], l, 5, bits, dtype=np.float32, bf16=True)
+    for w in range(W):
+        assert (pay[w].cpu().numpy() == want["payloads"][w]).all()
+        assert torch.equal(ref[w], pay[w])
