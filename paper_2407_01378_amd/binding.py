@@ -1,8 +1,11 @@
-"""ctypes binding of libthc.so: argument marshalling only.
+"""Binding of libthc.so: argument marshalling only.
 
 Every function has the name and argument order of its C entry point in
 include/thc.h and does no arithmetic of its own; PyTorch supplies device memory
-and the stream.  The library must have been built (python -m
+and the stream.  The entry points of a training step go through a native
+marshalling module (csrc/marshal.cpp), which answers None when an argument is
+not of the plain form it expects; the ctypes call next to it then does the
+checks and raises.  Both must have been built (python -m
 paper_2407_01378_amd.build): there is no fallback, a missing library raises.
 """
 import ctypes
@@ -17,6 +20,7 @@ THC_F32, THC_BF16 = 0, 1
 THC_OK = 0
 
 _lib = None
+_native = None   # the marshalling module (csrc/marshal.cpp), once the library is loaded
 
 _u8pp = ctypes.POINTER(ctypes.c_void_p)
 
@@ -185,8 +189,27 @@ def lib():
             fn = getattr(handle, name)
             fn.restype = res
             fn.argtypes = args
+        _load_marshal(handle)
         _lib = handle
     return _lib
+
+
+def _load_marshal(handle):
+    """The native marshalling module, told where the loaded library's entry points are."""
+    global _native
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise RuntimeError(f"{os.path.join(_PKG, '_marshal.so')} cannot be loaded ({e}): build it with "
+                           "`python -m paper_2407_01378_amd.build`") from e
+    for name in _marshal.names():
+        _marshal.bind(name, ctypes.cast(getattr(handle, name), ctypes.c_void_p).value)
+    _native = _marshal
+
+
+def _load_native():
+    lib()
+    return _native
 
 
 def exported_names():
@@ -251,53 +274,69 @@ def thc_sum_bytes(W, bits):
 
 # ------------------------------------------------------------------- entry points
 def rht_forward(x, chunk_log2, seed, y, stream=None):
-    _flat(x), _flat(y, torch.float32)
-    _check(lib().rht_forward(_ptr(x), _dtype_code(x), x.numel(), chunk_log2, seed, _ptr(y),
-                             _stream(stream)), "rht_forward")
+    rc = (_native or _load_native()).rht_forward(x, chunk_log2, seed, y, stream)
+    if rc is None:
+        _flat(x), _flat(y, torch.float32)
+        rc = lib().rht_forward(_ptr(x), _dtype_code(x), x.numel(), chunk_log2, seed, _ptr(y), _stream(stream))
+    _check(rc, "rht_forward")
     return y
 
 
 def rht_inverse(y, n, chunk_log2, seed, x, stream=None):
-    _flat(y, torch.float32), _flat(x, torch.float32)
-    _check(lib().rht_inverse(_ptr(y), n, chunk_log2, seed, _ptr(x), _stream(stream)),
-           "rht_inverse")
+    rc = (_native or _load_native()).rht_inverse(y, n, chunk_log2, seed, x, stream)
+    if rc is None:
+        _flat(y, torch.float32), _flat(x, torch.float32)
+        rc = lib().rht_inverse(_ptr(y), n, chunk_log2, seed, _ptr(x), _stream(stream))
+    _check(rc, "rht_inverse")
     return x
 
 
 def thc_chunk_absmax(grad, chunk_log2, seed, absmax, stream=None):
-    _flat(grad), _flat(absmax, torch.float32)
-    _check(lib().thc_chunk_absmax(_ptr(grad), _dtype_code(grad), grad.numel(), chunk_log2, seed,
-                                  _ptr(absmax), _stream(stream)), "thc_chunk_absmax")
+    rc = (_native or _load_native()).thc_chunk_absmax(grad, chunk_log2, seed, absmax, stream)
+    if rc is None:
+        _flat(grad), _flat(absmax, torch.float32)
+        rc = lib().thc_chunk_absmax(_ptr(grad), _dtype_code(grad), grad.numel(), chunk_log2, seed, _ptr(absmax),
+                                    _stream(stream))
+    _check(rc, "thc_chunk_absmax")
     return absmax
 
 
 def thc_scale_reduce(absmax_all, W, chunks, scale, stream=None):
-    _check(lib().thc_scale_reduce(_ptr(absmax_all), W, chunks, _ptr(scale), _stream(stream)),
-           "thc_scale_reduce")
+    rc = (_native or _load_native()).thc_scale_reduce(absmax_all, W, chunks, scale, stream)
+    if rc is None:
+        rc = lib().thc_scale_reduce(_ptr(absmax_all), W, chunks, _ptr(scale), _stream(stream))
+    _check(rc, "thc_scale_reduce")
     return scale
 
 
 def thc_encode(grad, chunk_log2, seed, worker, bits, shared_scale, payload, scale_out=None,
                stream=None):
-    _flat(grad), _flat(payload, torch.uint8)
-    _check(lib().thc_encode(_ptr(grad), _dtype_code(grad), grad.numel(), chunk_log2, seed, worker,
-                            bits, _ptr(shared_scale), _ptr(payload), _ptr(scale_out),
-                            _stream(stream)), "thc_encode")
+    rc = (_native or _load_native()).thc_encode(grad, chunk_log2, seed, worker, bits, shared_scale, payload,
+                                                scale_out, stream)
+    if rc is None:
+        _flat(grad), _flat(payload, torch.uint8)
+        rc = lib().thc_encode(_ptr(grad), _dtype_code(grad), grad.numel(), chunk_log2, seed, worker, bits,
+                              _ptr(shared_scale), _ptr(payload), _ptr(scale_out), _stream(stream))
+    _check(rc, "thc_encode")
     return payload
 
 
 def thc_aggregate(payloads, n, chunk_log2, bits, sums, stream=None):
-    W = len(payloads)
-    arr = (ctypes.c_void_p * max(W, 1))(*[p.data_ptr() for p in payloads])
-    _check(lib().thc_aggregate(ctypes.cast(arr, _u8pp), W, n, chunk_log2, bits, _ptr(sums),
-                               _stream(stream)), "thc_aggregate")
+    rc = (_native or _load_native()).thc_aggregate(payloads, n, chunk_log2, bits, sums, stream)
+    if rc is None:
+        W = len(payloads)
+        arr = (ctypes.c_void_p * max(W, 1))(*[p.data_ptr() for p in payloads])
+        rc = lib().thc_aggregate(ctypes.cast(arr, _u8pp), W, n, chunk_log2, bits, _ptr(sums), _stream(stream))
+    _check(rc, "thc_aggregate")
     return sums
 
 
 def thc_decode(sums, scale, W, n, chunk_log2, seed, bits, out, stream=None):
-    _flat(out, torch.float32)
-    _check(lib().thc_decode(_ptr(sums), _ptr(scale), W, n, chunk_log2, seed, bits, _ptr(out),
-                            _stream(stream)), "thc_decode")
+    rc = (_native or _load_native()).thc_decode(sums, scale, W, n, chunk_log2, seed, bits, out, stream)
+    if rc is None:
+        _flat(out, torch.float32)
+        rc = lib().thc_decode(_ptr(sums), _ptr(scale), W, n, chunk_log2, seed, bits, _ptr(out), _stream(stream))
+    _check(rc, "thc_decode")
     return out
 
 
@@ -311,9 +350,7 @@ def thc_encode_all_workspace_bytes(W, n, chunk_log2):
     return lib().thc_encode_all_workspace_bytes(W, n, chunk_log2)
 
 
-def _encode_all(name, grads, chunk_log2, seed, bits, payloads, scale, workspace, stream, check=False):
-    """check=True synchronises the device after the call and raises ThcError(-7) if a bounded
-    wait between workgroups expired (the workspace's first word); marshalling otherwise."""
+def _encode_all(name, grads, chunk_log2, seed, bits, payloads, scale, workspace, stream):
     W = len(grads)
     n = grads[0].numel()
     for g in grads:
@@ -322,10 +359,15 @@ def _encode_all(name, grads, chunk_log2, seed, bits, payloads, scale, workspace,
             raise ValueError("all workers must have gradients of one size and dtype")
     keep_g, pg = _ptr_array(grads)
     keep_p, pp = _ptr_array(payloads)
-    _check(getattr(lib(), name)(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, pp,
+    return getattr(lib(), name)(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, pp,
                                 _ptr(scale), _ptr(workspace),
-                                workspace.numel() * workspace.element_size(), _stream(stream)),
-           name)
+                                workspace.numel() * workspace.element_size(), _stream(stream))
+
+
+def _encode_all_done(rc, name, payloads, workspace, check):
+    """check=True synchronises the device after the call and raises ThcError(-7) if a bounded
+    wait between workgroups expired (the workspace's first word)."""
+    _check(rc, name)
     if check:
         torch.cuda.synchronize(workspace.device)
         if thc_encode_all_timed_out(workspace):
@@ -334,12 +376,21 @@ def _encode_all(name, grads, chunk_log2, seed, bits, payloads, scale, workspace,
 
 
 def thc_encode_all(grads, chunk_log2, seed, bits, payloads, scale, workspace, stream=None, check=False):
-    return _encode_all("thc_encode_all", grads, chunk_log2, seed, bits, payloads, scale, workspace, stream, check)
+    rc = (_native or _load_native()).thc_encode_all(grads, chunk_log2, seed, bits, payloads, scale, workspace,
+                                                    stream)
+    if rc is None:
+        rc = _encode_all("thc_encode_all", grads, chunk_log2, seed, bits, payloads, scale, workspace, stream)
+    return _encode_all_done(rc, "thc_encode_all", payloads, workspace, check)
+
 
 
 def thc_encode_all_cleared(grads, chunk_log2, seed, bits, payloads, scale, workspace, stream=None, check=False):
-    return _encode_all("thc_encode_all_cleared", grads, chunk_log2, seed, bits, payloads, scale,
-                       workspace, stream, check)
+    rc = (_native or _load_native()).thc_encode_all_cleared(grads, chunk_log2, seed, bits, payloads, scale, workspace,
+                                                            stream)
+    if rc is None:
+        rc = _encode_all("thc_encode_all_cleared", grads, chunk_log2, seed, bits, payloads, scale, workspace, stream)
+    return _encode_all_done(rc, "thc_encode_all_cleared", payloads, workspace, check)
+
 
 
 # ------------------------------------------------------------ several buckets per launch
@@ -370,44 +421,53 @@ def thc_batch_workspace_bytes(ns, W, chunk_log2):
 
 
 def thc_encode_all_batch(buckets, chunk_log2, bits, workspace, stream=None):
-    W = len(buckets[0]["grads"]) if buckets else 1
-    keep, arr = _bucket_array(buckets)
-    dt = _dtype_code(buckets[0]["grads"][0]) if buckets else THC_F32
-    _check(lib().thc_encode_all_batch(arr, len(buckets), dt, W, chunk_log2, bits, _ptr(workspace),
-                                      workspace.numel() * workspace.element_size(), _stream(stream)),
-           "thc_encode_all_batch")
+    rc = (_native or _load_native()).thc_encode_all_batch(buckets, chunk_log2, bits, workspace, stream)
+    if rc is None:
+        W = len(buckets[0]["grads"]) if buckets else 1
+        keep, arr = _bucket_array(buckets)
+        dt = _dtype_code(buckets[0]["grads"][0]) if buckets else THC_F32
+        rc = lib().thc_encode_all_batch(arr, len(buckets), dt, W, chunk_log2, bits, _ptr(workspace), workspace.numel()
+                                        * workspace.element_size(), _stream(stream))
+    _check(rc, "thc_encode_all_batch")
 
 
 def thc_aggregate_decode_batch(buckets, chunk_log2, bits, workspace, stream=None):
-    W = len(buckets[0]["payloads"]) if buckets else 1
-    keep, arr = _bucket_array(buckets)
-    _check(lib().thc_aggregate_decode_batch(arr, len(buckets), W, chunk_log2, bits, _ptr(workspace),
-                                            workspace.numel() * workspace.element_size(), _stream(stream)),
-           "thc_aggregate_decode_batch")
+    rc = (_native or _load_native()).thc_aggregate_decode_batch(buckets, chunk_log2, bits, workspace, stream)
+    if rc is None:
+        W = len(buckets[0]["payloads"]) if buckets else 1
+        keep, arr = _bucket_array(buckets)
+        rc = lib().thc_aggregate_decode_batch(arr, len(buckets), W, chunk_log2, bits, _ptr(workspace),
+                                              workspace.numel() * workspace.element_size(), _stream(stream))
+    _check(rc, "thc_aggregate_decode_batch")
 
 
 THC_STATIC_SCRATCH_BYTES = 2 << 20
 
 
 def thc_encode_all_static(grads, chunk_log2, seed, bits, payloads, scale, timed_out=None, stream=None):
-    W = len(grads)
-    n = grads[0].numel()
-    for g in grads:
-        _flat(g)
-        if g.numel() != n or g.dtype != grads[0].dtype:
-            raise ValueError("all workers must have gradients of one size and dtype")
-    keep_g, pg = _ptr_array(grads)
-    keep_p, pp = _ptr_array(payloads)
-    _check(lib().thc_encode_all_static(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, pp,
-                                       _ptr(scale), _ptr(timed_out), _stream(stream)),
-           "thc_encode_all_static")
+    rc = (_native or _load_native()).thc_encode_all_static(grads, chunk_log2, seed, bits, payloads, scale, timed_out,
+                                                           stream)
+    if rc is None:
+        W = len(grads)
+        n = grads[0].numel()
+        for g in grads:
+            _flat(g)
+            if g.numel() != n or g.dtype != grads[0].dtype:
+                raise ValueError("all workers must have gradients of one size and dtype")
+        keep_g, pg = _ptr_array(grads)
+        keep_p, pp = _ptr_array(payloads)
+        rc = lib().thc_encode_all_static(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, pp, _ptr(scale),
+                                         _ptr(timed_out), _stream(stream))
+    _check(rc, "thc_encode_all_static")
     return payloads
 
 
 def thc_workspace_clear(workspace, stream=None):
-    _flat(workspace)
-    _check(lib().thc_workspace_clear(_ptr(workspace), workspace.numel() * workspace.element_size(),
-                                     _stream(stream)), "thc_workspace_clear")
+    rc = (_native or _load_native()).thc_workspace_clear(workspace, stream)
+    if rc is None:
+        _flat(workspace)
+        rc = lib().thc_workspace_clear(_ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
+    _check(rc, "thc_workspace_clear")
     return workspace
 
 
@@ -425,11 +485,15 @@ def thc_aggregate_decode_is_fused(W, chunk_log2, bits):
 
 
 def thc_aggregate_decode(payloads, scale, n, chunk_log2, seed, bits, sums, out, stream=None):
-    W = len(payloads)
-    keep_p, pp = _ptr_array(payloads)
-    _flat(out, torch.float32)
-    _check(lib().thc_aggregate_decode(pp, W, _ptr(scale), n, chunk_log2, seed, bits, _ptr(sums),
-                                      _ptr(out), _stream(stream)), "thc_aggregate_decode")
+    rc = (_native or _load_native()).thc_aggregate_decode(payloads, scale, n, chunk_log2, seed, bits, sums, out,
+                                                          stream)
+    if rc is None:
+        W = len(payloads)
+        keep_p, pp = _ptr_array(payloads)
+        _flat(out, torch.float32)
+        rc = lib().thc_aggregate_decode(pp, W, _ptr(scale), n, chunk_log2, seed, bits, _ptr(sums), _ptr(out),
+                                        _stream(stream))
+    _check(rc, "thc_aggregate_decode")
     return out
 
 
@@ -448,13 +512,21 @@ def thc_sat_encode(grad, chunk_log2, seed, worker, bits, shared_scale, payload, 
 
 
 def thc_sat_encode_all(grads, chunk_log2, seed, bits, payloads, scale, workspace, stream=None, check=False):
-    return _encode_all("thc_sat_encode_all", grads, chunk_log2, seed, bits, payloads, scale, workspace,
-                       stream, check)
+    rc = (_native or _load_native()).thc_sat_encode_all(grads, chunk_log2, seed, bits, payloads, scale, workspace,
+                                                        stream)
+    if rc is None:
+        rc = _encode_all("thc_sat_encode_all", grads, chunk_log2, seed, bits, payloads, scale, workspace, stream)
+    return _encode_all_done(rc, "thc_sat_encode_all", payloads, workspace, check)
+
 
 
 def thc_sat_encode_all_cleared(grads, chunk_log2, seed, bits, payloads, scale, workspace, stream=None, check=False):
-    return _encode_all("thc_sat_encode_all_cleared", grads, chunk_log2, seed, bits, payloads, scale,
-                       workspace, stream, check)
+    rc = (_native or _load_native()).thc_sat_encode_all_cleared(grads, chunk_log2, seed, bits, payloads, scale, workspace,
+                                                                stream)
+    if rc is None:
+        rc = _encode_all("thc_sat_encode_all_cleared", grads, chunk_log2, seed, bits, payloads, scale, workspace, stream)
+    return _encode_all_done(rc, "thc_sat_encode_all_cleared", payloads, workspace, check)
+
 
 
 def thc_sat_aggregate(payloads, n, chunk_log2, bits, aggregate, overflow_count=None, stream=None):
@@ -477,11 +549,14 @@ def thc_sat_aggregate_decode_is_fused(W, chunk_log2, bits):
 
 def thc_sat_aggregate_decode(payloads, scale, n, chunk_log2, seed, bits, aggregate, overflow_count,
                              out, stream=None):
-    keep_p, pp = _ptr_array(payloads)
-    _flat(out, torch.float32)
-    _check(lib().thc_sat_aggregate_decode(pp, len(payloads), _ptr(scale), n, chunk_log2, seed, bits,
-                                          _ptr(aggregate), _ptr(overflow_count), _ptr(out),
-                                          _stream(stream)), "thc_sat_aggregate_decode")
+    rc = (_native or _load_native()).thc_sat_aggregate_decode(payloads, scale, n, chunk_log2, seed, bits, aggregate,
+                                                              overflow_count, out, stream)
+    if rc is None:
+        keep_p, pp = _ptr_array(payloads)
+        _flat(out, torch.float32)
+        rc = lib().thc_sat_aggregate_decode(pp, len(payloads), _ptr(scale), n, chunk_log2, seed, bits,
+                                            _ptr(aggregate), _ptr(overflow_count), _ptr(out), _stream(stream))
+    _check(rc, "thc_sat_aggregate_decode")
     return out
 
 
@@ -499,16 +574,23 @@ def rht_forward_full_absmax(x, log2_size, seed, y, absmax, stream=None):
 
 def rht_forward_full_deferred(x, log2_size, seed, y, absmax, stream=None):
     """Every pass but the last in y, the last one evaluated for absmax only."""
-    _flat(x), _flat(y, torch.float32), _flat(absmax, torch.float32)
-    _check(lib().rht_forward_full_deferred(_ptr(x), _dtype_code(x), x.numel(), log2_size, seed, _ptr(y),
-                                           _ptr(absmax), _stream(stream)), "rht_forward_full_deferred")
+    rc = (_native or _load_native()).rht_forward_full_deferred(x, log2_size, seed, y, absmax, stream)
+    if rc is None:
+        _flat(x), _flat(y, torch.float32), _flat(absmax, torch.float32)
+        rc = lib().rht_forward_full_deferred(_ptr(x), _dtype_code(x), x.numel(), log2_size, seed, _ptr(y),
+                                             _ptr(absmax), _stream(stream))
+    _check(rc, "rht_forward_full_deferred")
     return y
 
 
 def thc_full_encode_deferred(y, n, log2_size, seed, worker, bits, scale, payload, stream=None):
     """The last pass on the y of rht_forward_full_deferred, quantized into payload."""
-    _check(lib().thc_full_encode_deferred(_ptr(y), n, log2_size, seed, worker, bits, _ptr(scale), _ptr(payload),
-                                          _stream(stream)), "thc_full_encode_deferred")
+    rc = (_native or _load_native()).thc_full_encode_deferred(y, n, log2_size, seed, worker, bits, scale, payload,
+                                                              stream)
+    if rc is None:
+        rc = lib().thc_full_encode_deferred(_ptr(y), n, log2_size, seed, worker, bits, _ptr(scale), _ptr(payload),
+                                            _stream(stream))
+    _check(rc, "thc_full_encode_deferred")
     return payload
 
 
@@ -545,8 +627,12 @@ def thc_full_decode(sums, scale, W, log2_size, bits, yhat, stream=None):
 
 def thc_full_decode_inverse(sums, scale, W, n, log2_size, seed, bits, work, x, stream=None):
     """thc_full_decode + rht_inverse_full in one call; `work` is 2^log2_size fp32 of scratch."""
-    _check(lib().thc_full_decode_inverse(_ptr(sums), _ptr(scale), W, n, log2_size, seed, bits, _ptr(work),
-                                         _ptr(x), _stream(stream)), "thc_full_decode_inverse")
+    rc = (_native or _load_native()).thc_full_decode_inverse(sums, scale, W, n, log2_size, seed, bits, work, x,
+                                                             stream)
+    if rc is None:
+        rc = lib().thc_full_decode_inverse(_ptr(sums), _ptr(scale), W, n, log2_size, seed, bits, _ptr(work), _ptr(x),
+                                           _stream(stream))
+    _check(rc, "thc_full_decode_inverse")
     return x
 
 
@@ -585,27 +671,33 @@ def thc_encode_all_minmax_workspace_bytes(W, n, chunk_log2):
 
 
 def thc_encode_all_minmax(grads, chunk_log2, seed, bits, rotate, payloads, range_, workspace, stream=None):
-    W = len(grads)
-    n = grads[0].numel()
-    for g in grads:
-        _flat(g)
-        if g.numel() != n or g.dtype != grads[0].dtype:
-            raise ValueError("all workers must have gradients of one size and dtype")
-    keep_g, pg = _ptr_array(grads)
-    keep_p, pp = _ptr_array(payloads)
-    _check(lib().thc_encode_all_minmax(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits,
-                                       int(bool(rotate)), pp, _ptr(range_), _ptr(workspace),
-                                       workspace.numel() * workspace.element_size(), _stream(stream)),
-           "thc_encode_all_minmax")
+    rc = (_native or _load_native()).thc_encode_all_minmax(grads, chunk_log2, seed, bits, rotate, payloads, range_,
+                                                           workspace, stream)
+    if rc is None:
+        W = len(grads)
+        n = grads[0].numel()
+        for g in grads:
+            _flat(g)
+            if g.numel() != n or g.dtype != grads[0].dtype:
+                raise ValueError("all workers must have gradients of one size and dtype")
+        keep_g, pg = _ptr_array(grads)
+        keep_p, pp = _ptr_array(payloads)
+        rc = lib().thc_encode_all_minmax(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, int(bool(rotate)),
+                                         pp, _ptr(range_), _ptr(workspace), workspace.numel() *
+                                         workspace.element_size(), _stream(stream))
+    _check(rc, "thc_encode_all_minmax")
 
 
 def thc_aggregate_decode_minmax(payloads, range_, n, chunk_log2, seed, bits, rotate, out, stream=None):
-    W = len(payloads)
-    keep_p, pp = _ptr_array(payloads)
-    _flat(out, torch.float32)
-    _check(lib().thc_aggregate_decode_minmax(pp, W, _ptr(range_), n, chunk_log2, seed, bits,
-                                             int(bool(rotate)), _ptr(out), _stream(stream)),
-           "thc_aggregate_decode_minmax")
+    rc = (_native or _load_native()).thc_aggregate_decode_minmax(payloads, range_, n, chunk_log2, seed, bits, rotate,
+                                                                 out, stream)
+    if rc is None:
+        W = len(payloads)
+        keep_p, pp = _ptr_array(payloads)
+        _flat(out, torch.float32)
+        rc = lib().thc_aggregate_decode_minmax(pp, W, _ptr(range_), n, chunk_log2, seed, bits, int(bool(rotate)),
+                                               _ptr(out), _stream(stream))
+    _check(rc, "thc_aggregate_decode_minmax")
     return out
 
 
@@ -615,14 +707,19 @@ def topkc_num_chunks(n, C):
 
 
 def topkc_chunk_norms(grad, C, norms, stream=None):
-    _flat(grad), _flat(norms, torch.float16)
-    _check(lib().topkc_chunk_norms(_ptr(grad), _dtype_code(grad), grad.numel(), C, _ptr(norms),
-                                   _stream(stream)), "topkc_chunk_norms")
+    rc = (_native or _load_native()).topkc_chunk_norms(grad, C, norms, stream)
+    if rc is None:
+        _flat(grad), _flat(norms, torch.float16)
+        rc = lib().topkc_chunk_norms(_ptr(grad), _dtype_code(grad), grad.numel(), C, _ptr(norms), _stream(stream))
+    _check(rc, "topkc_chunk_norms")
     return norms
 
 
 def topkc_sum_norms(norms_all, W, P, s, stream=None):
-    _check(lib().topkc_sum_norms(_ptr(norms_all), W, P, _ptr(s), _stream(stream)), "topkc_sum_norms")
+    rc = (_native or _load_native()).topkc_sum_norms(norms_all, W, P, s, stream)
+    if rc is None:
+        rc = lib().topkc_sum_norms(_ptr(norms_all), W, P, _ptr(s), _stream(stream))
+    _check(rc, "topkc_sum_norms")
     return s
 
 
@@ -631,22 +728,32 @@ def topkc_select_workspace_bytes(P):
 
 
 def topkc_select(s, J, indices, workspace, stream=None):
-    _flat(s, torch.float16), _flat(indices, torch.int32)
-    _check(lib().topkc_select(_ptr(s), s.numel(), J, _ptr(indices), _ptr(workspace),
-                              workspace.numel() * workspace.element_size(), _stream(stream)), "topkc_select")
+    rc = (_native or _load_native()).topkc_select(s, J, indices, workspace, stream)
+    if rc is None:
+        _flat(s, torch.float16), _flat(indices, torch.int32)
+        rc = lib().topkc_select(_ptr(s), s.numel(), J, _ptr(indices), _ptr(workspace), workspace.numel() *
+                                workspace.element_size(), _stream(stream))
+    _check(rc, "topkc_select")
     return indices
 
 
 def topkc_gather_sum(grads, C, indices, J, values, stream=None):
-    keep, pg = _ptr_array(grads)
-    _flat(values, torch.float16)
-    _check(lib().topkc_gather_sum(pg, _dtype_code(grads[0]), len(grads), grads[0].numel(), C, _ptr(indices), J,
-                                  _ptr(values), _stream(stream)), "topkc_gather_sum")
+    rc = (_native or _load_native()).topkc_gather_sum(grads, C, indices, J, values, stream)
+    if rc is None:
+        keep, pg = _ptr_array(grads)
+        _flat(values, torch.float16)
+        rc = lib().topkc_gather_sum(pg, _dtype_code(grads[0]), len(grads), grads[0].numel(), C, _ptr(indices), J,
+                                    _ptr(values), _stream(stream))
+    _check(rc, "topkc_gather_sum")
     return values
 
 
 def topkc_scatter_mean(values, indices, J, C, W, out, stream=None):
-    _flat(out, torch.float32)
-    _check(lib().topkc_scatter_mean(_ptr(values), _ptr(indices), J, C, W, out.numel(), _ptr(out),
-                                    _stream(stream)), "topkc_scatter_mean")
+    rc = (_native or _load_native()).topkc_scatter_mean(values, indices, J, C, W, out, stream)
+    if rc is None:
+        _flat(out, torch.float32)
+        rc = lib().topkc_scatter_mean(_ptr(values), _ptr(indices), J, C, W, out.numel(), _ptr(out), _stream(stream))
+    _check(rc, "topkc_scatter_mean")
     return out
+
+

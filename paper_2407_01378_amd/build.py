@@ -1,4 +1,5 @@
-"""Compile the HIP sources into libthc.so, in-tree, for gfx950.
+"""Compile the HIP sources into libthc.so (gfx950) and the binding's native marshalling into
+_marshal.so, in-tree.
 
     python -m paper_2407_01378_amd.build
 
@@ -10,11 +11,13 @@ hipcc cross-compiles without a GPU.  Flags that matter for correctness:
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libthc.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 ARCH = "gfx950"
 
 
@@ -33,10 +36,29 @@ def command(out=LIB):
     ]
 
 
+def marshal_command(out=MARSHAL):
+    """The binding's marshalling module: host code against PyTorch's headers, no device code."""
+    import torch
+    base = os.path.dirname(torch.__file__)
+    return [
+        "hipcc", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wno-unused-command-line-argument",
+        f"-I{os.path.join(ROOT, 'include')}", f"-I{os.path.join(base, 'include')}",
+        f"-I{sysconfig.get_paths()['include']}",
+        f"-L{os.path.join(base, 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+        "-o", out, os.path.join(CSRC, "marshal.cpp"),
+    ]
+
+
 def build_library(verbose=True):
     """Always recompiles.  Returns the path of the shared library."""
-    tmp = LIB + ".tmp"
-    cmd = command(tmp)
+    _run(marshal_command(MARSHAL + ".tmp"), verbose)
+    os.replace(MARSHAL + ".tmp", MARSHAL)
+    _run(command(LIB + ".tmp"), verbose)
+    os.replace(LIB + ".tmp", LIB)
+    return LIB
+
+
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -47,8 +69,6 @@ def build_library(verbose=True):
         raise RuntimeError("hipcc failed")
     if verbose and log.strip():
         print(log)
-    os.replace(tmp, LIB)
-    return LIB
 
 
 if __name__ == "__main__":
