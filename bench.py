@@ -630,7 +630,7 @@ def main():
         high = path.l - 14
         valid = ((wl.n + (1 << 14) - 1) >> 14) << 14
         dom_bytes = wl.n * s_in + valid * 4
-        passes, s0 = (high + 8) // 9, 14
+        passes, s0 = (high + 10) // 11, 14
         for p in range(passes):
             m = (path.l - s0 + (passes - p) - 1) // (passes - p)
             block = 1 << (s0 + m)

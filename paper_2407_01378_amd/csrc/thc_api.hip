@@ -818,7 +818,9 @@ static int forward_full(const void* x, thc_dtype dt, uint64_t n, uint32_t log2_s
     a.out = y;
     a.in_bf16 = dt == THC_BF16;
     a.inv_sqrt_c = 1.0f;
+    a.zero_word = reinterpret_cast<uint32_t*>(absmax);   // raised by the last pass
     if (n != 0 && thc::launch_fast14(Mode::Forward, a, st) != hipSuccess) return THC_ERR_HIP;
+    if (n == 0 && absmax && thc::launch_zero_words(a.zero_word, 1, st) != hipSuccess) return THC_ERR_HIP;
     // (the zero padding behind the last chunk is not written: the first pass reads it as zero)
     thc::FullDeferred d{};
     d.kind = thc::FullLast::RangeOnly;

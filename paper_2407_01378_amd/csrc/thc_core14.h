@@ -252,6 +252,53 @@ __device__ __forceinline__ void x3d_load(const Shared& sh, float (&v)[kRegs], ui
     }
 }
 
+// Two waves trade half of their registers through LDS: the upper half of the one against the
+// lower half of the other, so that register bit 4 and the bit in which the waves' numbers differ
+// change places.  `upper`: this wave has the bit set; `mine` / `theirs`: 4 KB per wave.  Ends with
+// a barrier: the buffers may be rewritten.
+__device__ __forceinline__ void trade_halves(float (&v)[kRegs], float4* mine, const float4* theirs, bool upper,
+                                             uint32_t lane) {
+    // (the empty assembly statements differ, so the two branches are not merged into one that picks
+    // its registers by address, which would put v into memory)
+    if (upper) {
+        asm volatile("; upper wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mine[q * 64 + lane] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        asm volatile("; upper wave sent" ::: "memory");
+    } else {
+        asm volatile("; lower wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            mine[q * 64 + lane] = make_float4(v[16 + 4 * q], v[17 + 4 * q], v[18 + 4 * q], v[19 + 4 * q]);
+        asm volatile("; lower wave sent" ::: "memory");
+    }
+    __syncthreads();
+    if (upper) {
+        asm volatile("; upper wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = theirs[q * 64 + lane];
+            v[4 * q] = f.x;
+            v[4 * q + 1] = f.y;
+            v[4 * q + 2] = f.z;
+            v[4 * q + 3] = f.w;
+        }
+        asm volatile("; upper wave has" ::: "memory");
+    } else {
+        asm volatile("; lower wave" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = theirs[q * 64 + lane];
+            v[16 + 4 * q] = f.x;
+            v[17 + 4 * q] = f.y;
+            v[18 + 4 * q] = f.z;
+            v[19 + 4 * q] = f.w;
+        }
+        asm volatile("; lower wave has" ::: "memory");
+    }
+    __syncthreads();
+}
+
 // Stages 0..13 on a chunk that sits in layout L1 in v; result (unnormalised H_c x) in
 // layout L3.  Starts with a barrier (every thread is past its earlier reads of the
 // buffer); the buffer is still being read when it returns.  hook.at<K>() is called at
@@ -300,6 +347,7 @@ __device__ __forceinline__ float wave_absmax(const float (&v)[kRegs]) {
 #pragma unroll
     for (int i = 0; i < kRegs; i += 2)
         asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(v[i]), "v"(v[i + 1]));
+    asm volatile("s_nop 1" : "+v"(m));   // wait states between the assembly's write and a lane exchange
     // m >= 0: floats of one sign order like their bit patterns
     return __uint_as_float(wave_umax(__float_as_uint(m)));
 }

@@ -35,6 +35,8 @@ __global__ __launch_bounds__(kThreads) void per_worker_kernel(const ChunkArgs a)
     rotate_l1_to_l3<false>(sh, v, lane, wave);
 
     if constexpr (MODE == Mode::Forward) {
+        // (the first pass of a longer rotation also zeroes the word its last pass raises)
+        if (a.zero_word && p == 0 && t == 0) *a.zero_word = 0u;
         l3_to_l4d<false>(sh, v, lane, wave);
         float* y = static_cast<float*>(a.out) + g0;
 #pragma unroll

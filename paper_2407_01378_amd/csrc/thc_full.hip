@@ -4,44 +4,53 @@
 // separately rounded fp32 add and subtract), so results are bit-identical to the
 // stage-by-stage definition:
 //   stages 0..13    the chunk-2^14 kernels (thc_fast14.hip), data in registers and LDS
-//   stages 14..l-1  "high passes" over the fp32 array in global memory, up to 9 stages per
+//   stages 14..l-1  "high passes" over the fp32 array in global memory, up to 11 stages per
 //                   pass (this file), in place
 // plus the steps of the quantizer on rotated data, which the partial-rotation path fuses into
 // its rotation kernels: as elementwise kernels on stored values (range, encode, decode), and
 // as variants of the last forward pass that keep only the range of its results, or quantize
 // them once the shared scale is known, so that the rotated values are never stored.
-#include "thc_device.h"
+#include "thc_core14.h"
 #include "thc_internal.h"
+#include "thc_lanes.h"
 
 #pragma clang fp contract(off)
 
 namespace thc {
 namespace {
 
-constexpr int kThreads = 512;
-constexpr int kTileLog2 = 14;   // coordinates per workgroup
+using k14::butterflies;
+using k14::kRegs;
 
-// One pass over stages [s0, s0 + m), 1 <= m <= 9, s0 >= 14.  A tile is 512 "rows" of 32
-// consecutive floats; row bit b (b = 0..8) is stage s0 + b - skip for b >= skip = 9 - m
-// and an extension of the column index below that (no butterfly), so that short passes
-// still move whole 128-byte lines.  A thread holds 8 rows x 4 consecutive floats; the
-// three row-bit triples take turns in the registers, with one wave-local and one
-// cross-wave exchange through LDS in 16-byte units (8 consecutive lanes = 128 bytes).
+// One pass over stages [s0, s0 + M), 1 <= M <= 11, s0 >= 14.  A tile is 2^max(M, 6) "rows" of 32
+// consecutive floats (16 for M = 11); row bit b < M is stage s0 + b, row bits M.. of a short pass
+// extend the column index, so that it reads longer runs.  A thread holds 16 rows x 2 consecutive
+// floats (a wave reads four whole 128-byte lines per load, eight halves for M = 11); the rows:
+//   row bits 0..3   the slot of the thread's registers
+//   row bits 4, 5   lane bits 4, 5 (M = 11: row bits 4..6 are lane bits 3..5): they change places
+//                   with slot bit 3 by register swaps between lanes (thc_lanes.h), one after the other
+//   the rest        the wave: it changes places with slot bits 0.. through LDS, once, the two
+//                   floats of a pair in turn so that the buffer takes half the data
+// So passes of up to 6 stages need neither LDS nor barriers: every wave streams by itself, and
+// all others keep 32 waves per CU (64 registers, 64 KB of LDS at most).  Bound by memory (8 bytes per
+// coordinate in place, 4 for the range alone).  The shape before, 8 rows x 4 floats per thread,
+// exchanged twice for every pass through 64 KB of LDS and reached 9 stages, so 2^25 coordinates took
+// 14 + 6 + 5 stages where they now take 14 + 11: resnet50-sized round of 8 workers 1364 -> 1040 us.
 struct HighPassArgs {
     float* data;        // 2^l floats, transformed in place (unless `out`)
     float* out;         // last pass of the inverse: x (n floats); else null
     uint64_t n;         // coordinates to write to `out`
-    uint32_t s0, m;
-    uint32_t last;      // host side: the pass that multiplies by `factor` (a template argument of the kernels)
-    float factor;
+    uint32_t s0;
+    float factor;       // of the last pass
     uint32_t key0, key1;
-    uint64_t valid;     // floats of `data` that hold values; what lies beyond reads as zero and
-                        // is neither read nor, in a pass that is not the last, written (the zero
-                        // padding behind the gradient is implied, pass after pass, until the
-                        // last pass mixes it with everything)
+    uint64_t tiles;
+    uint64_t valid;     // floats of `data` that hold values, a multiple of 2^s0; what lies beyond
+                        // reads as zero and is neither read nor, in a pass that is not the last,
+                        // written (the zero padding behind the gradient is implied, pass after
+                        // pass, until the last pass mixes it with everything)
     uint32_t* absmax;   // last forward pass: receives max |value written| by an unsigned atomic
                         // maximum (zeroed beforehand); may be null
-    // last forward pass evaluated for the quantizer instead of being stored (encode_pass_kernel):
+    // last forward pass evaluated for the quantizer instead of being stored:
     const float* scale; // one float, shared by all workers
     uint32_t levels;    // largest grid index L
     uint32_t worker;
@@ -49,10 +58,305 @@ struct HighPassArgs {
 };
 
 // What a pass does with its results.
-constexpr int kInPlace = 0;    // written back to `data`
-constexpr int kToX = 1;        // inverse direction, last pass: sign diagonal, first n values to `out`
-constexpr int kRangeOnly = 2;  // forward direction, last pass: only their largest magnitude is kept
+enum class Kind : int {
+    InPlace = 0,       // written back to `data`
+    InPlaceLast = 1,   // the same, times `factor`; keeps the largest magnitude if asked
+    ToX = 2,           // inverse direction, last pass: sign diagonal, first n values to `out`
+    RangeOnly = 3,     // forward direction, last pass: only their largest magnitude is kept
+    Encode = 4         // forward direction, last pass: quantized and packed
+};
 
+// Shape of a pass of M stages: bits of the wave's number that are rows, and tiles and waves of a workgroup.
+// Workgroups have up to 8 (M <= 6) or 16 waves and take neighbouring tiles where one tile needs fewer: the
+// rows of a tile lie up to gigabytes apart, so the bytes a workgroup takes from each of them should be many
+// (2^29 coordinates, passes of 8 and 7 stages: 6.23 ms with one tile per workgroup, 5.65 ms like this).
+// A small array has too few tiles for that (2^20 coordinates: 512): there the launch groups fewer.
+constexpr int wave_rows(int M) { return M == 11 ? 4 : M > 6 ? M - 6 : 0; }
+constexpr int pass_tiles(int M) { return M <= 6 ? 8 : M <= 9 ? 16 >> wave_rows(M) : 1; }
+constexpr int pass_waves(int M) { return pass_tiles(M) << wave_rows(M); }
+// Lane bits that are columns (pairs of floats); the others are rows.
+constexpr int column_bits(int M) { return M == 11 ? 3 : 4; }
+
+// Row of slot s in a lane, before the stages ...
+template <int M>
+__device__ __forceinline__ uint32_t row_before(uint32_t s, uint32_t lane, uint32_t wave) {
+    return s | ((lane >> column_bits(M)) << 4) | (wave << (4 + 6 - column_bits(M)));
+}
+// ... and after them: slot bit 3 has changed places with the lane's row bits, one after the other (as far
+// as there are stages for them), slot bits 0.. with the wave's bits.  wave: 0 where waves are independent.
+template <int M>
+__device__ __forceinline__ uint32_t row_after(uint32_t s, uint32_t lane, uint32_t wave) {
+    const uint32_t l4 = (lane >> 4) & 1u, l5 = (lane >> 5) & 1u, top = (s >> 3) & 1u;
+    if constexpr (M <= 4) return s | (l4 << 4) | (l5 << 5);
+    if constexpr (M == 11) return (s << 7) | (wave & 7u) | ((lane >> 3) << 3) | ((wave >> 3) << 6);
+    if constexpr (M == 5) return (s & 7u) | (l4 << 3) | (top << 4) | (l5 << 5);
+    constexpr uint32_t nw = (uint32_t)wave_rows(M), kTraded = (1u << nw) - 1u;
+    const uint32_t mixed = (l4 << 3) | (l5 << 4);
+    if constexpr (nw < 4) {
+        return ((s & kTraded) << 6) | (s & 7u & ~kTraded) | (wave & kTraded) | mixed | (top << 5);
+    } else {
+        return (s << 6) | (wave & 7u) | mixed | ((wave >> 3) << 5);
+    }
+}
+
+// Tile of a workgroup or wave by its place in the launch order: workgroups go to the eight XCDs in turn, so
+// this order gives each XCD one contiguous eighth of the tiles.  Neighbouring tiles write neighbouring
+// 16-byte pieces of the same payload lines, which then meet in one L2 instead of leaving eight of
+// them as partial lines.  (The tiles of a workgroup stay together.)
+__device__ __forceinline__ uint64_t xcd_order(uint64_t place, uint64_t tiles, uint32_t together) {
+    const uint32_t log2 = 31u - (uint32_t)__builtin_clz(together);
+    const uint64_t group = place >> log2, groups = tiles >> log2;
+    if (groups & 7u) return place;
+    return (((group & 7u) * (groups >> 3) + (group >> 3)) << log2) | (place & (together - 1u));
+}
+
+// Where a tile lies.
+template <int M>
+struct Tile {
+    static constexpr uint32_t kExt = M < 6 ? 6u - M : 0u;   // row bits that extend the column
+    uint64_t block;   // first float of the 2^(s0 + M) block it belongs to
+    uint64_t base;    // first float of its row 0
+    uint32_t s0;
+    __device__ __forceinline__ Tile(uint32_t stage0, uint64_t tile) : s0(stage0) {
+        constexpr uint32_t kRowLog2 = (uint32_t)column_bits(M) + 1u + kExt;
+        const uint32_t jb_bits = stage0 - kRowLog2;         // column blocks per 2^s0 run
+        block = (tile >> jb_bits) << (stage0 + M);
+        base = block + ((tile & ((1ull << jb_bits) - 1ull)) << kRowLog2);
+    }
+    __device__ __forceinline__ uint64_t row_start(uint32_t row) const {
+        return base + ((uint64_t)(row & ((1u << M) - 1u)) << s0) + (uint64_t)((row >> M) * 32u);
+    }
+};
+
+// The thread's 16 rows x 2 floats of a tile.
+template <int M>
+__device__ __forceinline__ void load_rows(const HighPassArgs& a, const Tile<M>& T, uint32_t lane, uint32_t wave,
+                                          float2 (&raw)[16]) {
+    const uint32_t jq = lane & ((1u << column_bits(M)) - 1u);
+    // rows of the block that hold values (`valid` and the block are multiples of 2^s0)
+    const uint64_t rows64 = a.valid > T.block ? (a.valid - T.block) >> T.s0 : 0u;
+    const uint32_t rows = rows64 > (1ull << M) ? 1u << M : (uint32_t)rows64;
+    const float* src = a.data + T.row_start(row_before<M>(0u, lane, wave)) + 2u * jq;
+    if (rows == 1u << M) {
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const uint64_t off = ((uint64_t)(s & ((1 << M) - 1)) << T.s0) + (uint64_t)((s >> M) * 32);
+            raw[s] = *reinterpret_cast<const float2*>(src + off);
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const uint64_t off = ((uint64_t)(s & ((1 << M) - 1)) << T.s0) + (uint64_t)((s >> M) * 32);
+            raw[s] = make_float2(0.0f, 0.0f);
+            if ((row_before<M>((uint32_t)s, lane, wave) & ((1u << M) - 1u)) < rows)
+                raw[s] = *reinterpret_cast<const float2*>(src + off);
+        }
+    }
+}
+
+// The stages of the pass on one tile.  `xb`: the workgroup's buffer (M > 6), 16 floats per thread; it is
+// free again at the end.
+template <int M>
+__device__ __forceinline__ void rotate_tile(float (&v)[kRegs], float* xb, uint32_t lane, uint32_t wave) {
+    butterflies<1, (M < 4 ? M : 4) + 1>(v);   // (register bit 0 is the float of the pair, slot bits follow)
+    if constexpr (M == 11) {
+        lanes::swap_top_register_bit<8>(v);
+        butterflies<4, 5>(v);
+    }
+    if constexpr (M > 4) {
+        lanes::swap_top_register_bit<16>(v);
+        butterflies<4, 5>(v);
+    }
+    if constexpr (M > 5) {
+        lanes::swap_top_register_bit<32>(v);
+        butterflies<4, 5>(v);
+    }
+    if constexpr (M > 6) {
+        constexpr int nw = wave_rows(M), kW = 1 << nw, kHigh = 16 >> nw;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+                xb[((((uint32_t)(s & (kW - 1)) * kW + wave) * kHigh) + (s >> nw)) * 64u + lane] = v[2 * s + e];
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+                v[2 * s + e] = xb[(((wave * kW + (uint32_t)(s & (kW - 1))) * kHigh) + (s >> nw)) * 64u + lane];
+            __syncthreads();
+        }
+        butterflies<1, nw + 1>(v);
+    }
+}
+
+// Waves per SIMD the registers must allow: 8 (64 registers), but 4 for the inverse's last pass of 10 and 11
+// stages, whose output addresses and sign words do not fit (44.8 us with the spills, 27.8 us without,
+// 2^24 coordinates) and whose workgroup of 16 waves then has a CU to itself.
+constexpr int pass_waves_per_simd(int M, Kind kind) { return kind == Kind::ToX && M >= 10 ? 4 : 8; }
+
+template <int M, Kind KIND, int BITS>
+__global__ __launch_bounds__(64 * pass_waves(M), pass_waves_per_simd(M, KIND)) void high_pass_kernel(const HighPassArgs a) {
+    constexpr int kWaves = pass_waves(M);
+    constexpr bool kIndependent = M <= 6;
+    constexpr bool kRange = KIND == Kind::RangeOnly || KIND == Kind::InPlaceLast;
+    // exchange of the stages (M > 6) and, inside each wave's 4 KB, of the quantizer's runs
+    __shared__ float4 buf[(M > 6 || KIND == Kind::Encode) ? 256 * kWaves : 1];
+    constexpr uint32_t kTiles = (uint32_t)pass_tiles(M), kTileWaves = (uint32_t)kWaves / kTiles;
+    constexpr uint32_t kRows = M > 6 ? 1u << M : 64u;   // of a tile
+    __shared__ uint32_t signs[KIND == Kind::ToX ? kRows * kTiles : 1];
+    __shared__ uint32_t most[kWaves];
+    const uint32_t t = threadIdx.x, lane0 = t & 63u;
+    const uint32_t wave_all = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    const uint32_t mine_of = wave_all / kTileWaves, wave = wave_all % kTileWaves;   // tile of the workgroup, wave of the tile
+    const uint32_t together = blockDim.x / (64u * kTileWaves);   // tiles of this workgroup, at most kTiles
+    const uint64_t stride = (uint64_t)gridDim.x * together;
+    uint64_t tile = (uint64_t)blockIdx.x * together + mine_of;
+    float largest = 0.0f;
+    for (; tile < a.tiles; tile += stride) {
+        // (row offsets are recomputed from these on every trip: kept across the loop they would take
+        // more registers than the data)
+        uint32_t s0 = a.s0;
+        uint32_t lane = lane0;
+        asm volatile("" : "+s"(s0), "+v"(lane));
+        const uint32_t jq = lane & ((1u << column_bits(M)) - 1u), la = lane >> column_bits(M);
+        const Tile<M> now(s0, (KIND == Kind::Encode || M == 11) ? xcd_order(tile, a.tiles, together) : tile);
+        // a tile mixes values of one block of 2^(s0 + M) floats: if that block lies in the implied
+        // zero padding its results are zero too, and the next pass is told so instead of reading them
+        // (the last pass writes everything: an empty gradient gives zeros).  Tiles are in the order of
+        // their blocks, so all later ones lie there as well (and a workgroup's tiles in the same block).
+        if (KIND == Kind::InPlace && now.block >= a.valid) break;
+        float2 raw[16];
+        load_rows<M>(a, now, lane, wave, raw);
+        float v[kRegs];
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            v[2 * s] = raw[s].x;
+            v[2 * s + 1] = raw[s].y;
+        }
+        uint32_t* sign_of = signs + mine_of * kRows;   // ToX: of this tile's rows
+        if constexpr (KIND == Kind::ToX) {
+            // one sign word per row (32 coordinates; M = 11: half of one): the rows lie far apart, a lane
+            // computes a row's block.  Ordered by the barriers of the exchange, or inside the wave.
+#pragma unroll
+            for (uint32_t r = 0; r < kRows; r += 64u * kTileWaves) {
+                const uint32_t row = r + 64u * wave + lane;
+                const uint64_t g = now.row_start(row);
+                const u32x4 sb = sign_block(g >> 7, a.key0, a.key1);
+                const uint32_t which = (uint32_t)(g >> 5) & 3u;
+                sign_of[row] = (which == 0u ? sb.w[0] : which == 1u ? sb.w[1] : which == 2u ? sb.w[2] : sb.w[3]) >> ((uint32_t)g & 31u);
+            }
+            if constexpr (kIndependent) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        rotate_tile<M>(v, reinterpret_cast<float*>(buf + 256u * kTileWaves * mine_of), lane, wave);
+
+        if constexpr (KIND == Kind::RangeOnly || KIND == Kind::InPlaceLast) {
+#pragma unroll
+            for (int i = 0; i < kRegs; i += 2) {
+                if (KIND == Kind::InPlaceLast) {
+                    v[i] = v[i] * a.factor;
+                    v[i + 1] = v[i + 1] * a.factor;
+                }
+                asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(largest) : "v"(largest), "v"(v[i]), "v"(v[i + 1]));
+            }
+        }
+        if constexpr (KIND == Kind::InPlace || KIND == Kind::InPlaceLast) {
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+                *reinterpret_cast<float2*>(a.data + now.row_start(row_after<M>((uint32_t)s, lane, wave)) + 2u * jq) =
+                    make_float2(v[2 * s], v[2 * s + 1]);
+        } else if constexpr (KIND == Kind::ToX) {
+            // what lies below n, by row and column of the block (32-bit compares): rows before `full`, and of
+            // row `full` the columns before `rest`
+            const uint64_t left = a.n > now.block ? a.n - now.block : 0u;
+            const uint64_t full64 = left >> s0;
+            const uint32_t full = full64 > (1ull << M) ? 1u << M : (uint32_t)full64;
+            const uint32_t rest = full64 > (1ull << M) ? 0u : (uint32_t)(left & ((1ull << s0) - 1ull));
+            const uint32_t col0 = (uint32_t)(now.base - now.block) + 2u * jq;
+            float* out = a.out + now.base + 2u * jq;
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                const uint32_t row = row_after<M>((uint32_t)s, lane, wave);
+                const uint32_t k = row & ((1u << M) - 1u), ext = (row >> M) * 32u;
+                const uint32_t sw = sign_of[row] >> (2u * jq);
+                const float x = __uint_as_float(xor_masked(__float_as_uint(v[2 * s] * a.factor), sw << 31, 0x80000000u));
+                const float y = __uint_as_float(xor_masked(__float_as_uint(v[2 * s + 1] * a.factor), sw << 30, 0x80000000u));
+                float* dst = out + (((uint64_t)k << s0) + ext);
+                if (k < full + (col0 + ext + 2u <= rest ? 1u : 0u)) *reinterpret_cast<float2*>(dst) = make_float2(x, y);
+                else if ((a.n & 1u) && k == full && col0 + ext + 1u == rest) *dst = x;
+            }
+        } else if constexpr (KIND == Kind::Encode) {
+            // exchange inside the wave: 2 floats in each of 8 lanes -> 16 consecutive floats in one lane (run
+            // L of 64), the coordinates of one block of the rounding stream and 2 * BITS payload
+            // bytes; half of the slots at a time.  16-byte unit c of run L at column c ^ (L / 4 mod 4).
+            float4* mine = buf + 256u * wave_all;
+            uint64_t blk[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    const uint32_t L = M == 11 ? 8u * s + la : 8u * s + 2u * la + (jq >> 3);
+                    const uint32_t unit = 4u * L + (((jq >> 1) & 3u) ^ ((L >> 2) & 3u));
+                    reinterpret_cast<float2*>(mine)[2u * unit + (jq & 1u)] = make_float2(v[2 * (8 * h + s)], v[2 * (8 * h + s) + 1]);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const uint32_t from = (M == 11 ? lane & 7u : (lane >> 1) & 3u) << column_bits(M);   // a lane of the run's row
+                blk[h] = (now.row_start(row_after<M>(8u * h + (lane >> 3), from, wave)) >> 4) + (M == 11 ? 0u : lane & 1u);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float4 f = mine[4u * lane + ((uint32_t)i ^ ((lane >> 2) & 3u))];
+                    v[16 * h + 4 * i] = f.x;
+                    v[16 * h + 4 * i + 1] = f.y;
+                    v[16 * h + 4 * i + 2] = f.z;
+                    v[16 * h + 4 * i + 3] = f.w;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+            // same arithmetic and random stream as the fused encoders (quantize_store)
+            constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;
+            const float s = a.scale[0], two = s + s;
+            const bool ranged = two >= kMinRange;
+            const float inv = ranged ? (float)a.levels / two : 0.0f;
+            const float base = (ranged && !kOffset ? 0.5f * (float)a.levels : 0.0f) + 0x1p-9f;
+            uint32_t by[8], pk[BITS];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                k14::quantize_half<BITS, true, false, kOffset>(v, h, blk[h], -s, inv, base, a.levels, a.worker, a.key0,
+                                                               a.key1, by, a.factor);
+            k14::pack_bytes<BITS>(by, pk);
+            uint8_t* d0 = a.payload + blk[0] * (2u * BITS);
+            uint8_t* d1 = a.payload + blk[1] * (2u * BITS);
+            if constexpr (BITS == 8) {
+                *reinterpret_cast<uint4*>(d0) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+                *reinterpret_cast<uint4*>(d1) = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+            } else if constexpr (BITS == 4) {
+                *reinterpret_cast<uint2*>(d0) = make_uint2(pk[0], pk[1]);
+                *reinterpret_cast<uint2*>(d1) = make_uint2(pk[2], pk[3]);
+            } else {
+                *reinterpret_cast<uint32_t*>(d0) = pk[0];
+                *reinterpret_cast<uint32_t*>(d1) = pk[1];
+            }
+        }
+        // the next tile's sign words and exchange overwrite what other waves may still be reading
+        if constexpr (M > 6 && (KIND == Kind::ToX || KIND == Kind::Encode)) __syncthreads();
+    }
+    if constexpr (kRange) {
+        if (a.absmax) {   // (uniform over the grid) non-negative floats order like their bit patterns
+            if (KIND == Kind::RangeOnly) largest = largest * a.factor;   // (monotone: the largest stays the largest)
+            asm volatile("s_nop 1" : "+v"(largest));   // wait states between the assembly's write and a lane exchange
+            uint32_t m = wave_umax(__float_as_uint(largest));
+            if (lane0 == 0) most[wave_all] = m;
+            __syncthreads();
+            if (t == 0) {
+                for (uint32_t w = 0; w < blockDim.x / 64u; ++w) m = most[w] > m ? most[w] : m;
+                // (a stale read only costs an atomic more; most workgroups stay below the running maximum.
+                // One look per workgroup: one per wave, 16384 of them on one address, took longer than
+                // reading 134 MB.)
+                if (m > __hip_atomic_load(a.absmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a.absmax, m);
+            }
+        }
+    }
+}
+
+// ---- quantizer on stored values ------------------------------------------------------------
 // Stochastic rounding of rotated values (already normalised) onto the grid of [-s, s]:
 // same arithmetic and random stream as the fused encoders.
 struct FullQuant {
@@ -102,248 +406,6 @@ __device__ __forceinline__ void quantize_run(const float (&yv)[16], uint64_t blk
         *reinterpret_cast<uint2*>(dst) = make_uint2(pk[0], pk[1]);
     } else {
         *reinterpret_cast<uint32_t*>(dst) = pk[0];
-    }
-}
-
-__device__ __forceinline__ void row_butterflies(float (&v)[32], int bit, bool enabled) {
-    if (!enabled) return;   // uniform over the grid
-    const int h = 1 << bit;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        if ((r & h) == 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float lo = v[4 * r + e], hi = v[4 * (r + h) + e];
-                v[4 * r + e] = lo + hi;
-                v[4 * (r + h) + e] = lo - hi;
-            }
-        }
-    }
-}
-
-// Where a thread's share of a tile lies.
-struct Tile {
-    uint64_t base;
-    uint32_t skip, s0;
-    uint32_t jq, la, w;   // lane & 7, lane >> 3, wave
-    __device__ __forceinline__ uint64_t row_start(uint32_t row) const {   // first float of a row
-        const uint64_t k = row >> skip;
-        const uint32_t jext = row & ((1u << skip) - 1u);
-        return base + (k << s0) + (uint64_t)(jext * 32u);
-    }
-    __device__ __forceinline__ uint64_t offset(uint32_t row) const { return row_start(row) + 4u * jq; }
-};
-// `block` receives the first float of the 2^(s0 + m) block the tile belongs to.
-template <int SKIP>
-__device__ __forceinline__ Tile make_tile(const HighPassArgs& a, uint64_t tile, uint32_t t, uint64_t& block) {
-    Tile T;
-    T.skip = (uint32_t)SKIP;   // = 9 - a.m, a constant of the kernel so that the stage loops are straight-line code
-    T.s0 = a.s0;
-    const uint32_t lane = t & 63u;
-    T.jq = lane & 7u;
-    T.la = lane >> 3;
-    T.w = t >> 6;
-    const uint32_t jb_bits = a.s0 - 5u - T.skip;                  // column blocks per 2^s0 run
-    const uint64_t jb = tile & ((1ull << jb_bits) - 1ull);
-    const uint64_t hi = tile >> jb_bits;
-    block = hi << (a.s0 + a.m);
-    T.base = block + (jb << (5u + T.skip));
-    return T;
-}
-
-// Sixteen bytes of zeros: where rows in the implied padding are read from.
-__device__ const float4 kZeroRow = {0.0f, 0.0f, 0.0f, 0.0f};
-
-// Rows r + 8 la + 64 w, r = 0..7, of the tile: 8 loads back to back.  (A row in the implied
-// padding is loaded from kZeroRow instead: a select of the address, none of the values.)
-__device__ __forceinline__ void load_rows(const HighPassArgs& a, const Tile& T, float4 (&raw)[8]) {
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const uint64_t g = T.offset(r + 8u * T.la + 64u * T.w);   // a multiple of 4, as `valid` is
-        const float4* src = g < a.valid ? reinterpret_cast<const float4*>(a.data + g) : &kZeroRow;
-        raw[r] = *src;
-    }
-}
-__device__ __forceinline__ void take_rows(const float4 (&raw)[8], float (&v)[32]) {
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        v[4 * r] = raw[r].x;
-        v[4 * r + 1] = raw[r].y;
-        v[4 * r + 2] = raw[r].z;
-        v[4 * r + 3] = raw[r].w;
-    }
-}
-
-// The stages of the pass on one tile.  In: rows r + 8 la + 64 w; out: rows la + 8 w + 64 r.
-__device__ __forceinline__ void rotate_tile(const Tile& T, float (&v)[32], float4* xb) {
-    const uint32_t skip = T.skip, la = T.la, jq = T.jq, w = T.w;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) row_butterflies(v, b, (uint32_t)b >= skip);
-
-    // exchange 1, inside the wave's own 512 units: registers <-> lane bits 3..5
-    float4* mine = xb + 512u * w;
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-        mine[(r + 8u * la) * 8u + jq] = make_float4(v[4 * r], v[4 * r + 1], v[4 * r + 2], v[4 * r + 3]);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {   // now: row = la + 8 r + 64 w
-        const float4 q = mine[(la + 8u * r) * 8u + jq];
-        v[4 * r] = q.x;
-        v[4 * r + 1] = q.y;
-        v[4 * r + 2] = q.z;
-        v[4 * r + 3] = q.w;
-    }
-#pragma unroll
-    for (int b = 0; b < 3; ++b) row_butterflies(v, b, (uint32_t)(3 + b) >= skip);
-
-    // exchange 2, across waves: registers <-> wave index
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-        mine[(la + 8u * r) * 8u + jq] = make_float4(v[4 * r], v[4 * r + 1], v[4 * r + 2], v[4 * r + 3]);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {   // now: row = la + 8 w + 64 r
-        const float4 q = xb[512u * r + (la + 8u * w) * 8u + jq];
-        v[4 * r] = q.x;
-        v[4 * r + 1] = q.y;
-        v[4 * r + 2] = q.z;
-        v[4 * r + 3] = q.w;
-    }
-#pragma unroll
-    for (int b = 0; b < 3; ++b) row_butterflies(v, b, (uint32_t)(6 + b) >= skip);
-}
-
-// A workgroup takes two neighbouring tiles (they lie in the same 2^(s0 + m) block); the second
-// one's loads are in flight while the first one is transformed and stored.
-template <int KIND, int SKIP, bool LAST>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void high_pass_kernel(const HighPassArgs a) {
-    constexpr bool TO_X = KIND == kToX;
-    __shared__ float4 xb[4096];
-    const uint32_t t = threadIdx.x, lane = t & 63u;
-    uint64_t block;
-    Tile T = make_tile<SKIP>(a, 2ull * blockIdx.x, t, block);
-    // a tile mixes values of one block of 2^(s0 + m) floats: if that block lies in the implied
-    // zero padding its results are zero too, and the next pass is told so instead of reading them
-    // (the last pass writes everything: an empty gradient gives zeros)
-    if (!LAST && block >= a.valid) return;
-
-    float4 raw[8];
-    load_rows(a, T, raw);
-    float largest = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        float v[32];
-        take_rows(raw, v);
-        const Tile now = T;
-        if (k == 0) {
-            T = make_tile<SKIP>(a, 2ull * blockIdx.x + 1ull, t, block);
-            load_rows(a, T, raw);
-        }
-        rotate_tile(now, v, xb);
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const uint64_t g = now.offset(now.la + 8u * now.w + 64u * (uint32_t)r);
-            float o[4] = {v[4 * r], v[4 * r + 1], v[4 * r + 2], v[4 * r + 3]};
-            if (LAST) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = o[e] * a.factor;
-            }
-            if (!TO_X) {   // (two three-input maxima)
-                largest = fmaxf(fmaxf(largest, fabsf(o[0])), fabsf(o[1]));
-                largest = fmaxf(fmaxf(largest, fabsf(o[2])), fabsf(o[3]));
-            }
-            if constexpr (KIND == kRangeOnly) {
-                (void)g;
-            } else if constexpr (TO_X) {
-                if (g < a.n) {
-                    const u32x4 sb = sign_block(g >> 7, a.key0, a.key1);
-                    const uint32_t bits4 = sb.w[(g >> 5) & 3u] >> (g & 31u);   // g is a multiple of 4
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = flip_sign(o[e], (bits4 >> e) & 1u);
-                    if (g + 4u <= a.n) {
-                        *reinterpret_cast<float4*>(a.out + g) = make_float4(o[0], o[1], o[2], o[3]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (g + e < a.n) a.out[g + e] = o[e];
-                    }
-                }
-            } else {
-                *reinterpret_cast<float4*>(a.data + g) = make_float4(o[0], o[1], o[2], o[3]);
-            }
-        }
-        if (k == 0) {
-            // the second tile's values are first needed here, not where the scheduler would like them;
-            // its first exchange must not overwrite units another wave is still reading
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                asm volatile("" : "+v"(raw[r].x), "+v"(raw[r].y), "+v"(raw[r].z), "+v"(raw[r].w));
-            __syncthreads();
-        }
-    }
-    if (!TO_X && a.absmax) {   // (uniform over the grid) non-negative floats order like their bit patterns
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) largest = fmaxf(largest, __shfl_xor(largest, o, 64));
-        // (a stale read only costs an atomic more; most workgroups stay below the running maximum)
-        if (lane == 0 && __float_as_uint(largest) > __hip_atomic_load(a.absmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(a.absmax, __float_as_uint(largest));
-    }
-}
-
-// The last forward pass evaluated for the quantizer: the results of a tile are quantized and
-// packed instead of being stored (`data` is only read).  A workgroup takes two neighbouring
-// tiles; the second one's loads are in flight while the first one is quantized.
-template <int BITS, int SKIP>
-__global__ __launch_bounds__(kThreads) void encode_pass_kernel(const HighPassArgs a) {
-    __shared__ float4 xb[4096];
-    const uint32_t t = threadIdx.x, lane = t & 63u;
-    uint64_t block;
-    Tile T = make_tile<SKIP>(a, 2ull * blockIdx.x, t, block);
-    float4 raw[8];
-    load_rows(a, T, raw);
-    const FullQuant fq = full_quant(a.scale[0], a.levels);
-    float4* mine = xb + 512u * T.w;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        float v[32];
-        take_rows(raw, v);
-        rotate_tile(T, v, xb);
-        // exchange 3, inside the wave: 4 lanes x 4 floats of a row -> 16 consecutive floats in one
-        // lane, the coordinates of one block of the rounding stream and 2 * BITS payload bytes.
-        __syncthreads();   // every wave has taken its share of exchange 2 out of this wave's units
-#pragma unroll
-        for (int r = 0; r < 8; ++r)   // unit (row of the wave, jq), row of the wave = la + 8 r
-            mine[((uint32_t)r * 8u + T.la) * 8u + T.jq] =
-                make_float4(v[4 * r] * a.factor, v[4 * r + 1] * a.factor, v[4 * r + 2] * a.factor, v[4 * r + 3] * a.factor);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        const Tile now = T;
-        if (k == 0) {
-            T = make_tile<SKIP>(a, 2ull * blockIdx.x + 1ull, t, block);
-            load_rows(a, T, raw);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t run = lane + 64u * (uint32_t)h;   // (row of the wave, half of the row), 0 .. 127
-            const uint32_t rho = run >> 1, half = run & 1u;
-            const uint64_t g = now.row_start((rho & 7u) + 8u * now.w + 64u * (rho >> 3)) + 16u * half;
-            float yv[16];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float4 q = mine[rho * 8u + 4u * half + (uint32_t)i];
-                yv[4 * i] = q.x;
-                yv[4 * i + 1] = q.y;
-                yv[4 * i + 2] = q.z;
-                yv[4 * i + 3] = q.w;
-            }
-            quantize_run<BITS>(yv, g >> 4, fq, a.worker, a.key0, a.key1, a.payload);
-        }
-        if (k == 0) {
-            // the second tile's values are first needed here, not where the scheduler would like them
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                asm volatile("" : "+v"(raw[r].x), "+v"(raw[r].y), "+v"(raw[r].z), "+v"(raw[r].w));
-        }
     }
 }
 
@@ -399,35 +461,61 @@ __global__ __launch_bounds__(256) void full_decode_kernel(const SumT* sums, uint
     *reinterpret_cast<float4*>(yhat + g0) = make_float4(o[0], o[1], o[2], o[3]);
 }
 
-// One instantiation per number of stages of the pass (skip = 9 - m = 0 .. 8).
-template <int KIND, bool LAST>
-void launch_pass(uint32_t skip, dim3 grid, dim3 block, hipStream_t stream, const HighPassArgs& a) {
-    switch (skip) {
-        case 0: hipLaunchKernelGGL((high_pass_kernel<KIND, 0, LAST>), grid, block, 0, stream, a); break;
-        case 1: hipLaunchKernelGGL((high_pass_kernel<KIND, 1, LAST>), grid, block, 0, stream, a); break;
-        case 2: hipLaunchKernelGGL((high_pass_kernel<KIND, 2, LAST>), grid, block, 0, stream, a); break;
-        case 3: hipLaunchKernelGGL((high_pass_kernel<KIND, 3, LAST>), grid, block, 0, stream, a); break;
-        case 4: hipLaunchKernelGGL((high_pass_kernel<KIND, 4, LAST>), grid, block, 0, stream, a); break;
-        case 5: hipLaunchKernelGGL((high_pass_kernel<KIND, 5, LAST>), grid, block, 0, stream, a); break;
-        case 6: hipLaunchKernelGGL((high_pass_kernel<KIND, 6, LAST>), grid, block, 0, stream, a); break;
-        case 7: hipLaunchKernelGGL((high_pass_kernel<KIND, 7, LAST>), grid, block, 0, stream, a); break;
-        default: hipLaunchKernelGGL((high_pass_kernel<KIND, 8, LAST>), grid, block, 0, stream, a); break;
+// ---- launch ------------------------------------------------------------------------------------
+// Workgroups of a kernel that are resident at once.
+template <auto kernel>
+uint32_t resident_grid(int threads) {
+    static uint32_t cached = 0;   // one per kernel
+    if (cached == 0) {
+        int occ = 0, dev = 0;
+        hipDeviceProp_t prop;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, 0) != hipSuccess || occ < 1) return 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+        cached = (uint32_t)(occ * prop.multiProcessorCount);
+    }
+    return cached;
+}
+
+// One tile per workgroup (or independent wave), except for the range, whose workgroups stay so that few of
+// them report.
+template <int M, Kind KIND, int BITS = 4>
+void launch_pass_t(uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
+    constexpr int kFloatsLog2 = (M > 6 ? M : 6) + column_bits(M) + 1;   // of a tile
+    constexpr auto kernel = high_pass_kernel<M, KIND, BITS>;
+    a.tiles = 1ull << (log2_size - kFloatsLog2);
+    uint32_t together = (uint32_t)pass_tiles(M);
+    constexpr bool kReports = KIND == Kind::RangeOnly || KIND == Kind::InPlaceLast;
+    // (two workgroups per CU; half a one where each reports to the same word)
+    while (together > 1u && a.tiles / together < (kReports ? 128u : 512u)) together >>= 1;
+    const uint32_t threads = 64u * together << wave_rows(M);
+    uint64_t grid = a.tiles / together;
+    if (kReports) {
+        const uint32_t resident = resident_grid<kernel>((int)(64 * pass_waves(M)));   // (of full workgroups)
+        if (resident != 0 && grid > resident) grid = resident;
+    }
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)grid), dim3(threads), 0, stream, a);
+}
+template <Kind KIND, int BITS = 4>
+void launch_pass(uint32_t m, uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
+    switch (m) {
+        case 1: launch_pass_t<1, KIND, BITS>(log2_size, stream, a); break;
+        case 2: launch_pass_t<2, KIND, BITS>(log2_size, stream, a); break;
+        case 3: launch_pass_t<3, KIND, BITS>(log2_size, stream, a); break;
+        case 4: launch_pass_t<4, KIND, BITS>(log2_size, stream, a); break;
+        case 5: launch_pass_t<5, KIND, BITS>(log2_size, stream, a); break;
+        case 6: launch_pass_t<6, KIND, BITS>(log2_size, stream, a); break;
+        case 7: launch_pass_t<7, KIND, BITS>(log2_size, stream, a); break;
+        case 8: launch_pass_t<8, KIND, BITS>(log2_size, stream, a); break;
+        case 9: launch_pass_t<9, KIND, BITS>(log2_size, stream, a); break;
+        case 10: launch_pass_t<10, KIND, BITS>(log2_size, stream, a); break;
+        default: launch_pass_t<11, KIND, BITS>(log2_size, stream, a); break;
     }
 }
-template <int BITS>
-void launch_encode_pass(uint32_t skip, dim3 grid, dim3 block, hipStream_t stream, const HighPassArgs& a) {
-    switch (skip) {
-        case 0: hipLaunchKernelGGL((encode_pass_kernel<BITS, 0>), grid, block, 0, stream, a); break;
-        case 1: hipLaunchKernelGGL((encode_pass_kernel<BITS, 1>), grid, block, 0, stream, a); break;
-        case 2: hipLaunchKernelGGL((encode_pass_kernel<BITS, 2>), grid, block, 0, stream, a); break;
-        case 3: hipLaunchKernelGGL((encode_pass_kernel<BITS, 3>), grid, block, 0, stream, a); break;
-        case 4: hipLaunchKernelGGL((encode_pass_kernel<BITS, 4>), grid, block, 0, stream, a); break;
-        case 5: hipLaunchKernelGGL((encode_pass_kernel<BITS, 5>), grid, block, 0, stream, a); break;
-        case 6: hipLaunchKernelGGL((encode_pass_kernel<BITS, 6>), grid, block, 0, stream, a); break;
-        case 7: hipLaunchKernelGGL((encode_pass_kernel<BITS, 7>), grid, block, 0, stream, a); break;
-        default: hipLaunchKernelGGL((encode_pass_kernel<BITS, 8>), grid, block, 0, stream, a); break;
-    }
-}
+
+// Stages of a high pass at most.  11 stages move 64-byte pieces, at about 0.7 of the rate of whole lines,
+// and still beat a pass more (2^25 coordinates, 102 MB of them data: range 31.7 us, payload 42 us,
+// inverse 64 us; as 6 + 5 stages 32 + 22, 33 and 44 + 51 us).
+constexpr uint32_t kMaxStages = 11;
 
 }  // namespace
 
@@ -436,7 +524,7 @@ void launch_encode_pass(uint32_t skip, dim3 grid, dim3 block, hipStream_t stream
 // diagonal and writes the first n coordinates to x instead.  Forward direction: only the
 // first `valid` floats of data have been written (the rest is the zero padding, which the
 // first pass supplies by itself), and `absmax`, if not null, receives the largest
-// magnitude of the result (the word is zeroed here first).  `deferred`, forward direction:
+// magnitude of the result (the word was zeroed by an earlier launch).  `deferred`, forward direction:
 // RangeOnly = the last pass only reports the range and leaves data as the pass before it wrote
 // it; EncodeOnly = only the last pass runs, on such data, and its results go through the
 // quantizer into deferred->payload.
@@ -446,46 +534,39 @@ hipError_t launch_high_passes(float* data, uint32_t log2_size, float factor, flo
     const bool range_only = deferred && deferred->kind == FullLast::RangeOnly;
     const bool encode_only = deferred && deferred->kind == FullLast::EncodeOnly;
     if ((deferred && (x || range_only == encode_only)) || (range_only && !absmax)) return hipErrorInvalidValue;
-    if (absmax) {
-        const hipError_t e = launch_zero_words(reinterpret_cast<uint32_t*>(absmax), 1, stream);
-        if (e != hipSuccess) return e;
-    }
-    const uint32_t high = log2_size - kTileLog2;
-    const uint32_t passes = (high + 8u) / 9u;
-    const dim3 grid((uint32_t)(1ull << (log2_size - kTileLog2 - 1u))), block(kThreads);   // tile pairs (log2_size >= 15)
-    uint32_t s0 = kTileLog2;
+    uint32_t s0 = 14u;
+    const uint32_t passes = (log2_size - s0 + kMaxStages - 1u) / kMaxStages;
     for (uint32_t p = 0; p < passes; ++p) {
         const uint32_t left = log2_size - s0;
         // spread the stages evenly so that no pass is needlessly short
-        const uint32_t m = (left + (passes - p) - 1u) / (passes - p);
+        // (13 = 6 + 7, not 7 + 6: the pass that moves most goes without LDS)
+        const uint32_t m = passes - p == 2u && left == 13u ? 6u : (left + (passes - p) - 1u) / (passes - p);
+        const bool last = p + 1u == passes;
         HighPassArgs a{};
         a.data = data;
         a.s0 = s0;
-        a.m = m;
-        a.last = p + 1u == passes;
         a.factor = factor;
         a.key0 = key0;
         a.key1 = key1;
         a.n = n;
         a.valid = valid;
-        a.absmax = (a.last && !x) ? reinterpret_cast<uint32_t*>(absmax) : nullptr;
-        const uint32_t skip = 9u - m;
-        if (a.last && x) {
+        a.absmax = (last && !x) ? reinterpret_cast<uint32_t*>(absmax) : nullptr;
+        if (last && x) {
             a.out = x;
-            launch_pass<kToX, true>(skip, grid, block, stream, a);
-        } else if (a.last && range_only) {
-            launch_pass<kRangeOnly, true>(skip, grid, block, stream, a);
-        } else if (a.last && encode_only) {
+            launch_pass<Kind::ToX>(m, log2_size, stream, a);
+        } else if (last && range_only) {
+            launch_pass<Kind::RangeOnly>(m, log2_size, stream, a);
+        } else if (last && encode_only) {
             a.scale = deferred->scale;
             a.levels = deferred->levels;
             a.worker = deferred->worker;
             a.payload = deferred->payload;
-            if (deferred->bits == 2) launch_encode_pass<2>(skip, grid, block, stream, a);
-            else if (deferred->bits == 4) launch_encode_pass<4>(skip, grid, block, stream, a);
-            else launch_encode_pass<8>(skip, grid, block, stream, a);
+            if (deferred->bits == 2) launch_pass<Kind::Encode, 2>(m, log2_size, stream, a);
+            else if (deferred->bits == 4) launch_pass<Kind::Encode, 4>(m, log2_size, stream, a);
+            else launch_pass<Kind::Encode, 8>(m, log2_size, stream, a);
         } else if (!encode_only) {
-            if (a.last) launch_pass<kInPlace, true>(skip, grid, block, stream, a);
-            else launch_pass<kInPlace, false>(skip, grid, block, stream, a);
+            if (last) launch_pass<Kind::InPlaceLast>(m, log2_size, stream, a);
+            else launch_pass<Kind::InPlace>(m, log2_size, stream, a);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

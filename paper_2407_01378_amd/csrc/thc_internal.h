@@ -40,6 +40,7 @@ struct ChunkArgs {
     uint32_t out_bf16;      // inverse / decode: 1 = output is bf16 (round to nearest even)
     float inv_sqrt_c;       // fp32 nearest of c^(-1/2)
     uint32_t scale_shared;  // decode: 1 = scale_in is ONE float for all chunks (full rotation)
+    uint32_t* zero_word;    // forward: null, or a device word that the launch sets to zero
 };
 
 // Generic path: any chunk_log2 in [1, 14], any alignment the ABI allows.

@@ -80,13 +80,16 @@ __device__ __forceinline__ void lane_stage(float (&v)[kRegs], float s) {
 }
 #undef THC_LANE_FMAC8
 
-// Register bit 4 <-> lane bit 4 (SWAP 16) or lane bit 5 (SWAP 32).
+// Register bit 4 <-> lane bit 3 (SWAP 8), 4 (SWAP 16) or 5 (SWAP 32).
 template <int SWAP>
 __device__ __forceinline__ void swap_top_register_bit(float (&v)[kRegs]) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const uint32_t a = __float_as_uint(v[r]), b = __float_as_uint(v[r + 16]);
-        if constexpr (SWAP == 16) {
+        if constexpr (SWAP == 8) {   // rotation by 8 within a row of 16 = lane ^ 8, written in half of the lanes
+            v[r] = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)a, (int)b, 0x128, 0xF, 0xC, false));
+            v[r + 16] = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)b, (int)a, 0x128, 0xF, 0x3, false));
+        } else if constexpr (SWAP == 16) {
             const auto q = __builtin_amdgcn_permlane16_swap(a, b, false, false);
             v[r] = __uint_as_float(q[0]);
             v[r + 16] = __uint_as_float(q[1]);

@@ -59,52 +59,6 @@ struct SmallArgs {
 // Coordinate ranges by chunk size: CLASS 0: l <= 9, 1: l = 10, 11, 2: l = 12, 13.
 constexpr int class_of(uint32_t l) { return l <= 9 ? 0 : l <= 11 ? 1 : 2; }
 
-// The upper half of one wave's registers against the lower half of the other's (whose number
-// differs in bit PART of the wave's part): register bit 4 <-> that bit.  `upper`: this wave has
-// the bit set.  Ends with a barrier: the buffer may be rewritten.
-__device__ __forceinline__ void trade_halves(float (&v)[kRegs], float4* mine, const float4* theirs, bool upper,
-                                             uint32_t lane) {
-    // (the empty assembly statements differ, so the two branches are not merged into one that picks
-    // its registers by address, which would put v into memory)
-    if (upper) {
-        asm volatile("; upper wave" ::: "memory");
-#pragma unroll
-        for (int q = 0; q < 4; ++q) mine[q * 64 + lane] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        asm volatile("; upper wave sent" ::: "memory");
-    } else {
-        asm volatile("; lower wave" ::: "memory");
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            mine[q * 64 + lane] = make_float4(v[16 + 4 * q], v[17 + 4 * q], v[18 + 4 * q], v[19 + 4 * q]);
-        asm volatile("; lower wave sent" ::: "memory");
-    }
-    __syncthreads();
-    if (upper) {
-        asm volatile("; upper wave" ::: "memory");
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 f = theirs[q * 64 + lane];
-            v[4 * q] = f.x;
-            v[4 * q + 1] = f.y;
-            v[4 * q + 2] = f.z;
-            v[4 * q + 3] = f.w;
-        }
-        asm volatile("; upper wave has" ::: "memory");
-    } else {
-        asm volatile("; lower wave" ::: "memory");
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 f = theirs[q * 64 + lane];
-            v[16 + 4 * q] = f.x;
-            v[17 + 4 * q] = f.y;
-            v[18 + 4 * q] = f.z;
-            v[19 + 4 * q] = f.w;
-        }
-        asm volatile("; lower wave has" ::: "memory");
-    }
-    __syncthreads();
-}
-
 template <bool BF16, int CLASS, int BITS, SmallOp OP>
 __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const SmallArgs a, const FusedWorkerPtrs ptrs) {
     constexpr int kUnits = BF16 ? 4 : 8;
