@@ -9,6 +9,7 @@
 #pragma once
 
 #include "thc_device.h"
+#include "thc_lanes.h"
 #include "thc_layout14.h"
 
 #pragma clang fp contract(off)
@@ -341,13 +342,50 @@ __device__ __forceinline__ void rotate_l1_to_l3(Shared& sh, float (&v)[kRegs], u
     rotate_l1_to_l3<PRIO>(sh, v, lane, wave, none);
 }
 
+// The same rotation from layout L1 with the lanes of each wave permuted (thread 64 wave + lane owns the
+// 32 coordinates of block 64 wave + block_of_lane(lane)): stages 5..8 run between the lanes, so the
+// chunk passes LDS once on the way to layout L3.  The exchange uses the map of the last one (X3e) in the
+// opposite direction: a wave stores to its own 8 KB, a thread of layout L3 reads 32 words which it alone
+// then rewrites in X3e, and X3e's readers take back exactly what they stored here.  So the whole
+// item needs two barriers, one behind each set of stores, where the maps X1, X2, X3e needed five.
+// On return a value is negated where lane_negation() of its coordinate's bits i5..i8 says so.
+__device__ __forceinline__ bool odd_parity4(uint32_t x) { return (0x6996u >> (x & 15u)) & 1u; }
+template <bool PRIO>
+__device__ __forceinline__ void rotate_lanes_to_l3(Shared& sh, float (&v)[kRegs], uint32_t lane, uint32_t block,
+                                                   uint32_t wave) {
+    set_prio<PRIO, kPrioRotateEarly>();
+    butterflies<0, 5>(v);          // strides 1..16
+    lanes::lane_stage<0>(v, (block & 1u) ? -1.0f : 1.0f);   // strides 32..256
+    lanes::lane_stage<1>(v, (block & 2u) ? -1.0f : 1.0f);
+    lanes::lane_stage<2>(v, (block & 4u) ? -1.0f : 1.0f);
+    lanes::lane_stage<3>(v, (block & 8u) ? -1.0f : 1.0f);
+    set_prio<PRIO, kPrioExchange>();
+    float4* units = reinterpret_cast<float4*>(sh.xb);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        units[lay14::x3e_load_unit(wave, block, q)] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRegs; ++r) v[r] = sh.xb[lay14::x3e_store(wave, lane, r)];
+    set_prio<PRIO, kPrioRotateLate>();
+    butterflies<0, 5>(v);          // strides 512..8192
+}
+// L3 -> L4e with permuted lanes, behind rotate_lanes_to_l3 (one barrier).
+template <bool PRIO>
+__device__ __forceinline__ void l3_to_l4e_lanes(Shared& sh, float (&v)[kRegs], uint32_t lane, uint32_t block, uint32_t wave) {
+    set_prio<PRIO, kPrioExchange>();
+    x3e_store(sh, v, lane, wave);
+    __syncthreads();
+    x3e_load(sh, v, block, wave);
+    set_prio<PRIO, kPrioTail>();
+}
+
 // max |v| over this thread's registers, then over the wave.
 __device__ __forceinline__ float wave_absmax(const float (&v)[kRegs]) {
     float m = 0.0f;
 #pragma unroll
     for (int i = 0; i < kRegs; i += 2)
         asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(v[i]), "v"(v[i + 1]));
-    asm volatile("s_nop 1" : "+v"(m));   // wait states between the assembly's write and a lane exchange
     // m >= 0: floats of one sign order like their bit patterns
     return __uint_as_float(wave_umax(__float_as_uint(m)));
 }
@@ -530,14 +568,16 @@ __device__ __forceinline__ void pack_bytes(const uint32_t (&by)[8], uint32_t (&p
             pk[d] = by[4 * d] | (by[4 * d + 1] << 2) | (by[4 * d + 2] << 4) | (by[4 * d + 3] << 6);
     }
 }
-template <int BITS, bool CLAMP, bool FOLD, bool RANGED>
+template <int BITS, bool CLAMP, bool FOLD, bool RANGED, bool NEG = false>
 __device__ __forceinline__ void quantize_pack(const float (&v)[kRegs], float sub, float mul, float base,
                                               uint32_t L, uint64_t g, uint32_t worker, uint32_t key0,
-                                              uint32_t key1, uint32_t (&pk)[BITS]) {
+                                              uint32_t key1, uint32_t (&pk)[BITS], float norm = kInvSqrtC,
+                                              float sgn = 1.0f) {
     uint32_t by[8];                       // index bytes; by[m] serves payload word m / kSub
 #pragma unroll
     for (int half = 0; half < 2; ++half)
-        quantize_half<BITS, CLAMP, FOLD, RANGED>(v, half, (g >> 4) + half, sub, mul, base, L, worker, key0, key1, by);
+        quantize_half<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, (g >> 4) + half, sub, mul, base, L, worker, key0, key1, by,
+                                                      norm, sgn);
     pack_bytes<BITS>(by, pk);
 }
 
@@ -559,10 +599,11 @@ __device__ __forceinline__ void store_packed(const uint32_t (&pk)[BITS], uint8_t
 // grids t = fma(y + s, inv, u), which is the ranged form with sub = -s.  The clamp stays
 // dead there too when s is the chunk's largest magnitude: 0 <= y + s <= 2 s, and
 // 2 s * inv <= L (1 + 2^-24), so t < L + 255.5/256 + L 2^-24 < L + 1.
-template <int BITS, bool CLAMP>
+// NEG: the thread's values are negated where sgn = -1 (see rotate_lanes_to_l3); t: its block of 32.
+template <int BITS, bool CLAMP, bool NEG = false>
 __device__ __forceinline__ void quantize_store(const float (&v)[kRegs], float s, uint32_t L, uint64_t g0,
                                                uint32_t worker, uint32_t key0, uint32_t key1,
-                                               uint8_t* payload, uint32_t t) {
+                                               uint8_t* payload, uint32_t t, float sgn = 1.0f) {
     constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;   // both grids of this width
     const float two = s + s;
     const bool ranged = two >= kMinRange;   // false: an all-zero chunk, or one too small for L / two
@@ -572,9 +613,11 @@ __device__ __forceinline__ void quantize_store(const float (&v)[kRegs], float s,
     const uint64_t g = g0 + (uint64_t)t * 32u;
     uint32_t pk[BITS];   // 32 coordinates * BITS bits = BITS dwords
     if (s >= 0x1p-100f && s <= 0x1p100f)   // the same for every thread of the workgroup
-        quantize_pack<BITS, CLAMP, true, kOffset>(v, -128.0f * s, inv * kInvSqrtC, base, L, g, worker, key0, key1, pk);
+        quantize_pack<BITS, CLAMP, true, kOffset, NEG>(v, -128.0f * s, inv * (NEG && !kOffset ? kInvSqrtC * sgn : kInvSqrtC),
+                                                       base, L, g, worker, key0, key1, pk, kInvSqrtC, sgn);
     else
-        quantize_pack<BITS, CLAMP, false, kOffset>(v, -s, inv, base, L, g, worker, key0, key1, pk);
+        quantize_pack<BITS, CLAMP, false, kOffset, NEG>(v, -s, inv, base, L, g, worker, key0, key1, pk,
+                                                        NEG ? kInvSqrtC * sgn : kInvSqrtC, sgn);
     store_packed<BITS>(pk, payload + (g * BITS) / 8u);
 }
 
@@ -584,12 +627,13 @@ __device__ __forceinline__ void quantize_store(const float (&v)[kRegs], float s,
 template <int BITS, bool ROTATED = true, bool CLAMP = true>
 __device__ __forceinline__ void quantize_store_range(const float (&v)[kRegs], float lo, float hi, uint32_t L,
                                                      uint64_t g0, uint32_t worker, uint32_t key0,
-                                                     uint32_t key1, uint8_t* payload, uint32_t t) {
+                                                     uint32_t key1, uint8_t* payload, uint32_t t,
+                                                     float norm = kInvSqrtC) {
     const float width = hi - lo;
     const float inv = width >= kMinRange ? (float)L / width : 0.0f;
     const uint64_t g = g0 + (uint64_t)t * 32u;
     uint32_t pk[BITS];
-    quantize_pack<BITS, CLAMP, !ROTATED, true>(v, lo, inv, 0x1p-9f, L, g, worker, key0, key1, pk);
+    quantize_pack<BITS, CLAMP, !ROTATED, true>(v, lo, inv, 0x1p-9f, L, g, worker, key0, key1, pk, norm);
     store_packed<BITS>(pk, payload + (g * BITS) / 8u);
 }
 

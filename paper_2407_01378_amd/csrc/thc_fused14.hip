@@ -81,6 +81,7 @@ struct EncodeAllCtx {
     Shared& sh;
     Raw<kUnits> raw;        // input of the next item to enter the pipeline, in flight
     uint32_t t, lane, wave, nwords;
+    uint32_t block, tp;     // the lane's block of 32 coordinates in the wave (thc_lanes.h), in the chunk
     uint32_t w;             // worker of every item of this workgroup (the grid is a multiple of W)
     uint32_t dp;            // chunk stride between consecutive items of this workgroup
     uint32_t parity;        // which sign table the next front() reads
@@ -127,7 +128,7 @@ struct EncodeAllCtx {
         if (left > (uint64_t)kChunk) left = kChunk;
         uint64_t addr = reinterpret_cast<uint64_t>(bv.grad) + (p < a.chunks ? g0 * kElem : 0u);
         if constexpr (ODD) {
-            if (left != 0u) load_raw<kUnits, kElem, kDirect>(raw, reinterpret_cast<const void*>(addr), (uint32_t)left, t);
+            if (left != 0u) load_raw<kUnits, kElem, kDirect>(raw, reinterpret_cast<const void*>(addr), (uint32_t)left, tp);
         } else {
             // the descriptor is the same for every lane: it belongs in scalar registers
             addr = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32) |
@@ -138,7 +139,8 @@ struct EncodeAllCtx {
             typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 #pragma unroll
             for (int j = 0; j < kUnits; ++j) {
-                const uint32_t unit = kDirect ? kUnits * t + j : j * kThreads + t;
+                // fp32: the wave's own 8 KB in coalesced order, dealt out through its part of the buffer
+                const uint32_t unit = kDirect ? kUnits * tp + j : wave * 512u + j * 64u + lane;
                 const u4v q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, unit * 16u, 0, 0);
                 raw.u[j] = make_uint4(q.x, q.y, q.z, q.w);
             }
@@ -154,34 +156,37 @@ struct EncodeAllCtx {
     // which is read only after the barriers of this item's exchanges.
     __device__ __forceinline__ void front(float (&v)[kRegs], uint64_t p) {
         const bool more = p + dp < a.chunks;
-        if (kDirect) {
-            units_to_l1<kUnits, true>(sh.sign[parity], raw.u, v, t);
-            // the conversion is complete before the registers of `raw` are loaded again: without
-            // this the compiler moves it below the loads and copies `raw` out of their way
-#pragma unroll
-            for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));
-            asm volatile("" ::: "memory");
-            if (BATCH && more && p + dp >= boundary) nxt = view_of(p + dp);   // rarely: a new bucket
-            load(p + dp, nxt);
-            if (more) fill_signs(p + dp, nxt, parity ^ 1u);
-            parity ^= 1u;
+        if constexpr (kDirect) {
+            units_to_l1<kUnits, true>(sh.sign[parity], raw.u, v, tp);
         } else {
             load(p, cur);
-            __syncthreads();   // the previous item's last reads of the buffer and table are done
-            fill_signs(p, cur, 0u);
-            raw_to_lds<kUnits>(sh, raw, t);
-            __syncthreads();
-            lds_to_l1<kUnits, true>(sh, sh.sign[0], v, t);
-            if (BATCH && more && p + dp >= boundary) nxt = view_of(p + dp);
+            uint4* stage = reinterpret_cast<uint4*>(sh.xb) + 512u * wave;
+#pragma unroll
+            for (int j = 0; j < kUnits; ++j) stage[lay14::stage_unit((uint32_t)j * 64u + lane)] = raw.u[j];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            uint4 unit[kUnits];
+#pragma unroll
+            for (int k = 0; k < kUnits; ++k) unit[k] = stage[lay14::stage_unit(8u * block + k)];
+            units_to_l1<kUnits, true>(sh.sign[parity], unit, v, tp);
         }
-        rotate_l1_to_l3<true>(sh, v, lane, wave);
+        // the conversion is complete before the registers of `raw` are loaded again: without
+        // this the compiler moves it below the loads and copies `raw` out of their way
+#pragma unroll
+        for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));
+        asm volatile("" ::: "memory");
+        if (BATCH && more && p + dp >= boundary) nxt = view_of(p + dp);   // rarely: a new bucket
+        if (kDirect) load(p + dp, nxt);
+        if (more) fill_signs(p + dp, nxt, parity ^ 1u);
+        parity ^= 1u;
+        rotate_lanes_to_l3<true>(sh, v, lane, block, wave);
         // One word per wave, value | valid bit (non-negative floats order like their bit
         // patterns and leave bit 31 free).  The words travel between workgroups only
         // through device-scope stores and loads, which are served at the memory side, so
         // no cache write-back or invalidate is needed.  The slots start zeroed.
         if constexpr (MINMAX) {
             // (the scaling by 2^-7 is exact and monotone: it commutes with min and max)
-            const MinMax r = thread_minmax(v);
+            MinMax r = thread_minmax(v);
+            if (odd_parity4((lane & 3u) | ((wave >> 1) << 2))) r = MinMax{-r.hi, -r.lo};   // (i5, i6, i7, i8)
             const uint32_t khi = wave_umax(order_key(r.hi * kInvSqrtC));
             const uint32_t klo = wave_umax(order_key(-(r.lo * kInvSqrtC)));
             // one 8-byte word per wave, (key of the maximum) << 32 | key of the negated minimum:
@@ -192,7 +197,7 @@ struct EncodeAllCtx {
         } else if constexpr (WGWORD) {
             const float m = wave_absmax(v) * kInvSqrtC;
             if (lane == 0) sh.red[wave] = m;
-            // l3_to_l4e with the publication behind its first barrier
+            // l3_to_l4e_lanes with the publication behind a barrier in front
             __syncthreads();
             set_prio<true, kPrioExchange>();
             if (wave == 0 && lane == 0) {
@@ -203,7 +208,7 @@ struct EncodeAllCtx {
             }
             x3e_store(sh, v, lane, wave);
             __syncthreads();
-            x3e_load(sh, v, lane, wave);
+            x3e_load(sh, v, block, wave);
             set_prio<true, kPrioTail>();
             return;
         } else {
@@ -213,7 +218,7 @@ struct EncodeAllCtx {
                                    __float_as_uint(m) | 0x80000000u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
-        l3_to_l4e<true>(sh, v, lane, wave);
+        l3_to_l4e_lanes<true>(sh, v, lane, block, wave);
     }
 
     // Back half: wait until every wave of every worker of the chunk has published, take
@@ -290,6 +295,7 @@ struct EncodeAllCtx {
         const uint32_t sbits = wave_umax(mx);
         prev = (uint32_t)p;
         const uint64_t pl = p - cur.chunk0;   // the chunk's number inside its bucket
+        const float sgn = odd_parity4(block) ? -1.0f : 1.0f;   // the thread's values are negated
         if constexpr (MINMAX) {
             // (after an expired wait a word may be missing; zero then stands for "nothing seen")
             const uint32_t lbits = wave_umax(mx2);
@@ -302,15 +308,16 @@ struct EncodeAllCtx {
             }
             // (no clamp: lo and hi are the chunk's own extremes, see quantize_pack)
             quantize_store_range<BITS, true, false>(v, lo, hi, a.levels, pl << kChunkLog2, w, cur.key0, cur.key1,
-                                             global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), t);
+                                             global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), tp,
+                                             kInvSqrtC * sgn);
             return;
         }
         const float s = __uint_as_float(sbits);
         // (the view's pointers are re-tagged as global here: in a batched launch they come out of
         // the look-up's register barrier as plain addresses)
         if (w == 0 && t == 0) global_ptr<float>(reinterpret_cast<uint64_t>(cur.scale))[pl] = s;
-        quantize_store<BITS, false>(v, s, a.levels, pl << kChunkLog2, w, cur.key0, cur.key1,
-                                    global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), t);
+        quantize_store<BITS, false, true>(v, s, a.levels, pl << kChunkLog2, w, cur.key0, cur.key1,
+                                          global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), tp, sgn);
     }
 
     // After the workgroup's last item: its words have no later chunk to vouch for them, so
@@ -347,8 +354,9 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     using Ctx = EncodeAllCtx<BF16, ODD, BATCH, MINMAX, WGWORD>;
     const uint32_t t = threadIdx.x;
     const uint32_t p0 = blockIdx.x / a.W;
-    Ctx c{a, ptrs, batch, sh, {}, t, t & 63u, t >> 6, (MINMAX ? 2u : 1u) * Ctx::kWordsPerWorker * a.W, blockIdx.x - p0 * a.W,
-          gridDim.x / a.W, 0u, Ctx::kNone, 0u, 0u, {}, {}};
+    const uint32_t block = lanes::block_of_lane(t & 63u);
+    Ctx c{a, ptrs, batch, sh, {}, t, t & 63u, t >> 6, (MINMAX ? 2u : 1u) * Ctx::kWordsPerWorker * a.W, block,
+          (t & ~63u) | block, blockIdx.x - p0 * a.W, gridDim.x / a.W, 0u, Ctx::kNone, 0u, 0u, {}, {}};
     if (p0 >= a.chunks) return;
     // With more than one round of items, the second half of the grid starts about 2.6 us late
     // (6 x 1024 clocks; the halves are cut between chunks, so all workgroups of a chunk lie in
@@ -358,12 +366,12 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     if (a.chunks > c.dp && p0 >= (c.dp >> 1))
         for (int i = 0; i < kStaggerSleeps; ++i) __builtin_amdgcn_s_sleep(16);
     c.cur = c.nxt = c.view_of(p0);
+    if (Ctx::kDirect) c.load(p0, c.cur);
+    c.fill_signs(p0, c.cur, 0u);
+    __syncthreads();
+    // the first chunk's input has arrived before the loop is entered, as every later
+    // chunk's has by the time its item starts (see the end of the wait in back())
     if (Ctx::kDirect) {
-        c.load(p0, c.cur);
-        c.fill_signs(p0, c.cur, 0u);
-        __syncthreads();
-        // the first chunk's input has arrived before the loop is entered, as every later
-        // chunk's has by the time its item starts (see the end of the wait in back())
 #pragma unroll
         for (int j = 0; j < Ctx::kUnits; ++j)
             asm volatile("" : "+v"(c.raw.u[j].x), "+v"(c.raw.u[j].y), "+v"(c.raw.u[j].z), "+v"(c.raw.u[j].w));

@@ -20,6 +20,7 @@
 #pragma once
 
 #include "thc_device.h"
+#include "thc_layout14.h"
 
 #pragma clang fp contract(off)
 
@@ -28,11 +29,7 @@ namespace lanes {
 
 constexpr int kRegs = 32;
 
-// Bits i5..i10 of the block a lane owns.
-__device__ __forceinline__ uint32_t block_of_lane(uint32_t lane) {
-    const uint32_t b2 = (lane >> 2) & 1u, b3 = (lane >> 3) & 1u;
-    return lane ^ b2 ^ (b2 << 1) ^ (b3 << 2);
-}
+using lay14::block_of_lane;
 
 // The inline assembly hides its register accesses from the compiler's hazard recognizer: a
 // lane exchange may read a register two wait states after it was written at the earliest, so

@@ -37,6 +37,18 @@
 namespace thc {
 namespace lay14 {
 
+// ---- lanes of a wave with the butterfly stages 5..8 between them (thc_lanes.h) ----------------
+// Bits i5..i10 of the block of 32 coordinates that a lane owns: i5 = l0^l2, i6 = l1^l2, i7 = l2^l3,
+// i8 = l3, i9 = l4, i10 = l5, so that the exchanges between lanes l and l ^ 1, l ^ 2, l ^ 7, l ^ 15 flip
+// exactly one of i5..i8.  In this order X3e is used in both directions: layout L1 stores to the units
+// it later loads, and a thread of layout L3 loads the words it later stores.
+THC_HD uint32_t block_of_lane(uint32_t lane) {
+    const uint32_t b2 = (lane >> 2) & 1u, b3 = (lane >> 3) & 1u;
+    return lane ^ b2 ^ (b2 << 1) ^ (b3 << 2);
+}
+// fp32 input of one wave (512 units of 16 bytes): where unit u is kept; lane order in, block order out.
+THC_HD uint32_t stage_unit(uint32_t u) { return u ^ ((u >> 4) & 7u); }
+
 // ---- E0: raw input units (16 bytes each) from load order to L1 order -------------------
 // Load order: thread t (0..511), round j holds unit 512 j + t.  L1 order: thread T needs
 // units per*T .. per*T + per-1 (per = 4 for bf16: 8 coordinates a unit; 8 for fp32: 4 a unit).

@@ -196,17 +196,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             }
             units_to_l1<kUnits, true>(sx, raw.u, v);
         } else {
-            // unit u of the wave at u ^ swz(u), swz = (u >> 4) & 7: 128-bit stores and loads both
-            // reach all columns (the readers that are served together differ in all of block's low bits)
 #pragma unroll
-            for (int j = 0; j < kUnits; ++j) {
-                const uint32_t u = (uint32_t)j * 64u + lane;
-                stage[u ^ ((u >> 4) & 7u)] = raw.u[j];
-            }
+            for (int j = 0; j < kUnits; ++j) stage[lay14::stage_unit((uint32_t)j * 64u + lane)] = raw.u[j];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             uint4 unit[kUnits];
 #pragma unroll
-            for (int k = 0; k < kUnits; ++k) unit[k] = stage[8u * block + ((uint32_t)k ^ ((block >> 1) & 7u))];
+            for (int k = 0; k < kUnits; ++k) unit[k] = stage[lay14::stage_unit(8u * block + k)];
             units_to_l1<kUnits, true>(sx, unit, v);
         }
 #pragma unroll
