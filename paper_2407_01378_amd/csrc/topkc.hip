@@ -55,13 +55,6 @@ __device__ __forceinline__ void load8(const void* grad, uint64_t g, uint64_t n, 
     }
 }
 
-// Squared norm of every chunk of C = 8 * lanes_per_chunk coordinates: squares in fp32,
-// summed as a balanced tree over adjacent pairs (inside the thread, then across lanes
-// 1, 2, 4, ... apart), rounded to fp16.  Group k (8 coordinates) belongs to thread k mod T of
-// a grid of T threads; a thread takes four groups T apart per trip, loaded before any is
-// used (streaming loads, the gradient is read once), so a wave keeps 4 KB in flight.  T is a
-// multiple of 64 and the loop bounds are too: the lanes of a wave stay together, which the
-// lane exchanges need.
 template <bool BF16>
 __device__ __forceinline__ void raw8(const void* grad, uint64_t g, uint64_t n, uint4 (&q)[2]) {
     // whole groups only; BF16: one 16-byte unit, fp32: two
@@ -87,41 +80,67 @@ __device__ __forceinline__ void widen8(const uint4 (&q)[2], float (&x)[8]) {
         for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(w[e]);
     }
 }
+// The value of the lane N above, within a row of 16 lanes (0 past the row's end).
+template <int N>
+__device__ __forceinline__ float from_lane_above(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x100 + N, 0xF, 0xF, true));
+}
+// Adds up over the chunk's lanes, adjacent pairs first; the sum is whole in the chunk's lowest
+// lane, the only one that stores it.
 __device__ __forceinline__ void norm_of_group(const float (&x)[8], uint64_t k, uint64_t groups,
-                                              uint32_t lanes_per_chunk, uint16_t* norms) {
+                                              uint32_t lanes_per_chunk, uint32_t lanes_log2, uint16_t* norms) {
     float s[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) s[e] = x[e] * x[e];
     float t = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
-    for (uint32_t o = 1; o < lanes_per_chunk; o <<= 1) t = t + __shfl_xor(t, (int)o, 64);
+    if (lanes_per_chunk > 1u) t = t + from_lane_above<1>(t);
+    if (lanes_per_chunk > 2u) t = t + from_lane_above<2>(t);
+    if (lanes_per_chunk > 4u) t = t + from_lane_above<4>(t);
+    if (lanes_per_chunk > 8u) t = t + from_lane_above<8>(t);
+    if (lanes_per_chunk > 16u) t = t + __shfl_down(t, 16, 64);
+    if (lanes_per_chunk > 32u) t = t + __shfl_down(t, 32, 64);
     if (k < groups && (k & (uint64_t)(lanes_per_chunk - 1u)) == 0)
-        norms[k / lanes_per_chunk] = (uint16_t)f32_to_f16_bits(t);
+        norms[k >> lanes_log2] = (uint16_t)f32_to_f16_bits(t);
 }
+
+// Squared norm of every chunk of C = 8 * lanes_per_chunk coordinates: squares in fp32,
+// summed as a balanced tree over adjacent pairs (inside the thread, then across lanes
+// 1, 2, 4, ... apart), rounded to fp16.  Bound by reading the gradient once, so what counts is
+// bytes in flight: a workgroup takes a tile of kNormUnroll x 256 groups of 8 coordinates, and a
+// thread loads its kNormUnroll groups (256 apart: whole lines per wave) before it uses any.
+// Measured (launches of a round, every gradient another): 108 M bf16, C = 64: 44.8 -> 34.4 us (6.3 TB/s)
+// against one group per thread and trip of a grid-wide stride, which kept one load in flight up to
+// 200 M coordinates; on one buffer again and again: 7 M bf16 8.9 -> 3.5 us, 1 G bf16 345 -> 323 us.  Two groups per
+// thread: 331 us at 1 G, eight: 329 us, and 5 % slower than four on fp32.
+constexpr int kNormUnroll = 4;
 template <bool BF16>
 __global__ __launch_bounds__(256) void norms_kernel(const void* grad, uint64_t n, uint32_t lanes_per_chunk,
-                                                    uint64_t groups, uint16_t* norms) {
-    const uint64_t T = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t whole = (n / 8u) & ~63ull;   // groups below this are complete, in complete waves
-    uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; k - (k & 63u) + 3u * T + 64u <= whole; k += 4u * T) {
-        uint4 q[4][2];
+                                                    uint32_t lanes_log2, uint64_t groups, uint64_t tiles,
+                                                    uint16_t* norms) {
+    constexpr uint64_t kTile = kNormUnroll * 256u;
+    const uint64_t whole = n / 8u;   // groups below this are complete
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const uint64_t k = tile * kTile + threadIdx.x;
+        if ((tile + 1u) * kTile <= whole) {
+            uint4 q[kNormUnroll][2];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) raw8<BF16>(grad, (k + u * T) * 8u, n, q[u]);
+            for (int u = 0; u < kNormUnroll; ++u) raw8<BF16>(grad, (k + u * 256u) * 8u, n, q[u]);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float x[8];
-            widen8<BF16>(q[u], x);
-            norm_of_group(x, k + u * T, groups, lanes_per_chunk, norms);
+            for (int u = 0; u < kNormUnroll; ++u) {
+                float x[8];
+                widen8<BF16>(q[u], x);
+                norm_of_group(x, k + u * 256u, groups, lanes_per_chunk, lanes_log2, norms);
+            }
+        } else {   // the gradient ends in this tile: the element-wise loader; all lanes stay for the exchanges
+#pragma unroll 1
+            for (int u = 0; u < kNormUnroll; ++u) {
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+                if (k + u * 256u < groups) load8<BF16>(grad, (k + u * 256u) * 8u, n, x);
+                norm_of_group(x, k + u * 256u, groups, lanes_per_chunk, lanes_log2, norms);
+            }
         }
-    }
-    // the rest, a group per trip, with the element-wise loader where the gradient ends
-    const uint64_t bound = (groups + 63u) & ~63ull;
-    for (; k < bound; k += T) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = 0.0f;
-        if (k < groups) load8<BF16>(grad, k * 8u, n, x);
-        norm_of_group(x, k, groups, lanes_per_chunk, norms);
     }
 }
 
@@ -482,8 +501,7 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_dense_kernel(
     }
 }
 
-// Largest grid of the norm kernel, in blocks of 256 threads (measured on a 2.6 GB gradient:
-// 2048 .. 16384 blocks read at 4.8 .. 5.4 TB/s, 32768 and 65536 at 5.7, 262144 at 5.5).
+// Largest grid of the norm kernel, in blocks of 256 threads.
 constexpr uint64_t kNormBlocks = 32768;
 
 uint32_t blocks_for(uint64_t threads, uint32_t per_block) {
@@ -497,14 +515,13 @@ hipError_t launch_topkc_norms(const void* grad, bool bf16, uint64_t n, uint32_t 
     const uint64_t P = (n + C - 1) / C;
     const uint64_t threads = P * (C / 8u);
     if (threads == 0) return hipSuccess;
-    // (a thread per group while that is at most kNormBlocks blocks, grid-stride beyond)
-    uint64_t blocks = blocks_for(threads, 256);
-    if (blocks > kNormBlocks) blocks = kNormBlocks;
-    const dim3 grid((uint32_t)blocks), block(256);
+    const uint64_t tiles = (threads + kNormUnroll * 256u - 1) / (kNormUnroll * 256u);
+    const dim3 grid((uint32_t)(tiles < kNormBlocks ? tiles : kNormBlocks)), block(256);
+    const uint32_t lanes = C / 8u, lanes_log2 = 31u - (uint32_t)__builtin_clz(lanes);
     if (bf16)
-        hipLaunchKernelGGL(norms_kernel<true>, grid, block, 0, stream, grad, n, C / 8u, threads, norms);
+        hipLaunchKernelGGL(norms_kernel<true>, grid, block, 0, stream, grad, n, lanes, lanes_log2, threads, tiles, norms);
     else
-        hipLaunchKernelGGL(norms_kernel<false>, grid, block, 0, stream, grad, n, C / 8u, threads, norms);
+        hipLaunchKernelGGL(norms_kernel<false>, grid, block, 0, stream, grad, n, lanes, lanes_log2, threads, tiles, norms);
     return hipGetLastError();
 }
 
