@@ -173,20 +173,72 @@ __global__ __launch_bounds__(256) void sum_norms4_kernel(const uint16_t* norms_a
 // Workspace words: [0,256) histogram of the keys' high bytes, [256,512) histogram of the
 // low bytes inside the threshold bucket, [512] threshold bucket, [513] still to take
 // inside it, [514] threshold key T, [515] how many keys equal to T are taken, then per
-// segment of kSegment keys the pair (keys above T, keys equal to T), scanned in place.
+// segment of kSegment keys the pair (keys above T, keys equal to T).
+// The keys are a few MB, so a launch and a chain of dependent loads cost more than the bytes: the
+// walk over a histogram is done by every wave of the kernel that needs its result (256 words from
+// L2) and block 0 notes the result for the kernels after it.
+// Measured, five launches in the place of nine: 2048 keys 28.9 -> 13.7 us, 1.7 M 38.0 -> 30.7, 20.3 M 174 -> 106.
 constexpr uint32_t kSegment = 2048;
 constexpr uint32_t kHdr = 516;
 
-// PASS 0: histogram of key >> 8.  PASS 1: of key & 255 among keys with key >> 8 == ws[512].
+// One wave walks a 256-bin histogram from the top: the largest bin b whose count together
+// with the counts above it reaches `want` (bin 0 if none does), and the count above it.
+// Lane i holds bins 4 i .. 4 i + 3.  All 64 lanes call it; all get the result.
+struct Found {
+    uint32_t bin, above;
+};
+__device__ __forceinline__ Found find_bin(const uint32_t* hist, uint32_t want) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t* bins = hist + 4u * lane;   // (the workspace is only 4-byte aligned)
+    const uint4 c = make_uint4(bins[0], bins[1], bins[2], bins[3]);
+    const uint32_t tot = c.x + c.y + c.z + c.w;
+    uint32_t suf = tot;   // -> this lane's bins and all above them
+#pragma unroll
+    for (uint32_t o = 1; o < 64u; o <<= 1) {
+        const uint32_t y = __shfl_down(suf, o, 64);
+        if (lane + o < 64u) suf += y;
+    }
+    const uint32_t s4 = suf - tot;   // everything above bin 4 lane + 3
+    const uint32_t s3 = s4 + c.w, s2 = s3 + c.z, s1 = s2 + c.y, s0 = s1 + c.x;
+    int best = -1;
+    uint32_t above = 0;
+    if (s3 >= want) { best = 3; above = s4; }
+    else if (s2 >= want) { best = 2; above = s3; }
+    else if (s1 >= want) { best = 1; above = s2; }
+    else if (s0 >= want) { best = 0; above = s1; }
+    const unsigned long long found = __ballot(best >= 0);
+    Found r = {0u, (uint32_t)__shfl(s1, 0, 64)};   // nothing reaches `want`: bin 0, as the walk from the top would end
+    if (found != 0ull) {
+        const int winner = 63 - __builtin_clzll(found);
+        r.bin = 4u * (uint32_t)winner + (uint32_t)__shfl(best, winner, 64);
+        r.above = __shfl(above, winner, 64);
+    }
+    return r;
+}
+
+// PASS 0: histogram of key >> 8.  PASS 1: of key & 255 among keys in the bucket in which the
+// J-th largest key lies (block 0 notes the bucket and how many to take inside it).
 // VEC (s 16-byte aligned): a thread takes 8 consecutive keys per load and adds runs of equal
 // bins with one LDS atomic each (norms that underflow to zero, or lie in one bucket, come in
 // runs); the keys past the last whole group of 8 are left to the first block.
+// A round's keys lie in a few tens of bins: kCopies histograms, one per lane modulo kCopies and
+// an odd number of words apart, keep the lanes of a wave off one LDS word.
+constexpr uint32_t kCopies = 16;
 template <int PASS, bool VEC>
-__global__ __launch_bounds__(256) void hist_kernel(const uint16_t* s, uint64_t P, uint32_t* ws) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0u;
+__global__ __launch_bounds__(256) void hist_kernel(const uint16_t* s, uint64_t P, uint32_t J, uint32_t* ws) {
+    __shared__ uint32_t copies[kCopies * 257u];
+    for (uint32_t i = threadIdx.x; i < kCopies * 257u; i += 256u) copies[i] = 0u;
+    uint32_t bucket = 0u;
+    if (PASS == 1) {
+        const Found f = find_bin(ws, J);
+        bucket = f.bin;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ws[512] = f.bin;
+            ws[513] = J - f.above;   // still to take inside the bucket (>= 1)
+        }
+    }
     __syncthreads();
-    const uint32_t bucket = PASS == 1 ? ws[512] : 0u;
+    uint32_t* h = copies + (threadIdx.x & (kCopies - 1u)) * 257u;
     auto bin_of = [&](uint32_t key) -> int {
         if (PASS == 0) return (int)(key >> 8);
         return (key >> 8) == bucket ? (int)(key & 255u) : -1;
@@ -196,7 +248,7 @@ __global__ __launch_bounds__(256) void hist_kernel(const uint16_t* s, uint64_t P
     if (VEC) {
         const uint64_t groups = P / 8u;
         for (uint64_t g = tid; g < groups; g += stride) {
-            const uint4 q = load_last_use(reinterpret_cast<const uint4*>(s) + g);
+            const uint4 q = reinterpret_cast<const uint4*>(s)[g];
             const uint32_t w[4] = {q.x, q.y, q.z, q.w};
             int cur = -1;
             uint32_t cnt = 0;
@@ -224,75 +276,67 @@ __global__ __launch_bounds__(256) void hist_kernel(const uint16_t* s, uint64_t P
         }
     }
     __syncthreads();
-    const uint32_t c = h[threadIdx.x];
+    uint32_t c = 0u;
+#pragma unroll
+    for (uint32_t i = 0; i < kCopies; ++i) c += copies[i * 257u + threadIdx.x];
     if (c) atomicAdd(&ws[256 * PASS + threadIdx.x], c);
 }
 
-// One wave walks the 256-bin histogram from the top: the largest bin b whose count together
-// with the counts above it reaches `want` (bin 0 if none does), and the count above it.
-// PASS 0: finds the bucket in which the J-th largest key lies.  PASS 1: finds the key itself
-// and how many of its equals to take.  Lane i holds bins 4 i .. 4 i + 3.
-template <int PASS>
-__global__ __launch_bounds__(64) void find_kernel(uint32_t* ws, uint32_t J) {
-    if (blockIdx.x != 0) return;
-    const uint32_t lane = threadIdx.x;
-    const uint32_t want = PASS == 0 ? J : ws[513];
-    const uint32_t* bins = ws + 256 * PASS + 4u * lane;   // (the workspace is only 4-byte aligned)
-    const uint4 c = make_uint4(bins[0], bins[1], bins[2], bins[3]);
-    const uint32_t tot = c.x + c.y + c.z + c.w;
-    uint32_t suf = tot;   // -> this lane's bins and all above them
-    for (uint32_t o = 1; o < 64u; o <<= 1) {
-        const uint32_t y = __shfl_down(suf, o, 64);
-        if (lane + o < 64u) suf += y;
-    }
-    const uint32_t s4 = suf - tot;   // everything above bin 4 lane + 3
-    const uint32_t s3 = s4 + c.w, s2 = s3 + c.z, s1 = s2 + c.y, s0 = s1 + c.x;
-    int best = -1;
-    uint32_t above = 0;
-    if (s3 >= want) { best = 3; above = s4; }
-    else if (s2 >= want) { best = 2; above = s3; }
-    else if (s1 >= want) { best = 1; above = s2; }
-    else if (s0 >= want) { best = 0; above = s1; }
-    const unsigned long long found = __ballot(best >= 0);
-    uint32_t b = 0, ab = __shfl(s1, 0, 64);   // nothing reaches `want`: bin 0, as the walk from the top would end
-    if (found != 0ull) {
-        const int winner = 63 - __builtin_clzll(found);
-        b = 4u * (uint32_t)winner + (uint32_t)__shfl(best, winner, 64);
-        ab = __shfl(above, winner, 64);
-    }
-    if (lane == 0) {
-        if (PASS == 0) {
-            ws[512] = b;
-            ws[513] = want - ab;          // still to take inside bucket b (>= 1)
-        } else {
-            ws[514] = (ws[512] << 8) | b;
-            ws[515] = want - ab;          // keys equal to T that are taken (>= 1)
+// The 8 keys of segment `base` that belong to this thread, index order = (thread, k) order, two to a word;
+// past the end: 0 (and not counted by the callers).
+template <bool VEC>
+__device__ __forceinline__ void load_keys(const uint16_t* s, uint64_t P, uint64_t base, uint32_t (&w)[4]) {
+    const uint64_t p = base + 8u * threadIdx.x;
+    if (VEC && p + 8u <= P) {
+        const uint4 q = *reinterpret_cast<const uint4*>(s + p);
+        w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+    } else {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t lo = p + 2 * d < P ? s[p + 2 * d] : 0u;
+            const uint32_t hi = p + 2 * d + 1 < P ? s[p + 2 * d + 1] : 0u;
+            w[d] = lo | (hi << 16);
         }
     }
 }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
 
+// Finds the threshold key (block 0 notes it and how many of its equals to take) and counts, per
+// segment, the keys above it and equal to it.
+template <bool VEC>
 __global__ __launch_bounds__(256) void seg_count_kernel(const uint16_t* s, uint64_t P, uint32_t* ws) {
-    __shared__ uint32_t cnt[2];
-    if (threadIdx.x < 2) cnt[threadIdx.x] = 0u;
-    __syncthreads();
-    const uint32_t T = ws[514];
+    __shared__ uint32_t wave_cnt[4];
     const uint64_t base = (uint64_t)blockIdx.x * kSegment;
-    uint32_t above = 0, equal = 0;
-    for (uint32_t i = threadIdx.x; i < kSegment; i += 256u) {
-        const uint64_t p = base + i;
-        if (p < P) {
-            const uint32_t key = s[p];
-            above += key > T;
-            equal += key == T;
-        }
+    uint32_t w[4];
+    load_keys<VEC>(s, P, base, w);
+    const uint32_t want = ws[513];
+    const Found f = find_bin(ws + 256, want);
+    const uint32_t T = (ws[512] << 8) | f.bin;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ws[514] = T;
+        ws[515] = want - f.above;   // keys equal to T that are taken (>= 1)
     }
-    if (above) atomicAdd(&cnt[0], above);
-    if (equal) atomicAdd(&cnt[1], equal);
+    uint32_t both = 0;   // above | equal << 16, at most kSegment each
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t key = (w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
+        if (base + 8u * threadIdx.x + k < P) both += (key > T ? 1u : 0u) + (key == T ? 0x10000u : 0u);
+    }
+    both = wave_sum(both);
+    if ((threadIdx.x & 63u) == 0) wave_cnt[threadIdx.x >> 6] = both;
     __syncthreads();
-    if (threadIdx.x < 2) ws[kHdr + 2u * blockIdx.x + threadIdx.x] = cnt[threadIdx.x];
+    if (threadIdx.x == 0) {
+        both = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
+        ws[kHdr + 2u * blockIdx.x] = both & 0xFFFFu;
+        ws[kHdr + 2u * blockIdx.x + 1u] = both >> 16;
+    }
 }
 
-// Exclusive scan of the per-segment pairs, one workgroup (segments are few: P / 2048).
+// Exclusive scan of the per-segment pairs, one workgroup: for more than kOwnPrefix segments.
 __global__ __launch_bounds__(1024) void seg_scan_kernel(uint32_t* ws, uint32_t segments) {
     __shared__ uint32_t wave_tot[2][16];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
@@ -336,56 +380,75 @@ __global__ __launch_bounds__(1024) void seg_scan_kernel(uint32_t* ws, uint32_t s
 
 // Ordered compaction: chunk p is selected if its key is above T, or equal to T with fewer
 // than `need` equal keys before it; its place is (#above before) + min(#equal before, need).
+// SCANNED: the pairs are scanned already; else a workgroup adds up those before its own.  Up to
+// kOwnPrefix segments (4 M keys) that is at most 8 loads per thread, out of L2, in the place of a launch.
+constexpr uint32_t kOwnPrefix = 2048;
+template <bool VEC, bool SCANNED>
 __global__ __launch_bounds__(256) void write_indices_kernel(const uint16_t* s, uint64_t P, const uint32_t* ws,
                                                             uint32_t* indices) {
-    __shared__ uint32_t wave_tot[2][4];
-    const uint32_t T = ws[514], need = ws[515];
+    __shared__ uint32_t wave_tot[2][4], wave_pre[2][4];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint64_t base = (uint64_t)blockIdx.x * kSegment;
-    uint32_t above_before = ws[kHdr + 2u * blockIdx.x], equal_before = ws[kHdr + 2u * blockIdx.x + 1u];
-    // a thread owns 8 consecutive keys, so index order = (thread, k) order
-    uint32_t key[8];
-    uint32_t a = 0, e = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint64_t p = base + 8u * threadIdx.x + k;
-        key[k] = p < P ? (uint32_t)s[p] : 0xFFFFFFFFu;   // sentinel: neither above (masked) nor equal
-        if (p < P) {
-            a += key[k] > T;
-            e += key[k] == T;
+    uint32_t w[4];
+    load_keys<VEC>(s, P, base, w);
+    const uint32_t T = ws[514], need = ws[515];
+    uint32_t above_before = 0, equal_before = 0;
+    if (SCANNED) {
+        above_before = ws[kHdr + 2u * blockIdx.x];
+        equal_before = ws[kHdr + 2u * blockIdx.x + 1u];
+    } else {
+        uint32_t pa = 0, pe = 0;
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 256u) {
+            pa += ws[kHdr + 2u * i];
+            pe += ws[kHdr + 2u * i + 1u];
+        }
+        pa = wave_sum(pa);
+        pe = wave_sum(pe);
+        if (lane == 0) {
+            wave_pre[0][wave] = pa;
+            wave_pre[1][wave] = pe;
         }
     }
-    // exclusive scan of (a, e) over the 256 threads
-    uint32_t ia = a, ie = e;
+    // this thread's keys above T and equal to it, a bit each
+    uint32_t is_above = 0, is_equal = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t key = (w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
+        if (base + 8u * threadIdx.x + k < P) {
+            is_above |= (key > T ? 1u : 0u) << k;
+            is_equal |= (key == T ? 1u : 0u) << k;
+        }
+    }
+    // exclusive scan of (above | equal << 16) over the 256 threads: at most kSegment each
+    const uint32_t own = (uint32_t)__popc(is_above) | ((uint32_t)__popc(is_equal) << 16);
+    uint32_t inc = own;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t ua = __shfl_up(ia, o, 64), ue = __shfl_up(ie, o, 64);
-        if (lane >= (uint32_t)o) {
-            ia += ua;
-            ie += ue;
-        }
+        const uint32_t u = __shfl_up(inc, o, 64);
+        if (lane >= (uint32_t)o) inc += u;
     }
     if (lane == 63) {
-        wave_tot[0][wave] = ia;
-        wave_tot[1][wave] = ie;
+        wave_tot[0][wave] = inc & 0xFFFFu;
+        wave_tot[1][wave] = inc >> 16;
     }
     __syncthreads();
-    for (uint32_t w = 0; w < wave; ++w) {
-        above_before += wave_tot[0][w];
-        equal_before += wave_tot[1][w];
+    if (!SCANNED) {
+        above_before = wave_pre[0][0] + wave_pre[0][1] + wave_pre[0][2] + wave_pre[0][3];
+        equal_before = wave_pre[1][0] + wave_pre[1][1] + wave_pre[1][2] + wave_pre[1][3];
     }
-    above_before += ia - a;
-    equal_before += ie - e;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint64_t p = base + 8u * threadIdx.x + k;
-        if (p < P) {
-            const bool is_above = key[k] > T, is_equal = key[k] == T;
-            if (is_above || (is_equal && equal_before < need))
-                indices[above_before + min(equal_before, need)] = (uint32_t)p;
-            above_before += is_above;
-            equal_before += is_equal;
-        }
+    for (uint32_t v = 0; v < wave; ++v) {
+        above_before += wave_tot[0][v];
+        equal_before += wave_tot[1][v];
+    }
+    above_before += (inc - own) & 0xFFFFu;
+    equal_before += (inc - own) >> 16;
+    for (uint32_t left = is_above | is_equal; left != 0u; left &= left - 1u) {
+        const uint32_t bit = left & (0u - left);
+        const bool eq = (is_equal & bit) != 0u;
+        if (!eq || equal_before < need)
+            indices[above_before + min(equal_before, need)] =
+                (uint32_t)(base + 8u * threadIdx.x) + (uint32_t)__builtin_ctz(bit);
+        if (eq) ++equal_before; else ++above_before;
     }
 }
 
@@ -539,23 +602,29 @@ uint64_t topkc_select_workspace_words(uint64_t P) {
     return kHdr + 2u * ((P + kSegment - 1) / kSegment);
 }
 
+template <bool VEC>
+static void select_kernels(const uint16_t* s, uint64_t P, uint32_t J, uint32_t* indices, uint32_t* ws,
+                           uint32_t segments, hipStream_t stream) {
+    uint32_t hb = blocks_for(P, 256 * 16);
+    if (hb > 1024) hb = 1024;
+    hipLaunchKernelGGL((hist_kernel<0, VEC>), dim3(hb), dim3(256), 0, stream, s, P, J, ws);
+    hipLaunchKernelGGL((hist_kernel<1, VEC>), dim3(hb), dim3(256), 0, stream, s, P, J, ws);
+    hipLaunchKernelGGL(seg_count_kernel<VEC>, dim3(segments), dim3(256), 0, stream, s, P, ws);
+    if (segments <= kOwnPrefix) {
+        hipLaunchKernelGGL((write_indices_kernel<VEC, false>), dim3(segments), dim3(256), 0, stream, s, P, ws, indices);
+    } else {
+        hipLaunchKernelGGL(seg_scan_kernel, dim3(1), dim3(1024), 0, stream, ws, segments);
+        hipLaunchKernelGGL((write_indices_kernel<VEC, true>), dim3(segments), dim3(256), 0, stream, s, P, ws, indices);
+    }
+}
+
 hipError_t launch_topkc_select(const uint16_t* s, uint64_t P, uint32_t J, uint32_t* indices, uint32_t* ws,
                                hipStream_t stream) {
     const uint32_t segments = (uint32_t)((P + kSegment - 1) / kSegment);
     hipError_t e = launch_zero_words(ws, kHdr, stream);
     if (e != hipSuccess) return e;
-    uint32_t hb = blocks_for(P, 256 * 16);
-    if (hb > 2048) hb = 2048;
-    const bool vec = (reinterpret_cast<uintptr_t>(s) & 15u) == 0;
-    if (vec) hipLaunchKernelGGL((hist_kernel<0, true>), dim3(hb), dim3(256), 0, stream, s, P, ws);
-    else hipLaunchKernelGGL((hist_kernel<0, false>), dim3(hb), dim3(256), 0, stream, s, P, ws);
-    hipLaunchKernelGGL(find_kernel<0>, dim3(1), dim3(64), 0, stream, ws, J);
-    if (vec) hipLaunchKernelGGL((hist_kernel<1, true>), dim3(hb), dim3(256), 0, stream, s, P, ws);
-    else hipLaunchKernelGGL((hist_kernel<1, false>), dim3(hb), dim3(256), 0, stream, s, P, ws);
-    hipLaunchKernelGGL(find_kernel<1>, dim3(1), dim3(64), 0, stream, ws, J);
-    hipLaunchKernelGGL(seg_count_kernel, dim3(segments), dim3(256), 0, stream, s, P, ws);
-    hipLaunchKernelGGL(seg_scan_kernel, dim3(1), dim3(1024), 0, stream, ws, segments);
-    hipLaunchKernelGGL(write_indices_kernel, dim3(segments), dim3(256), 0, stream, s, P, ws, indices);
+    if ((reinterpret_cast<uintptr_t>(s) & 15u) == 0) select_kernels<true>(s, P, J, indices, ws, segments, stream);
+    else select_kernels<false>(s, P, J, indices, ws, segments, stream);
     return hipGetLastError();
 }
 
