@@ -370,7 +370,8 @@ __device__ __forceinline__ void rotate_lanes_to_l3(Shared& sh, float (&v)[kRegs]
     set_prio<PRIO, kPrioRotateLate>();
     butterflies<0, 5>(v);          // strides 512..8192
 }
-// L3 -> L4e with permuted lanes, behind rotate_lanes_to_l3 (one barrier).
+// L3 -> L4e with permuted lanes, behind rotate_lanes_to_l3 (one barrier); v then holds the 32 coordinates
+// of the thread's block.
 template <bool PRIO>
 __device__ __forceinline__ void l3_to_l4e_lanes(Shared& sh, float (&v)[kRegs], uint32_t lane, uint32_t block, uint32_t wave) {
     set_prio<PRIO, kPrioExchange>();
@@ -457,16 +458,6 @@ __device__ __forceinline__ float order_value(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
-// L3 -> L4e through the buffer (two barriers); v then holds coordinates 32 t .. 32 t + 31.
-template <bool PRIO>
-__device__ __forceinline__ void l3_to_l4e(Shared& sh, float (&v)[kRegs], uint32_t lane, uint32_t wave) {
-    __syncthreads();
-    set_prio<PRIO, kPrioExchange>();
-    x3e_store(sh, v, lane, wave);
-    __syncthreads();
-    x3e_load(sh, v, lane, wave);
-    set_prio<PRIO, kPrioTail>();
-}
 // L3 -> L4d: v[4 h + e] is coordinate 2048 h + 4 t + e.
 template <bool PRIO>
 __device__ __forceinline__ void l3_to_l4d(Shared& sh, float (&v)[kRegs], uint32_t lane, uint32_t wave) {
