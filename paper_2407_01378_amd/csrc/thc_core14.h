@@ -348,7 +348,7 @@ __device__ __forceinline__ void rotate_l1_to_l3(Shared& sh, float (&v)[kRegs], u
 // opposite direction: a wave stores to its own 8 KB, a thread of layout L3 reads 32 words which it alone
 // then rewrites in X3e, and X3e's readers take back exactly what they stored here.  So the whole
 // item needs two barriers, one behind each set of stores, where the maps X1, X2, X3e needed five.
-// On return a value is negated where lane_negation() of its coordinate's bits i5..i8 says so.
+// On return a value is negated where its coordinate's bits i5..i8 have odd parity (odd_parity4).
 __device__ __forceinline__ bool odd_parity4(uint32_t x) { return (0x6996u >> (x & 15u)) & 1u; }
 template <bool PRIO>
 __device__ __forceinline__ void rotate_lanes_to_l3(Shared& sh, float (&v)[kRegs], uint32_t lane, uint32_t block,
