@@ -349,7 +349,9 @@ int thc_sat_aggregate_decode(const uint8_t* const* payloads, uint32_t W, const f
  * zero-padded gradient itself (no sign diagonal, no butterflies, no normalisation).
  * Payloads and sums have the formats of thc_encode / thc_aggregate (use thc_aggregate). */
 
-/* range[2p], range[2p+1] = min, max over chunk p of one worker's y. */
+/* range[2p], range[2p+1] = min, max over chunk p of one worker's y.  With rotate != 0 a rotated
+ * value that is exactly zero counts as +0, so that the range's bits do not depend on the order in
+ * which a kernel takes the partners of a stage. */
 int thc_chunk_minmax(const void* grad, thc_dtype dt, uint64_t n, uint32_t chunk_log2, uint64_t seed,
                      int rotate, float* range, void* stream);
 

@@ -435,6 +435,12 @@ __device__ __forceinline__ MinMax chunk_minmax(Shared& sh, const float (&v)[kReg
     return MinMax{lo, hi};
 }
 
+// An end of a rotated chunk's range, from the unnormalised extreme.  An exact zero counts as +0: its
+// sign would depend on the order of the partners in the last subtraction that gave it (the lane
+// exchanges undo a negation, which turns +0 into -0), and the range is the same bit for bit in all
+// forms of the call.
+__device__ __forceinline__ float rotated_end(float x) { return (x + 0.0f) * kInvSqrtC; }
+
 // (min, max) over this thread's registers.
 __device__ __forceinline__ MinMax thread_minmax(const float (&v)[kRegs]) {
     float lo = v[0], hi = v[0];

@@ -18,7 +18,7 @@ namespace {
 // one chunk's chain of loads, exchanges and barriers, not a throughput.  Absmax and Encode therefore
 // run stages 5..8 between lanes (rotate_lanes_to_l3): one exchange less, three barriers instead
 // of six up to the range.  Forward keeps the LDS maps (its layout L4d has no form with permuted lanes, and
-// long calls of it are bound by memory: 6 TB/s), and MinMax does (a zero's sign reaches the range).
+// long calls of it are bound by memory: 6 TB/s); MinMax keeps them too, the lanes have not been timed there.
 // Measured at 7 M bf16 (433 chunks): range 8.0 -> 6.5 us, 8-bit encode 11.1 -> 9.4; per-call round of
 // eight workers 177 -> 154 us.
 template <bool BF16, Mode MODE, int BITS>
@@ -64,8 +64,8 @@ __global__ __launch_bounds__(kThreads) void per_worker_kernel(const ChunkArgs a)
     } else if constexpr (MODE == Mode::MinMax) {
         const MinMax r = chunk_minmax(sh, v, lane, wave);
         if (t == 0) {
-            static_cast<float*>(a.out)[2 * p] = r.lo * kInvSqrtC;
-            static_cast<float*>(a.out)[2 * p + 1] = r.hi * kInvSqrtC;
+            static_cast<float*>(a.out)[2 * p] = rotated_end(r.lo);
+            static_cast<float*>(a.out)[2 * p + 1] = rotated_end(r.hi);
         }
     } else if (a.range_in) {   // Encode on the min/max grid
         const float lo = a.range_in[2 * p], hi = a.range_in[2 * p + 1];

@@ -187,8 +187,8 @@ struct EncodeAllCtx {
             // (the scaling by 2^-7 is exact and monotone: it commutes with min and max)
             MinMax r = thread_minmax(v);
             if (odd_parity4((lane & 3u) | ((wave >> 1) << 2))) r = MinMax{-r.hi, -r.lo};   // (i5, i6, i7, i8)
-            const uint32_t khi = wave_umax(order_key(r.hi * kInvSqrtC));
-            const uint32_t klo = wave_umax(order_key(-(r.lo * kInvSqrtC)));
+            const uint32_t khi = wave_umax(order_key(rotated_end(r.hi)));
+            const uint32_t klo = wave_umax(order_key(-rotated_end(r.lo)));
             // one 8-byte word per wave, (key of the maximum) << 32 | key of the negated minimum:
             // an aligned 8-byte store is one transaction, so a reader sees both or neither
             if (lane == 0)

@@ -148,7 +148,10 @@ __global__ __launch_bounds__(kThreads) void generic_kernel(const ChunkArgs a) {
     }
     if (rotate) {
 #pragma unroll
-        for (int j = 0; j < kEpt; ++j) v[j] = v[j] * a.inv_sqrt_c;
+        for (int j = 0; j < kEpt; ++j) {
+            if constexpr (MODE == Mode::MinMax) v[j] = v[j] + 0.0f;   // an exact zero counts as +0 in a range
+            v[j] = v[j] * a.inv_sqrt_c;
+        }
     }
 
     if constexpr (MODE == Mode::Forward) {

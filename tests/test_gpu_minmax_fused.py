@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import paper_2407_01378_amd as thc
+from oracle import thc as O
 from oracle import thc_minmax as M
 from synth import to_numpy_bits
 
@@ -115,6 +116,46 @@ def test_one_pass_minmax_constant_and_zero_chunks():
     assert torch.equal(got["out"], xs[0])
     got = run_fused([torch.zeros(n, device=DEV) for _ in range(W)], 1, bits, True)
     assert int(got["range"].abs().max().item()) == 0 and int(got["out"].abs().max().item()) == 0
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rotate", [True, False])
+def test_one_pass_minmax_zeros_have_the_sign_that_the_per_step_calls_give_them(rotate, dtype):
+    """Ranges bit for bit (== does not tell -0 from 0): all-zero chunks of either sign, chunks that
+    rotate into one value and zeros (the sign diagonal itself, and its negative), and zeros whose
+    signs add up to a -0."""
+    W, c, seed = 3, 1 << 14, 29
+    n = 7 * c + 4001                                       # the ragged end is all zeros
+    diagonal = 1.0 - 2.0 * torch.from_numpy(O.sign_bits(0, n, seed).astype(np.float32)).to(DEV)
+    xs = []
+    for w in range(W):
+        x = torch.zeros(n, device=DEV)
+        x[c:2 * c] = diagonal[c:2 * c]
+        x[2 * c:3 * c] = -diagonal[2 * c:3 * c]
+        x[3 * c:4 * c] = -0.0
+        x[4 * c:5 * c] = diagonal[4 * c:5 * c] * -0.0
+        x[5 * c:6 * c] = _rand(c, torch.float32, 70 + w)
+        xs.append(x.to(dtype))
+    print(f"minmax signs of zeros rotate={rotate} dtype={dtype}", flush=True)
+    got = run_fused(xs, seed, 4, rotate)
+    ref = run_minmax(xs, L14, seed, 4, rotate, torch.float32)
+    same = got["range"].view(torch.int32) == ref["range"].view(torch.int32)
+    assert bool(same.all()), (got["range"].tolist(), ref["range"].tolist())
+    for w in range(W):
+        assert torch.equal(got["payloads"][w], ref["payloads"][w])
+    assert torch.equal(got["out"].view(torch.int32), ref["out"].view(torch.int32))
+    if rotate:
+        zeros = got["range"].view(torch.int32)[[0, 3, 4, 6, 7]]
+        assert int(zeros.abs().max()) == 0, got["range"].tolist()
+        # a gradient at an odd address (other kernels), and the chunk sizes that only they take
+        odd = torch.empty(n + 1, dtype=dtype, device=DEV)[1:].copy_(xs[0])
+        for l in (14, 9):
+            per = 2 * thc.thc_num_chunks(n, l)
+            a, b = torch.empty(per, device=DEV), torch.empty(per, device=DEV)
+            thc.thc_chunk_minmax(xs[0], l, seed, True, a)
+            thc.thc_chunk_minmax(odd, l, seed, True, b)
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+            assert not bool((a.view(torch.int32) == -(1 << 31)).any())
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
