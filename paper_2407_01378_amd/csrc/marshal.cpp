@@ -91,7 +91,14 @@ struct Args {
     }
     uint64_t u64(int i) { return ok ? as_u64(a[i]) : 0u; }
     uint32_t u32(int i) { return (uint32_t)u64(i); }
-    bool truth(int i) { return ok && PyObject_IsTrue(a[i]) == 1; }
+    bool truth(int i) {
+        const int t = ok ? PyObject_IsTrue(a[i]) : 0;
+        if (t < 0) {   // (it has none, an array of several elements for instance)
+            PyErr_Clear();
+            ok = false;
+        }
+        return t == 1;
+    }
     void* stream(int i) {
         if (!ok) return nullptr;
         if (a[i] == Py_None) return c10::hip::getCurrentHIPStream().stream();
@@ -152,12 +159,14 @@ PyObject* finish(const Args& c, F&& call) {
 
 #define THC_FN(NAME) PyObject* NAME(PyObject*, PyObject* const* args, Py_ssize_t n)
 
-// Tensors may throw (a tensor without storage, say): the binding's own path then reports it.
+// Tensors may throw (a tensor without storage, say, or a subclass that answers in Python, whose error
+// may still be pending): the binding's own path then reports it.
 template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
 PyObject* guarded(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     try {
         return F(self, args, n);
     } catch (...) {
+        PyErr_Clear();
         Py_RETURN_NONE;
     }
 }

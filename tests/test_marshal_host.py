@@ -77,3 +77,32 @@ def test_other_forms_are_handed_back():
         thc.rht_forward(_f(2 * N)[::2], 10, 0, _f(1024), NO_STREAM)
     with pytest.raises(TypeError):
         thc.topkc_chunk_norms(_f(), 8, _f(8), NO_STREAM)
+
+
+class _AnswersInPython(torch.Tensor):
+    """A tensor whose sizes are asked for in Python, where the answer is an error."""
+
+    @staticmethod
+    def __new__(cls, n):
+        return torch.Tensor._make_wrapper_subclass(cls, (n,), dtype=torch.float32,
+                                                   dispatch_sizes_strides_policy="sizes")
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        raise KeyError("no answer")
+
+
+def test_errors_of_the_arguments_reach_the_caller():
+    """An argument that raises when it is looked at: its error, before anything is launched."""
+    g, p = [_f(0), _f(0)], [_f(16, torch.uint8) for _ in range(2)]   # (no coordinates: a call would do nothing)
+    ws = _f(4096, torch.uint8)
+    with pytest.raises(RuntimeError, match="ambiguous"):
+        thc.thc_encode_all_minmax(g, 14, 0, 4, torch.ones(2), p, _f(2), ws, NO_STREAM)
+    with pytest.raises(RuntimeError, match="ambiguous"):
+        thc.thc_aggregate_decode_minmax(p, _f(2), 0, 14, 0, 4, torch.ones(2), _f(0), NO_STREAM)
+    with pytest.raises(KeyError, match="no answer"):
+        thc.rht_forward(_AnswersInPython(8), 10, 0, _f(1024), NO_STREAM)
+    m = _native()
+    assert m.thc_encode_all_minmax(g, 14, 0, 4, torch.ones(2), p, _f(2), ws, NO_STREAM) is None
+    assert m.rht_forward(_AnswersInPython(8), 10, 0, _f(1024), NO_STREAM) is None
+    assert m.thc_encode_all_minmax(g, 14, 0, 4, torch.ones(1), p, _f(2), ws, NO_STREAM) == 0
