@@ -361,12 +361,15 @@ struct Buckets {
     int dt = THC_F32;
 
     enum Key { kN, kSeed, kGrads, kPayloads, kScale, kOut, kKeys };
-    static PyObject* item(PyObject* dict, Key k) {   // borrowed; null if absent or None
+    static PyObject* value(PyObject* dict, Key k) {   // borrowed; null if absent
         static PyObject* const keys[kKeys] = {
             PyUnicode_InternFromString("n"),        PyUnicode_InternFromString("seed"),
             PyUnicode_InternFromString("grads"),    PyUnicode_InternFromString("payloads"),
             PyUnicode_InternFromString("scale"),    PyUnicode_InternFromString("out")};
-        PyObject* o = PyDict_GetItem(dict, keys[k]);
+        return PyDict_GetItem(dict, keys[k]);
+    }
+    static PyObject* item(PyObject* dict, Key k) {   // the same, and null if None
+        PyObject* o = value(dict, k);
         return o == Py_None ? nullptr : o;
     }
     Buckets(Args& c, PyObject* list, bool encode) {
@@ -385,8 +388,13 @@ struct Buckets {
                 return;
             }
             thc_bucket& b = records[(size_t)i];
-            for (int side = encode ? 0 : 1; side < 2; ++side) {   // (the decoder does not look at gradients)
+            for (int side = 0; side < 2; ++side) {
                 PyObject* o = item(d, side == 0 ? kGrads : kPayloads);
+                if (!encode && side == 0) {   // (the decoder reads no gradients, but a list of anything else is an error)
+                    if (o) List(c, o, false);
+                    if (!c.ok) return;
+                    continue;
+                }
                 if (!o) {   // (what a bucket needs is the library's to check; the first one has to name the workers)
                     if (i == 0 && side == (encode ? 0 : 1)) c.ok = false;
                     continue;
@@ -408,8 +416,8 @@ struct Buckets {
             o = item(d, kOut);
             t = o ? c.as_tensor(o) : nullptr;
             b.out = c.ptr<float>(t);
-            PyObject* count_o = item(d, kN);
-            PyObject* seed_o = item(d, kSeed);
+            PyObject* count_o = value(d, kN);
+            PyObject* seed_o = value(d, kSeed);   // (0 where there is none; None is not a number)
             if (!count_o) c.ok = false;
             b.n = count_o ? c.as_u64(count_o) : 0u;
             b.seed = seed_o ? c.as_u64(seed_o) : 0u;

@@ -106,3 +106,22 @@ def test_errors_of_the_arguments_reach_the_caller():
     assert m.thc_encode_all_minmax(g, 14, 0, 4, torch.ones(2), p, _f(2), ws, NO_STREAM) is None
     assert m.rht_forward(_AnswersInPython(8), 10, 0, _f(1024), NO_STREAM) is None
     assert m.thc_encode_all_minmax(g, 14, 0, 4, torch.ones(1), p, _f(2), ws, NO_STREAM) == 0
+
+
+def test_buckets_are_checked_as_the_binding_checks_them():
+    g, p, ws = [_f(0), _f(0)], [_f(16, torch.uint8) for _ in range(2)], _f(4096, torch.uint8)
+
+    def bucket(**other):
+        return [dict(dict(n=0, seed=0, grads=g, payloads=p, scale=_f(1), out=_f(0)), **other)]
+
+    thc.thc_encode_all_batch(bucket(), 14, 4, ws, NO_STREAM)
+    thc.thc_aggregate_decode_batch(bucket(grads=None), 14, 4, ws, NO_STREAM)
+    for fn in (thc.thc_encode_all_batch, thc.thc_aggregate_decode_batch):
+        with pytest.raises(TypeError):
+            fn(bucket(seed=None), 14, 4, ws, NO_STREAM)
+        with pytest.raises(TypeError):
+            fn(bucket(n=None), 14, 4, ws, NO_STREAM)
+        with pytest.raises(AttributeError):
+            fn(bucket(grads=[1, 2]), 14, 4, ws, NO_STREAM)
+        with pytest.raises(AttributeError):
+            fn(bucket(scale=1), 14, 4, ws, NO_STREAM)
