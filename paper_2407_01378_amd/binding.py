@@ -346,6 +346,13 @@ def _ptr_array(tensors):
     return arr, ctypes.cast(arr, _u8pp)
 
 
+def _payload_array(payloads, W, n):
+    """The library reads W pointers (none where there are no coordinates)."""
+    if n and len(payloads) < W:
+        raise ValueError(f"{W} workers, but payloads of {len(payloads)}")
+    return _ptr_array(payloads)
+
+
 def thc_encode_all_workspace_bytes(W, n, chunk_log2):
     return lib().thc_encode_all_workspace_bytes(W, n, chunk_log2)
 
@@ -358,7 +365,7 @@ def _encode_all(name, grads, chunk_log2, seed, bits, payloads, scale, workspace,
         if g.numel() != n or g.dtype != grads[0].dtype:
             raise ValueError("all workers must have gradients of one size and dtype")
     keep_g, pg = _ptr_array(grads)
-    keep_p, pp = _ptr_array(payloads)
+    keep_p, pp = _payload_array(payloads, W, n)
     return getattr(lib(), name)(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, pp,
                                 _ptr(scale), _ptr(workspace),
                                 workspace.numel() * workspace.element_size(), _stream(stream))
@@ -394,12 +401,16 @@ def thc_encode_all_cleared(grads, chunk_log2, seed, bits, payloads, scale, works
 
 
 # ------------------------------------------------------------ several buckets per launch
-def _bucket_array(buckets):
+def _bucket_array(buckets, W=0, reads=("payloads",)):
     """buckets: list of dicts with keys n, seed and any of grads (list of W tensors), payloads
-    (list of W tensors), scale, out.  Returns (keep-alive objects, ctypes array)."""
+    (list of W tensors), scale, out.  reads: the lists of which the library reads W pointers (none
+    in a bucket without coordinates).  Returns (keep-alive objects, ctypes array)."""
     arr = (ThcBucket * max(len(buckets), 1))()
     keep = []
     for i, b in enumerate(buckets):
+        for key in reads:
+            if b["n"] and b.get(key) is not None and len(b[key]) < W:
+                raise ValueError(f"{W} workers, but {key} of {len(b[key])} in bucket {i}")
         if b.get("grads") is not None:
             kg, pg = _ptr_array(b["grads"])
             keep.append(kg)
@@ -424,7 +435,7 @@ def thc_encode_all_batch(buckets, chunk_log2, bits, workspace, stream=None):
     rc = (_native or _load_native()).thc_encode_all_batch(buckets, chunk_log2, bits, workspace, stream)
     if rc is None:
         W = len(buckets[0]["grads"]) if buckets else 1
-        keep, arr = _bucket_array(buckets)
+        keep, arr = _bucket_array(buckets, W, ("grads", "payloads"))
         dt = _dtype_code(buckets[0]["grads"][0]) if buckets else THC_F32
         rc = lib().thc_encode_all_batch(arr, len(buckets), dt, W, chunk_log2, bits, _ptr(workspace), workspace.numel()
                                         * workspace.element_size(), _stream(stream))
@@ -435,7 +446,7 @@ def thc_aggregate_decode_batch(buckets, chunk_log2, bits, workspace, stream=None
     rc = (_native or _load_native()).thc_aggregate_decode_batch(buckets, chunk_log2, bits, workspace, stream)
     if rc is None:
         W = len(buckets[0]["payloads"]) if buckets else 1
-        keep, arr = _bucket_array(buckets)
+        keep, arr = _bucket_array(buckets, W)
         rc = lib().thc_aggregate_decode_batch(arr, len(buckets), W, chunk_log2, bits, _ptr(workspace),
                                               workspace.numel() * workspace.element_size(), _stream(stream))
     _check(rc, "thc_aggregate_decode_batch")
@@ -455,7 +466,7 @@ def thc_encode_all_static(grads, chunk_log2, seed, bits, payloads, scale, timed_
             if g.numel() != n or g.dtype != grads[0].dtype:
                 raise ValueError("all workers must have gradients of one size and dtype")
         keep_g, pg = _ptr_array(grads)
-        keep_p, pp = _ptr_array(payloads)
+        keep_p, pp = _payload_array(payloads, W, n)
         rc = lib().thc_encode_all_static(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, pp, _ptr(scale),
                                          _ptr(timed_out), _stream(stream))
     _check(rc, "thc_encode_all_static")
@@ -681,7 +692,7 @@ def thc_encode_all_minmax(grads, chunk_log2, seed, bits, rotate, payloads, range
             if g.numel() != n or g.dtype != grads[0].dtype:
                 raise ValueError("all workers must have gradients of one size and dtype")
         keep_g, pg = _ptr_array(grads)
-        keep_p, pp = _ptr_array(payloads)
+        keep_p, pp = _payload_array(payloads, W, n)
         rc = lib().thc_encode_all_minmax(pg, _dtype_code(grads[0]), W, n, chunk_log2, seed, bits, int(bool(rotate)),
                                          pp, _ptr(range_), _ptr(workspace), workspace.numel() *
                                          workspace.element_size(), _stream(stream))

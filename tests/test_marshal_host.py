@@ -125,3 +125,29 @@ def test_buckets_are_checked_as_the_binding_checks_them():
             fn(bucket(grads=[1, 2]), 14, 4, ws, NO_STREAM)
         with pytest.raises(AttributeError):
             fn(bucket(scale=1), 14, 4, ws, NO_STREAM)
+
+
+def test_lists_shorter_than_the_workers_are_refused():
+    """The library reads as many pointers as there are workers: a shorter list may not reach it.  (bits
+    = 3, so that a call that does get through ends at the library's argument checks.)"""
+    g, p, scale, ws = _pieces()
+    for fn in (thc.thc_encode_all, thc.thc_encode_all_cleared, thc.thc_sat_encode_all, thc.thc_sat_encode_all_cleared):
+        with pytest.raises(ValueError, match="3 workers"):
+            fn(g, 14, 0, 3, p[:2], scale, ws, stream=NO_STREAM)
+    with pytest.raises(ValueError, match="3 workers"):
+        thc.thc_encode_all_static(g, 14, 0, 3, p[:2], scale, None, NO_STREAM)
+    with pytest.raises(ValueError, match="3 workers"):
+        thc.thc_encode_all_minmax(g, 14, 0, 3, True, [], _f(2), ws, NO_STREAM)
+    whole = dict(n=N, grads=g, payloads=p, scale=scale, out=_f())
+    for short in (dict(whole, payloads=p[:2]), dict(whole, grads=g[:2])):
+        with pytest.raises(ValueError, match="3 workers"):
+            thc.thc_encode_all_batch([whole, short], 14, 3, ws, NO_STREAM)
+    with pytest.raises(ValueError, match="3 workers"):
+        thc.thc_aggregate_decode_batch([whole, dict(whole, payloads=p[:2])], 14, 3, ws, NO_STREAM)
+    # longer lists, lists that are not read and buckets without coordinates pass on
+    for call in (lambda: thc.thc_encode_all(g[:2], 14, 0, 3, p, scale, ws, NO_STREAM),
+                 lambda: thc.thc_encode_all_batch([whole, dict(whole, n=0, grads=[], payloads=[])], 14, 3, ws, NO_STREAM),
+                 lambda: thc.thc_aggregate_decode_batch([whole, dict(whole, grads=g[:1])], 14, 3, ws, NO_STREAM)):
+        with pytest.raises(thc.ThcError) as e:
+            call()
+        assert e.value.status == -2
