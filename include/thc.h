@@ -15,8 +15,8 @@
  *   - The caller owns every buffer.  Unless an entry point says otherwise the
  *     library allocates nothing.  Process-wide state, all of it: the poll limit set by
  *     thc_set_spin_limit (one unsynchronised word read by every one-pass encode
- *     launch), the device's compute-unit count and per-kernel occupancy (queried once,
- *     then cached), and for thc_encode_all_static the per-device address of its fixed
+ *     launch), each device's compute-unit count, occupancy and LDS limit per kernel and
+ *     workgroup shape (queried or set once, then cached), and for thc_encode_all_static the per-device address of its fixed
  *     device array.  Nothing else survives a call.
  *   - Inputs and outputs of one call must not overlap.
  *   - n is the number of gradient coordinates of ONE worker, c = 2^chunk_log2 the

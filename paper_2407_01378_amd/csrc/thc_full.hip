@@ -13,6 +13,7 @@
 #include "thc_core14.h"
 #include "thc_internal.h"
 #include "thc_lanes.h"
+#include "thc_resident.h"
 
 #pragma clang fp contract(off)
 
@@ -462,20 +463,6 @@ __global__ __launch_bounds__(256) void full_decode_kernel(const SumT* sums, uint
 }
 
 // ---- launch ------------------------------------------------------------------------------------
-// Workgroups of a kernel that are resident at once.
-template <auto kernel>
-uint32_t resident_grid(int threads) {
-    static uint32_t cached = 0;   // one per kernel
-    if (cached == 0) {
-        int occ = 0, dev = 0;
-        hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, 0) != hipSuccess || occ < 1) return 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-        cached = (uint32_t)(occ * prop.multiProcessorCount);
-    }
-    return cached;
-}
-
 // One tile per workgroup (or independent wave), except for the range, whose workgroups stay so that few of
 // them report.
 template <int M, Kind KIND, int BITS = 4>
@@ -490,7 +477,7 @@ void launch_pass_t(uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
     const uint32_t threads = 64u * together << wave_rows(M);
     uint64_t grid = a.tiles / together;
     if (kReports) {
-        const uint32_t resident = resident_grid<kernel>((int)(64 * pass_waves(M)));   // (of full workgroups)
+        const uint32_t resident = resident_grid<kernel>((uint32_t)(64 * pass_waves(M)));   // (of full workgroups)
         if (resident != 0 && grid > resident) grid = resident;
     }
     hipLaunchKernelGGL(kernel, dim3((uint32_t)grid), dim3(threads), 0, stream, a);

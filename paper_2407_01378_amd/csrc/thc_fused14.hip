@@ -15,6 +15,7 @@
 #include "thc_core14.h"
 #include "thc_internal.h"
 #include "thc_payload.h"
+#include "thc_resident.h"
 
 #pragma clang fp contract(off)
 
@@ -739,31 +740,10 @@ __global__ __launch_bounds__(256) void aggregate_fast_kernel(const FusedPayloadP
     }
 }
 
-int g_cus = 0;
-int device_cus() {
-    if (g_cus == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            g_cus = prop.multiProcessorCount;
-    }
-    return g_cus;
-}
-
-// Workgroups of `kernel` that are resident at once on the whole device.  The occupancy
-// query is slow (tens of microseconds), so the answer is kept per kernel.
+// Workgroups of `kernel` that are resident at once on the whole device.
 template <auto kernel>
 uint32_t resident_grid() {
-    static uint32_t cached = 0;   // one per kernel
-    if (cached == 0) {
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kThreads, 0) != hipSuccess || occ < 1)
-            return 0;
-        const int cus = device_cus();
-        if (cus <= 0) return 0;
-        cached = (uint32_t)(occ * cus);
-    }
-    return cached;
+    return thc::resident_grid<kernel>(kThreads);
 }
 
 template <bool BF16, int BITS, bool ODD, bool BATCH>

@@ -15,6 +15,7 @@
 // written for coalescing instead of for the rotation's register layout.
 #include "thc_core14.h"
 #include "thc_internal.h"
+#include "thc_resident.h"
 
 #pragma clang fp contract(off)
 
@@ -428,23 +429,10 @@ __global__ __launch_bounds__(256) void unrotated_decode_kernel(const SUM* sums, 
 // bucket: 4096 blocks 32.4 us, 16384 blocks 29.2 us, 65536 blocks 28.8 us).
 constexpr uint64_t kElementwiseBlocks = 16384;
 
-template <auto kernel>
-uint32_t resident_grid_minmax() {
-    static uint32_t cached = 0;   // one per kernel
-    if (cached == 0) {
-        int occ = 0, dev = 0;
-        hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kThreads, 0) != hipSuccess || occ < 1) return 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-        cached = (uint32_t)(occ * prop.multiProcessorCount);
-    }
-    return cached;
-}
-
 template <bool BF16, int BITS>
 hipError_t launch_unrotated_t(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, hipStream_t stream) {
     if (BF16 && (a.n & 1u) == 0u) {
-        uint32_t G = resident_grid_minmax<encode_all_unrotated_bf16_kernel<BITS>>();
+        uint32_t G = resident_grid<encode_all_unrotated_bf16_kernel<BITS>>(kThreads);
         if (G == 0) return hipErrorInvalidValue;
         const uint64_t total = a.chunks * a.W;
         if (G > total) G = (uint32_t)total;
@@ -453,7 +441,7 @@ hipError_t launch_unrotated_t(const EncodeAllArgs& a, const FusedWorkerPtrs& ptr
         hipLaunchKernelGGL((encode_all_unrotated_bf16_kernel<BITS>), dim3(G), dim3(kThreads), 0, stream, a, ptrs);
         return hipGetLastError();
     }
-    uint32_t G = resident_grid_minmax<encode_all_unrotated_kernel<BF16, BITS>>();
+    uint32_t G = resident_grid<encode_all_unrotated_kernel<BF16, BITS>>(kThreads);
     if (G == 0) return hipErrorInvalidValue;
     const uint64_t total = a.chunks * a.W;
     if (G > total) G = (uint32_t)total;

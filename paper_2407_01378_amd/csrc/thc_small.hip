@@ -22,6 +22,7 @@
 #include "thc_internal.h"
 #include "thc_lanes.h"
 #include "thc_payload.h"
+#include "thc_resident.h"
 
 #pragma clang fp contract(off)
 
@@ -469,29 +470,6 @@ __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const Smal
 }
 
 // ------------------------------------------------------------------------------ launch
-int device_cus() {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            cus = prop.multiProcessorCount;
-    }
-    return cus;
-}
-
-template <auto kernel>
-uint32_t resident_grid(uint32_t waves, uint32_t lds) {
-    static uint32_t cached[kMaxWaves + 1];   // by size of the workgroup (which fixes its LDS up to a few KB)
-    if (cached[waves] == 0) {
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, (int)(64u * waves), lds) != hipSuccess || occ < 1)
-            return 0;
-        cached[waves] = (uint32_t)(occ * device_cus());
-    }
-    return cached[waves];
-}
-
 template <bool BF16, int CLASS, int BITS, SmallOp OP>
 hipError_t launch_encode_t(const SmallArgs& a, const FusedWorkerPtrs& ptrs, hipStream_t stream) {
     constexpr auto kernel = small_encode_kernel<BF16, CLASS, BITS, OP>;
@@ -501,16 +479,8 @@ hipError_t launch_encode_t(const SmallArgs& a, const FusedWorkerPtrs& ptrs, hipS
     const uint32_t lds = waves * (!BF16 ? 8192u : (CLASS == 2 ? 4096u : 0u)) +
                          2u * 4u * (a.regions << (unit_log2 - 5u)) +
                          2u * 4u * (a.regions << rows_log2) * ((a.groups * wpw + 3u) & ~3u);
-    if (lds > 65536u) {   // (idempotent; a launch with more than the default limit needs it)
-        static bool raised = false;
-        if (!raised) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    163840) != hipSuccess)
-                return hipErrorInvalidValue;
-            raised = true;
-        }
-    }
-    uint64_t G = resident_grid<kernel>(waves, lds);
+    if (!allow_lds<kernel>(lds)) return hipErrorInvalidValue;
+    uint64_t G = resident_grid<kernel>(64u * waves, lds);
     if (G == 0) return hipErrorInvalidValue;
     if (G > a.items) G = a.items;
     hipLaunchKernelGGL(kernel, dim3((uint32_t)G), dim3(64u * waves), lds, stream, a, ptrs);

@@ -1,0 +1,77 @@
+"""Grids of the small-chunk encoder without a GPU, through a stand-in for the HIP calls of a launch
+(tests/fake_hip.cpp): what one call asks for depends neither on the calls before it nor on the other
+devices of the process.  Each sequence of calls runs in a process of its own, without PyTorch."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+import paper_2407_01378_amd as thc
+from paper_2407_01378_amd import binding
+
+TESTS = os.path.dirname(os.path.abspath(__file__))
+
+CHILD = """
+import ctypes, json, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+lib.thc_encode_all_workspace_bytes.restype = ctypes.c_uint64
+u64, vp = ctypes.c_uint64, ctypes.c_void_p
+seen = []
+for device, l, W, dtype, bits, n in json.loads(sys.argv[3]):
+    fake.fake_use(device)
+    at = (vp * W)(*[0x10000 * (w + 1) for w in range(W)])   # (addresses that only a launch would use)
+    need = lib.thc_encode_all_workspace_bytes(W, u64(n), l)
+    before = fake.fake_queries()
+    rc = lib.thc_encode_all(at, dtype, W, u64(n), l, u64(1), bits, at, vp(0x1000), vp(0x2000), u64(need), None)
+    seen.append([rc, fake.fake_grid(), fake.fake_block(), fake.fake_lds(), fake.fake_queries() - before])
+print(json.dumps(seen))
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    thc.lib()
+    fake = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    res = subprocess.run(["hipcc", "-O1", "-std=c++17", "-fPIC", "-shared", "-o", fake, os.path.join(TESTS, "fake_hip.cpp")],
+                         stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout[-3000:]
+
+    def calls(*sequence):
+        res = subprocess.run([sys.executable, "-c", CHILD, fake, binding.LIB_PATH, json.dumps(sequence)],
+                             stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+        assert res.returncode == 0, res.stderr[-3000:]
+        return json.loads(res.stdout.splitlines()[-1])
+    return calls
+
+
+F32, BF16 = 0, 1
+WIDE = (5, 1, F32, 4, 1 << 24)      # 8 waves and 84 KB: one workgroup per CU
+NARROW = (9, 8, F32, 4, 1 << 24)    # 8 waves of the same kernel and 66 KB: two
+
+
+def test_a_grid_does_not_depend_on_earlier_calls(run):
+    first, second = run((0, *WIDE), (0, *NARROW))
+    assert first == run((0, *WIDE))[0] and first[0] == 0 and first[1] == 256 and first[3] > 81920
+    assert second[:4] == run((0, *NARROW))[0][:4] and second[1] == 512 and 65536 < second[3] < 81920
+    back = run((0, *NARROW), (0, *WIDE))
+    assert [b[:4] for b in back] == [second[:4], first[:4]]
+
+
+def test_every_device_is_told_of_the_workgroups_beyond_64_kb(run):
+    seen = run((0, *WIDE), (1, *WIDE), (0, *WIDE), (7, 13, 4, F32, 8, 1 << 22), (1, 13, 4, F32, 8, 1 << 22))
+    assert [s[0] for s in seen] == [0] * 5
+    assert seen[0][:4] == seen[1][:4] == seen[2][:4]
+
+
+def test_answers_are_kept_per_shape_and_beyond_the_table(run):
+    # more shapes of one kernel than the table has room for (devices count too), then the first ones again
+    shapes = [(d, *s) for d in range(12) for s in (WIDE, NARROW, (6, 2, F32, 4, 1 << 24))]
+    seen = run(*shapes, *shapes[:9])
+    assert all(s[0] == 0 for s in seen)
+    for k, s in enumerate(seen):
+        assert s[:4] == seen[k % 3][:4]
+    assert [s[4] for s in seen[:9]] == [1] * 9
+    assert sum(s[4] for s in seen[-9:]) <= 4      # (what the overflow displaced is asked for again, no more)
