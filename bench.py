@@ -633,6 +633,8 @@ def main():
         passes, s0 = (high + 10) // 11, 14
         for p in range(passes):
             m = (path.l - s0 + (passes - p) - 1) // (passes - p)
+            if passes - p == 2 and path.l - s0 == 13:
+                m = 6                     # 13 stages go as 6 + 7
             block = 1 << (s0 + m)
             reach = min(path.size, (valid + block - 1) // block * block)
             dom_bytes += valid * 4 + (0 if p + 1 == passes else reach) * 4

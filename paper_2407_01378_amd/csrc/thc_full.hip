@@ -526,7 +526,9 @@ hipError_t launch_high_passes(float* data, uint32_t log2_size, float factor, flo
     for (uint32_t p = 0; p < passes; ++p) {
         const uint32_t left = log2_size - s0;
         // spread the stages evenly so that no pass is needlessly short
-        // (13 = 6 + 7, not 7 + 6: the pass that moves most goes without LDS)
+        // (13 = 6 + 7, not 7 + 6: the pass that moves most goes without LDS.  2^27 coordinates, of them 70 M fp32
+        // data: range 255 us and payload 90 us against 270 and 98 us, inverse 540 against 531; 108 M bf16: the
+        // same either way)
         const uint32_t m = passes - p == 2u && left == 13u ? 6u : (left + (passes - p) - 1u) / (passes - p);
         const bool last = p + 1u == passes;
         HighPassArgs a{};
