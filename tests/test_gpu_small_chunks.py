@@ -85,3 +85,30 @@ def test_small_chunks_on_the_signed_grid(l, W, bits):
     for w in range(W):
         assert (pay[w].cpu().numpy() == want["payloads"][w]).all()
         assert torch.equal(ref[w], pay[w])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("l,W,bits,n", [(5, 3, 4, 20_001), (6, 1, 8, 33), (7, 8, 2, 40_961), (8, 2, 4, 16_384), (9, 17, 8, 5_001),
+                                        (10, 4, 4, 100_003), (11, 5, 2, 2_047), (12, 8, 8, 12_289), (13, 2, 4, 70_000)])
+def test_gradients_off_the_16_byte_grid_match_the_oracle(l, W, bits, n, dtype):
+    """These take the generic kernels, one launch per step and worker (test_launch_shapes_host.py)."""
+    print(f"unaligned l={l} W={W} bits={bits} n={n} {dtype}", flush=True)
+    xs = [torch.empty(n + 1, dtype=dtype, device=DEV)[1:].copy_(x) for x in _grads(W, n, dtype, 5 * l + W)]
+    assert all(x.data_ptr() % 16 for x in xs)
+    check_against_oracle(xs, run_path(xs, l, 6, bits), l, 6, bits)
+    fused = run_path_fused(xs, l, 6, bits)
+    check_against_oracle(xs, fused, l, 6, bits)
+    timed = run_path_timed(xs, l, 6, bits)
+    assert torch.equal(timed["out"], fused["out"])
+    mixed = [xs[0]] + [x.clone() for x in xs[1:]]   # one gradient off the grid is enough
+    again = run_path_fused(mixed, l, 6, bits)
+    assert all(torch.equal(a, b) for a, b in zip(again["payloads"], fused["payloads"]))
+    own = torch.empty_like(fused["payloads"][0])    # the worker's own range as the grid
+    scale = torch.empty_like(fused["scale"])
+    thc.thc_encode(xs[0], l, 6, 0, bits, None, own, scale)
+    torch.cuda.synchronize()
+    bf = dtype == torch.bfloat16
+    y = O.rht_forward(to_numpy_bits(xs[0]), l, 6, dtype=np.float32, bf16=bf)
+    s = O.chunk_absmax(y, l)
+    assert (scale.cpu().numpy() == s).all()
+    assert (own.cpu().numpy() == O.pack(O.quantize(y, s, l, 0, 6, bits, dtype=np.float32), bits)).all()

@@ -20,13 +20,16 @@ lib = ctypes.CDLL(sys.argv[2])
 lib.thc_encode_all_workspace_bytes.restype = ctypes.c_uint64
 u64, vp = ctypes.c_uint64, ctypes.c_void_p
 seen = []
-for device, l, W, dtype, bits, n in json.loads(sys.argv[3]):
+for device, l, W, dtype, bits, n, *off in json.loads(sys.argv[3]):
     fake.fake_use(device)
     at = (vp * W)(*[0x10000 * (w + 1) for w in range(W)])   # (addresses that only a launch would use)
     need = lib.thc_encode_all_workspace_bytes(W, u64(n), l)
     before = fake.fake_queries()
-    rc = lib.thc_encode_all(at, dtype, W, u64(n), l, u64(1), bits, at, vp(0x1000), vp(0x2000), u64(need), None)
-    seen.append([rc, fake.fake_grid(), fake.fake_block(), fake.fake_lds(), fake.fake_queries() - before])
+    grads = (vp * W)(*[a + (off[0] if off else 0) for a in at])
+    launches = fake.fake_launches()
+    rc = lib.thc_encode_all(grads, dtype, W, u64(n), l, u64(1), bits, at, vp(0x1000), vp(0x2000), u64(need), None)
+    seen.append([rc, fake.fake_grid(), fake.fake_block(), fake.fake_lds(), fake.fake_queries() - before,
+                 fake.fake_launches() - launches])
 print(json.dumps(seen))
 """
 
@@ -75,3 +78,14 @@ def test_answers_are_kept_per_shape_and_beyond_the_table(run):
         assert s[:4] == seen[k % 3][:4]
     assert [s[4] for s in seen[:9]] == [1] * 9
     assert sum(s[4] for s in seen[-9:]) <= 4      # (what the overflow displaced is asked for again, no more)
+
+
+@pytest.mark.parametrize("dtype,off", [(F32, 4), (BF16, 2)])
+def test_gradients_off_the_16_byte_grid_take_the_generic_kernels(run, dtype, off):
+    W, n = 3, 100_003
+    for l in range(5, 14):
+        on, generic = run((0, l, W, dtype, 4, n), (0, l, W, dtype, 4, n, off))
+        assert on[0] == generic[0] == 0
+        assert on[5] == 1
+        # clear + W ranges + their maximum + W encoders, tiles of 2^14 coordinates
+        assert generic[5] == 2 * W + 2 and generic[1:4] == [(n + (1 << 14) - 1) >> 14, 1024, 0]
