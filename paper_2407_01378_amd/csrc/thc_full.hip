@@ -482,27 +482,26 @@ void launch_pass_t(uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
     }
     hipLaunchKernelGGL(kernel, dim3((uint32_t)grid), dim3(threads), 0, stream, a);
 }
-template <Kind KIND, int BITS = 4>
-void launch_pass(uint32_t m, uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
-    switch (m) {
-        case 1: launch_pass_t<1, KIND, BITS>(log2_size, stream, a); break;
-        case 2: launch_pass_t<2, KIND, BITS>(log2_size, stream, a); break;
-        case 3: launch_pass_t<3, KIND, BITS>(log2_size, stream, a); break;
-        case 4: launch_pass_t<4, KIND, BITS>(log2_size, stream, a); break;
-        case 5: launch_pass_t<5, KIND, BITS>(log2_size, stream, a); break;
-        case 6: launch_pass_t<6, KIND, BITS>(log2_size, stream, a); break;
-        case 7: launch_pass_t<7, KIND, BITS>(log2_size, stream, a); break;
-        case 8: launch_pass_t<8, KIND, BITS>(log2_size, stream, a); break;
-        case 9: launch_pass_t<9, KIND, BITS>(log2_size, stream, a); break;
-        case 10: launch_pass_t<10, KIND, BITS>(log2_size, stream, a); break;
-        default: launch_pass_t<11, KIND, BITS>(log2_size, stream, a); break;
-    }
-}
-
 // Stages of a high pass at most.  11 stages move 64-byte pieces, at about 0.7 of the rate of whole lines,
 // and still beat a pass more (2^25 coordinates, 102 MB of them data: range 31.7 us, payload 42 us,
 // inverse 64 us; as 6 + 5 stages 32 + 22, 33 and 44 + 51 us).
-constexpr uint32_t kMaxStages = 11;
+constexpr int kMaxStages = 11;
+
+// Whether a plan has a pass of M stages of this kind: the first of two takes half of 12 .. 19 stages, a pass
+// that is the last (or the only) one may have any number.
+constexpr bool pass_exists(Kind kind, int M) { return kind != Kind::InPlace || (M >= 6 && M <= 10); }
+
+template <Kind KIND, int BITS = 4, int M = 1>
+hipError_t launch_pass(uint32_t m, uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
+    if constexpr (M <= kMaxStages) {
+        if (m != (uint32_t)M) return launch_pass<KIND, BITS, M + 1>(m, log2_size, stream, a);
+        if constexpr (pass_exists(KIND, M)) {
+            launch_pass_t<M, KIND, BITS>(log2_size, stream, a);
+            return hipGetLastError();
+        }
+    }
+    return hipErrorInvalidValue;   // (no plan asks for it)
+}
 
 }  // namespace
 
@@ -522,7 +521,7 @@ hipError_t launch_high_passes(float* data, uint32_t log2_size, float factor, flo
     const bool encode_only = deferred && deferred->kind == FullLast::EncodeOnly;
     if ((deferred && (x || range_only == encode_only)) || (range_only && !absmax)) return hipErrorInvalidValue;
     uint32_t s0 = 14u;
-    const uint32_t passes = (log2_size - s0 + kMaxStages - 1u) / kMaxStages;
+    const uint32_t passes = (log2_size - s0 + kMaxStages - 1u) / (uint32_t)kMaxStages;
     for (uint32_t p = 0; p < passes; ++p) {
         const uint32_t left = log2_size - s0;
         // spread the stages evenly so that no pass is needlessly short
@@ -540,24 +539,24 @@ hipError_t launch_high_passes(float* data, uint32_t log2_size, float factor, flo
         a.n = n;
         a.valid = valid;
         a.absmax = (last && !x) ? reinterpret_cast<uint32_t*>(absmax) : nullptr;
+        hipError_t e = hipSuccess;
         if (last && x) {
             a.out = x;
-            launch_pass<Kind::ToX>(m, log2_size, stream, a);
+            e = launch_pass<Kind::ToX>(m, log2_size, stream, a);
         } else if (last && range_only) {
-            launch_pass<Kind::RangeOnly>(m, log2_size, stream, a);
+            e = launch_pass<Kind::RangeOnly>(m, log2_size, stream, a);
         } else if (last && encode_only) {
             a.scale = deferred->scale;
             a.levels = deferred->levels;
             a.worker = deferred->worker;
             a.payload = deferred->payload;
-            if (deferred->bits == 2) launch_pass<Kind::Encode, 2>(m, log2_size, stream, a);
-            else if (deferred->bits == 4) launch_pass<Kind::Encode, 4>(m, log2_size, stream, a);
-            else launch_pass<Kind::Encode, 8>(m, log2_size, stream, a);
+            if (deferred->bits == 2) e = launch_pass<Kind::Encode, 2>(m, log2_size, stream, a);
+            else if (deferred->bits == 4) e = launch_pass<Kind::Encode, 4>(m, log2_size, stream, a);
+            else e = launch_pass<Kind::Encode, 8>(m, log2_size, stream, a);
         } else if (!encode_only) {
-            if (last) launch_pass<Kind::InPlaceLast>(m, log2_size, stream, a);
-            else launch_pass<Kind::InPlace>(m, log2_size, stream, a);
+            e = last ? launch_pass<Kind::InPlaceLast>(m, log2_size, stream, a)
+                     : launch_pass<Kind::InPlace>(m, log2_size, stream, a);
         }
-        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         // what is not zero afterwards: the blocks of 2^(s0 + m) floats that held a value
         const uint64_t block = 1ull << (s0 + m);

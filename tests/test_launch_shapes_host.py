@@ -1,6 +1,7 @@
-"""Grids of the small-chunk encoder without a GPU, through a stand-in for the HIP calls of a launch
-(tests/fake_hip.cpp): what one call asks for depends neither on the calls before it nor on the other
-devices of the process.  Each sequence of calls runs in a process of its own, without PyTorch."""
+"""Launches without a GPU, through a stand-in for the HIP calls of a launch (tests/fake_hip.cpp).  Grids
+of the small-chunk encoder: what one call asks for depends neither on the calls before it nor on the
+other devices of the process.  Full rotation: every plan finds its passes.  Each sequence of calls runs
+in a process of its own, without PyTorch."""
 import json
 import os
 import subprocess
@@ -47,6 +48,7 @@ def run(tmp_path_factory):
                              stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
         assert res.returncode == 0, res.stderr[-3000:]
         return json.loads(res.stdout.splitlines()[-1])
+    calls.fake = fake
     return calls
 
 
@@ -89,3 +91,38 @@ def test_gradients_off_the_16_byte_grid_take_the_generic_kernels(run, dtype, off
         assert on[5] == 1
         # clear + W ranges + their maximum + W encoders, tiles of 2^14 coordinates
         assert generic[5] == 2 * W + 2 and generic[1:4] == [(n + (1 << 14) - 1) >> 14, 1024, 0]
+
+
+FULL_CHILD = """
+import ctypes, json, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+u32, u64, vp = ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p
+x, y, m, p = vp(0x10000), vp(0x20000), vp(0x30000), vp(0x40000)
+seen = []
+def count(call):
+    before = fake.fake_launches()
+    rc = call()
+    return [rc, fake.fake_launches() - before]
+for l in range(15, 34):
+    for n in (1, (1 << l) - 1):
+        seen.append([l] + [count(c) for c in (
+            lambda: lib.rht_forward_full(x, 0, u64(n), u32(l), u64(1), y, None),
+            lambda: lib.rht_forward_full_deferred(x, 1, u64(n), u32(l), u64(1), y, m, None),
+            lambda: lib.rht_inverse_full(y, u64(n), u32(l), u64(1), x, None),
+            *[lambda b=b: lib.thc_full_encode_deferred(y, u64(n), u32(l), u64(1), u32(0), u32(b), m, p, None)
+              for b in (2, 4, 8)])])
+print(json.dumps(seen))
+"""
+
+
+def test_every_full_rotation_has_its_passes(run):
+    res = subprocess.run([sys.executable, "-c", FULL_CHILD, run.fake, binding.LIB_PATH],
+                         stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+    assert res.returncode == 0, res.stderr[-3000:]
+    seen = json.loads(res.stdout.splitlines()[-1])
+    assert len(seen) == 38
+    for l, forward, deferred, inverse, *encodes in seen:
+        passes = 1 if l <= 25 else 2       # up to 11 stages each behind the 14 of the chunk kernels
+        assert forward == deferred == inverse == [0, 1 + passes], l
+        assert encodes == [[0, 1]] * 3, l
