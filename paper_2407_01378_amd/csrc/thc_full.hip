@@ -33,10 +33,12 @@ using k14::kRegs;
 //   the rest        the wave: it changes places with slot bits 0.. through LDS, once, the two
 //                   floats of a pair in turn so that the buffer takes half the data
 // So passes of up to 6 stages need neither LDS nor barriers: every wave streams by itself, and
-// all others keep 32 waves per CU (64 registers, 64 KB of LDS at most).  Bound by memory (8 bytes per
-// coordinate in place, 4 for the range alone).  The shape before, 8 rows x 4 floats per thread,
-// exchanged twice for every pass through 64 KB of LDS and reached 9 stages, so 2^25 coordinates took
-// 14 + 6 + 5 stages where they now take 14 + 11: resnet50-sized round of 8 workers 1364 -> 1040 us.
+// the others keep 32 waves per CU (64 registers, 64 KB of LDS per 16 waves, in the inverse's last pass of
+// 9 stages 68), except for the inverse's last pass of 10 and 11 stages: 128 registers, 68 and 72 KB
+// (the exchange and a sign word per row), 16 waves.  Bound by memory (8 bytes per coordinate in
+// place, 4 for the range alone).  The shape before, 8 rows x 4 floats per thread, exchanged
+// twice for every pass through 64 KB of LDS and reached 9 stages, so 2^25 coordinates took
+// 14 + 6 + 5 stages where they now take 14 + 11: resnet50-sized round of 8 workers 1366 -> 1021 us.
 struct HighPassArgs {
     float* data;        // 2^l floats, transformed in place (unless `out`)
     float* out;         // last pass of the inverse: x (n floats); else null

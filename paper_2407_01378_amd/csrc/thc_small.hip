@@ -3,14 +3,17 @@
 // Encode.  A chunk this small needs no agreement between workgroups: one workgroup holds the
 // same coordinates of ALL workers at once, a wave 2^11 coordinates of one worker (32 per
 // thread, in registers), so the shared range of a chunk is a maximum over a few words in LDS
-// behind one barrier.  Every gradient is read once.  The rotation stays inside the wave up to
-// chunks of 2^11: 5 stages between registers, 4 between lanes by data-parallel primitives and
-// 2 after a swap of a lane bit into the registers (thc_lanes.h).  Chunks of 2^12 and 2^13 span
-// two and four waves, which trade half of their registers through LDS before each further
-// stage.  Bound by vector-ALU issue (about 24 operations per worker-coordinate) for large
-// inputs, by the latency of the two launches for small ones.
+// behind one barrier.  Up to 16 waves' worth of workers (16 up to chunks of 2^11, 8 at 2^12, 4 at
+// 2^13) every gradient is read once; more take rounds, and all rounds but the last are loaded and
+// rotated a second time for the quantizer (8 workers at 2^13: 1.5 times the work).  The rotation
+// stays inside the wave up to chunks of 2^11: 5 stages between registers, 4 between lanes by
+// data-parallel primitives and 2 after a swap of a lane bit into the registers (thc_lanes.h).
+// Chunks of 2^12 and 2^13 span two and four waves, which trade half of their registers through LDS
+// before each further stage.  Bound by vector-ALU issue for large inputs (6.5 M coordinates, 8 workers,
+// chunk 2^12, 8 bits, by the counters: 27.8 operations per worker-coordinate, VALU busy 94 % of
+// the time with 16 waves per CU, 52 us), by the issue of the two launches for small ones.
 //   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 72 us
-//   (3.4 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 22 us.  Before: one range and one encode
+//   (3.4 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 15.6 us.  Before: one range and one encode
 //   launch per worker of the generic kernels, which load element by element and take a
 //   barrier per stage above 2^4.
 //

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(1024) void seg_scan_kernel(uint32_t* ws, uint32_t s
 // Ordered compaction: chunk p is selected if its key is above T, or equal to T with fewer
 // than `need` equal keys before it; its place is (#above before) + min(#equal before, need).
 // SCANNED: the pairs are scanned already; else a workgroup adds up those before its own.  Up to
-// kOwnPrefix segments (4 M keys) that is at most 8 loads per thread, out of L2, in the place of a launch.
+// kOwnPrefix segments (4 M keys) that is at most 16 loads per thread, out of L2, in the place of a launch.
 constexpr uint32_t kOwnPrefix = 2048;
 template <bool VEC, bool SCANNED>
 __global__ __launch_bounds__(256) void write_indices_kernel(const uint16_t* s, uint64_t P, const uint32_t* ws,
