@@ -381,6 +381,52 @@ __device__ __forceinline__ void l3_to_l4e_lanes(Shared& sh, float (&v)[kRegs], u
     set_prio<PRIO, kPrioTail>();
 }
 
+// The decoders' rotation, from layout L1 with permuted lanes straight to layout L4d: stages 5..8 between
+// lanes, 9 and 10 behind register swaps (thc_lanes.h), so that a wave finishes its 2^11 coordinates by
+// itself, one exchange of 128-bit accesses (X4d), and the last three stages in the layout of the stores.
+// A chunk crosses LDS once, where the maps X1, X2, X3d take it through three times, with 32-bit accesses on
+// one side of each: what a single chunk's chain waits for (decoder of 8 workers x 50257 coordinates, 4 chunks:
+// 9.0 -> 6.1 us; 7 M coordinates, 433 chunks, u16 sums: 10.4 -> 9.2 us; large decodes are bound by memory).
+// The caller's buffer is free (every wave is past a barrier behind its last reads); it is still being read on return.
+// On return a value is negated where its coordinate's bits i5..i8 have odd parity: in layout L4d that is the same
+// for all values of a thread (l4d_negated).
+// hook.at<K>() is called at three points that are some hundred clocks apart (K = 0 in front of the first stage,
+// 1 behind the lane stages, 2 behind the barrier): a persistent kernel hangs the next item's global loads there.
+template <class Hook>
+__device__ __forceinline__ void rotate_lanes_to_l4d(Shared& sh, float (&v)[kRegs], uint32_t lane, uint32_t block,
+                                                    uint32_t wave, Hook& hook) {
+    hook.template at<0>();
+    butterflies<0, 5>(v);          // strides 1..16
+    lanes::lane_stage<0>(v, (block & 1u) ? -1.0f : 1.0f);   // strides 32..256
+    lanes::lane_stage<1>(v, (block & 2u) ? -1.0f : 1.0f);
+    lanes::lane_stage<2>(v, (block & 4u) ? -1.0f : 1.0f);
+    lanes::lane_stage<3>(v, (block & 8u) ? -1.0f : 1.0f);
+    hook.template at<1>();
+    lanes::swap_top_register_bit<16>(v);
+    butterflies<4, 5>(v);          // stride 512
+    lanes::swap_top_register_bit<32>(v);
+    butterflies<4, 5>(v);          // stride 1024
+    float4* units = reinterpret_cast<float4*>(sh.xb);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        units[lay14::x4d_store_unit(wave, lane, q)] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    __syncthreads();
+    hook.template at<2>();
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+        const float4 f = units[lay14::x4d_load_unit(wave, lane, h)];
+        v[4 * h] = f.x;
+        v[4 * h + 1] = f.y;
+        v[4 * h + 2] = f.z;
+        v[4 * h + 3] = f.w;
+    }
+    butterflies<2, 5>(v);          // strides 2048..8192
+}
+// Whether the values of a thread of layout L4d (lane = i2..i7, wave = i8..i10) come negated.
+__device__ __forceinline__ bool l4d_negated(uint32_t lane, uint32_t wave) {
+    return odd_parity4((lane >> 3) | ((wave & 1u) << 3));
+}
+
 // max |v| over this thread's registers, then over the wave.
 __device__ __forceinline__ float wave_absmax(const float (&v)[kRegs]) {
     float m = 0.0f;
@@ -634,27 +680,33 @@ __device__ __forceinline__ void quantize_store_range(const float (&v)[kRegs], fl
     store_packed<BITS>(pk, payload + (g * BITS) / 8u);
 }
 
-// Output side of the inverse rotation: x = D (v * norm), norm = 2^-7, from layout L4d; the
-// first `valid` coordinates of the chunk are stored.  (The first pass of a longer rotation
-// passes norm = 1: its normalisation is one multiplication at the very end.)
+// Output side of the inverse rotation: x = D (v * norm), from layout L4d; the first `valid` coordinates
+// of the chunk are stored.  norm: 2^-7, negative where the thread's values are negated (a pass of a longer
+// rotation takes +-1: its normalisation is one multiplication at the very end).  The product
+// is taken with + 0 added in the same rounding: an exact zero, which the lane exchanges leave as +0 in a
+// negated thread too, stays the +0 that the stage's subtraction gives.
+// The stores go through a buffer descriptor that ends behind the last coordinate (its range check is made
+// for each dword): no ragged path, and the compiler knows how many stores are behind a load it waits for.
 template <bool SIGNED = true>
 __device__ __forceinline__ void store_signed_l4d(const SignTable& tab, const float (&v)[kRegs], float* out,
-                                                 uint32_t valid, uint32_t t, float norm = kInvSqrtC) {
+                                                 uint32_t valid, uint32_t t, float norm) {
+    uint64_t addr = reinterpret_cast<uint64_t>(out);   // the same for every lane: in scalar registers
+    addr = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)addr);
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(addr), 0, (int)(valid * 4u), 0x00020000);
 #pragma unroll
     for (int h = 0; h < 8; ++h) {
         const uint32_t i0 = h * 2048u + t * 4u;
         const uint32_t sb = SIGNED ? tab.sgn[i0 >> 5] >> (i0 & 31u) : 0u;   // bits 0..3: signs of the 4 coordinates
         float x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            x[e] = __uint_as_float(__float_as_uint(v[4 * h + e] * norm) ^ ((sb << (31 - e)) & 0x80000000u));
-        if (i0 + 4u <= valid) {
-            store_streaming(out + i0, x[0], x[1], x[2], x[3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (i0 + e < valid) out[i0 + e] = x[e];
+        for (int e = 0; e < 4; ++e) {
+            x[e] = __builtin_fmaf(v[4 * h + e], norm, 0.0f);
+            if (SIGNED) x[e] = __uint_as_float(xor_masked(__float_as_uint(x[e]), sb << (31 - e), 0x80000000u));
         }
+        const u32x4_vec q = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+        __builtin_amdgcn_raw_buffer_store_b128(q, rsrc, i0 * 4u, 0, kStreamingStore);
     }
 }
 

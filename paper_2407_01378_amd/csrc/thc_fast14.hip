@@ -17,8 +17,8 @@ namespace {
 // A call of one worker often has fewer chunks than the chip holds at once (512): the time is then
 // one chunk's chain of loads, exchanges and barriers, not a throughput.  Absmax and Encode therefore
 // run stages 5..8 between lanes (rotate_lanes_to_l3): one exchange less, three barriers instead
-// of six up to the range.  Forward keeps the LDS maps (its layout L4d has no form with permuted lanes, and
-// long calls of it are bound by memory: 6 TB/s); MinMax keeps them too, the lanes have not been timed there.
+// of six up to the range.  Forward keeps the LDS maps (long calls
+// of it are bound by memory: 6 TB/s); MinMax keeps them too, the lanes have not been timed there.
 // Measured at 7 M bf16 (433 chunks): range 8.0 -> 6.5 us, 8-bit encode 11.1 -> 9.4; per-call round of
 // eight workers 177 -> 154 us.
 template <bool BF16, Mode MODE, int BITS>
@@ -125,6 +125,7 @@ template <int SRC, bool SIGNED = true>
 __global__ __launch_bounds__(kThreads) void inverse_kernel(const ChunkArgs a) {
     __shared__ Shared sh;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    const uint32_t block = lay14::block_of_lane(lane), tp = (t & ~63u) | block;   // the thread's 32 coordinates
     const uint64_t p = blockIdx.x;
     const uint64_t g0 = p << kChunkLog2;
     const uint64_t left = a.n - g0;
@@ -136,7 +137,8 @@ __global__ __launch_bounds__(kThreads) void inverse_kernel(const ChunkArgs a) {
         load_raw<8, 4>(raw, static_cast<const float*>(a.in) + g0, (uint32_t)kChunk, t);
         raw_to_lds<8>(sh, raw, t);
         __syncthreads();
-        lds_to_l1<8, false>(sh, sh.sign[0], v, t);
+        lds_to_l1<8, false>(sh, sh.sign[0], v, tp);
+        // (a wave reads the units of its own 8 KB of the buffer, and the exchange stores there: no barrier)
     } else {
         // symmetric grid: yhat = S q - s;  min/max grid: yhat = S q + lo
         const bool ranged = a.range_in != nullptr;
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void inverse_kernel(const ChunkArgs a) {
             // 32 coordinates = 4 * bits bytes per thread
             const uint32_t bits = a.bits;
             const uint32_t* src = reinterpret_cast<const uint32_t*>(
-                static_cast<const uint8_t*>(a.in) + (g0 * bits) / 8u + (uint64_t)t * (4u * bits));
+                static_cast<const uint8_t*>(a.in) + (g0 * bits) / 8u + (uint64_t)tp * (4u * bits));
             const int centre = (int)(a.levels >> 1);
             uint32_t word[8];
 #pragma unroll
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(kThreads) void inverse_kernel(const ChunkArgs a) {
                 v[r] = (float)((int)A - centre) * q;
             }
         } else if constexpr (SRC == 1) {
-            const uint4* src = reinterpret_cast<const uint4*>(static_cast<const uint8_t*>(a.in) + g0) + 2 * t;
+            const uint4* src = reinterpret_cast<const uint4*>(static_cast<const uint8_t*>(a.in) + g0) + 2 * tp;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const uint4 w = src[k];
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void inverse_kernel(const ChunkArgs a) {
                         v[16 * k + 4 * d + b] = (float)((ww[d] >> (8 * b)) & 0xFFu) * q - s;
             }
         } else {
-            const uint4* src = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.in) + g0) + 4 * t;
+            const uint4* src = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.in) + g0) + 4 * tp;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint4 w = src[k];
@@ -187,9 +189,10 @@ __global__ __launch_bounds__(kThreads) void inverse_kernel(const ChunkArgs a) {
             }
         }
     }
-    rotate_l1_to_l3<false>(sh, v, lane, wave);
-    l3_to_l4d<false>(sh, v, lane, wave);
-    store_signed_l4d<SIGNED>(sh.sign[0], v, static_cast<float*>(a.out) + g0, valid, t, a.inv_sqrt_c);
+    NoHook none;
+    rotate_lanes_to_l4d(sh, v, lane, block, wave, none);   // (its barrier also orders the sign table)
+    store_signed_l4d<SIGNED>(sh.sign[0], v, static_cast<float*>(a.out) + g0, valid, t,
+                             l4d_negated(lane, wave) ? -a.inv_sqrt_c : a.inv_sqrt_c);
 }
 
 template <bool BF16, Mode MODE>

@@ -417,21 +417,34 @@ __global__ __launch_bounds__(256) void zero_words_kernel(uint32_t* dst, uint64_t
 
 __global__ void copy_word_kernel(const uint32_t* src, uint32_t* dst) { *dst = *src; }
 
+// The same number, of which the compiler no longer knows that it is the same for every item of a
+// persistent kernel: addresses that follow from it are computed anew instead of being kept in
+// registers (some 40 of the decoders' 128, with spills on their account) across the loop.
+__device__ __forceinline__ uint32_t this_item(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // ------------------------------------------------------------- aggregate_decode
 // One chunk per work item, persistent grid.  Thread t owns coordinates 32 t .. 32 t + 31
 // (layout L1): 4 * BITS payload bytes (BITS dwords) per worker.
-// Called from inside the rotation of the current chunk: loads and sums the first three
-// worker groups of the workgroup's NEXT chunk, one exchange of latency apart.
+// Called from inside the rotation of the current chunk: the first four worker groups of the workgroup's
+// NEXT chunk are loaded, two at a time, and the first two added.
 template <int BITS, bool BATCH, bool WIDE>
 struct NextChunkLoads {
+    static constexpr uint32_t kAdded = 2u;
     PayloadSum<BITS, BATCH, WIDE>& sum;
     uint64_t byte0;
     bool active;
     template <int K>
     __device__ __forceinline__ void at() {
         if (!active) return;
-        if (K > 0) sum.add(K - 1);
-        sum.issue(byte0, K);
+        if (K == 0) {
+            sum.begin(byte0);
+        } else if ((uint32_t)K - 1u < sum.groups()) {
+            sum.template add<(K - 1) & 1>(K - 1);
+            sum.template issue<(K - 1) & 1>(byte0, K + 1);
+        }
     }
 };
 
@@ -453,9 +466,11 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
     __shared__ Shared sh;
     using Sum = PayloadSum<BITS, BATCH, WIDE>;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    const uint32_t block = lay14::block_of_lane(lane), tp = (t & ~63u) | block;   // the thread's 32 coordinates
+    const float norm = l4d_negated(lane, wave) ? -kInvSqrtC : kInvSqrtC;
     const float Lf = (float)((1u << BITS) - 1u);
     const float Wf = (float)a.W;
-    const uint64_t thread_byte = (uint64_t)t * (4u * BITS);
+    const uint64_t thread_byte = (uint64_t)tp * (4u * BITS);
 
     uint32_t bidx = 0u;
     uint64_t boundary = 0u;   // first chunk of the bucket after bidx
@@ -480,11 +495,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
     Sum sum{ptrs, cur.pp, a.W};
     sum.clear();
     {   // the first chunk's payload, without overlap
-        const uint64_t byte0 = (((blockIdx.x - cur.chunk0) << kChunkLog2) * BITS) / 8u + thread_byte;
-        for (uint32_t g = 0; g < sum.groups(); ++g) {
-            sum.issue(byte0, g);
-            sum.add(g);
-        }
+        sum.all((((blockIdx.x - cur.chunk0) << kChunkLog2) * BITS) / 8u + thread_byte);
     }
     for (uint64_t p = blockIdx.x; p < a.chunks; p += gridDim.x) {
         const uint64_t pl = p - cur.chunk0;      // the chunk's number inside its bucket
@@ -507,8 +518,8 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
         for (int r = 0; r < kRegs; ++r) v[r] = (float)S[r] * qf - s;
 
         if (!BATCH && a.sums) {   // the caller also wants the integer aggregate
-            if (BITS == 8 || WIDE) store_sums16(S, static_cast<uint16_t*>(a.sums) + g0 + 32u * t);
-            else store_sums8(S, static_cast<uint8_t*>(a.sums) + g0 + 32u * t);
+            if (BITS == 8 || WIDE) store_sums16(S, static_cast<uint16_t*>(a.sums) + g0 + 32u * tp);
+            else store_sums8(S, static_cast<uint8_t*>(a.sums) + g0 + 32u * tp);
         }
 
         // the next chunk's payload arrives while this one rotates
@@ -519,16 +530,10 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
         sum.pp = nxt.pp;
         NextChunkLoads<BITS, BATCH, WIDE> next{sum, (((pn - nxt.chunk0) << kChunkLog2) * BITS) / 8u + thread_byte, more};
         sum.clear();
-        rotate_l1_to_l3<false>(sh, v, lane, wave, next);
-        if (next.active) {
-            sum.add(2);
-            for (uint32_t g = 3; g < sum.groups(); ++g) {
-                sum.issue(next.byte0, g);
-                sum.add(g);
-            }
-        }
-        l3_to_l4d<false>(sh, v, lane, wave);
-        store_signed_l4d(sh.sign[0], v, global_ptr<float>(reinterpret_cast<uint64_t>(cur.out)) + g0, valid, t);
+        const uint32_t ti = this_item(t), li = ti & 63u;
+        rotate_lanes_to_l4d(sh, v, li, block, wave, next);   // (its barrier also orders the sign table)
+        store_signed_l4d(sh.sign[0], v, global_ptr<float>(reinterpret_cast<uint64_t>(cur.out)) + g0, valid, ti, norm);
+        if (more) sum.rest(next.byte0, next.kAdded);   // (its first loads were issued in front of the stores: no wait for them)
         cur = nxt;
     }
 }
@@ -539,21 +544,16 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
 // from a = 0, which leaves a = z_0 after the first worker), so the running value never
 // needs more than BITS bits.  Optionally stores the packed aggregate (a + M) and counts
 // the coordinates with at least one clipped step.
-// Called from inside the rotation of the current chunk: loads the first worker group of
+// Called from inside the rotation of the current chunk: loads the first two worker groups of
 // the workgroup's next chunk.
-template <int BITS, int GROUP>
+template <class Loads>
 struct NextSatLoads {
-    PayloadWords<BITS> (&x)[GROUP];
-    const FusedPayloadPtrs& ptrs;
-    uint32_t W;
+    Loads& loads;
     uint64_t byte0;
     bool active;
     template <int K>
     __device__ __forceinline__ void at() {
-        if (K != 0 || !active) return;
-#pragma unroll
-        for (int j = 0; j < GROUP; ++j)
-            if ((uint32_t)j < W) x[j] = load_payload_words<BITS>(ptrs.p[j] + byte0);
+        if (K == 0 && active) loads.begin(byte0);
     }
 };
 
@@ -565,17 +565,16 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void sat_aggregate_decode_
     constexpr int kGroup = (BITS == 8 || COUNT) ? 2 : 4;   // the counting form needs the registers
     constexpr uint32_t kField = (1u << BITS) - 1u;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    const uint32_t block = lay14::block_of_lane(lane), tp = (t & ~63u) | block;   // the thread's 32 coordinates
+    const float norm = l4d_negated(lane, wave) ? -kInvSqrtC : kInvSqrtC;
     const float Lf = (float)(2 * M);
     const float Wf = (float)a.W;
     uint32_t clipped_total = 0u;
-    const uint64_t thread_byte = (uint64_t)t * (4u * BITS);
+    const uint64_t thread_byte = (uint64_t)tp * (4u * BITS);
 
-    PayloadWords<BITS> first[kGroup];   // the first worker group of the chunk about to start
-    {
-        NextSatLoads<BITS, kGroup> now{first, ptrs, a.W, (((uint64_t)blockIdx.x << kChunkLog2) * BITS) / 8u + thread_byte,
-                                       blockIdx.x < a.chunks};
-        now.template at<0>();
-    }
+    using Loads = PayloadLoads<BITS, false, kGroup>;
+    Loads loads{ptrs, nullptr, a.W, {}};
+    if (blockIdx.x < a.chunks) loads.begin((((uint64_t)blockIdx.x << kChunkLog2) * BITS) / 8u + thread_byte);
     for (uint64_t p = blockIdx.x; p < a.chunks; p += gridDim.x) {
         const uint64_t g0 = p << kChunkLog2;
         const uint64_t left = a.n - g0;
@@ -591,11 +590,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void sat_aggregate_decode_
             clip[r] = 0u;
         }
         const uint64_t byte0 = (g0 * BITS) / 8u + thread_byte;
-        for (uint32_t w0 = 0; w0 < a.W; w0 += kGroup) {
-            PayloadWords<BITS> x[kGroup];
-#pragma unroll
-            for (int j = 0; j < kGroup; ++j)
-                if (w0 + j < a.W) x[j] = w0 == 0 ? first[j] : load_payload_words<BITS>(ptrs.p[w0 + j] + byte0);
+        auto combine = [&](const PayloadWords<BITS>(&x)[kGroup], uint32_t w0) {
 #pragma unroll
             for (int j = 0; j < kGroup; ++j)
                 if (w0 + j < a.W) {
@@ -608,6 +603,12 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void sat_aggregate_decode_
                         acc[r] = c;
                     }
                 }
+        };
+        for (uint32_t g = 0; g < loads.groups(); g += 2u) {
+            combine(loads.x[0], g * kGroup);
+            loads.template issue<0>(byte0, g + 2u);
+            if (g + 1u < loads.groups()) combine(loads.x[1], (g + 1u) * kGroup);
+            loads.template issue<1>(byte0, g + 3u);
         }
         if (COUNT) {
 #pragma unroll
@@ -642,11 +643,10 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void sat_aggregate_decode_
         for (int r = 0; r < kRegs; ++r) v[r] = (float)acc[r] * qf;
         // the next chunk's first payloads arrive while this one rotates
         const uint64_t pn = p + gridDim.x;
-        NextSatLoads<BITS, kGroup> next{first, ptrs, a.W, ((pn << kChunkLog2) * BITS) / 8u + thread_byte,
-                                        pn < a.chunks};
-        rotate_l1_to_l3<false>(sh, v, lane, wave, next);
-        l3_to_l4d<false>(sh, v, lane, wave);
-        store_signed_l4d(sh.sign[0], v, a.out + g0, valid, t);
+        NextSatLoads<Loads> next{loads, ((pn << kChunkLog2) * BITS) / 8u + thread_byte, pn < a.chunks};
+        const uint32_t ti = this_item(t), li = ti & 63u;
+        rotate_lanes_to_l4d(sh, v, li, block, wave, next);   // (its barrier also orders the sign table)
+        store_signed_l4d(sh.sign[0], v, a.out + g0, valid, ti, norm);
     }
     if (COUNT) {   // one atomic per wave
 #pragma unroll

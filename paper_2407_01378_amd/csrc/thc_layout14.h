@@ -127,5 +127,20 @@ THC_HD uint32_t x3d_load_unit(uint32_t wave, uint32_t lane, uint32_t h) {  // h 
 }
 THC_HD uint32_t x3d_load(uint32_t wave, uint32_t lane, uint32_t h) { return x3d_load_unit(wave, lane, h) << 2; }
 
+// ---- X4d: 11 stages inside the wave -> L4d, whole buffer, 16-byte units ---------------------
+// Behind the register swaps of thc_lanes.h a thread holds register = i0..i3, i10 and its lane l stands for
+// block b = block_of_lane(l): i5..i8 = b0..b3, i4 = l4, i9 = l5 (i4 and i9 have changed places, then i9
+// and i10).  Unit of (i2..i13): u0 u1 u2 = i2^i5, i3^i6, i4^i7 | u3..u11 = i5..i13.
+// Stores: eight consecutive lanes differ in i5, i6, i7, so u0..u2 take all values.  Loads: the lanes
+// served together differ in i2, i3 and in (i4, i5, i6) of one parity, so u0..u3 do.
+THC_HD uint32_t x4d_store_unit(uint32_t wave, uint32_t lane, uint32_t q) {  // q = (i2, i3, i10); wave = i11..i13
+    const uint32_t i5to8 = block_of_lane(lane) & 15u, i4 = (lane >> 4) & 1u, i9 = lane >> 5;
+    return ((i5to8 & 7u) ^ (q & 3u) ^ (i4 << 2)) | (i5to8 << 3) | (i9 << 7) | ((q >> 2) << 8) | (wave << 9);
+}
+// reader (L4d): wave = i8..i10, lane = i2..i7, loads registers (i0, i1) of group h = (i11..i13)
+THC_HD uint32_t x4d_load_unit(uint32_t wave, uint32_t lane, uint32_t h) {  // h = 0..7
+    return ((lane & 7u) ^ (lane >> 3)) | ((lane >> 3) << 3) | (wave << 6) | (h << 9);
+}
+
 }  // namespace lay14
 }  // namespace thc

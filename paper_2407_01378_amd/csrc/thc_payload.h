@@ -51,52 +51,140 @@ __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* 
     return r;
 }
 
-// Sum of the workers' payload words of one thread (its 32 coordinates) in sub-word lanes,
-// built up group by group: a group is the payload of kGroup workers in flight at once.
-// WIDE: 16-bit accumulators for 4-bit payloads too (W * L > 255: more than 17 workers); lane q
-// then holds coordinates q (low half) and q + 16 / BITS (high half) of the dword's 32 / BITS.
-// GROUP 0: at most 16 registers of payload in flight.
-template <int BITS, bool BATCH = false, bool WIDE = false, int GROUP = 0>
-struct PayloadSum {
-    static_assert(!(WIDE && BITS == 8), "8-bit payloads always sum in 16-bit lanes");
-    static constexpr int kWords = BITS;                        // payload dwords per worker per thread
-    static constexpr int kLanes = BITS == 8 ? 2 : (WIDE ? 16 : 8) / BITS;   // sub-word accumulators per dword
-    static constexpr uint32_t kMask = BITS == 8 ? 0x00FF00FFu
-                                      : WIDE    ? (BITS == 4 ? 0x000F000Fu : 0x00030003u)
-                                                : (BITS == 4 ? 0x0F0F0F0Fu : 0x03030303u);
-    static constexpr int kGroup = GROUP != 0 ? GROUP : (BITS == 8 ? 2 : 4);
+// The workers' payload words of one thread (its 32 coordinates) on their way into registers, group by
+// group: a group is the payload of GROUP workers.  Two groups can be in flight at once (buffers 0 and 1, 32
+// registers): while one is combined the next one's loads are on their way.
+template <int BITS, bool BATCH, int GROUP = BITS == 8 ? 2 : 4>
+struct PayloadLoads {
+    static constexpr uint32_t kGroup = GROUP;
     const FusedPayloadPtrs& ptrs;   // single bucket: the payload pointers, in the kernel arguments
     ConstU64Ptr pp;                 // batched: those of the bucket being summed, in its record
     uint32_t W;
-    uint32_t acc[kWords][kLanes];
-    PayloadWords<BITS> x[kGroup];
+    PayloadWords<BITS> x[2][GROUP];
 
+    __device__ __forceinline__ const uint8_t* pointer(uint32_t w) const {
+        return BATCH ? global_ptr<const uint8_t>(pp[w]) : ptrs.p[w];
+    }
+    __device__ __forceinline__ uint32_t groups() const { return (W + kGroup - 1u) / kGroup; }
+    // Loads of one group into buffer B (nothing past the last worker).  A whole group has no condition per
+    // worker: its pointers come in one scalar load.
+    template <int B>
+    __device__ __forceinline__ void issue(uint64_t byte0, uint32_t group) {
+        const uint32_t w0 = group * kGroup;
+        if (w0 >= W) return;
+        if (w0 + kGroup <= W) {
+#pragma unroll
+            for (uint32_t j = 0; j < kGroup; ++j) x[B][j] = load_payload_words<BITS>(pointer(w0 + j) + byte0);
+            // (the empty assembly statements differ, so that the two branches are not merged into one that
+            // picks its registers by address, which would put x into memory)
+            asm volatile("; whole group");
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j + 1u < kGroup; ++j)
+                if (w0 + j < W) {
+                    x[B][j] = load_payload_words<BITS>(pointer(w0 + j) + byte0);
+                    asm volatile("; worker of a part of a group");
+                }
+            asm volatile("; part of a group");
+        }
+    }
+    __device__ __forceinline__ void begin(uint64_t byte0) {
+        issue<0>(byte0, 0u);
+        issue<1>(byte0, 1u);
+    }
+};
+
+// Their exact sum in sub-word lanes.
+//   One group at a time, added as soon as it was loaded, is a chain of memory latencies for a thread that
+//   sums more than the few groups that ride along with the previous chunk's rotation: 64 workers x 2^21
+//   coordinates (128 chunks, 4 bits) 45 -> 22 us with two groups in flight and the 8-bit lanes below.
+// WIDE: 16-bit accumulators for 4-bit payloads too (W * L > 255: more than 17 workers); lane q
+// then holds coordinates q (low half) and q + 4 (high half) of the dword's 8.  The workers
+// meet in 8-bit lanes first, kFlush groups of them (16 * 15 <= 255), which takes half the operations.
+template <int BITS, bool BATCH = false, bool WIDE = false>
+struct PayloadSum : PayloadLoads<BITS, BATCH> {
+    static_assert(!(WIDE && BITS != 4), "8-bit payloads always sum in 16-bit lanes, 2-bit ones in 8-bit lanes");
+    using Loads = PayloadLoads<BITS, BATCH>;
+    using Loads::groups;
+    using Loads::kGroup;
+    using Loads::W;
+    using Loads::x;
+    static constexpr int kWords = BITS;                        // payload dwords per worker per thread
+    static constexpr int kLanes = BITS == 8 ? 2 : 8 / BITS;    // sub-word accumulators per dword while adding
+    static constexpr uint32_t kMask = BITS == 8 ? 0x00FF00FFu : BITS == 4 ? 0x0F0F0F0Fu : 0x03030303u;
+    static constexpr uint32_t kFlush = 16u / kGroup;           // WIDE: groups that fit the 8-bit lanes
+    uint32_t acc[kWords][kLanes];
+    uint32_t wide[WIDE ? kWords : 1][4];
+
+    __device__ __forceinline__ PayloadSum(const FusedPayloadPtrs& ptrs, ConstU64Ptr pp, uint32_t W)
+        : Loads{ptrs, pp, W, {}} {}
     __device__ __forceinline__ void clear() {
 #pragma unroll
         for (int d = 0; d < kWords; ++d)
 #pragma unroll
             for (int k = 0; k < kLanes; ++k) acc[d][k] = 0u;
     }
-    __device__ __forceinline__ void issue(uint64_t byte0, uint32_t group) {
-#pragma unroll
-        for (int j = 0; j < kGroup; ++j)
-            if (group * kGroup + j < W) {
-                const uint8_t* src = BATCH ? global_ptr<const uint8_t>(pp[group * kGroup + j])
-                                           : ptrs.p[group * kGroup + j];
-                x[j] = load_payload_words<BITS>(src + byte0);
-            }
-    }
+    template <int B>
     __device__ __forceinline__ void add(uint32_t group) {
+        const uint32_t w0 = group * kGroup;
+        if (w0 + kGroup <= W) {
 #pragma unroll
-        for (int j = 0; j < kGroup; ++j)
-            if (group * kGroup + j < W) {
+            for (uint32_t j = 0; j < kGroup; j += 2u)
 #pragma unroll
                 for (int d = 0; d < kWords; ++d)
 #pragma unroll
-                    for (int q = 0; q < kLanes; ++q) acc[d][q] += (x[j].w[d] >> (BITS * q)) & kMask;
-            }
+                    for (int q = 0; q < kLanes; ++q)   // (one three-operand addition for two workers)
+                        acc[d][q] += ((x[B][j].w[d] >> (BITS * q)) & kMask) + ((x[B][j + 1].w[d] >> (BITS * q)) & kMask);
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j + 1u < kGroup; ++j)
+                if (w0 + j < W) {
+#pragma unroll
+                    for (int d = 0; d < kWords; ++d)
+#pragma unroll
+                        for (int q = 0; q < kLanes; ++q) acc[d][q] += (x[B][j].w[d] >> (BITS * q)) & kMask;
+                }
+        }
     }
-    __device__ __forceinline__ uint32_t groups() const { return (W + kGroup - 1) / kGroup; }
+    // WIDE, behind the addition of `group`: the 8-bit lanes into the wide ones before they could overflow.
+    __device__ __forceinline__ void flush(uint32_t group) {
+        if constexpr (WIDE) {
+            if ((group + 1u) % kFlush == 0u || group + 1u == groups()) {
+#pragma unroll
+                for (int d = 0; d < kWords; ++d)
+#pragma unroll
+                    for (int q = 0; q < kLanes; ++q) {
+                        wide[d][q] += acc[d][q] & 0x00FF00FFu;
+                        wide[d][q + 2] += (acc[d][q] >> 8) & 0x00FF00FFu;
+                        acc[d][q] = 0u;
+                    }
+            }
+        }
+    }
+    // Adds the groups from `from` on (even, less than kFlush; the caller has added those before), the first
+    // two of which are in flight.
+    __device__ __forceinline__ void rest(uint64_t byte0, uint32_t from) {
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int d = 0; d < kWords; ++d)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) wide[d][k] = 0u;
+        }
+        for (uint32_t g = from; g < groups(); g += 2u) {
+            add<0>(g);
+            flush(g);
+            this->template issue<0>(byte0, g + 2u);
+            if (g + 1u < groups()) {
+                add<1>(g + 1u);
+                flush(g + 1u);
+            }
+            this->template issue<1>(byte0, g + 3u);
+        }
+    }
+    __device__ __forceinline__ void all(uint64_t byte0) {
+        this->begin(byte0);
+        rest(byte0, 0u);
+    }
 
     // Sub-word lanes -> one sum per coordinate.
     __device__ __forceinline__ void unpack(uint32_t (&S)[32]) const {
@@ -107,12 +195,11 @@ struct PayloadSum {
                 S[4 * d + 1] = acc[d][1] & 0xFFFFu;
                 S[4 * d + 2] = acc[d][0] >> 16;
                 S[4 * d + 3] = acc[d][1] >> 16;
-            } else if (WIDE) {       // dword d: 32/BITS coordinates; lane q = coordinates q and q + 16/BITS
-                constexpr int per = 32 / BITS;
+            } else if (WIDE) {       // dword d: 8 coordinates; lane q = coordinates q and q + 4
 #pragma unroll
-                for (int q = 0; q < kLanes; ++q) {
-                    S[per * d + q] = acc[d][q] & 0xFFFFu;
-                    S[per * d + kLanes + q] = acc[d][q] >> 16;
+                for (int q = 0; q < 4; ++q) {
+                    S[8 * d + q] = wide[d][q] & 0xFFFFu;
+                    S[8 * d + 4 + q] = wide[d][q] >> 16;
                 }
             } else {                 // dword d: 32/BITS coordinates; lane q byte b = coordinate (8/BITS) b + q
                 constexpr int per = 32 / BITS;

@@ -376,16 +376,9 @@ __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const Smal
     float s = 0.0f;
     if (exists) s = a.scale[g >> l];
     if constexpr (SRC == 0) {
-        // up to 32 registers of payload in flight (nothing else is live yet)
-        PayloadSum<BITS, false, WIDE, BITS == 8 ? 4 : 8> sum{ptrs, nullptr, a.W};
+        PayloadSum<BITS, false, WIDE> sum{ptrs, nullptr, a.W};
         sum.clear();
-        if (exists) {
-            const uint64_t byte0 = (g * BITS) / 8u;
-            for (uint32_t k = 0; k < sum.groups(); ++k) {
-                sum.issue(byte0, k);
-                sum.add(k);
-            }
-        }
+        if (exists) sum.all((g * BITS) / 8u);
         if (wave == 0) *reinterpret_cast<u32x4*>(&sign[4 * lane]) = sign_block((base >> 7) + lane, a.key0, a.key1);
         sum.unpack(S);
         if (a.sums && exists) {
