@@ -17,7 +17,8 @@
 //   launch per worker of the generic kernels, which load element by element and take a
 //   barrier per stage above 2^4.
 //
-// Decode.  A workgroup of four waves owns 2^13 coordinates; a thread sums the workers' payload
+// Decode.  A workgroup of four waves owns 2^13 coordinates (fewer, down to the 2^11 of a wave or a chunk, where
+// that spreads a short gradient over the CUs: 2^20 coordinates are 128 workgroups of four); a thread sums the workers' payload
 // words of its 32 coordinates, five stages run in registers, the wave re-shuffles through its
 // own 8 KB of LDS, the rest of the stages follow, and the result leaves in 128-byte lines.
 // Bound by memory.
@@ -346,8 +347,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
 }
 
 // ------------------------------------------------------------------------------ decode
-constexpr int kDecodeThreads = 256;
-constexpr uint32_t kDecodeLog2 = 13;   // coordinates of a workgroup
+constexpr int kDecodeThreads = 256;    // of a workgroup, at most
+constexpr uint32_t kDecodeLog2 = 13;   // its coordinates
 
 struct SmallDecodeArgs {
     uint64_t n, padded;
@@ -368,7 +369,7 @@ __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const Smal
     __shared__ alignas(16) uint32_t sign[1u << (kDecodeLog2 - 5u)];
     const uint32_t t = threadIdx.x, lane = t & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
-    const uint64_t base = (uint64_t)blockIdx.x << kDecodeLog2;
+    const uint64_t base = (uint64_t)blockIdx.x * (blockDim.x * 32u);
     const uint64_t g = base + 32u * t;
     const bool exists = g < a.padded;   // (chunks are whole multiples of a thread's 32 coordinates)
     const uint32_t l = a.l;
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const Smal
         PayloadSum<BITS, false, WIDE> sum{ptrs, nullptr, a.W};
         sum.clear();
         if (exists) sum.all((g * BITS) / 8u);
-        if (wave == 0) *reinterpret_cast<u32x4*>(&sign[4 * lane]) = sign_block((base >> 7) + lane, a.key0, a.key1);
+        if (t < blockDim.x / 4u) *reinterpret_cast<u32x4*>(&sign[4 * t]) = sign_block((base >> 7) + t, a.key0, a.key1);
         sum.unpack(S);
         if (a.sums && exists) {
             if (BITS == 8 || WIDE) store_sums16(S, static_cast<uint16_t*>(a.sums) + g);
@@ -392,7 +393,7 @@ __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const Smal
         for (int k = 0; k < kVecs; ++k)
             q[k] = exists ? load_last_use(reinterpret_cast<const uint4*>(static_cast<const uint8_t*>(a.in) + g * SRC) + k)
                           : make_uint4(0u, 0u, 0u, 0u);
-        if (wave == 0) *reinterpret_cast<u32x4*>(&sign[4 * lane]) = sign_block((base >> 7) + lane, a.key0, a.key1);
+        if (t < blockDim.x / 4u) *reinterpret_cast<u32x4*>(&sign[4 * t]) = sign_block((base >> 7) + t, a.key0, a.key1);
 #pragma unroll
         for (int k = 0; k < kVecs; ++k) {
             const uint32_t x[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
@@ -556,7 +557,10 @@ bool small_applicable(Mode mode, const ChunkArgs& c) {
 static hipError_t small_decode(k14::SmallDecodeArgs& a, const FusedPayloadPtrs& ptrs, int src, uint32_t bits, bool wide,
                                hipStream_t stream) {
     using namespace k14;
-    const dim3 grid((uint32_t)((a.padded + (1ull << kDecodeLog2) - 1u) >> kDecodeLog2)), block(kDecodeThreads);
+    // 2^11 coordinates per wave, at least a chunk per workgroup: two workgroups for every CU before they grow
+    uint32_t log2 = kDecodeLog2;
+    while (log2 > (a.l > kWaveLog2 ? a.l : kWaveLog2) && (a.padded >> log2) < 2u * (uint64_t)device_cus()) --log2;
+    const dim3 grid((uint32_t)((a.padded + (1ull << log2) - 1u) >> log2)), block(1u << (log2 - 5u));
     if (grid.x == 0) return hipSuccess;
 #define THC_SMALL_DECODE(S, B, WI) hipLaunchKernelGGL((small_decode_kernel<S, B, WI>), grid, block, 0, stream, a, ptrs)
     if (src == 0) {
