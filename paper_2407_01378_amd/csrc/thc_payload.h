@@ -31,6 +31,9 @@ template <int BITS>
 struct PayloadWords {
     uint32_t w[BITS];
 };
+// Read for the last time - but 8-bit payloads take two loads per thread from the same lines, and a line that the
+// first one marks as used up may be gone before the second: 8 workers x 2^24 coordinates, encode + decode,
+// 153 us so, 143 us as ordinary loads (4 bits, one load per thread: the same either way).
 template <int BITS>
 __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* p) {
     PayloadWords<BITS> r;
@@ -41,7 +44,8 @@ __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* 
     } else {
 #pragma unroll
         for (int k = 0; k < BITS / 4; ++k) {
-            const uint4 q = load_last_use(reinterpret_cast<const uint4*>(p) + k);
+            const uint4* src = reinterpret_cast<const uint4*>(p) + k;
+            const uint4 q = BITS == 8 ? *src : load_last_use(src);
             r.w[4 * k] = q.x;
             r.w[4 * k + 1] = q.y;
             r.w[4 * k + 2] = q.z;
