@@ -805,6 +805,10 @@ uint32_t thc_full_log2(uint64_t n) {
     return (1ull << l) >= n ? l : 0;
 }
 
+static hipError_t first_pass(Mode mode, const ChunkArgs& a, hipStream_t st) {
+    return a.chunk_log2 == 15 ? thc::launch_full_first15(mode, a, st) : thc::launch_fast14(mode, a, st);
+}
+
 static int forward_full(const void* x, thc_dtype dt, uint64_t n, uint32_t log2_size, uint64_t seed,
                         float* y, float* absmax, void* stream, bool defer_last = false) {
     int rc = check_full(n, log2_size);
@@ -813,19 +817,19 @@ static int forward_full(const void* x, thc_dtype dt, uint64_t n, uint32_t log2_s
     if (!y || (n != 0 && !x)) return THC_ERR_NULL;
     if (!aligned(x, 16) || !aligned(y, 16)) return THC_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    ChunkArgs a = base_args(n, 14, seed);
+    ChunkArgs a = base_args(n, thc::full_first_log2(n, log2_size), seed);
     a.in = x;
     a.out = y;
     a.in_bf16 = dt == THC_BF16;
     a.inv_sqrt_c = 1.0f;
     a.zero_word = reinterpret_cast<uint32_t*>(absmax);   // raised by the last pass
-    if (n != 0 && thc::launch_fast14(Mode::Forward, a, st) != hipSuccess) return THC_ERR_HIP;
+    if (n != 0 && first_pass(Mode::Forward, a, st) != hipSuccess) return THC_ERR_HIP;
     if (n == 0 && absmax && thc::launch_zero_words(a.zero_word, 1, st) != hipSuccess) return THC_ERR_HIP;
     // (the zero padding behind the last chunk is not written: the first pass reads it as zero)
     thc::FullDeferred d{};
     d.kind = thc::FullLast::RangeOnly;
     return finish(thc::launch_high_passes(y, log2_size, full_factor(log2_size), nullptr, 0, a.key0, a.key1, st,
-                                          a.padded, absmax, defer_last ? &d : nullptr));
+                                          a.padded, absmax, a.chunk_log2, defer_last ? &d : nullptr));
 }
 
 int rht_forward_full(const void* x, thc_dtype dt, uint64_t n, uint32_t log2_size, uint64_t seed,
@@ -861,10 +865,11 @@ int thc_full_encode_deferred(const float* y, uint64_t n, uint32_t log2_size, uin
     d.bits = bits;
     d.worker = worker;
     d.payload = payload;
+    const uint32_t first = thc::full_first_log2(n, log2_size);
     // (the kernel only reads y; `valid` is what rht_forward_full_deferred left behind for this n)
     return finish(thc::launch_high_passes(const_cast<float*>(y), log2_size, full_factor(log2_size), nullptr, 0,
                                           (uint32_t)seed, (uint32_t)(seed >> 32), static_cast<hipStream_t>(stream),
-                                          padded_coords(n, 14), nullptr, &d));
+                                          padded_coords(n, first), nullptr, first, &d));
 }
 
 int rht_inverse_full(float* y, uint64_t n, uint32_t log2_size, uint64_t seed, float* x, void* stream) {
@@ -875,13 +880,13 @@ int rht_inverse_full(float* y, uint64_t n, uint32_t log2_size, uint64_t seed, fl
     if (!aligned(x, 16) || !aligned(y, 16)) return THC_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint64_t total = 1ull << log2_size;
-    ChunkArgs a = base_args(total, 14, seed);
+    ChunkArgs a = base_args(total, thc::full_first_log2(total, log2_size), seed);
     a.in = y;
     a.out = y;
     a.inv_sqrt_c = 1.0f;
-    if (thc::launch_fast14(Mode::Plain, a, st) != hipSuccess) return THC_ERR_HIP;
+    if (first_pass(Mode::Plain, a, st) != hipSuccess) return THC_ERR_HIP;
     return finish(thc::launch_high_passes(y, log2_size, full_factor(log2_size), x, n, a.key0, a.key1, st,
-                                          total, nullptr));
+                                          total, nullptr, a.chunk_log2));
 }
 
 int thc_full_absmax(const float* y, uint32_t log2_size, float* absmax, void* stream) {
@@ -929,7 +934,7 @@ int thc_full_decode_inverse(const void* sums, const float* scale, uint32_t W, ui
     if (!aligned(sums, 16) || !aligned(scale, 4) || !aligned(work, 16) || !aligned(x, 16)) return THC_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint64_t total = 1ull << log2_size;
-    ChunkArgs a = base_args(total, 14, seed);
+    ChunkArgs a = base_args(total, thc::full_first_log2(total, log2_size), seed);
     a.in = sums;
     a.out = work;
     a.scale_in = scale;
@@ -939,9 +944,9 @@ int thc_full_decode_inverse(const void* sums, const float* scale, uint32_t W, ui
     a.bits = bits;
     a.sum_bytes = sum_bytes;
     a.inv_sqrt_c = 1.0f;
-    if (thc::launch_fast14(Mode::PlainDecode, a, st) != hipSuccess) return THC_ERR_HIP;
+    if (first_pass(Mode::PlainDecode, a, st) != hipSuccess) return THC_ERR_HIP;
     return finish(thc::launch_high_passes(work, log2_size, full_factor(log2_size), x, n, a.key0, a.key1, st,
-                                          total, nullptr));
+                                          total, nullptr, a.chunk_log2));
 }
 
 // ----------------------------------------------------------------------------- TopKC

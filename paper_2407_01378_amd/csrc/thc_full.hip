@@ -4,7 +4,8 @@
 // separately rounded fp32 add and subtract), so results are bit-identical to the
 // stage-by-stage definition:
 //   stages 0..13    the chunk-2^14 kernels (thc_fast14.hip), data in registers and LDS
-//   stages 14..l-1  "high passes" over the fp32 array in global memory, up to 11 stages per
+//                   (0..14 for two sizes: thc_full15.hip)
+//   the rest        "high passes" over the fp32 array in global memory, up to 11 stages per
 //                   pass (this file), in place
 // plus the steps of the quantizer on rotated data, which the partial-rotation path fuses into
 // its rotation kernels: as elementwise kernels on stored values (range, encode, decode), and
@@ -507,7 +508,7 @@ hipError_t launch_pass(uint32_t m, uint32_t log2_size, hipStream_t stream, HighP
 
 }  // namespace
 
-// Stages 14 .. l-1 on data (2^l floats, stages 0..13 already done), in place; the last pass
+// Stages first_log2 .. l-1 on data (2^l floats, the stages before them already done), in place; the last pass
 // multiplies by `factor`, and for the inverse direction (`x` non-null) applies the sign
 // diagonal and writes the first n coordinates to x instead.  Forward direction: only the
 // first `valid` floats of data have been written (the rest is the zero padding, which the
@@ -518,11 +519,11 @@ hipError_t launch_pass(uint32_t m, uint32_t log2_size, hipStream_t stream, HighP
 // quantizer into deferred->payload.
 hipError_t launch_high_passes(float* data, uint32_t log2_size, float factor, float* x, uint64_t n,
                               uint32_t key0, uint32_t key1, hipStream_t stream, uint64_t valid,
-                              float* absmax, const FullDeferred* deferred) {
+                              float* absmax, uint32_t first_log2, const FullDeferred* deferred) {
     const bool range_only = deferred && deferred->kind == FullLast::RangeOnly;
     const bool encode_only = deferred && deferred->kind == FullLast::EncodeOnly;
     if ((deferred && (x || range_only == encode_only)) || (range_only && !absmax)) return hipErrorInvalidValue;
-    uint32_t s0 = 14u;
+    uint32_t s0 = first_log2;
     const uint32_t passes = (log2_size - s0 + kMaxStages - 1u) / (uint32_t)kMaxStages;
     for (uint32_t p = 0; p < passes; ++p) {
         const uint32_t left = log2_size - s0;

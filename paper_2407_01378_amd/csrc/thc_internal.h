@@ -177,7 +177,17 @@ hipError_t launch_sat_aggregate(const FusedPayloadPtrs& ptrs, uint32_t W, uint32
                                 uint64_t payload_bytes, uint64_t padded, uint8_t* aggregate,
                                 unsigned long long* overflow, hipStream_t stream);
 
-// ---- full rotation (thc_full.hip) -----------------------------------------------------
+// ---- full rotation (thc_full.hip, thc_full15.hip) ------------------------------------------
+// Stages of the first pass over n coordinates of 2^log2_size: chunks of 2^14, or of 2^15 where 11 or 12 stages would
+// be left behind them (a pass of 11 moves 64-byte pieces, 12 take two passes).  A device holds 512 chunks of 2^15 at
+// once, and a few more than that take as long as 1024: with less than 9/16 of 2^25 to read the chunks stay
+// at 2^14 (eight workers x 17 M fp32: 762 us so, 769 us with 2^15; x 25.6 M: 1021 and 952 us).
+// All forward calls for one gradient agree on it; the inverse direction reads the whole array (n = 2^log2_size).
+inline uint32_t full_first_log2(uint64_t n, uint32_t log2_size) {
+    return log2_size == 26u || (log2_size == 25u && n > 9ull << 21) ? 15u : 14u;
+}
+// The first pass over chunks of 2^15: Forward, Plain or PlainDecode.
+hipError_t launch_full_first15(Mode mode, const ChunkArgs& a, hipStream_t stream);
 // The last forward pass put off until the shared scale is known: evaluated for the range only
 // (every earlier pass runs as usual), or run on its own with its results quantized instead of
 // stored.  (No FullDeferred at all: every pass runs and stores.)
@@ -190,7 +200,7 @@ struct FullDeferred {
 };
 hipError_t launch_high_passes(float* data, uint32_t log2_size, float factor, float* x, uint64_t n,
                               uint32_t key0, uint32_t key1, hipStream_t stream, uint64_t valid,
-                              float* absmax, const FullDeferred* deferred = nullptr);
+                              float* absmax, uint32_t first_log2, const FullDeferred* deferred = nullptr);
 hipError_t launch_full_absmax(const float* y, uint32_t log2_size, float* absmax, hipStream_t stream);
 hipError_t launch_full_encode(const float* y, uint32_t log2_size, const float* scale, uint32_t levels,
                               uint32_t bits, uint32_t worker, uint32_t key0, uint32_t key1,
