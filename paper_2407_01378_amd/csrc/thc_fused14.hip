@@ -27,14 +27,35 @@ constexpr uint32_t kWaves = kThreads / 64;
 // Second argument of __launch_bounds__ (waves per SIMD the compiler must allow): two
 // workgroups of 8 waves per CU = 4 waves on each of the 4 SIMDs = at most 128 VGPRs.
 constexpr int kWavesPerSimd = 4;
-// Pauses of the wait for the peers' range words, in units of 64 clocks (s_sleep).
+// How the workgroups of a chunk tell one another its range (template argument of the encoder).
+enum class Words : int {
+    PerWave = 0,    // every wave publishes a word and reads all words: up to 16 workers
+    PerGroup = 1,   // one word per workgroup (the waves' maxima meet in LDS), read by every wave: up to 32
+    OneReader = 2,  // the same, read by one wave for all: beyond
+    Quick = 3       // PerWave for a launch of at most one workgroup per CU and one item each: nothing to overlap
+};
+constexpr uint32_t kPerWaveMaxWorkers = 16;
+constexpr uint32_t kPerGroupMaxWorkers = 32;
+// Pauses of the wait for the peers' range words, in units of 64 clocks (s_sleep): in front of the first read,
+// and between reads.  A word takes about 2 us from one workgroup to another, the peers of a chunk
+// publish up to about 2 us apart, and reads that come back incomplete load the path the words travel on.
+//   PerWave    8 workers x 1600 chunks: 16 .. 48 alike, 8 and 64 2 to 3 % slower
+//   PerGroup   32 workers x 512 chunks 270 us with 32, 256 with 40, 184 chunks the same; 24 x 244 chunks 94.7 -> 92
+//   OneReader  an eighth of the reads; a longer pause from the 8th round on, because how long a workgroup is out of
+//              the way of the other one on its CU decides whether the two stay half an item apart.  64 workers, bf16, 4 bits,
+//              128 chunks 140 -> 130 us, 256 chunks 279 -> 248; 8 bits, 245 chunks 363 -> 284 (32 workers x 184
+//              chunks would lose 5 %)
+//   few rounds 64 workers x 1 chunk 24.7 -> 24.4, x 16 chunks 35.0 -> 34.6
+//   Quick      4 chunks x 8 workers 14.7 -> 14.4 us with the decoder, 2 chunks x 2 workers 13.0 -> 12.4
 constexpr int kFirstPollSleep = 32;
+constexpr int kFirstPollSleepPerGroup = 40;
+constexpr int kFirstPollSleepLate = 48;
+constexpr uint32_t kLateRound = 8;
+constexpr int kFirstPollSleepFewRounds = 16;   // PerGroup, OneReader
+constexpr uint32_t kFewRounds = 4;
+constexpr int kFirstPollSleepQuick = 8;
 constexpr int kPollSleep = 8;
-// Above this many workers the one-pass encoder publishes one range word per workgroup.
-#ifndef THC_WGWORD_ABOVE
-#define THC_WGWORD_ABOVE 16
-#endif
-constexpr uint32_t kPerWaveWordsMaxWorkers = THC_WGWORD_ABOVE;
+constexpr int kPollSleepOneReader = 4;
 // ------------------------------------------------------------------ encode_all
 __device__ __forceinline__ ConstRecordPtr batch_record(const BatchArgs& batch, uint32_t k) {
     return (ConstRecordPtr)(batch.records + (uint64_t)k * batch.record_bytes);
@@ -61,14 +82,16 @@ struct BucketView {
 // symmetrically around zero: every wave publishes two words (the maximum, then the negated
 // minimum, both through order_key() so that both are combined by a maximum), `scale` receives
 // (lo, hi) pairs, and the quantizer subtracts lo.
-// WGWORD: one range word per WORKGROUP instead of one per wave (the waves' maxima are combined
+// WORDS PerGroup, OneReader: one range word per WORKGROUP instead of one per wave (the waves' maxima are combined
 // through LDS at the barrier that opens the last exchange, and wave 0 publishes and clears).
 // For many workers: with W = 64 a chunk would otherwise have 512 words, every polling wave
 // would read 2 KB per poll, and that traffic delays the words it waits for.  At W = 8 the
 // later publication costs more than the lighter polls save, so the per-wave form stays.
-template <bool BF16, bool ODD, bool BATCH, bool MINMAX = false, bool WGWORD = false>
+template <bool BF16, bool ODD, bool BATCH, bool MINMAX = false, Words WORDS = Words::PerWave>
 struct EncodeAllCtx {
-    static_assert(!(MINMAX && WGWORD), "the per-workgroup word exists for the symmetric grid only");
+    static constexpr bool WGWORD = WORDS == Words::PerGroup || WORDS == Words::OneReader;
+    static constexpr bool kQuick = WORDS == Words::Quick;
+    static_assert(!MINMAX || WORDS == Words::PerWave, "the other forms exist for the symmetric grid only");
     static constexpr uint32_t kWordsPerWorker = WGWORD ? 1u : kWaves;
     static constexpr int kUnits = BF16 ? 4 : 8;
     static constexpr int kElem = BF16 ? 2 : 4;
@@ -156,7 +179,7 @@ struct EncodeAllCtx {
     // layout.  The direct form also fills the sign table of the workgroup's next item,
     // which is read only after the barriers of this item's exchanges.
     __device__ __forceinline__ void front(float (&v)[kRegs], uint64_t p) {
-        const bool more = p + dp < a.chunks;
+        const bool more = !kQuick && p + dp < a.chunks;
         if constexpr (kDirect) {
             units_to_l1<kUnits, true>(sh.sign[parity], raw.u, v, tp);
         } else {
@@ -176,7 +199,7 @@ struct EncodeAllCtx {
         for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));
         asm volatile("" ::: "memory");
         if (BATCH && more && p + dp >= boundary) nxt = view_of(p + dp);   // rarely: a new bucket
-        if (kDirect) load(p + dp, nxt);
+        if (kDirect && !kQuick) load(p + dp, nxt);
         if (more) fill_signs(p + dp, nxt, parity ^ 1u);
         parity ^= 1u;
         rotate_lanes_to_l3<true>(sh, v, lane, block, wave);
@@ -230,13 +253,19 @@ struct EncodeAllCtx {
         const uint32_t* slot = a.slots + p * nwords;
         uint32_t mx = 0u, mx2 = 0u;   // mx2: MINMAX only, the negated minima
         bool done = false;
-        // The peers of a chunk publish up to about 2 us apart and a word takes about as long
-        // to travel, so the first read waits a little: reads that come back incomplete are not
-        // free (they load the path the words travel on), and measured on the headline bucket a
-        // first read after 32 x 64 clocks and further reads 8 x 64 clocks apart make the launch
-        // 3 % faster than reading at once and every 64 clocks.
-        __builtin_amdgcn_s_sleep(kFirstPollSleep);
-        for (uint32_t spins = 0;; ++spins) {
+        bool polls = true;
+        if constexpr (WGWORD) {
+            if (WORDS == Words::OneReader) polls = __builtin_amdgcn_readfirstlane((int)wave) == 0;
+            if (polls) {
+                if (a.chunks <= kFewRounds * (uint64_t)dp) __builtin_amdgcn_s_sleep(kFirstPollSleepFewRounds);
+                else if (WORDS == Words::PerGroup) __builtin_amdgcn_s_sleep(kFirstPollSleepPerGroup);
+                else if (p < kLateRound * (uint64_t)dp) __builtin_amdgcn_s_sleep(kFirstPollSleep);
+                else __builtin_amdgcn_s_sleep(kFirstPollSleepLate);
+            }
+        } else {
+            __builtin_amdgcn_s_sleep(kQuick ? kFirstPollSleepQuick : kFirstPollSleep);
+        }
+        for (uint32_t spins = 0; polls; ++spins) {
             if constexpr (MINMAX) {
                 const uint32_t half = kWaves * a.W;
                 const uint64_t* pair = pairs(p);
@@ -268,18 +297,19 @@ struct EncodeAllCtx {
                 done = __all(all_valid != 0u);
             }
             if (done || spins >= a.max_spins) break;
-            __builtin_amdgcn_s_sleep(kPollSleep);
+            __builtin_amdgcn_s_sleep(WORDS == Words::OneReader ? kPollSleepOneReader : kPollSleep);
         }
         // Every earlier vector-memory operation of the wave has completed (the read of the range
         // words just did), among them the loads of the next item's input.  Passing those
         // registers through an empty asm tells the compiler so: the next item then starts
         // without a wait on them, which would also wait for the stores issued below.
-        if (kDirect) {
+        // (OneReader: a wave that has not polled waits for them here.)
+        if (kDirect && !kQuick) {
 #pragma unroll
             for (int j = 0; j < kUnits; ++j)
                 asm volatile("" : "+v"(raw.u[j].x), "+v"(raw.u[j].y), "+v"(raw.u[j].z), "+v"(raw.u[j].w));
         }
-        if (!done && lane == 0)
+        if (polls && !done && lane == 0)
             __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // The workspace leaves the kernel as it entered it, all zero.  A peer's wave
         // publishes for this chunk only after the barriers of this item's rotation,
@@ -293,7 +323,12 @@ struct EncodeAllCtx {
                 __hip_atomic_store(&a.slots[(uint64_t)prev * nwords + kWordsPerWorker * w + (WGWORD ? 0u : wave)],
                                    0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        const uint32_t sbits = wave_umax(mx);
+        uint32_t sbits = wave_umax(mx);
+        if constexpr (WORDS == Words::OneReader) {   // (red is written again behind the next item's first barrier)
+            if (polls && lane == 0) sh.red[0] = __uint_as_float(sbits);
+            __syncthreads();
+            sbits = __float_as_uint(sh.red[0]);
+        }
         prev = (uint32_t)p;
         const uint64_t pl = p - cur.chunk0;   // the chunk's number inside its bucket
         const float sgn = odd_parity4(block) ? -1.0f : 1.0f;   // the thread's values are negated
@@ -347,12 +382,12 @@ constexpr int kStaggerSleeps = 6;   // late start of half the grid, in units of 
 // Items are (chunk, worker) pairs; workgroup g of a grid of G (a multiple of W) takes worker
 // g mod W of chunks g / W, g / W + G / W, ...  The peers of an item are therefore items of
 // the same round of other workgroups, and with every workgroup resident no wait is circular.
-template <bool BF16, int BITS, bool ODD, bool BATCH, bool MINMAX = false, bool WGWORD = false>
+template <bool BF16, int BITS, bool ODD, bool BATCH, bool MINMAX = false, Words WORDS = Words::PerWave>
 __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(const EncodeAllArgs a,
                                                                  const FusedWorkerPtrs ptrs,
                                                                  const BatchArgs batch) {
     __shared__ Shared sh;
-    using Ctx = EncodeAllCtx<BF16, ODD, BATCH, MINMAX, WGWORD>;
+    using Ctx = EncodeAllCtx<BF16, ODD, BATCH, MINMAX, WORDS>;
     const uint32_t t = threadIdx.x;
     const uint32_t p0 = blockIdx.x / a.W;
     const uint32_t block = lanes::block_of_lane(t & 63u);
@@ -364,7 +399,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     // the same half and nobody waits longer for a peer).  Measured, 50 buckets of 1600 chunks with a decode launch in between: 4 to 7
     // such units shorten the step by 1.3 to 3 %, 9 and more lengthen it, quarters or eighths
     // of the grid in steps do no better.
-    if (a.chunks > c.dp && p0 >= (c.dp >> 1))
+    if (!Ctx::kQuick && a.chunks > c.dp && p0 >= (c.dp >> 1))
         for (int i = 0; i < kStaggerSleeps; ++i) __builtin_amdgcn_s_sleep(16);
     c.cur = c.nxt = c.view_of(p0);
     if (Ctx::kDirect) c.load(p0, c.cur);
@@ -382,6 +417,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
         c.front(v, p);
         c.template back<BITS>(v, p);
         if (BATCH) c.cur = c.nxt;
+        if (Ctx::kQuick) break;
     }
     c.finish();
 }
@@ -749,7 +785,8 @@ uint32_t resident_grid() {
 template <bool BF16, int BITS, bool ODD, bool BATCH>
 hipError_t launch_encode_all_t(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch,
                                hipStream_t stream) {
-    uint32_t G = resident_grid<encode_all_kernel<BF16, BITS, ODD, BATCH>>();
+    const uint32_t resident = resident_grid<encode_all_kernel<BF16, BITS, ODD, BATCH>>();
+    uint32_t G = resident;
     if (G == 0) return hipErrorInvalidValue;
     const uint64_t total = a.chunks * a.W;
     if (G > total) G = (uint32_t)total;
@@ -757,13 +794,19 @@ hipError_t launch_encode_all_t(const EncodeAllArgs& a, const FusedWorkerPtrs& pt
     // fewer resident workgroups than workers would leave peers that never run
     if (G < a.W) return hipErrorInvalidConfiguration;
     G -= G % a.W;
+#define THC_ENCODE_ALL(WORDS)                                                                                          \
+    do {                                                                                                              \
+        hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, false, false, WORDS>), dim3(G), dim3(kThreads), 0,      \
+                           stream, a, ptrs, batch);                                                                   \
+        return hipGetLastError();                                                                                     \
+    } while (0)
     if constexpr (!BATCH) {
-        if (a.W > kPerWaveWordsMaxWorkers) {   // many workers: one range word per workgroup
-            hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, false, false, true>), dim3(G), dim3(kThreads), 0,
-                               stream, a, ptrs, batch);
-            return hipGetLastError();
-        }
+        if (a.W > kPerGroupMaxWorkers) THC_ENCODE_ALL(Words::OneReader);
+        if (a.W > kPerWaveMaxWorkers) THC_ENCODE_ALL(Words::PerGroup);
+        // every workgroup has one item, and a CU (each holds two) to itself
+        if (G == total && 2u * G <= resident) THC_ENCODE_ALL(Words::Quick);
     }
+#undef THC_ENCODE_ALL
     hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, BATCH>), dim3(G), dim3(kThreads), 0, stream, a, ptrs,
                        batch);
     return hipGetLastError();

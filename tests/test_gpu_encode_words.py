@@ -1,0 +1,44 @@
+"""The one-pass encoder's forms of agreement (a word per wave, per workgroup, one reader per workgroup, and the
+launch of at most one workgroup per CU), on both sides of the worker counts where they change, with one item
+per workgroup, a few and more than eight rounds: scales and payloads are those of the per-worker calls, and
+the workspace comes back clear."""
+import pytest
+import torch
+
+import paper_2407_01378_amd as thc
+
+pytestmark = pytest.mark.gpu
+GRID = 512   # workgroups that are resident at once
+
+
+@pytest.mark.parametrize("W", [1, 2, 15, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("rounds,dtype,bits", [(0, torch.bfloat16, 4), (0, torch.float32, 8), (3, torch.bfloat16, 2),
+                                               (10, torch.bfloat16, 4), (10, torch.float32, 8)])
+def test_agreement_matches_the_per_worker_calls(W, rounds, dtype, bits):
+    per_round = GRID // W
+    chunks = min(rounds * per_round + 1, 256) if W == 1 else rounds * per_round + 1
+    n = (chunks << 14) - 1234   # even and ragged
+    if rounds == 0:
+        n -= 1                  # odd
+    print(f"W={W} chunks={chunks} n={n} {dtype} {bits} bits", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(W)
+    xs = [torch.randn(n, generator=gen, device="cuda").mul_(10.0 ** (w % 3)).to(dtype) for w in range(W)]
+    P, nb = thc.thc_num_chunks(n, 14), thc.thc_payload_bytes(n, 14, bits)
+    ws = torch.empty(thc.thc_encode_all_workspace_bytes(W, n, 14), dtype=torch.uint8, device="cuda")
+    thc.thc_workspace_clear(ws)
+    scale = torch.full((P,), float("nan"), device="cuda")
+    payloads = [torch.full((nb,), 0xAA, dtype=torch.uint8, device="cuda") for _ in range(W)]
+    thc.thc_encode_all_cleared(xs, 14, 7, bits, payloads, scale, ws)
+    torch.cuda.synchronize()
+    assert int(ws.count_nonzero()) == 0
+    absmax = torch.empty(W * P, device="cuda")
+    for w in range(W):
+        thc.thc_chunk_absmax(xs[w], 14, 7, absmax[w * P:(w + 1) * P])
+    shared = torch.empty(P, device="cuda")
+    thc.thc_scale_reduce(absmax, W, P, shared)
+    assert torch.equal(scale, shared)
+    ref = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    for w in range(W):
+        thc.thc_encode(xs[w], 14, 7, w, bits, shared, ref)
+        assert torch.equal(payloads[w], ref), w
