@@ -103,15 +103,23 @@ __device__ __forceinline__ uint32_t row_after(uint32_t s, uint32_t lane, uint32_
     }
 }
 
-// Tile of a workgroup or wave by its place in the launch order: workgroups go to the eight XCDs in turn, so
-// this order gives each XCD one contiguous eighth of the tiles.  Neighbouring tiles write neighbouring
-// 16-byte pieces of the same payload lines, which then meet in one L2 instead of leaving eight of
-// them as partial lines.  (The tiles of a workgroup stay together.)
-__device__ __forceinline__ uint64_t xcd_order(uint64_t place, uint64_t tiles, uint32_t together) {
+// Tile of a workgroup or wave by its place in the launch order: workgroups go to the eight XCDs in turn, and
+// neighbouring tiles write neighbouring 16-byte pieces of the same payload lines, which should meet in one L2
+// instead of leaving eight of them as partial lines.  So this order gives each XCD runs of
+// 2^run_log2 tiles, a line's worth, and all eight together one contiguous range of columns: 2^25 coordinates, 10 stages,
+// 4 bits, 36 us (each XCD one contiguous eighth of the tiles 38.5, tiles in turn 44).  What the chip holds at once (512
+// workgroups) is one range either way, and eighths are a little faster there (2^24: 308 and 311 us of a round).
+// Passes of 11 stages take the contiguous eighths, too (run_log2 large): their tiles are half lines of the array (17 M coordinates, eight workers
+// 752 us so, 772 and more with runs).  (The tiles of a workgroup stay together.)
+__device__ __forceinline__ uint64_t xcd_order(uint64_t place, uint64_t tiles, uint32_t together, uint32_t run_log2) {
     const uint32_t log2 = 31u - (uint32_t)__builtin_clz(together);
-    const uint64_t group = place >> log2, groups = tiles >> log2;
+    const uint64_t group = place >> log2, groups = tiles >> log2, j = group >> 3;
     if (groups & 7u) return place;
-    return (((group & 7u) * (groups >> 3) + (group >> 3)) << log2) | (place & (together - 1u));
+    const uint32_t eighth = 60u - (uint32_t)__builtin_clzll(groups);   // (the number of tiles is a power of two)
+    uint32_t run = run_log2 > log2 ? run_log2 - log2 : 0u;
+    if (run > eighth || groups <= 512u) run = eighth;
+    return ((((j >> run) << (3u + run)) | ((group & 7u) << run) | (j & ((1u << run) - 1u))) << log2) |
+           (place & (together - 1u));
 }
 
 // Where a tile lies.
@@ -206,6 +214,7 @@ __global__ __launch_bounds__(64 * pass_waves(M), pass_waves_per_simd(M, KIND)) v
     __shared__ float4 buf[(M > 6 || KIND == Kind::Encode) ? 256 * kWaves : 1];
     constexpr uint32_t kTiles = (uint32_t)pass_tiles(M), kTileWaves = (uint32_t)kWaves / kTiles;
     constexpr uint32_t kRows = M > 6 ? 1u << M : 64u;   // of a tile
+    constexpr uint32_t kRunLog2 = M == 11 ? 63u : BITS == 8 ? 2u : BITS == 4 ? 3u : 4u;   // tiles of a payload line (32 columns each)
     __shared__ uint32_t signs[KIND == Kind::ToX ? kRows * kTiles : 1];
     __shared__ uint32_t most[kWaves];
     const uint32_t t = threadIdx.x, lane0 = t & 63u;
@@ -222,7 +231,7 @@ __global__ __launch_bounds__(64 * pass_waves(M), pass_waves_per_simd(M, KIND)) v
         uint32_t lane = lane0;
         asm volatile("" : "+s"(s0), "+v"(lane));
         const uint32_t jq = lane & ((1u << column_bits(M)) - 1u), la = lane >> column_bits(M);
-        const Tile<M> now(s0, (KIND == Kind::Encode || M == 11) ? xcd_order(tile, a.tiles, together) : tile);
+        const Tile<M> now(s0, (KIND == Kind::Encode || M == 11) ? xcd_order(tile, a.tiles, together, kRunLog2) : tile);
         // a tile mixes values of one block of 2^(s0 + M) floats: if that block lies in the implied
         // zero padding its results are zero too, and the next pass is told so instead of reading them
         // (the last pass writes everything: an empty gradient gives zeros).  Tiles are in the order of
