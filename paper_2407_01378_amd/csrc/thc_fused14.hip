@@ -466,10 +466,10 @@ __device__ __forceinline__ uint32_t this_item(uint32_t x) {
 // (layout L1): 4 * BITS payload bytes (BITS dwords) per worker.
 // Called from inside the rotation of the current chunk: the first four worker groups of the workgroup's
 // NEXT chunk are loaded, two at a time, and the first two added.
-template <int BITS, bool BATCH, bool WIDE>
+template <class Sum>
 struct NextChunkLoads {
     static constexpr uint32_t kAdded = 2u;
-    PayloadSum<BITS, BATCH, WIDE>& sum;
+    Sum& sum;
     uint64_t byte0;
     bool active;
     template <int K>
@@ -495,12 +495,13 @@ struct DecodeView {
 };
 
 // RANGED: `scale` holds (lo, hi) pairs of the min/max grid instead of the symmetric scale.
-template <int BITS, bool BATCH, bool RANGED = false, bool WIDE = false>
+// ONCE: how payloads are read (load_payload_words).
+template <int BITS, bool BATCH, bool RANGED = false, bool WIDE = false, bool ONCE = BITS != 8>
 __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kernel(const AggDecodeArgs a,
                                                                        const FusedPayloadPtrs ptrs,
                                                                        const BatchArgs batch) {
     __shared__ Shared sh;
-    using Sum = PayloadSum<BITS, BATCH, WIDE>;
+    using Sum = PayloadSum<BITS, BATCH, WIDE, ONCE>;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint32_t block = lay14::block_of_lane(lane), tp = (t & ~63u) | block;   // the thread's 32 coordinates
     const float norm = l4d_negated(lane, wave) ? -kInvSqrtC : kInvSqrtC;
@@ -564,7 +565,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
         DecodeView nxt = cur;
         if (BATCH && more && pn >= boundary) nxt = view_of(pn);   // rarely: a new bucket
         sum.pp = nxt.pp;
-        NextChunkLoads<BITS, BATCH, WIDE> next{sum, (((pn - nxt.chunk0) << kChunkLog2) * BITS) / 8u + thread_byte, more};
+        NextChunkLoads<Sum> next{sum, (((pn - nxt.chunk0) << kChunkLog2) * BITS) / 8u + thread_byte, more};
         sum.clear();
         const uint32_t ti = this_item(t), li = ti & 63u;
         rotate_lanes_to_l4d(sh, v, li, block, wave, next);   // (its barrier also orders the sign table)
@@ -830,38 +831,36 @@ hipError_t launch_encode_all_pick(const EncodeAllArgs& a, const FusedWorkerPtrs&
     return launch_encode_all_t<false, 8, false, BATCH>(a, ptrs, batch, stream);
 }
 
-// 4-bit payloads of so many workers that the sums need 16 bits.
-template <int BITS, bool BATCH, bool RANGED>
-hipError_t launch_aggregate_decode_wide(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs, const BatchArgs& batch,
+template <int BITS, bool BATCH, bool RANGED, bool WIDE, bool ONCE = BITS != 8>
+hipError_t launch_aggregate_decode_t(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs, const BatchArgs& batch,
                                         hipStream_t stream) {
-    uint32_t G = resident_grid<aggregate_decode_kernel<BITS, BATCH, RANGED, true>>();
+    uint32_t G = resident_grid<aggregate_decode_kernel<BITS, BATCH, RANGED, WIDE, ONCE>>();
     if (G == 0) return hipErrorInvalidValue;
     if (G > a.chunks) G = (uint32_t)a.chunks;
-    hipLaunchKernelGGL((aggregate_decode_kernel<BITS, BATCH, RANGED, true>), dim3(G), dim3(kThreads), 0, stream, a,
-                       ptrs, batch);
+    hipLaunchKernelGGL((aggregate_decode_kernel<BITS, BATCH, RANGED, WIDE, ONCE>), dim3(G), dim3(kThreads), 0, stream,
+                       a, ptrs, batch);
     return hipGetLastError();
 }
+// 4-bit payloads of so many workers that the sums need 16 bits.
 // (2-bit payloads would need more than 85 workers, beyond what the one-launch forms take)
 __host__ inline bool wide_sums(uint32_t W, uint32_t bits) { return bits == 4u && W * 15u > 255u; }
 
-template <bool BATCH>
+// 8-bit payloads of all workers together that outgrow the last-level cache (256 MB) beside the output are read as
+// for the last time.  Encode + decode of 8 workers, ordinary loads | last use: 134 MB of payloads 144 | 153 us, 160 MB
+// 167 | 178, 210 MB 228 | 229, 268 MB 300 | 297; batched 112 MB 128 | 136, 480 MB 670 | 654, 1048 MB 1127 | 1111.
+__host__ inline bool stream_payloads(const AggDecodeArgs& a) {
+    return a.chunks * a.W > (224ull << 20) / (uint64_t)kChunk;
+}
+
+template <bool BATCH, bool RANGED>
 hipError_t launch_aggregate_decode_pick(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs, const BatchArgs& batch,
                                         uint32_t bits, hipStream_t stream) {
     if (a.chunks == 0) return hipSuccess;
-    if (wide_sums(a.W, bits)) return launch_aggregate_decode_wide<4, BATCH, false>(a, ptrs, batch, stream);
-    uint32_t G = 0;
-    if (bits == 2) G = resident_grid<aggregate_decode_kernel<2, BATCH>>();
-    else if (bits == 4) G = resident_grid<aggregate_decode_kernel<4, BATCH>>();
-    else G = resident_grid<aggregate_decode_kernel<8, BATCH>>();
-    if (G == 0) return hipErrorInvalidValue;
-    if (G > a.chunks) G = (uint32_t)a.chunks;
-    if (bits == 2)
-        hipLaunchKernelGGL((aggregate_decode_kernel<2, BATCH>), dim3(G), dim3(kThreads), 0, stream, a, ptrs, batch);
-    else if (bits == 4)
-        hipLaunchKernelGGL((aggregate_decode_kernel<4, BATCH>), dim3(G), dim3(kThreads), 0, stream, a, ptrs, batch);
-    else
-        hipLaunchKernelGGL((aggregate_decode_kernel<8, BATCH>), dim3(G), dim3(kThreads), 0, stream, a, ptrs, batch);
-    return hipGetLastError();
+    if (wide_sums(a.W, bits)) return launch_aggregate_decode_t<4, BATCH, RANGED, true>(a, ptrs, batch, stream);
+    if (bits == 2) return launch_aggregate_decode_t<2, BATCH, RANGED, false>(a, ptrs, batch, stream);
+    if (bits == 4) return launch_aggregate_decode_t<4, BATCH, RANGED, false>(a, ptrs, batch, stream);
+    if (stream_payloads(a)) return launch_aggregate_decode_t<8, BATCH, RANGED, false, true>(a, ptrs, batch, stream);
+    return launch_aggregate_decode_t<8, BATCH, RANGED, false, false>(a, ptrs, batch, stream);
 }
 
 }  // namespace
@@ -977,33 +976,18 @@ bool aggregate_decode_fused_applicable(uint32_t W, uint32_t chunk_log2, uint32_t
 
 hipError_t launch_aggregate_decode_fused(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs,
                                          uint32_t bits, hipStream_t stream) {
-    return k14::launch_aggregate_decode_pick<false>(a, ptrs, BatchArgs{}, bits, stream);
+    return k14::launch_aggregate_decode_pick<false, false>(a, ptrs, BatchArgs{}, bits, stream);
 }
 
 // a.scale holds (lo, hi) pairs.
 hipError_t launch_aggregate_decode_ranged(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs,
                                           uint32_t bits, hipStream_t stream) {
-    using namespace k14;
-    if (a.chunks == 0) return hipSuccess;
-    if (wide_sums(a.W, bits)) return launch_aggregate_decode_wide<4, false, true>(a, ptrs, BatchArgs{}, stream);
-    uint32_t G = bits == 2   ? resident_grid<aggregate_decode_kernel<2, false, true>>()
-                 : bits == 4 ? resident_grid<aggregate_decode_kernel<4, false, true>>()
-                             : resident_grid<aggregate_decode_kernel<8, false, true>>();
-    if (G == 0) return hipErrorInvalidValue;
-    if (G > a.chunks) G = (uint32_t)a.chunks;
-    const BatchArgs none{};
-    if (bits == 2)
-        hipLaunchKernelGGL((aggregate_decode_kernel<2, false, true>), dim3(G), dim3(kThreads), 0, stream, a, ptrs, none);
-    else if (bits == 4)
-        hipLaunchKernelGGL((aggregate_decode_kernel<4, false, true>), dim3(G), dim3(kThreads), 0, stream, a, ptrs, none);
-    else
-        hipLaunchKernelGGL((aggregate_decode_kernel<8, false, true>), dim3(G), dim3(kThreads), 0, stream, a, ptrs, none);
-    return hipGetLastError();
+    return k14::launch_aggregate_decode_pick<false, true>(a, ptrs, BatchArgs{}, bits, stream);
 }
 
 hipError_t launch_aggregate_decode_batch(const AggDecodeArgs& a, const BatchArgs& batch, uint32_t bits,
                                          hipStream_t stream) {
-    return k14::launch_aggregate_decode_pick<true>(a, FusedPayloadPtrs{}, batch, bits, stream);
+    return k14::launch_aggregate_decode_pick<true, false>(a, FusedPayloadPtrs{}, batch, bits, stream);
 }
 
 bool sat_aggregate_decode_fused_applicable(uint32_t W, uint32_t chunk_log2) {

@@ -31,10 +31,10 @@ template <int BITS>
 struct PayloadWords {
     uint32_t w[BITS];
 };
-// Read for the last time - but 8-bit payloads take two loads per thread from the same lines, and a line that the
-// first one marks as used up may be gone before the second: 8 workers x 2^24 coordinates, encode + decode,
-// 153 us so, 143 us as ordinary loads (4 bits, one load per thread: the same either way).
-template <int BITS>
+// Read for the last time (ONCE) - but 8-bit payloads take two loads per thread from the same lines, and a line that the
+// first one marks as used up may be gone before the second: as long as the payloads fit the last-level cache
+// beside the rest they are read by ordinary loads (stream_payloads; 4 bits, one load per thread: the same either way).
+template <int BITS, bool ONCE = BITS != 8>
 __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* p) {
     PayloadWords<BITS> r;
     if (BITS == 2) {
@@ -45,7 +45,7 @@ __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* 
 #pragma unroll
         for (int k = 0; k < BITS / 4; ++k) {
             const uint4* src = reinterpret_cast<const uint4*>(p) + k;
-            const uint4 q = BITS == 8 ? *src : load_last_use(src);
+            const uint4 q = ONCE ? load_last_use(src) : *src;
             r.w[4 * k] = q.x;
             r.w[4 * k + 1] = q.y;
             r.w[4 * k + 2] = q.z;
@@ -58,7 +58,7 @@ __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* 
 // The workers' payload words of one thread (its 32 coordinates) on their way into registers, group by
 // group: a group is the payload of GROUP workers.  Two groups can be in flight at once (buffers 0 and 1, 32
 // registers): while one is combined the next one's loads are on their way.
-template <int BITS, bool BATCH, int GROUP = BITS == 8 ? 2 : 4>
+template <int BITS, bool BATCH, int GROUP = BITS == 8 ? 2 : 4, bool ONCE = BITS != 8>
 struct PayloadLoads {
     static constexpr uint32_t kGroup = GROUP;
     const FusedPayloadPtrs& ptrs;   // single bucket: the payload pointers, in the kernel arguments
@@ -78,7 +78,7 @@ struct PayloadLoads {
         if (w0 >= W) return;
         if (w0 + kGroup <= W) {
 #pragma unroll
-            for (uint32_t j = 0; j < kGroup; ++j) x[B][j] = load_payload_words<BITS>(pointer(w0 + j) + byte0);
+            for (uint32_t j = 0; j < kGroup; ++j) x[B][j] = load_payload_words<BITS, ONCE>(pointer(w0 + j) + byte0);
             // (the empty assembly statements differ, so that the two branches are not merged into one that
             // picks its registers by address, which would put x into memory)
             asm volatile("; whole group");
@@ -86,7 +86,7 @@ struct PayloadLoads {
 #pragma unroll
             for (uint32_t j = 0; j + 1u < kGroup; ++j)
                 if (w0 + j < W) {
-                    x[B][j] = load_payload_words<BITS>(pointer(w0 + j) + byte0);
+                    x[B][j] = load_payload_words<BITS, ONCE>(pointer(w0 + j) + byte0);
                     asm volatile("; worker of a part of a group");
                 }
             asm volatile("; part of a group");
@@ -105,10 +105,10 @@ struct PayloadLoads {
 // WIDE: 16-bit accumulators for 4-bit payloads too (W * L > 255: more than 17 workers); lane q
 // then holds coordinates q (low half) and q + 4 (high half) of the dword's 8.  The workers
 // meet in 8-bit lanes first, kFlush groups of them (16 * 15 <= 255), which takes half the operations.
-template <int BITS, bool BATCH = false, bool WIDE = false>
-struct PayloadSum : PayloadLoads<BITS, BATCH> {
+template <int BITS, bool BATCH = false, bool WIDE = false, bool ONCE = BITS != 8>
+struct PayloadSum : PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE> {
     static_assert(!(WIDE && BITS != 4), "8-bit payloads always sum in 16-bit lanes, 2-bit ones in 8-bit lanes");
-    using Loads = PayloadLoads<BITS, BATCH>;
+    using Loads = PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE>;
     using Loads::groups;
     using Loads::kGroup;
     using Loads::W;

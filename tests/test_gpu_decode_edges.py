@@ -67,3 +67,26 @@ def test_sums_of_every_number_of_workers(W, bits, l):
             total[:, k] += (r >> (bits * k)) & ((1 << bits) - 1)
     got = sums.cpu().numpy().view(np.uint8 if one else np.uint16)
     assert (got == total.reshape(-1)[: P << l]).all()
+
+
+@pytest.mark.parametrize("chunks", [224, 225])   # 64 workers: the last size read by ordinary loads, the first by streaming ones
+def test_8_bit_payloads_around_the_size_of_the_last_level_cache(chunks):
+    W, l, bits, seed = 64, 14, 8, 11
+    n = (chunks << l) - 5
+    gen = torch.Generator(device="cuda").manual_seed(chunks)
+    payloads = [torch.randint(0, 256, (chunks << l,), dtype=torch.uint8, device="cuda", generator=gen) for _ in range(W)]
+    scale = torch.rand(chunks, device="cuda", generator=gen) + 0.5
+    sums = torch.zeros(chunks << l, dtype=torch.int16, device="cuda")
+    thc.thc_aggregate(payloads, n, l, bits, sums)
+    total = sum(p.to(torch.int32) for p in payloads)
+    assert torch.equal(total.to(torch.int16), sums)
+    want = torch.empty(n, device="cuda")
+    thc.thc_decode(sums, scale, W, n, l, seed, bits, want)
+    one = torch.full((n,), 7.0, device="cuda")
+    mine = torch.zeros_like(sums)
+    thc.thc_aggregate_decode(payloads, scale, n, l, seed, bits, mine, one)
+    assert torch.equal(one, want) and torch.equal(mine, sums)
+    many = torch.full((n,), 7.0, device="cuda")
+    ws = torch.empty(thc.thc_batch_workspace_bytes([n], W, l), dtype=torch.uint8, device="cuda")
+    thc.thc_aggregate_decode_batch([dict(n=n, seed=seed, payloads=payloads, scale=scale, out=many)], l, bits, ws)
+    assert torch.equal(many, want)
