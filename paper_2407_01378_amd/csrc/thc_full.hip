@@ -35,11 +35,11 @@ using k14::kRegs;
 //                   floats of a pair in turn so that the buffer takes half the data
 // So passes of up to 6 stages need neither LDS nor barriers: every wave streams by itself, and
 // the others keep 32 waves per CU (64 registers, 64 KB of LDS per 16 waves, in the inverse's last pass of
-// 9 stages 68), except for the inverse's last pass of 10 and 11 stages: 128 registers, 68 and 72 KB
+// 9 stages 68), except for the inverse's last pass of 10 stages: 128 registers, 68 KB
 // (the exchange and a sign word per row), 16 waves.  Bound by memory (8 bytes per coordinate in
 // place, 4 for the range alone).  The shape before, 8 rows x 4 floats per thread, exchanged
 // twice for every pass through 64 KB of LDS and reached 9 stages, so 2^25 coordinates took
-// 14 + 6 + 5 stages where they now take 14 + 11: resnet50-sized round of 8 workers 1366 -> 1021 us.
+// 14 + 6 + 5 stages, then 14 + 11: round of 8 workers x 25.6 M fp32 1366 -> 1021 us (15 + 10 since: 934 us).
 struct HighPassArgs {
     float* data;        // 2^l floats, transformed in place (unless `out`)
     float* out;         // last pass of the inverse: x (n floats); else null
@@ -200,8 +200,8 @@ __device__ __forceinline__ void rotate_tile(float (&v)[kRegs], float* xb, uint32
     }
 }
 
-// Waves per SIMD the registers must allow: 8 (64 registers), but 4 for the inverse's last pass of 10 and 11
-// stages, whose output addresses and sign words do not fit (44.8 us with the spills, 27.8 us without,
+// Waves per SIMD the registers must allow: 8 (64 registers), but 4 for the inverse's last pass of 10 stages,
+// whose output addresses and sign words do not fit (44.8 us with the spills, 27.8 us without,
 // 2^24 coordinates) and whose workgroup of 16 waves then has a CU to itself.
 constexpr int pass_waves_per_simd(int M, Kind kind) { return kind == Kind::ToX && M >= 10 ? 4 : 8; }
 
@@ -495,13 +495,15 @@ void launch_pass_t(uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
     hipLaunchKernelGGL(kernel, dim3((uint32_t)grid), dim3(threads), 0, stream, a);
 }
 // Stages of a high pass at most.  11 stages move 64-byte pieces, at about 0.7 of the rate of whole lines,
-// and still beat a pass more (2^25 coordinates, 102 MB of them data: range 31.7 us, payload 42 us,
-// inverse 64 us; as 6 + 5 stages 32 + 22, 33 and 44 + 51 us).
+// and still beat a pass more (2^25 coordinates behind chunks of 2^14, 102 MB of them data: range 31.7 us, payload
+// 42 us, inverse 64 us; as 6 + 5 stages 32 + 22, 33 and 44 + 51 us).
 constexpr int kMaxStages = 11;
 
 // Whether a plan has a pass of M stages of this kind: the first of two takes half of 12 .. 19 stages, a pass
-// that is the last (or the only) one may have any number.
-constexpr bool pass_exists(Kind kind, int M) { return kind != Kind::InPlace || (M >= 6 && M <= 10); }
+// that is the last (or the only) one may have any number (11 only forward: 2^25 coordinates, a short gradient).
+constexpr bool pass_exists(Kind kind, int M) {
+    return kind == Kind::InPlace ? M >= 6 && M <= 10 : kind != Kind::ToX || M <= 10;
+}
 
 template <Kind KIND, int BITS = 4, int M = 1>
 hipError_t launch_pass(uint32_t m, uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {

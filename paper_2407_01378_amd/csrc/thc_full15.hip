@@ -3,8 +3,7 @@
 //
 // What it is for: the passes behind it move a row of the array per 2^s0 coordinates, and with 11 stages left
 // behind chunks of 2^14 those rows are 64-byte pieces, which memory serves at 0.7 of the rate of whole
-// lines; with 12 left they are two passes.  One stage more in front makes 10 stages (whole lines) of the
-// 11, and one pass of the two: see full_first_log2.
+// lines.  One stage more in front makes 10 stages (whole lines) of the 11: see full_first_log2.
 //
 // Bound by memory.  A wave's 2^11 coordinates are loaded in whole 1 KB runs, a lane holding 2^RB consecutive
 // coordinates of several runs (16 bytes each), so nothing is staged: stages 0..RB-1 between registers, RB..RB+3
@@ -12,7 +11,7 @@
 // One exchange through LDS then brings i11..i14 into the registers, half of them at a time so that it takes
 // 64 KB: two workgroups and 32 waves per CU, whose loads and stores overlap the other's arithmetic.
 // Measured, 25.6 M fp32 coordinates in 2^25: 45 us (39 us over chunks of 2^14: 780 chunks are 1.5 rounds), the range
-// behind it 21.5 us instead of 32.5, the quantizing pass 38.5 instead of 42.5, the inverse 35 + 49 instead of 29 + 66.
+// behind it 21.5 us instead of 32.5, the quantizing pass 36 instead of 42.5, the inverse 35 + 49 instead of 29 + 66.
 #include "thc_core14.h"
 #include "thc_internal.h"
 

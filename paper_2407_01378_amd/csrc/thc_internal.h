@@ -178,13 +178,13 @@ hipError_t launch_sat_aggregate(const FusedPayloadPtrs& ptrs, uint32_t W, uint32
                                 unsigned long long* overflow, hipStream_t stream);
 
 // ---- full rotation (thc_full.hip, thc_full15.hip) ------------------------------------------
-// Stages of the first pass over n coordinates of 2^log2_size: chunks of 2^14, or of 2^15 where 11 or 12 stages would
-// be left behind them (a pass of 11 moves 64-byte pieces, 12 take two passes).  A device holds 512 chunks of 2^15 at
+// Stages of the first pass over n coordinates of 2^log2_size: chunks of 2^14, or of 2^15 where 11 stages would
+// be left behind them (a pass of 11 moves 64-byte pieces).  A device holds 512 chunks of 2^15 at
 // once, and a few more than that take as long as 1024: with less than 9/16 of 2^25 to read the chunks stay
-// at 2^14 (eight workers x 17 M fp32: 762 us so, 769 us with 2^15; x 25.6 M: 1021 and 952 us).
+// at 2^14 (eight workers x 17 M fp32: 762 us so, 769 us with 2^15; x 25.6 M: 1021 and 934 us).
 // All forward calls for one gradient agree on it; the inverse direction reads the whole array (n = 2^log2_size).
 inline uint32_t full_first_log2(uint64_t n, uint32_t log2_size) {
-    return log2_size == 26u || (log2_size == 25u && n > 9ull << 21) ? 15u : 14u;
+    return log2_size == 25u && n > 9ull << 21 ? 15u : 14u;
 }
 // The first pass over chunks of 2^15: Forward, Plain or PlainDecode.
 hipError_t launch_full_first15(Mode mode, const ChunkArgs& a, hipStream_t stream);

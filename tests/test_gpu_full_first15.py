@@ -1,5 +1,5 @@
-"""The full rotation of 2^25 and 2^26 coordinates, whose first pass covers chunks of 2^15 (of 2^25: from a
-length of 9/16 on): the whole pipeline against the oracle on both sides of that length, with one- and two-byte
+"""The full rotation of 2^25 coordinates, whose first pass covers chunks of 2^15 from a length of 9/16 on (and
+of 2^26, with chunks of 2^14 and a pass more): the whole pipeline against the oracle on both sides of that length, with one- and two-byte
 sums, and the rotated values against the stages one by one, so that a wrong unit of the exchange is
 seen where the oracle would take too long."""
 import pytest
