@@ -20,7 +20,7 @@ namespace {
 // of six up to the range.  Forward keeps the LDS maps (long calls
 // of it are bound by memory: 6 TB/s); MinMax keeps them too, the lanes have not been timed there.
 // Measured at 7 M bf16 (433 chunks): range 8.0 -> 6.5 us, 8-bit encode 11.1 -> 9.4; per-call round of
-// eight workers 177 -> 154 us.
+// eight workers 177 -> 153 us.
 template <bool BF16, Mode MODE, int BITS>
 __global__ __launch_bounds__(kThreads) void per_worker_kernel(const ChunkArgs a) {
     __shared__ Shared sh;

@@ -12,8 +12,8 @@
 // before each further stage.  Bound by vector-ALU issue for large inputs (6.5 M coordinates, 8 workers,
 // chunk 2^12, 8 bits, by the counters: 27.8 operations per worker-coordinate, VALU busy 94 % of
 // the time with 16 waves per CU, 52 us), by the issue of the two launches for small ones.
-//   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 72 us
-//   (3.4 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 15.6 us.  Before: one range and one encode
+//   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 70 us
+//   (3.5 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 14.7 us.  Before: one range and one encode
 //   launch per worker of the generic kernels, which load element by element and take a
 //   barrier per stage above 2^4.
 //
