@@ -57,13 +57,14 @@ __global__ __launch_bounds__(kThreads, 8) void first_pass15_kernel(const ChunkAr
         const uint32_t left = rest < (1ull << kLog2) ? (uint32_t)rest : 1u << kLog2;
         const uint8_t* in = static_cast<const uint8_t*>(a.in) + g0 * kElem;
         // (reads past the range return zero; the check is made for each dword, so the last coordinate of an
-        // odd count of bf16 is fetched by itself)
+        // odd count of bf16 is fetched by itself.  The whole place of a unit is in the vector offset: the
+        // scalar offset is not part of the documented range check)
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint8_t*>(in), 0, (int)(SRC == From::BF16 ? (left & ~1u) * 2u : left * 4u), 0x00020000);
         u32x4_vec raw[kRuns];
 #pragma unroll
         for (int j = 0; j < kRuns; ++j)
-            raw[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, wave * (2048u * kElem) + b * 16u, j * 1024, 0);
+            raw[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, wave * (2048u * kElem) + b * 16u + (uint32_t)j * 1024u, 0, 0);
         if (SRC == From::BF16 && (left & 1u)) {
             const uint32_t last = left - 1u;   // coordinate 2 d of unit j of one thread
             const uint32_t word = reinterpret_cast<const uint16_t*>(in)[last];

@@ -44,3 +44,28 @@ def test_forward_and_inverse_match_the_stages_one_by_one(l, n, dtype):
     inv = _stages(y, 0, l)[:n] * factor
     assert torch.equal(back.abs(), inv.abs())
     assert torch.allclose(back, x.float(), rtol=0, atol=float(x.float().abs().max()) * 1e-5)
+
+
+@pytest.mark.parametrize("rest", [1, 2, 255, 257, 1025, 1535, 1537, 1791, 1793, 2049])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_a_short_last_chunk_is_padded_with_zeros_whatever_lies_behind_it(rest, dtype):
+    """Of the last chunk of 2^15 only `rest` coordinates exist; the memory behind them is the caller's and
+    holds large values.  The bounds of its loads are those of the gradient for every run of a wave (2^9
+    bf16 or 2^8 fp32 coordinates apart)."""
+    l, n = 25, (600 << 15) + rest
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rest)
+    whole = torch.full((n + (1 << 15),), 1e6, device="cuda", dtype=dtype)
+    x = whole[:n]
+    x.copy_(torch.randn(n, generator=g, device="cuda"))
+    y = torch.full((1 << l,), float("nan"), device="cuda")
+    absmax = torch.empty(1, device="cuda")
+    thc.rht_forward_full_absmax(x, l, 7, y, absmax)
+    P = thc.thc_num_chunks(n, 14)
+    ref = torch.zeros(1 << l, device="cuda")
+    thc.rht_forward(x.clone(), 14, 7, ref[:P << 14])
+    ref[:P << 14] *= 128.0   # (exact: the chunks' own factor is a power of two)
+    _stages(ref, 14, l)
+    ref *= torch.tensor(2.0 ** (-l / 2), dtype=torch.float64).float().item()
+    assert torch.equal(y, ref)
+    assert torch.equal(absmax[0], ref.abs().max())
