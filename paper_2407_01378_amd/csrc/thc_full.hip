@@ -48,6 +48,7 @@ struct HighPassArgs {
     float factor;       // of the last pass
     uint32_t key0, key1;
     uint64_t tiles;
+    uint32_t xcd_run_log2;   // see xcd_order
     uint64_t valid;     // floats of `data` that hold values, a multiple of 2^s0; what lies beyond
                         // reads as zero and is neither read nor, in a pass that is not the last,
                         // written (the zero padding behind the gradient is implied, pass after
@@ -105,21 +106,32 @@ __device__ __forceinline__ uint32_t row_after(uint32_t s, uint32_t lane, uint32_
 
 // Tile of a workgroup or wave by its place in the launch order: workgroups go to the eight XCDs in turn, and
 // neighbouring tiles write neighbouring 16-byte pieces of the same payload lines, which should meet in one L2
-// instead of leaving eight of them as partial lines.  So this order gives each XCD runs of
-// 2^run_log2 tiles, a line's worth, and all eight together one contiguous range of columns: 2^25 coordinates, 10 stages,
-// 4 bits, 36 us (each XCD one contiguous eighth of the tiles 38.5, tiles in turn 44).  What the chip holds at once (512
-// workgroups) is one range either way, and eighths are a little faster there (2^24: 308 and 311 us of a round).
-// Passes of 11 stages take the contiguous eighths, too (run_log2 large): their tiles are half lines of the array (17 M coordinates, eight workers
-// 752 us so, 772 and more with runs).  (The tiles of a workgroup stay together.)
-__device__ __forceinline__ uint64_t xcd_order(uint64_t place, uint64_t tiles, uint32_t together, uint32_t run_log2) {
+// instead of leaving eight of them as partial lines.  This order gives each XCD runs of 2^run_log2 workgroups
+// (xcd_run_log2).  (The tiles of a workgroup stay together.)
+__device__ __forceinline__ uint64_t xcd_order(uint64_t place, uint32_t run_log2, uint32_t together) {
     const uint32_t log2 = 31u - (uint32_t)__builtin_clz(together);
-    const uint64_t group = place >> log2, groups = tiles >> log2, j = group >> 3;
-    if (groups & 7u) return place;
-    const uint32_t eighth = 60u - (uint32_t)__builtin_clzll(groups);   // (the number of tiles is a power of two)
-    uint32_t run = run_log2 > log2 ? run_log2 - log2 : 0u;
-    if (run > eighth || groups <= 512u) run = eighth;
-    return ((((j >> run) << (3u + run)) | ((group & 7u) << run) | (j & ((1u << run) - 1u))) << log2) |
+    const uint64_t group = place >> log2, j = group >> 3;
+    return ((((j >> run_log2) << (3u + run_log2)) | ((group & 7u) << run_log2) | (j & ((1ull << run_log2) - 1ull))) << log2) |
            (place & (together - 1u));
+}
+// Workgroups of such a run, of a launch of `groups` (a power of two).
+//   a payload line's worth of tiles  all XCDs together then read one contiguous range of columns: 2^25 coordinates,
+//                                    10 stages, 4 bits, 36 us (each XCD one contiguous eighth of the tiles
+//                                    38.5, tiles in turn 44); 2^29, 7 stages, 2 bits 467 (eighths 481)
+//   a contiguous eighth              where the chip holds the launch at once (512 workgroups; 2^24: a round of 308 us,
+//                                    with runs 311); for passes of 11 stages, whose tiles are half lines of the array
+//                                    (17 M coordinates, eight workers 752 us, with runs 772 and more); for up to 6
+//                                    stages, where a workgroup of eight independent waves is a line's worth or half
+//                                    of it already (2^26: 4 bits 43 us, with runs 48; 2 bits 42, with runs 56), and
+//                                    for 7 at 2 bits (2^27: 118 and 121 us)
+inline uint32_t xcd_run_log2(int M, int bits, uint64_t groups, uint32_t together) {
+    if (groups < 16u) return 0u;   // (as launched)
+    const uint32_t eighth = 60u - (uint32_t)__builtin_clzll(groups);
+    if (M <= 6 || M == 11 || (M == 7 && bits == 2) || groups <= 512u) return eighth;
+    const uint32_t line = bits == 8 ? 2u : bits == 4 ? 3u : 4u;   // tiles of a payload line (32 columns each)
+    const uint32_t log2 = 31u - (uint32_t)__builtin_clz(together);
+    const uint32_t run = line > log2 ? line - log2 : 0u;
+    return run < eighth ? run : eighth;
 }
 
 // Where a tile lies.
@@ -214,7 +226,6 @@ __global__ __launch_bounds__(64 * pass_waves(M), pass_waves_per_simd(M, KIND)) v
     __shared__ float4 buf[(M > 6 || KIND == Kind::Encode) ? 256 * kWaves : 1];
     constexpr uint32_t kTiles = (uint32_t)pass_tiles(M), kTileWaves = (uint32_t)kWaves / kTiles;
     constexpr uint32_t kRows = M > 6 ? 1u << M : 64u;   // of a tile
-    constexpr uint32_t kRunLog2 = M == 11 ? 63u : BITS == 8 ? 2u : BITS == 4 ? 3u : 4u;   // tiles of a payload line (32 columns each)
     __shared__ uint32_t signs[KIND == Kind::ToX ? kRows * kTiles : 1];
     __shared__ uint32_t most[kWaves];
     const uint32_t t = threadIdx.x, lane0 = t & 63u;
@@ -231,7 +242,7 @@ __global__ __launch_bounds__(64 * pass_waves(M), pass_waves_per_simd(M, KIND)) v
         uint32_t lane = lane0;
         asm volatile("" : "+s"(s0), "+v"(lane));
         const uint32_t jq = lane & ((1u << column_bits(M)) - 1u), la = lane >> column_bits(M);
-        const Tile<M> now(s0, (KIND == Kind::Encode || M == 11) ? xcd_order(tile, a.tiles, together, kRunLog2) : tile);
+        const Tile<M> now(s0, (KIND == Kind::Encode || M == 11) ? xcd_order(tile, a.xcd_run_log2, together) : tile);
         // a tile mixes values of one block of 2^(s0 + M) floats: if that block lies in the implied
         // zero padding its results are zero too, and the next pass is told so instead of reading them
         // (the last pass writes everything: an empty gradient gives zeros).  Tiles are in the order of
@@ -488,6 +499,7 @@ void launch_pass_t(uint32_t log2_size, hipStream_t stream, HighPassArgs& a) {
     while (together > 1u && a.tiles / together < (kReports ? 128u : 512u)) together >>= 1;
     const uint32_t threads = 64u * together << wave_rows(M);
     uint64_t grid = a.tiles / together;
+    a.xcd_run_log2 = xcd_run_log2(M, BITS, grid, together);
     if (kReports) {
         const uint32_t resident = resident_grid<kernel>((uint32_t)(64 * pass_waves(M)));   // (of full workgroups)
         if (resident != 0 && grid > resident) grid = resident;

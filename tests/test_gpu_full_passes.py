@@ -74,3 +74,28 @@ def test_two_passes_match_the_stages_one_by_one(l, n, dtype):
     _stages(ref, 0, l).mul_(factor)
     assert torch.equal(back.abs(), ref[:n].abs())      # (the diagonal changes signs only, which the input has)
     assert float((back - x.float()).norm()) <= 1e-5 * float(x.float().norm())
+
+
+@pytest.mark.parametrize("l,frac", [
+    (17, 1.0), (18, 0.9), (20, 0.6),   # passes of 3 .. 6 stages: few workgroups, in order or in eighths
+    (23, 0.8), (24, 0.8),              # 9 and 10 stages, one round of workgroups: eighths
+    (25, 0.5), (25, 0.8),              # 11 stages: eighths; 10: runs of a payload line's worth
+    (26, 0.51), (27, 0.51),            # 6 stages: eighths; 7: eighths at 2 bits, runs otherwise
+])
+def test_quantizing_pass_takes_every_tile_once_in_any_order(l, frac):
+    """The deferred payload is that of the stored rotation, whatever order the tiles are dealt out in."""
+    n = int(frac * (1 << l)) - 1
+    g = torch.Generator(device="cuda")
+    g.manual_seed(l)
+    x = torch.randn(n, generator=g, device="cuda")
+    y, work = torch.empty(1 << l, device="cuda"), torch.empty(1 << l, device="cuda")
+    scale, ranged = torch.empty(1, device="cuda"), torch.empty(1, device="cuda")
+    thc.rht_forward_full_absmax(x, l, 7, y, scale)
+    thc.rht_forward_full_deferred(x, l, 7, work, ranged)
+    assert float(ranged) == float(scale)
+    for bits in (2, 4, 8):
+        stored = torch.full(((bits << l) // 8,), 0xAA, dtype=torch.uint8, device="cuda")
+        deferred = torch.full_like(stored, 0x55)
+        thc.thc_full_encode(y, l, 7, 1, bits, scale, stored)
+        thc.thc_full_encode_deferred(work, n, l, 7, 1, bits, scale, deferred)
+        assert torch.equal(stored, deferred), bits
