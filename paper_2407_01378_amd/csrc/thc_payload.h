@@ -32,8 +32,8 @@ struct PayloadWords {
     uint32_t w[BITS];
 };
 // Read for the last time (ONCE) - but 8-bit payloads take two loads per thread from the same lines, and a line that the
-// first one marks as used up may be gone before the second: as long as the payloads fit the last-level cache
-// beside the rest they are read by ordinary loads (stream_payloads; 4 bits, one load per thread: the same either way).
+// first one marks as used up may be gone before the second: unless stream_payloads they are read by ordinary
+// loads (4 bits, one load per thread: the same either way).
 template <int BITS, bool ONCE = BITS != 8>
 __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* p) {
     PayloadWords<BITS> r;
@@ -117,6 +117,11 @@ struct PayloadSum : PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE> {
     static constexpr int kLanes = BITS == 8 ? 2 : 8 / BITS;    // sub-word accumulators per dword while adding
     static constexpr uint32_t kMask = BITS == 8 ? 0x00FF00FFu : BITS == 4 ? 0x0F0F0F0Fu : 0x03030303u;
     static constexpr uint32_t kFlush = 16u / kGroup;           // WIDE: groups that fit the 8-bit lanes
+    // While the previous chunk rotates: one group in flight (buffer 0) instead of two.  8-bit payloads of what comes
+    // near the last-level cache or outgrows it are served from both places, and more loads in flight do not help
+    // there: 8 workers behind their encoder, 25 M coordinates 217.4 -> 215.3 us, 29 M 253.5 -> 252, 34 M 286.5 ->
+    // 284.8; smaller ones the same either way (17 M 141).  4 bits: 8 x 26 M 188.5 us with two, 190 with one.
+    static constexpr bool kOneAhead = BITS == 8;
     uint32_t acc[kWords][kLanes];
     uint32_t wide[WIDE ? kWords : 1][4];
 
@@ -183,6 +188,13 @@ struct PayloadSum : PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE> {
                 flush(g + 1u);
             }
             this->template issue<1>(byte0, g + 3u);
+        }
+    }
+    // The same with one group in flight, `from` in buffer 0.
+    __device__ __forceinline__ void rest_one_ahead(uint64_t byte0, uint32_t from) {
+        for (uint32_t g = from; g < groups(); ++g) {
+            if (g != from) this->template issue<0>(byte0, g);
+            add<0>(g);
         }
     }
     __device__ __forceinline__ void all(uint64_t byte0) {

@@ -49,7 +49,7 @@ def test_nothing_is_written_behind_a_ragged_end(n):
 @pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 8, 11, 12, 13, 15, 16, 17, 18, 19, 20, 31, 32, 33, 47, 63, 64])
 @pytest.mark.parametrize("l", [10, 14])
 def test_sums_of_every_number_of_workers(W, bits, l):
-    n = 3 * (1 << 14) + 77   # (with more chunks than a device holds at once: test_gpu_timed_path.py)
+    n = 3 * (1 << 14) + 77   # (with more chunks than a device holds at once: the next test)
     rng = np.random.default_rng(W * 10 + bits)
     count = thc.thc_payload_bytes(n, l, bits)
     raw = rng.integers(0, 256, (W, count), dtype=np.uint8)
@@ -67,6 +67,91 @@ def test_sums_of_every_number_of_workers(W, bits, l):
             total[:, k] += (r >> (bits * k)) & ((1 << bits) - 1)
     got = sums.cpu().numpy().view(np.uint8 if one else np.uint16)
     assert (got == total.reshape(-1)[: P << l]).all()
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("W", [1, 3, 4, 5, 9, 12, 17, 18, 33, 47, 64])
+def test_sums_of_every_number_of_workers_while_the_previous_chunk_rotates(W, bits):
+    """More chunks than a device holds workgroups (two per CU), so that a workgroup's later chunks are loaded and
+    summed piece by piece inside the rotation of the one before: a single group, parts of groups, odd numbers of
+    groups, sums of 16 bits of 4-bit payloads.  One call with and without the integer sums, and the batched call
+    over two buckets, against thc_aggregate + thc_decode; the sums against torch."""
+    l, seed = 14, 3
+    resident = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = ((2 * resident + 9) << l) - 1111   # (a third item for some workgroups, a ragged last one)
+    print(f"decoder W={W} bits={bits} n={n}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(W * 10 + bits)
+    P, nb = thc.thc_num_chunks(n, l), thc.thc_payload_bytes(n, l, bits)
+    payloads = [torch.randint(0, 256, (nb,), dtype=torch.uint8, device="cuda", generator=gen) for _ in range(W)]
+    for p in payloads:
+        p[nb // 2: nb // 2 + nb // 8] = 255   # the largest sums
+    scale = torch.rand(P, device="cuda", generator=gen) + 0.5
+    one = thc.thc_sum_bytes(W, bits) == 1
+    sums = torch.zeros(P << l, dtype=torch.uint8 if one else torch.int16, device="cuda")
+    thc.thc_aggregate(payloads, n, l, bits, sums)
+    fields = torch.zeros((nb, 8 // bits), dtype=torch.int32, device="cuda")
+    for p in payloads:
+        for k in range(8 // bits):
+            fields[:, k] += ((p >> (bits * k)) & ((1 << bits) - 1)).to(torch.int32)
+    assert torch.equal(fields.view(-1).to(sums.dtype), sums)
+    want = torch.empty(n, device="cuda")
+    thc.thc_decode(sums, scale, W, n, l, seed, bits, want)
+    fused = thc.thc_aggregate_decode_is_fused(W, l, bits)   # (one worker of 8 bits takes the two steps)
+    for keep in (True, False) if fused else (True,):
+        mine, out = torch.zeros_like(sums), torch.full((n,), float("nan"), device="cuda")
+        thc.thc_aggregate_decode(payloads, scale, n, l, seed, bits, mine if keep else None, out)
+        assert torch.equal(out, want), keep
+        assert not keep or torch.equal(mine, sums)
+    if not fused:
+        return
+    # two buckets: chunks 0 .. cut - 1 and the rest, each numbered from zero (their signs follow the bucket's seed)
+    cut = resident - 3
+    parts = [(0, cut << l), (cut << l, n)]
+    outs = [torch.full((b - a,), float("nan"), device="cuda") for a, b in parts]
+    buckets = [dict(n=b - a, seed=seed + k, payloads=[p[a * bits // 8:] for p in payloads], scale=scale[a >> l:].clone(),
+                    out=outs[k]) for k, (a, b) in enumerate(parts)]
+    ws = torch.empty(thc.thc_batch_workspace_bytes([b - a for a, b in parts], W, l), dtype=torch.uint8, device="cuda")
+    thc.thc_aggregate_decode_batch(buckets, l, bits, ws)
+    for k, (a, b) in enumerate(parts):
+        ref = torch.empty(b - a, device="cuda")
+        thc.thc_decode(sums[a:], buckets[k]["scale"], W, b - a, l, seed + k, bits, ref)
+        assert torch.equal(outs[k], ref), k
+
+
+@pytest.mark.parametrize("count", [False, True])
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("W", [1, 3, 4, 5, 9, 18, 33, 64])
+def test_saturating_decoder_of_every_number_of_workers_over_several_rounds(W, bits, count):
+    """The same for the saturating decoder, whose workgroups load the first two groups of the next chunk one item
+    ahead: aggregate, output and number of clipped coordinates against thc_sat_aggregate + thc_sat_decode."""
+    l, seed = 14, 3
+    resident = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = ((resident + 9) << l) - 1111
+    print(f"saturating decoder W={W} bits={bits} n={n}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(W * 10 + bits)
+    P, nb = thc.thc_num_chunks(n, l), thc.thc_payload_bytes(n, l, bits)
+    # (the largest index on the grid of 2 M + 1 points is 2 M = 2^bits - 2, never all ones)
+    low = torch.tensor(sum(1 << (bits * k) for k in range(8 // bits)), dtype=torch.uint8, device="cuda")
+    payloads = []
+    for _ in range(W):
+        p = torch.randint(0, 256, (nb,), dtype=torch.uint8, device="cuda", generator=gen)
+        ones = p.clone()
+        for k in range(1, bits):
+            ones &= p >> k
+        payloads.append(p - (ones & low))   # fields of all ones lose their lowest bit
+    scale = torch.rand(P, device="cuda", generator=gen) + 0.5
+    aggregate, clipped = torch.zeros(nb, dtype=torch.uint8, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")
+    thc.thc_sat_aggregate(payloads, n, l, bits, aggregate, clipped)
+    want = torch.empty(n, device="cuda")
+    thc.thc_sat_decode(aggregate, scale, W, n, l, seed, bits, want)
+    for keep in (True, False):
+        mine, mine_clipped = torch.zeros_like(aggregate), torch.zeros_like(clipped)
+        out = torch.full((n,), float("nan"), device="cuda")
+        thc.thc_sat_aggregate_decode(payloads, scale, n, l, seed, bits, mine if keep else None,
+                                     mine_clipped if count else None, out)
+        assert torch.equal(out, want), keep
+        assert not keep or torch.equal(mine, aggregate)
+        assert not count or torch.equal(mine_clipped, clipped)
 
 
 @pytest.mark.parametrize("chunks", [224, 225])   # 64 workers: the last size read by ordinary loads, the first by streaming ones
