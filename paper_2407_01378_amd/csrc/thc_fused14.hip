@@ -594,8 +594,8 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
 // from a = 0, which leaves a = z_0 after the first worker), so the running value never
 // needs more than BITS bits.  Optionally stores the packed aggregate (a + M) and counts
 // the coordinates with at least one clipped step.
-// Called from inside the rotation of the current chunk: loads the first two worker groups of
-// the workgroup's next chunk.
+// Called from inside the rotation of the current chunk: loads the first two worker groups (8 bits: the
+// first) of the workgroup's next chunk.
 template <class Loads>
 struct NextSatLoads {
     Loads& loads;
@@ -603,11 +603,11 @@ struct NextSatLoads {
     bool active;
     template <int K>
     __device__ __forceinline__ void at() {
-        if (K == 0 && active) loads.begin(byte0);
+        if (K == 0 && active) loads.begin_ahead(byte0);
     }
 };
 
-template <int BITS, bool COUNT>
+template <int BITS, bool COUNT, bool ONCE = BITS != 8>
 __global__ __launch_bounds__(kThreads, kWavesPerSimd) void sat_aggregate_decode_kernel(
     const SatAggDecodeArgs a, const FusedPayloadPtrs ptrs) {
     __shared__ Shared sh;
@@ -622,9 +622,9 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void sat_aggregate_decode_
     uint32_t clipped_total = 0u;
     const uint64_t thread_byte = (uint64_t)tp * (4u * BITS);
 
-    using Loads = PayloadLoads<BITS, false, kGroup>;
+    using Loads = PayloadLoads<BITS, false, kGroup, ONCE>;
     Loads loads{ptrs, nullptr, a.W, {}};
-    if (blockIdx.x < a.chunks) loads.begin((((uint64_t)blockIdx.x << kChunkLog2) * BITS) / 8u + thread_byte);
+    if (blockIdx.x < a.chunks) loads.begin_ahead((((uint64_t)blockIdx.x << kChunkLog2) * BITS) / 8u + thread_byte);
     for (uint64_t p = blockIdx.x; p < a.chunks; p += gridDim.x) {
         const uint64_t g0 = p << kChunkLog2;
         const uint64_t left = a.n - g0;
@@ -654,11 +654,18 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void sat_aggregate_decode_
                     }
                 }
         };
-        for (uint32_t g = 0; g < loads.groups(); g += 2u) {
-            combine(loads.x[0], g * kGroup);
-            loads.template issue<0>(byte0, g + 2u);
-            if (g + 1u < loads.groups()) combine(loads.x[1], (g + 1u) * kGroup);
-            loads.template issue<1>(byte0, g + 3u);
+        if constexpr (Loads::kOneAhead) {
+            for (uint32_t g = 0; g < loads.groups(); ++g) {
+                if (g != 0u) loads.template issue<0>(byte0, g);
+                combine(loads.x[0], g * kGroup);
+            }
+        } else {
+            for (uint32_t g = 0; g < loads.groups(); g += 2u) {
+                combine(loads.x[0], g * kGroup);
+                loads.template issue<0>(byte0, g + 2u);
+                if (g + 1u < loads.groups()) combine(loads.x[1], (g + 1u) * kGroup);
+                loads.template issue<1>(byte0, g + 3u);
+            }
         }
         if (COUNT) {
 #pragma unroll
@@ -858,13 +865,6 @@ hipError_t launch_aggregate_decode_t(const AggDecodeArgs& a, const FusedPayloadP
 // (2-bit payloads would need more than 85 workers, beyond what the one-launch forms take)
 __host__ inline bool wide_sums(uint32_t W, uint32_t bits) { return bits == 4u && W * 15u > 255u; }
 
-// 8-bit payloads of all workers together that outgrow the last-level cache (256 MB) beside the output are read as
-// for the last time.  Encode + decode of 8 workers, ordinary loads | last use: 134 MB of payloads 144 | 153 us, 160 MB
-// 167 | 178, 210 MB 228 | 229, 268 MB 300 | 297; batched 112 MB 128 | 136, 480 MB 670 | 654, 1048 MB 1127 | 1111.
-__host__ inline bool stream_payloads(const AggDecodeArgs& a) {
-    return a.chunks * a.W > (224ull << 20) / (uint64_t)kChunk;
-}
-
 template <bool BATCH, bool RANGED>
 hipError_t launch_aggregate_decode_pick(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs, const BatchArgs& batch,
                                         uint32_t bits, hipStream_t stream) {
@@ -872,7 +872,7 @@ hipError_t launch_aggregate_decode_pick(const AggDecodeArgs& a, const FusedPaylo
     if (wide_sums(a.W, bits)) return launch_aggregate_decode_t<4, BATCH, RANGED, true>(a, ptrs, batch, stream);
     if (bits == 2) return launch_aggregate_decode_t<2, BATCH, RANGED, false>(a, ptrs, batch, stream);
     if (bits == 4) return launch_aggregate_decode_t<4, BATCH, RANGED, false>(a, ptrs, batch, stream);
-    if (stream_payloads(a)) return launch_aggregate_decode_t<8, BATCH, RANGED, false, true>(a, ptrs, batch, stream);
+    if (stream_payloads(a.W, a.chunks << kChunkLog2)) return launch_aggregate_decode_t<8, BATCH, RANGED, false, true>(a, ptrs, batch, stream);
     return launch_aggregate_decode_t<8, BATCH, RANGED, false, false>(a, ptrs, batch, stream);
 }
 
@@ -1012,21 +1012,24 @@ hipError_t launch_sat_aggregate_decode_fused(const SatAggDecodeArgs& a, const Fu
     using namespace k14;
     if (a.chunks == 0) return hipSuccess;
     uint32_t G = 0;
-#define THC_SATDEC(B, C)                                                                          \
+#define THC_SATDEC(...)                                                                            \
     do {                                                                                          \
-        G = resident_grid<sat_aggregate_decode_kernel<B, C>>();                                   \
+        G = resident_grid<sat_aggregate_decode_kernel<__VA_ARGS__>>();                            \
         if (G == 0) return hipErrorInvalidValue;                                                  \
         if ((uint64_t)G > a.chunks) G = (uint32_t)a.chunks;                                       \
-        hipLaunchKernelGGL((sat_aggregate_decode_kernel<B, C>), dim3(G), dim3(kThreads), 0, stream, \
+        hipLaunchKernelGGL((sat_aggregate_decode_kernel<__VA_ARGS__>), dim3(G), dim3(kThreads), 0, stream, \
                            a, ptrs);                                                              \
     } while (0)
+    const bool once = bits == 8 && stream_payloads(a.W, a.chunks << kChunkLog2);
     if (a.overflow) {
         if (bits == 2) THC_SATDEC(2, true);
         else if (bits == 4) THC_SATDEC(4, true);
+        else if (once) THC_SATDEC(8, true, true);
         else THC_SATDEC(8, true);
     } else {
         if (bits == 2) THC_SATDEC(2, false);
         else if (bits == 4) THC_SATDEC(4, false);
+        else if (once) THC_SATDEC(8, false, true);
         else THC_SATDEC(8, false);
     }
 #undef THC_SATDEC

@@ -55,12 +55,32 @@ __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* 
     return r;
 }
 
+// 8-bit payloads, `coords` of each of W workers, that outgrow the last-level cache (256 MB) beside the output are
+// read as for the last time.  line_mb: payloads of all workers in MiB; less for a decoder that also stores the sums.
+// Encoder and decoder, ordinary loads | last use, us:
+//   chunk 2^14, exact sums  8 workers x 17 M 144 | 153, x 25 M 220 | 220, x 34 M 294 | 292; 4 x 67 M 310 | 306; 16 x 17 M 304 | 297;
+//                           batched 112 MB 128 | 136, 480 MB 670 | 654, 1048 MB 1127 | 1111
+//   saturating              8 x 21 M 186 | 190, x 25 M 221 | 221, x 34 M 294 | 292, x 67 M 580 | 567
+//   small chunks            8 x 17 M 147 | 154, x 21 M 193 | 193, x 25 M 230 | 227, x 34 M 304 | 301
+// Up to 8 M coordinates (more than 28 workers) ordinary loads hold longer: 64 x 5 M 375 | 387 us, 64 x 8 M 609 | 612, 32 x
+// 8 M 333 | 336, saturating 378 | 390, 595 | 599 and 332 | 337, small chunks 32 x 8 M 330 | 335; 32 x 9 M 391 | 388, 390 | 383.
+constexpr uint64_t kStreamLineMb = 224, kStreamLineMbWithSums = 176;
+inline bool stream_payloads(uint32_t W, uint64_t coords, uint64_t line_mb = kStreamLineMb) {
+    return W * coords > line_mb << 20 && coords > 8ull << 20;
+}
+
 // The workers' payload words of one thread (its 32 coordinates) on their way into registers, group by
 // group: a group is the payload of GROUP workers.  Two groups can be in flight at once (buffers 0 and 1, 32
 // registers): while one is combined the next one's loads are on their way.
 template <int BITS, bool BATCH, int GROUP = BITS == 8 ? 2 : 4, bool ONCE = BITS != 8>
 struct PayloadLoads {
     static constexpr uint32_t kGroup = GROUP;
+    // For a persistent kernel's next chunk: one group in flight (buffer 0) instead of two.  8-bit payloads that come
+    // near the size of the last-level cache or outgrow it are served from both places, and more loads in flight do
+    // not help there: 8 workers behind their encoder, 25 M coordinates 217.4 -> 215.3 us, 29 M 253.5 -> 252, 34 M
+    // 286.5 -> 284.8; saturating 32 M 279 -> 273, 17 M 154.5 -> 153.3; smaller ones the same either way (17 M
+    // 141).  4 bits: 8 x 26 M 188.5 us with two, 190 with one.
+    static constexpr bool kOneAhead = BITS == 8;
     const FusedPayloadPtrs& ptrs;   // single bucket: the payload pointers, in the kernel arguments
     ConstU64Ptr pp;                 // batched: those of the bucket being summed, in its record
     uint32_t W;
@@ -96,6 +116,10 @@ struct PayloadLoads {
         issue<0>(byte0, 0u);
         issue<1>(byte0, 1u);
     }
+    __device__ __forceinline__ void begin_ahead(uint64_t byte0) {
+        if constexpr (kOneAhead) issue<0>(byte0, 0u);
+        else begin(byte0);
+    }
 };
 
 // Their exact sum in sub-word lanes.
@@ -111,17 +135,13 @@ struct PayloadSum : PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE> {
     using Loads = PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE>;
     using Loads::groups;
     using Loads::kGroup;
+    using Loads::kOneAhead;
     using Loads::W;
     using Loads::x;
     static constexpr int kWords = BITS;                        // payload dwords per worker per thread
     static constexpr int kLanes = BITS == 8 ? 2 : 8 / BITS;    // sub-word accumulators per dword while adding
     static constexpr uint32_t kMask = BITS == 8 ? 0x00FF00FFu : BITS == 4 ? 0x0F0F0F0Fu : 0x03030303u;
     static constexpr uint32_t kFlush = 16u / kGroup;           // WIDE: groups that fit the 8-bit lanes
-    // While the previous chunk rotates: one group in flight (buffer 0) instead of two.  8-bit payloads of what comes
-    // near the last-level cache or outgrows it are served from both places, and more loads in flight do not help
-    // there: 8 workers behind their encoder, 25 M coordinates 217.4 -> 215.3 us, 29 M 253.5 -> 252, 34 M 286.5 ->
-    // 284.8; smaller ones the same either way (17 M 141).  4 bits: 8 x 26 M 188.5 us with two, 190 with one.
-    static constexpr bool kOneAhead = BITS == 8;
     uint32_t acc[kWords][kLanes];
     uint32_t wide[WIDE ? kWords : 1][4];
 

@@ -361,8 +361,8 @@ struct SmallDecodeArgs {
     float* out;
 };
 
-// SRC: 0 the workers' payloads, 1 stored u8 sums, 2 stored u16 sums.  WIDE: see PayloadSum.
-template <int SRC, int BITS, bool WIDE>
+// SRC: 0 the workers' payloads, 1 stored u8 sums, 2 stored u16 sums.  WIDE, ONCE: see PayloadSum.
+template <int SRC, int BITS, bool WIDE, bool ONCE = BITS != 8>
 __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const SmallDecodeArgs a,
                                                                       const FusedPayloadPtrs ptrs) {
     __shared__ float4 xb4[4 * 512];
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const Smal
     float s = 0.0f;
     if (exists) s = a.scale[g >> l];
     if constexpr (SRC == 0) {
-        PayloadSum<BITS, false, WIDE> sum{ptrs, nullptr, a.W};
+        PayloadSum<BITS, false, WIDE, ONCE> sum{ptrs, nullptr, a.W};
         sum.clear();
         if (exists) sum.all((g * BITS) / 8u);
         if (t < blockDim.x / 4u) *reinterpret_cast<u32x4*>(&sign[4 * t]) = sign_block((base >> 7) + t, a.key0, a.key1);
@@ -562,11 +562,12 @@ static hipError_t small_decode(k14::SmallDecodeArgs& a, const FusedPayloadPtrs& 
     while (log2 > (a.l > kWaveLog2 ? a.l : kWaveLog2) && (a.padded >> log2) < 2u * (uint64_t)device_cus()) --log2;
     const dim3 grid((uint32_t)((a.padded + (1ull << log2) - 1u) >> log2)), block(1u << (log2 - 5u));
     if (grid.x == 0) return hipSuccess;
-#define THC_SMALL_DECODE(S, B, WI) hipLaunchKernelGGL((small_decode_kernel<S, B, WI>), grid, block, 0, stream, a, ptrs)
+#define THC_SMALL_DECODE(...) hipLaunchKernelGGL((small_decode_kernel<__VA_ARGS__>), grid, block, 0, stream, a, ptrs)
     if (src == 0) {
         if (wide) THC_SMALL_DECODE(0, 4, true);
         else if (bits == 2) THC_SMALL_DECODE(0, 2, false);
         else if (bits == 4) THC_SMALL_DECODE(0, 4, false);
+        else if (stream_payloads(a.W, a.padded, kStreamLineMbWithSums)) THC_SMALL_DECODE(0, 8, false, true);
         else THC_SMALL_DECODE(0, 8, false);
     } else if (src == 1) {
         if (bits == 2) THC_SMALL_DECODE(1, 2, false);

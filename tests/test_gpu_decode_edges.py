@@ -154,7 +154,7 @@ def test_saturating_decoder_of_every_number_of_workers_over_several_rounds(W, bi
         assert not count or torch.equal(mine_clipped, clipped)
 
 
-@pytest.mark.parametrize("chunks", [224, 225])   # 64 workers: the last size read by ordinary loads, the first by streaming ones
+@pytest.mark.parametrize("chunks", [224, 225])   # 64 workers, 224 MiB and a little more: ordinary loads on both sides (less than 8 M coordinates)
 def test_8_bit_payloads_around_the_size_of_the_last_level_cache(chunks):
     W, l, bits, seed = 64, 14, 8, 11
     n = (chunks << l) - 5
@@ -175,3 +175,32 @@ def test_8_bit_payloads_around_the_size_of_the_last_level_cache(chunks):
     ws = torch.empty(thc.thc_batch_workspace_bytes([n], W, l), dtype=torch.uint8, device="cuda")
     thc.thc_aggregate_decode_batch([dict(n=n, seed=seed, payloads=payloads, scale=scale, out=many)], l, bits, ws)
     assert torch.equal(many, want)
+
+
+@pytest.mark.parametrize("form,l,chunks", [   # 16 workers: the last size read by ordinary loads, the first as for the last time
+    ("exact", 14, 896), ("exact", 14, 897), ("sat", 14, 896), ("sat", 14, 897), ("sat counted", 14, 897),
+    ("exact", 12, 2816), ("exact", 12, 2817), ("exact", 5, 360449),
+])
+def test_8_bit_payloads_on_both_sides_of_the_line_of_streaming_loads(form, l, chunks):
+    W, bits, seed = 16, 8, 11
+    n = (chunks << l) - 5
+    gen = torch.Generator(device="cuda").manual_seed(chunks)
+    payloads = [torch.randint(0, 255, (chunks << l,), dtype=torch.uint8, device="cuda", generator=gen) for _ in range(W)]
+    scale = torch.rand(chunks, device="cuda", generator=gen) + 0.5
+    want, out = torch.empty(n, device="cuda"), torch.full((n,), 7.0, device="cuda")
+    if form == "exact":
+        sums = torch.zeros(chunks << l, dtype=torch.int16, device="cuda")
+        mine = torch.zeros_like(sums)
+        thc.thc_aggregate(payloads, n, l, bits, sums)
+        thc.thc_decode(sums, scale, W, n, l, seed, bits, want)
+        thc.thc_aggregate_decode(payloads, scale, n, l, seed, bits, mine, out)
+        assert torch.equal(sum(p.to(torch.int32) for p in payloads).to(torch.int16), sums)
+    else:
+        sums = torch.zeros(chunks << l, dtype=torch.uint8, device="cuda")
+        mine = torch.zeros_like(sums)
+        clipped = torch.zeros(2, dtype=torch.int64, device="cuda")
+        thc.thc_sat_aggregate(payloads, n, l, bits, sums, clipped[:1])
+        thc.thc_sat_decode(sums, scale, W, n, l, seed, bits, want)
+        thc.thc_sat_aggregate_decode(payloads, scale, n, l, seed, bits, mine, clipped[1:] if form != "sat" else None, out)
+        assert form == "sat" or int(clipped[0]) == int(clipped[1])
+    assert torch.equal(out, want) and torch.equal(mine, sums)
