@@ -4,7 +4,7 @@
 // separately rounded fp32 add and subtract), so results are bit-identical to the
 // stage-by-stage definition:
 //   stages 0..13    the chunk-2^14 kernels (thc_fast14.hip), data in registers and LDS
-//                   (0..14 for two sizes: thc_full15.hip)
+//                   (0..14 for 2^25 coordinates: thc_full15.hip)
 //   the rest        "high passes" over the fp32 array in global memory, up to 11 stages per
 //                   pass (this file), in place
 // plus the steps of the quantizer on rotated data, which the partial-rotation path fuses into
@@ -258,15 +258,15 @@ __global__ __launch_bounds__(64 * pass_waves(M), pass_waves_per_simd(M, KIND)) v
         }
         uint32_t* sign_of = signs + mine_of * kRows;   // ToX: of this tile's rows
         if constexpr (KIND == Kind::ToX) {
-            // one sign word per row (32 coordinates; M = 11: half of one): the rows lie far apart, a lane
-            // computes a row's block.  Ordered by the barriers of the exchange, or inside the wave.
+            // one sign word per row (32 coordinates; with 11 stages it would be half of one): the rows lie far apart, a
+            // lane computes a row's block.  Ordered by the barriers of the exchange, or inside the wave.
 #pragma unroll
             for (uint32_t r = 0; r < kRows; r += 64u * kTileWaves) {
                 const uint32_t row = r + 64u * wave + lane;
                 const uint64_t g = now.row_start(row);
                 const u32x4 sb = sign_block(g >> 7, a.key0, a.key1);
                 const uint32_t which = (uint32_t)(g >> 5) & 3u;
-                sign_of[row] = (which == 0u ? sb.w[0] : which == 1u ? sb.w[1] : which == 2u ? sb.w[2] : sb.w[3]) >> ((uint32_t)g & 31u);
+                sign_of[row] = which == 0u ? sb.w[0] : which == 1u ? sb.w[1] : which == 2u ? sb.w[2] : sb.w[3];
             }
             if constexpr (kIndependent) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }

@@ -168,7 +168,8 @@ __global__ __launch_bounds__(kThreads, 8) void first_pass15_kernel(const ChunkAr
     }
     butterflies<0, 3>(v);
     // The values are negated where i_RB .. i_(RB+3) have odd parity, which are bits of t.  The last stage undoes
-    // it in its multiply-adds by +-1 (one rounding, of the same sum: an exact zero is +0 as the stage gives it).
+    // it in its multiply-adds by +-1 (one rounding, of the same sum: a difference of equal values is +0 as the stage gives
+    // it; only the sign of a sum of two zeros can be another).
     const float sgn = k14::odd_parity4(t >> RB) ? -1.0f : 1.0f;
 #pragma unroll
     for (int r = 0; r < kRegs; ++r)
