@@ -258,7 +258,9 @@ int thc_encode_all_static(const void* const* grads, thc_dtype dt, uint32_t W, ui
                           float* scale, uint32_t* timed_out, void* stream);
 
 /* Upper bound on the polls of one inter-workgroup wait inside thc_encode_all (default
- * 2^22, about seconds).  A tuning and test knob: with a tiny limit the waits expire, the
+ * 2^22, about seconds).  It counts polls, not time: a poll is a read of the chunk's range words
+ * and a pause of 512 clocks, or of 256 with more than 32 workers, where one wave of a workgroup
+ * polls for all.  A tuning and test knob: with a tiny limit the waits expire, the
  * error word is set and every wave still exits.  PROCESS-GLOBAL and not thread-safe: the
  * value is read when a call is enqueued, by every thread's calls; changing it while another
  * thread encodes makes that thread's waits expire early, which only the error word of its

@@ -32,13 +32,52 @@ def test_agreement_matches_the_per_worker_calls(W, rounds, dtype, bits):
     thc.thc_encode_all_cleared(xs, 14, 7, bits, payloads, scale, ws)
     torch.cuda.synchronize()
     assert int(ws.count_nonzero()) == 0
+    _matches_the_per_worker_calls(xs, bits, scale, payloads)
+
+
+def _matches_the_per_worker_calls(xs, bits, scale, payloads):
+    W, P = len(xs), scale.numel()
     absmax = torch.empty(W * P, device="cuda")
     for w in range(W):
         thc.thc_chunk_absmax(xs[w], 14, 7, absmax[w * P:(w + 1) * P])
     shared = torch.empty(P, device="cuda")
     thc.thc_scale_reduce(absmax, W, P, shared)
     assert torch.equal(scale, shared)
-    ref = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    ref = torch.empty_like(payloads[0])
     for w in range(W):
         thc.thc_encode(xs[w], 14, 7, w, bits, shared, ref)
         assert torch.equal(payloads[w], ref), w
+
+
+@pytest.mark.parametrize("W,rounds,dtype,bits", [
+    (20, 3, torch.bfloat16, 4), (20, 10, torch.float32, 2),     # a word per workgroup, every wave reads
+    (64, 3, torch.bfloat16, 4), (64, 10, torch.float32, 8),     # one reader, early and late pause
+    (2, 0, torch.bfloat16, 4), (8, 0, torch.float32, 8),        # one item per workgroup and CU
+])
+def test_expired_wait_of_every_form_of_agreement(W, rounds, dtype, bits):
+    """Failure handling forced from the host: with a poll limit of zero a wait gives up after one read.  Every wave
+    still ends, over several rounds the error word is set (a word takes longer from one workgroup to another
+    than the pause in front of that read), and a cleared workspace is good again."""
+    n = ((rounds * (GRID // W) + 1) << 14) - 1234
+    print(f"expired wait W={W} n={n} {dtype} {bits} bits", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(W)
+    xs = [torch.randn(n, generator=gen, device="cuda").mul_(10.0 ** (w % 3)).to(dtype) for w in range(W)]
+    P, nb = thc.thc_num_chunks(n, 14), thc.thc_payload_bytes(n, 14, bits)
+    ws = torch.empty(thc.thc_encode_all_workspace_bytes(W, n, 14), dtype=torch.uint8, device="cuda")
+    thc.thc_workspace_clear(ws)
+    scale = torch.full((P,), float("nan"), device="cuda")
+    payloads = [torch.full((nb,), 0xAA, dtype=torch.uint8, device="cuda") for _ in range(W)]
+    torch.cuda.synchronize()
+    try:
+        thc.thc_set_spin_limit(0)
+        thc.thc_encode_all_cleared(xs, 14, 7, bits, payloads, scale, ws)
+        torch.cuda.synchronize()            # returns: nothing hangs
+    finally:
+        thc.thc_set_spin_limit(1 << 22)
+    assert rounds == 0 or thc.thc_encode_all_timed_out(ws)
+    thc.thc_workspace_clear(ws)
+    thc.thc_encode_all_cleared(xs, 14, 7, bits, payloads, scale, ws)
+    torch.cuda.synchronize()
+    assert int(ws.count_nonzero()) == 0
+    _matches_the_per_worker_calls(xs, bits, scale, payloads)

@@ -10,11 +10,15 @@ The model restates the protocol, it shares nothing with the kernels:
   rotated kernels   per item: [workgroup barrier] publish, wait for all words of the chunk,
                     clear the own word of the workgroup's PREVIOUS chunk
   one word per workgroup (more than 16 workers): wave 0 publishes behind the barrier and clears
+  one reader (more than 32 workers): the same, and wave 0 alone polls; it hands the result to the other
+                    waves through the cell in which it gathered the workgroup's own maximum
   pipelined kernel  (unrotated bf16) no barriers: publish item k + 1, wait for item k,
                     clear the own word of item k - 2
   both              the workgroups of a chunk count themselves off for a workgroup's last
                     chunk(s); the last one clears all of the chunk's words and the counter
-and a deliberately wrong variant (the pipelined kernel clearing item k - 1) must be caught.
+and deliberately wrong variants (the pipelined kernel clearing item k - 1, the one reader without a barrier
+in front of the hand-over or in front of the cell's next use) must be caught.  With a bound on the polls of a
+wait every wave still ends, and the waves of a workgroup go on with one and the same result.
 """
 import random
 
@@ -31,6 +35,7 @@ class World:
         self.P = words_per_workgroup or V     # publishing waves per workgroup
         self.word = {(c, w, v): 0 for c in range(chunks) for w in range(W) for v in range(self.P)}
         self.done = [0] * chunks
+        self.expired = False      # a wait has given up
         self.seen = {}            # (w, v, c) -> the words a wave saw when its wait ended
 
     def all_words(self, c):
@@ -109,6 +114,50 @@ def workgroup_word_wave(world, bar, w, v, items):
         yield from _count_off(world, prev)
 
 
+def one_reader_wave(world, bar, w, v, items, limit=None, handover_barrier=True, rotation_barrier=True):
+    """One word per workgroup, read by wave 0 for all.  bar.cell: a place per wave for its maximum; the first one
+    then carries the result of the wait.  limit: polls after which the wait gives up."""
+    if not hasattr(bar, "cell"):
+        bar.cell, bar.results = [0] * bar.parties, {}
+    prev = None
+    for c in items:
+        if rotation_barrier:
+            yield from _barrier(bar)      # the rotation's exchange
+        yield "maximum"
+        bar.cell[v] = 100 + c
+        yield from _barrier(bar)
+        if v == 0:
+            assert bar.cell == [100 + c] * bar.parties, "a maximum was overwritten before it was gathered"
+            yield "publish"
+            world.word[(c, w, 0)] = 100 + c
+        yield from _barrier(bar)          # the last exchange
+        if v == 0:
+            polls, done = 0, False
+            while not done and (limit is None or polls <= limit):
+                yield "poll"
+                words = world.all_words(c)
+                done = all(x != 0 for x in words)
+                polls += 1
+            if not done:
+                world.expired = True
+            elif prev is not None:
+                yield "clear"
+                world.word[(prev, w, 0)] = 0
+            yield "hand over"
+            bar.cell[0] = ("result", c, tuple(words))
+        if handover_barrier:
+            yield from _barrier(bar)
+        yield "take over"
+        got = bar.cell[0]
+        assert got[:2] == ("result", c) if isinstance(got, tuple) else False, "a wave took something else over"
+        assert bar.results.setdefault(c, got) == got
+        world.seen[(w, v, c)] = list(got[2])
+        prev = c
+    yield from _barrier(bar)
+    if v == 0 and prev is not None:
+        yield from _count_off(world, prev)
+
+
 def pipelined_wave(world, bar, w, v, items, clear_lag=2):
     """No barrier between items: the range of item k + 1 is published before the wait for item k."""
     if not items:
@@ -157,11 +206,14 @@ def run(kind, W, V, groups, rounds, seed, words_per_workgroup=None, **kw):
                 raise Hang(f"no progress: {len(waves)} waves stuck")
         else:
             idle = 0
+    assert len(world.seen) == chunks * W * V
+    if world.expired:             # (the workspace then has to be cleared, and maxima may be missing)
+        assert all(x in (0, 100 + c) for (w, v, c), words in world.seen.items() for x in words)
+        return world
     assert all(x == 0 for x in world.word.values()), "a range word is left set"
     assert all(x == 0 for x in world.done), "a counter is left set"
     for (w, v, c), words in world.seen.items():
         assert all(x == 100 + c for x in words), "a wave saw a word of another chunk"
-    assert len(world.seen) == chunks * W * V
     return world
 
 
@@ -175,6 +227,31 @@ def test_rotated_protocol_clears_itself_and_never_hangs(W, V, groups, rounds):
 def test_workgroup_word_protocol_clears_itself_and_never_hangs(W, V, groups, rounds):
     for seed in range(300):
         run(workgroup_word_wave, W, V, groups, rounds, seed, words_per_workgroup=1)
+
+
+@pytest.mark.parametrize("W,V,groups,rounds", [(2, 2, 1, 1), (2, 3, 1, 4), (3, 2, 2, 3), (5, 2, 1, 4)])
+def test_one_reader_protocol_clears_itself_and_never_hangs(W, V, groups, rounds):
+    for seed in range(300):
+        assert not run(one_reader_wave, W, V, groups, rounds, seed, words_per_workgroup=1).expired
+
+
+@pytest.mark.parametrize("limit", [0, 3])
+@pytest.mark.parametrize("W,V,groups,rounds", [(2, 2, 1, 1), (2, 3, 1, 4), (3, 2, 2, 3)])
+def test_one_reader_that_gives_up_ends_with_one_result_per_workgroup(W, V, groups, rounds, limit):
+    expired = sum(run(one_reader_wave, W, V, groups, rounds, seed, words_per_workgroup=1, limit=limit).expired
+                  for seed in range(300))
+    assert expired > 0
+
+
+@pytest.mark.parametrize("without", ["handover_barrier", "rotation_barrier"])
+def test_the_model_catches_a_missing_barrier_around_the_hand_over(without):
+    caught = 0
+    for seed in range(300):
+        try:
+            run(one_reader_wave, 2, 3, 1, 5, seed, words_per_workgroup=1, **{without: False})
+        except (Hang, AssertionError):
+            caught += 1
+    assert caught > 0
 
 
 @pytest.mark.parametrize("W,V,groups,rounds", [(2, 2, 1, 1), (2, 2, 1, 2), (2, 2, 1, 3), (3, 2, 2, 4), (2, 3, 1, 6), (4, 1, 2, 5)])
