@@ -112,6 +112,13 @@ struct PayloadLoads {
             asm volatile("; part of a group");
         }
     }
+    // The same of a group that is known to be whole.
+    template <int B>
+    __device__ __forceinline__ void issue_whole(uint64_t byte0, uint32_t group) {
+#pragma unroll
+        for (uint32_t j = 0; j < kGroup; ++j)
+            x[B][j] = load_payload_words<BITS, ONCE>(pointer(group * kGroup + j) + byte0);
+    }
     __device__ __forceinline__ void begin(uint64_t byte0) {
         issue<0>(byte0, 0u);
         issue<1>(byte0, 1u);
@@ -153,52 +160,61 @@ struct PayloadSum : PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE> {
 #pragma unroll
             for (int k = 0; k < kLanes; ++k) acc[d][k] = 0u;
     }
+    __device__ __forceinline__ void add_whole(const PayloadWords<BITS> (&y)[kGroup]) {
+#pragma unroll
+        for (uint32_t j = 0; j < kGroup; j += 2u)
+#pragma unroll
+            for (int d = 0; d < kWords; ++d)
+#pragma unroll
+                for (int q = 0; q < kLanes; ++q)   // (one three-operand addition for two workers)
+                    acc[d][q] += ((y[j].w[d] >> (BITS * q)) & kMask) + ((y[j + 1].w[d] >> (BITS * q)) & kMask);
+    }
+    __device__ __forceinline__ void add_one(const PayloadWords<BITS>& y) {
+#pragma unroll
+        for (int d = 0; d < kWords; ++d)
+#pragma unroll
+            for (int q = 0; q < kLanes; ++q) acc[d][q] += (y.w[d] >> (BITS * q)) & kMask;
+    }
     template <int B>
     __device__ __forceinline__ void add(uint32_t group) {
         const uint32_t w0 = group * kGroup;
         if (w0 + kGroup <= W) {
-#pragma unroll
-            for (uint32_t j = 0; j < kGroup; j += 2u)
-#pragma unroll
-                for (int d = 0; d < kWords; ++d)
-#pragma unroll
-                    for (int q = 0; q < kLanes; ++q)   // (one three-operand addition for two workers)
-                        acc[d][q] += ((x[B][j].w[d] >> (BITS * q)) & kMask) + ((x[B][j + 1].w[d] >> (BITS * q)) & kMask);
+            add_whole(x[B]);
         } else {
 #pragma unroll
             for (uint32_t j = 0; j + 1u < kGroup; ++j)
-                if (w0 + j < W) {
+                if (w0 + j < W) add_one(x[B][j]);
+        }
+    }
+    // WIDE: the 8-bit lanes into the wide ones, before they could overflow.
+    __device__ __forceinline__ void flush() {
+        if constexpr (WIDE) {
 #pragma unroll
-                    for (int d = 0; d < kWords; ++d)
+            for (int d = 0; d < kWords; ++d)
 #pragma unroll
-                        for (int q = 0; q < kLanes; ++q) acc[d][q] += (x[B][j].w[d] >> (BITS * q)) & kMask;
+                for (int q = 0; q < kLanes; ++q) {
+                    wide[d][q] += acc[d][q] & 0x00FF00FFu;
+                    wide[d][q + 2] += (acc[d][q] >> 8) & 0x00FF00FFu;
+                    acc[d][q] = 0u;
                 }
         }
     }
-    // WIDE, behind the addition of `group`: the 8-bit lanes into the wide ones before they could overflow.
+    // The same behind the addition of `group`, where it is due.
     __device__ __forceinline__ void flush(uint32_t group) {
-        if constexpr (WIDE) {
-            if ((group + 1u) % kFlush == 0u || group + 1u == groups()) {
-#pragma unroll
-                for (int d = 0; d < kWords; ++d)
-#pragma unroll
-                    for (int q = 0; q < kLanes; ++q) {
-                        wide[d][q] += acc[d][q] & 0x00FF00FFu;
-                        wide[d][q + 2] += (acc[d][q] >> 8) & 0x00FF00FFu;
-                        acc[d][q] = 0u;
-                    }
-            }
-        }
+        if (WIDE && ((group + 1u) % kFlush == 0u || group + 1u == groups())) flush();
     }
-    // Adds the groups from `from` on (even, less than kFlush; the caller has added those before), the first
-    // two of which are in flight.
-    __device__ __forceinline__ void rest(uint64_t byte0, uint32_t from) {
+    __device__ __forceinline__ void clear_wide() {
         if constexpr (WIDE) {
 #pragma unroll
             for (int d = 0; d < kWords; ++d)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) wide[d][k] = 0u;
         }
+    }
+    // Adds the groups from `from` on (even, less than kFlush; the caller has added those before), the first
+    // two of which are in flight.
+    __device__ __forceinline__ void rest(uint64_t byte0, uint32_t from) {
+        clear_wide();
         for (uint32_t g = from; g < groups(); g += 2u) {
             add<0>(g);
             flush(g);
@@ -220,6 +236,46 @@ struct PayloadSum : PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE> {
     __device__ __forceinline__ void all(uint64_t byte0) {
         this->begin(byte0);
         rest(byte0, 0u);
+    }
+    // The same for a kernel in which nothing rides along with the sum, and where its wait is a good part of the time.
+    // The workers beyond the whole groups are loaded first and added last, so that the loop has whole
+    // groups only: no condition between a load and its use, each wait is for its own group alone (`all` waits for the
+    // first worker of a part of a group before it loads the second), and less code to fetch for few workers.
+    // Small-chunk decoder, `all` | this, 2^10 coordinates per chunk, us: 64 workers x 2^20 at 8 bits 22.7 | 18.0,
+    // at 4 bits 15.6 | 13.5, at 2 bits 14.4 | 9.4; 8 workers 6.9 | 6.5, 5.7 | 5.5, 5.7 | 5.4; 1 worker at 2 bits 6.2 | 6.0.
+    // (The decoder of chunks of 2^14 has no registers left for it.)
+    __device__ __forceinline__ void all_alone(uint64_t byte0) {
+        const uint32_t whole = W / kGroup, more = W % kGroup;
+        PayloadWords<BITS> y[kGroup - 1u];
+#pragma unroll
+        for (uint32_t j = 0; j + 1u < kGroup; ++j)
+            if (j < more) y[j] = load_payload_words<BITS, ONCE>(this->pointer(whole * kGroup + j) + byte0);
+        clear_wide();
+        if (whole > 1u) {
+            this->template issue_whole<0>(byte0, 0u);
+            this->template issue_whole<1>(byte0, 1u);
+            uint32_t g = 0;
+            for (; g + 3u < whole; g += 2u) {
+                add_whole(x[0]);
+                this->template issue_whole<0>(byte0, g + 2u);
+                add_whole(x[1]);
+                this->template issue_whole<1>(byte0, g + 3u);
+                if ((g + 2u) % kFlush == 0u) flush();
+            }
+            const bool three = (whole & 1u) != 0u;   // groups left: two or three
+            add_whole(x[0]);
+            if (three) this->template issue_whole<0>(byte0, g + 2u);
+            add_whole(x[1]);
+            if ((g + 2u) % kFlush == 0u) flush();
+            if (three) add_whole(x[0]);
+        } else if (whole != 0u) {
+            this->template issue_whole<0>(byte0, 0u);
+            add_whole(x[0]);
+        }
+#pragma unroll
+        for (uint32_t j = 0; j + 1u < kGroup; ++j)
+            if (j < more) add_one(y[j]);
+        flush();   // (at most three whole groups and three workers since the last time: 15 * 15 <= 255)
     }
 
     // Sub-word lanes -> one sum per coordinate.

@@ -363,7 +363,7 @@ struct SmallDecodeArgs {
 
 // SRC: 0 the workers' payloads, 1 stored u8 sums, 2 stored u16 sums.  WIDE, ONCE: see PayloadSum.
 template <int SRC, int BITS, bool WIDE, bool ONCE = BITS != 8>
-__global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const SmallDecodeArgs a,
+__global__ __launch_bounds__(kDecodeThreads, 4) void small_decode_kernel(const SmallDecodeArgs a,
                                                                       const FusedPayloadPtrs ptrs) {
     __shared__ float4 xb4[4 * 512];
     __shared__ alignas(16) uint32_t sign[1u << (kDecodeLog2 - 5u)];
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kDecodeThreads) void small_decode_kernel(const Smal
     if constexpr (SRC == 0) {
         PayloadSum<BITS, false, WIDE, ONCE> sum{ptrs, nullptr, a.W};
         sum.clear();
-        sum.all((from * BITS) / 8u);
+        sum.all_alone((from * BITS) / 8u);
         if (t < blockDim.x / 4u) *reinterpret_cast<u32x4*>(&sign[4 * t]) = sign_block((base >> 7) + t, a.key0, a.key1);
         sum.unpack(S);
         if (a.sums && exists) {
