@@ -18,7 +18,7 @@
 //   barrier per stage above 2^4.
 //
 // Decode.  A workgroup of four waves owns 2^13 coordinates (fewer, down to the 2^11 of a wave or a chunk, where
-// that spreads a short gradient over the CUs: 2^20 coordinates are 128 workgroups of four); a thread sums the workers' payload
+// that spreads a short gradient over the CUs: small_decode_log2); a thread sums the workers' payload
 // words of its 32 coordinates, five stages run in registers, the wave re-shuffles through its
 // own 8 KB of LDS, the rest of the stages follow, and the result leaves in 128-byte lines.
 // Bound by memory.
@@ -556,12 +556,38 @@ bool small_applicable(Mode mode, const ChunkArgs& c) {
     return mode == Mode::Decode && !c.sat && k14::aligned16(c.in) && (c.padded >> k14::kDecodeLog2) < 0x7FFFFFFFull;
 }
 
+// Coordinates of a workgroup (log2): 2^11 per wave, at least a chunk.  Four waves, and fewer where that spreads a
+// short gradient over the CUs.  W: payloads that are summed (1 for stored sums).  The lines, in workgroups of four waves on 256
+// CUs, and the decoder in us with one | two | four waves (chunk 2^10):
+//   more than two for each CU     four
+//   more than one                 four; 3 and 4 payloads two: 2.6 M coordinates, 4 at 4 bits 10.6 | 6.0 | 7.3, at 8 bits 11.2 | 7.0 | 8.4;
+//                                 2 at 4 bits 10.8 | 7.0 | 6.2, 8 at 4 bits 11.1 | 7.8 | 7.6
+//   more than one for two CUs     up to 4 payloads four: 2^21, 1 at 2 bits 6.4 | 7.3 | 6.1, 2 at 4 bits 6.7 | 7.0 | 6.1, 4 at 4
+//                                 bits 6.4 | 6.1 | 6.5; more one: 1.3 M, 8 at 4 bits 5.6 | 7.2 | 6.4, 8 at 8 bits 6.5 | 8.0 | 7.2
+//   more than one for four CUs    up to 4 payloads two: 2^20, 2 at 4 bits 6.0 | 5.9 | 6.2, 4 at 8 bits 6.7 | 5.9 | 6.2; more one: 8 at 4
+//                                 bits 5.5 | 6.4 | 6.4, 16 at 4 bits 6.4 | 6.6 | 6.6
+//   more than two                 one: 2^19, 2 at 4 bits 5.3 | 5.8 | 5.9, 16 at 8 bits 6.4 | 8.0 | 7.8
+//   up to two (one payload: four) four with up to 8 payloads: every further XCD that takes part costs more than its waves
+//                                 save (2^14, 1 at 2 bits 5.3 | 5.2 | 4.9, stored sums 4.9 | 4.6 | 4.5)
+static uint32_t small_decode_log2(uint64_t padded, uint32_t l, uint32_t W) {
+    const uint64_t groups = (padded + (1ull << k14::kDecodeLog2) - 1u) >> k14::kDecodeLog2, cus = device_cus();
+    uint32_t log2 = k14::kDecodeLog2;
+    if (groups > cus) {
+        if (groups < 2u * cus && (W == 3u || W == 4u)) log2 = k14::kWaveLog2 + 1u;
+    } else if (2u * groups > cus) {
+        if (W > 4u) log2 = k14::kWaveLog2;
+    } else if (4u * groups > cus) {
+        log2 = W > 4u ? k14::kWaveLog2 : k14::kWaveLog2 + 1u;
+    } else if (groups > (W == 1u ? 4u : 2u) || W > 8u) {
+        log2 = k14::kWaveLog2;
+    }
+    return log2 > l ? log2 : l;
+}
+
 static hipError_t small_decode(k14::SmallDecodeArgs& a, const FusedPayloadPtrs& ptrs, int src, uint32_t bits, bool wide,
                                hipStream_t stream) {
     using namespace k14;
-    // 2^11 coordinates per wave, at least a chunk per workgroup: two workgroups for every CU before they grow
-    uint32_t log2 = kDecodeLog2;
-    while (log2 > (a.l > kWaveLog2 ? a.l : kWaveLog2) && (a.padded >> log2) < 2u * (uint64_t)device_cus()) --log2;
+    const uint32_t log2 = small_decode_log2(a.padded, a.l, src == 0 ? a.W : 1u);
     const dim3 grid((uint32_t)((a.padded + (1ull << log2) - 1u) >> log2)), block(1u << (log2 - 5u));
     if (grid.x == 0) return hipSuccess;
 #define THC_SMALL_DECODE(...) hipLaunchKernelGGL((small_decode_kernel<__VA_ARGS__>), grid, block, 0, stream, a, ptrs)

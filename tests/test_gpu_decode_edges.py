@@ -204,3 +204,31 @@ def test_8_bit_payloads_on_both_sides_of_the_line_of_streaming_loads(form, l, ch
         thc.thc_sat_aggregate_decode(payloads, scale, n, l, seed, bits, mine, clipped[1:] if form != "sat" else None, out)
         assert form == "sat" or int(clipped[0]) == int(clipped[1])
     assert torch.equal(out, want) and torch.equal(mine, sums)
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("l", [5, 10, 11, 12, 13])
+@pytest.mark.parametrize("W", [1, 3, 4, 5, 8, 9, 18])
+def test_small_chunk_decoder_in_workgroups_of_every_width(W, l, bits):
+    """Workgroups of four, two and one wave, on both sides of each length where the width changes (2, 4, a quarter, half, once
+    and twice the number of CUs, in workgroups of four waves).  The sums of a call and of thc_aggregate, the output of it and of thc_decode,
+    which deals the chunks out in its own widths; and two lengths of one gradient agree where both have whole chunks."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    seed, before = 5, None
+    gen = torch.Generator(device="cuda").manual_seed(W * 10 + bits)
+    most = (2 * cus) << 13
+    flat = [torch.randint(0, 256, (most * bits // 8,), dtype=torch.uint8, device="cuda", generator=gen) for _ in range(W)]
+    scales = torch.rand(most >> l, device="cuda", generator=gen) + 0.5
+    for groups in (1, 2, 3, 4, 5, cus // 4, cus // 4 + 1, cus // 2, cus // 2 + 1, cus, cus + 1, 2 * cus - 1, 2 * cus):
+        n = (groups << 13) - (1 << 13) + 33 if groups == 1 else (groups << 13) - 31
+        P, nb = thc.thc_num_chunks(n, l), thc.thc_payload_bytes(n, l, bits)
+        payloads, scale = [f[:nb] for f in flat], scales[:P]
+        sums = torch.zeros(P << l, dtype=torch.uint8 if thc.thc_sum_bytes(W, bits) == 1 else torch.int16, device="cuda")
+        thc.thc_aggregate(payloads, n, l, bits, sums)
+        want, out, mine = torch.empty(n, device="cuda"), torch.full((n,), float("nan"), device="cuda"), torch.zeros_like(sums)
+        thc.thc_decode(sums, scale, W, n, l, seed, bits, want)
+        thc.thc_aggregate_decode(payloads, scale, n, l, seed, bits, mine, out)
+        assert torch.equal(mine, sums) and torch.equal(out, want), groups
+        whole = 0 if before is None else before.numel() >> l << l
+        assert whole == 0 or torch.equal(out[:whole], before[:whole]), groups
+        before = out
