@@ -30,7 +30,7 @@ constexpr int kWavesPerSimd = 4;
 // How the workgroups of a chunk tell one another its range (template argument of the encoder).
 enum class Words : int {
     PerWave = 0,    // every wave publishes a word and reads all words: up to 16 workers
-    PerGroup = 1,   // one word per workgroup (the waves' maxima meet in LDS), read by every wave: up to 32
+    PerGroup = 1,   // one word per workgroup (the waves' maxima meet in LDS), read by every wave: up to 32, and see one_reader
     OneReader = 2,  // the same, read by one wave for all: beyond
     Quick = 3       // PerWave for a launch of at most one workgroup per CU and one item each: nothing to overlap
 };
@@ -45,7 +45,8 @@ constexpr uint32_t kPerGroupMaxWorkers = 32;
 //              the way of the other one on its CU decides whether the two stay half an item apart.  64 workers, bf16, 4 bits,
 //              128 chunks 140 -> 130 us, 256 chunks 279 -> 248; 8 bits, 245 chunks 363 -> 284 (32 workers x 184
 //              chunks would lose 5 %)
-//   few rounds 64 workers x 1 chunk 24.7 -> 24.4, x 16 chunks 35.0 -> 34.6
+//   few rounds bf16 and up to 4 bits 16: 32 workers x 48 chunks 24.1 us (32: 24.4), 64 x 16 chunks 19.6 (20.2); fp32 or 8
+//              bits, where an item is longer, 32: 32 x 64 chunks bf16 8 bits 32.1 (16: 35.5), fp32 4 bits 43.2 (46.1), 64 x 32 fp32 41.0 (44.6)
 //   Quick      4 chunks x 8 workers 14.7 -> 14.4 us with the decoder, 2 chunks x 2 workers 13.0 -> 12.4
 constexpr int kFirstPollSleep = 32;
 constexpr int kFirstPollSleepPerGroup = 40;
@@ -257,7 +258,8 @@ struct EncodeAllCtx {
         if constexpr (WGWORD) {
             if (WORDS == Words::OneReader) polls = __builtin_amdgcn_readfirstlane((int)wave) == 0;
             if (polls) {
-                if (a.chunks <= kFewRounds * (uint64_t)dp) __builtin_amdgcn_s_sleep(kFirstPollSleepFewRounds);
+                constexpr int kFew = BF16 && BITS <= 4 ? kFirstPollSleepFewRounds : kFirstPollSleep;
+                if (a.chunks <= kFewRounds * (uint64_t)dp) __builtin_amdgcn_s_sleep(kFew);
                 else if (WORDS == Words::PerGroup) __builtin_amdgcn_s_sleep(kFirstPollSleepPerGroup);
                 else if (p < kLateRound * (uint64_t)dp) __builtin_amdgcn_s_sleep(kFirstPollSleep);
                 else __builtin_amdgcn_s_sleep(kFirstPollSleepLate);
@@ -803,6 +805,15 @@ uint32_t resident_grid() {
     return thc::resident_grid<kernel>(kThreads);
 }
 
+// More than 32 workers, dp chunks per round: one reader per workgroup, except for short items (bf16, up to 4 bits) in five to seven
+// rounds of an even number of chunks, where the late half of the grid is the other workgroup of every CU, so
+// that the two are half an item apart anyway and one wave's hand-over only adds to the item.  4 bits, every wave |
+// one reader, us: 64 workers x 40 chunks 37.3 | 40.6, x 56 52.6 | 53.3, x 64 61.8 | 60.0; 48 x 60 42.2 | 46.1, 40 x 72 42.7 | 46.5;
+// an odd number of chunks, 56 x 45 42.2 | 41.0, 44 x 66 48.6 | 46.9, 33 x 90 48.3 | 46.3; bf16 8 bits, 64 x 48 56.0 | 50.9.
+inline bool one_reader(const EncodeAllArgs& a, uint64_t dp, bool short_item) {
+    return !(short_item && (dp & 1u) == 0u && a.chunks > kFewRounds * dp && a.chunks < kLateRound * dp);
+}
+
 template <bool BF16, int BITS, bool ODD, bool BATCH>
 hipError_t launch_encode_all_t(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch,
                                hipStream_t stream) {
@@ -822,7 +833,7 @@ hipError_t launch_encode_all_t(const EncodeAllArgs& a, const FusedWorkerPtrs& pt
         return hipGetLastError();                                                                                     \
     } while (0)
     if constexpr (!BATCH) {
-        if (a.W > kPerGroupMaxWorkers) THC_ENCODE_ALL(Words::OneReader);
+        if (a.W > kPerGroupMaxWorkers && one_reader(a, G / a.W, BF16 && BITS <= 4)) THC_ENCODE_ALL(Words::OneReader);
         if (a.W > kPerWaveMaxWorkers) THC_ENCODE_ALL(Words::PerGroup);
         // every workgroup has one item, and a CU (each holds two) to itself
         if (G == total && 2u * G <= resident) THC_ENCODE_ALL(Words::Quick);

@@ -11,9 +11,9 @@ pytestmark = pytest.mark.gpu
 GRID = 512   # workgroups that are resident at once
 
 
-@pytest.mark.parametrize("W", [1, 2, 15, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("W", [1, 2, 15, 16, 17, 32, 33, 36, 64])
 @pytest.mark.parametrize("rounds,dtype,bits", [(0, torch.bfloat16, 4), (0, torch.float32, 8), (3, torch.bfloat16, 2),
-                                               (10, torch.bfloat16, 4), (10, torch.float32, 8)])
+                                               (3, torch.float32, 4), (6, torch.bfloat16, 4), (7, torch.bfloat16, 4), (10, torch.bfloat16, 4), (10, torch.float32, 8)])
 def test_agreement_matches_the_per_worker_calls(W, rounds, dtype, bits):
     per_round = GRID // W
     chunks = min(rounds * per_round + 1, 256) if W == 1 else rounds * per_round + 1
@@ -51,7 +51,8 @@ def _matches_the_per_worker_calls(xs, bits, scale, payloads):
 
 @pytest.mark.parametrize("W,rounds,dtype,bits", [
     (20, 3, torch.bfloat16, 4), (20, 10, torch.float32, 2),     # a word per workgroup, every wave reads
-    (64, 3, torch.bfloat16, 4), (64, 10, torch.float32, 8),     # one reader, early and late pause
+    (64, 3, torch.bfloat16, 4),                                 # the same beyond 32 workers
+    (64, 3, torch.float32, 4), (64, 10, torch.bfloat16, 8),     # one reader, few rounds and the late pause
     (2, 0, torch.bfloat16, 4), (8, 0, torch.float32, 8),        # one item per workgroup and CU
 ])
 def test_expired_wait_of_every_form_of_agreement(W, rounds, dtype, bits):
