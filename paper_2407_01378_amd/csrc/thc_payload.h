@@ -55,18 +55,24 @@ __device__ __forceinline__ PayloadWords<BITS> load_payload_words(const uint8_t* 
     return r;
 }
 
-// 8-bit payloads, `coords` of each of W workers, that outgrow the last-level cache (256 MB) beside the output are
-// read as for the last time.  line_mb: payloads of all workers in MiB; less for a decoder that also stores the sums.
-// Encoder and decoder, ordinary loads | last use, us:
-//   chunk 2^14, exact sums  8 workers x 17 M 144 | 153, x 25 M 220 | 220, x 34 M 294 | 292; 4 x 67 M 310 | 306; 16 x 17 M 304 | 297;
+// 8-bit payloads, `coords` of each of W workers, that are read as for the last time: those that outgrow the last-level
+// cache (256 MB) beside the output, and, by the decoders of chunks of 2^14, those of a pass that about fills it with its
+// gradients, where lines that are done with make room.  Encoder and decoder, three sets of buffers in turn, ordinary
+// loads | last use, us:
+//   chunk 2^14, exact sums  bf16, 8 workers: 22 MiB of payloads 34.1 | 33.8, 32 45.7 | 41.7, 40 58.0 | 54.6, 48 65.9 | 64.2, 58 75.3 | 74.2,
+//                           72 90.4 | 92.3; 32 workers 26 43.7 | 43.4, 32 53.0 | 48.3, 54 78.1 | 72.6; fp32, 8 workers 22 41.3 | 40.1, 32 54.5 | 53.0,
+//                           48 75.5 | 76.5, 54 85.4 | 88.4, 62 94.4 | 97.4
+//                           8 workers x 17 M 144 | 153, x 25 M 220 | 220, x 34 M 294 | 292; 4 x 67 M 310 | 306; 16 x 17 M 304 | 297;
 //                           batched 112 MB 128 | 136, 480 MB 670 | 654, 1048 MB 1127 | 1111
-//   saturating              8 x 21 M 186 | 190, x 25 M 221 | 221, x 34 M 294 | 292, x 67 M 580 | 567
-//   small chunks            8 x 17 M 147 | 154, x 21 M 193 | 193, x 25 M 230 | 227, x 34 M 304 | 301
+//   saturating              8 workers, 32 MiB 45.4 | 42.0, 48 67.3 | 64.0; x 21 M 186 | 190, x 25 M 221 | 221, x 34 M 294 | 292, x 67 M 580 | 567
+//   min/max                 8 workers, 32 MiB 48.4 | 45.2, 48 70.0 | 69.6
+//   small chunks            8 workers x 6 M 62 | 67, x 17 M 147 | 154, x 21 M 193 | 193, x 25 M 230 | 227, x 34 M 304 | 301 (it also stores the sums)
 // Up to 8 M coordinates (more than 28 workers) ordinary loads hold longer: 64 x 5 M 375 | 387 us, 64 x 8 M 609 | 612, 32 x
 // 8 M 333 | 336, saturating 378 | 390, 595 | 599 and 332 | 337, small chunks 32 x 8 M 330 | 335; 32 x 9 M 391 | 388, 390 | 383.
-constexpr uint64_t kStreamLineMb = 224, kStreamLineMbWithSums = 176;
-inline bool stream_payloads(uint32_t W, uint64_t coords, uint64_t line_mb = kStreamLineMb) {
-    return W * coords > line_mb << 20 && coords > 8ull << 20;
+inline bool stream_payloads(uint32_t W, uint64_t coords, bool small_chunks = false) {
+    const uint64_t bytes = W * coords;
+    if (!small_chunks && bytes > 20ull << 20 && bytes <= 52ull << 20) return true;
+    return bytes > (small_chunks ? 176ull : 224ull) << 20 && coords > 8ull << 20;
 }
 
 // The workers' payload words of one thread (its 32 coordinates) on their way into registers, group by

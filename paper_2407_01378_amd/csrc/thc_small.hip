@@ -595,7 +595,7 @@ static hipError_t small_decode(k14::SmallDecodeArgs& a, const FusedPayloadPtrs& 
         if (wide) THC_SMALL_DECODE(0, 4, true);
         else if (bits == 2) THC_SMALL_DECODE(0, 2, false);
         else if (bits == 4) THC_SMALL_DECODE(0, 4, false);
-        else if (stream_payloads(a.W, a.padded, kStreamLineMbWithSums)) THC_SMALL_DECODE(0, 8, false, true);
+        else if (stream_payloads(a.W, a.padded, true)) THC_SMALL_DECODE(0, 8, false, true);
         else THC_SMALL_DECODE(0, 8, false);
     } else if (src == 1) {
         if (bits == 2) THC_SMALL_DECODE(1, 2, false);

@@ -177,7 +177,9 @@ def test_8_bit_payloads_around_the_size_of_the_last_level_cache(chunks):
     assert torch.equal(many, want)
 
 
-@pytest.mark.parametrize("form,l,chunks", [   # 16 workers: the last size read by ordinary loads, the first as for the last time
+@pytest.mark.parametrize("form,l,chunks", [   # 16 workers: both sides of 20, 52 and 224 MiB, of 176 for small chunks
+    ("exact", 14, 80), ("exact", 14, 81), ("exact", 14, 208), ("exact", 14, 209), ("sat", 14, 81), ("sat", 14, 209),
+    ("sat counted", 14, 208),
     ("exact", 14, 896), ("exact", 14, 897), ("sat", 14, 896), ("sat", 14, 897), ("sat counted", 14, 897),
     ("exact", 12, 2816), ("exact", 12, 2817), ("exact", 5, 360449),
 ])
