@@ -181,7 +181,9 @@ hipError_t launch_sat_aggregate(const FusedPayloadPtrs& ptrs, uint32_t W, uint32
 // Stages of the first pass over n coordinates of 2^log2_size: chunks of 2^14, or of 2^15 where 11 stages would
 // be left behind them (a pass of 11 moves 64-byte pieces).  A device holds 512 chunks of 2^15 at
 // once, and a few more than that take as long as 1024: with less than 9/16 of 2^25 to read the chunks stay
-// at 2^14 (eight workers x 17 M fp32: 762 us so, 769 us with 2^15; x 25.6 M: 1021 and 934 us).
+// at 2^14 (eight workers x 17 M fp32: 762 us so, 769 us with 2^15; x 25.6 M: 1021 and 934 us).  2^26: chunks of 2^15 would
+// turn two passes of 6 stages into one of 11, which is slower forward for long gradients (first pass, range and payload of
+// 67 M fp32 277 and 291 us, bf16 250 and 266; 33.6 M 158 and 147).
 // All forward calls for one gradient agree on it; the inverse direction reads the whole array (n = 2^log2_size).
 inline uint32_t full_first_log2(uint64_t n, uint32_t log2_size) {
     return log2_size == 25u && n > 9ull << 21 ? 15u : 14u;
