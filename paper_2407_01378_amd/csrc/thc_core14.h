@@ -696,7 +696,7 @@ __device__ __forceinline__ void store_signed_l4d(const SignTable& tab, const flo
             if (SIGNED) x[e] = __uint_as_float(xor_masked(__float_as_uint(x[e]), sb << (31 - e), 0x80000000u));
         }
         const u32x4_vec q = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
-        __builtin_amdgcn_raw_buffer_store_b128(q, rsrc, i0 * 4u, 0, kStreamingStore);
+        __builtin_amdgcn_raw_buffer_store_b128(q, rsrc, i0 * 4u, 0, kStreaming);
     }
 }
 

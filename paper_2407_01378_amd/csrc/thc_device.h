@@ -120,7 +120,7 @@ __device__ __forceinline__ uint2 load_last_use(const uint2* p) {
     const u32x2_vec q = __builtin_nontemporal_load(reinterpret_cast<const u32x2_vec*>(p));
     return make_uint2(q.x, q.y);
 }
-constexpr int kStreamingStore = 2;   // the cache policy of such a store through a buffer descriptor (nt)
+constexpr int kStreaming = 2;   // the cache policy of such an access through a buffer descriptor (nt)
 __device__ __forceinline__ void store_streaming(float* p, float a, float b, float c, float d) {
     const f32x4_vec q = {a, b, c, d};
     __builtin_nontemporal_store(q, reinterpret_cast<f32x4_vec*>(p));

@@ -57,6 +57,12 @@ constexpr uint32_t kFewRounds = 4;
 constexpr int kFirstPollSleepQuick = 8;
 constexpr int kPollSleep = 8;
 constexpr int kPollSleepOneReader = 4;
+// fp32 gradients of all workers that do not fit the last-level cache (256 MB, and a quarter more, because part of them is
+// still there) are read as for the last time: 64 KB per item.  A pass over 8 workers with one | two | three sets of
+// gradients in turn, us, ordinary loads -> these: 134 MB 43.2 -> 47.4 | 44.0 -> 46.6 | 49.1 -> 47.4, 268 MB 77.1 -> 81.0 |
+// 83.7 -> 80.9 | 83.9 -> 81.8, 336 MB 99.6 -> 99.7 | 101.7 -> 99.0; 818 MB 238 -> 228; 64 workers, 537 MB 183 -> 162.  A
+// thread of bf16 input loads its own 64 bytes, four times from the same lines, and needs the caches for it.
+constexpr uint64_t kStreamedItems = (320ull << 20) >> 16;
 // ------------------------------------------------------------------ encode_all
 __device__ __forceinline__ ConstRecordPtr batch_record(const BatchArgs& batch, uint32_t k) {
     return (ConstRecordPtr)(batch.records + (uint64_t)k * batch.record_bytes);
@@ -161,14 +167,18 @@ struct EncodeAllCtx {
             const uint32_t bytes = (uint32_t)left * kElem;   // a multiple of 4: the count is even
             __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                 reinterpret_cast<void*>(addr), 0, bytes, 0x00020000);
-            typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+            auto units = [&](auto policy) {
+                typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 #pragma unroll
-            for (int j = 0; j < kUnits; ++j) {
-                // fp32: the wave's own 8 KB in coalesced order, dealt out through its part of the buffer
-                const uint32_t unit = kDirect ? kUnits * tp + j : wave * 512u + j * 64u + lane;
-                const u4v q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, unit * 16u, 0, 0);
-                raw.u[j] = make_uint4(q.x, q.y, q.z, q.w);
-            }
+                for (int j = 0; j < kUnits; ++j) {
+                    // fp32: the wave's own 8 KB in coalesced order, dealt out through its part of the buffer
+                    const uint32_t unit = kDirect ? kUnits * tp + j : wave * 512u + j * 64u + lane;
+                    const u4v q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, unit * 16u, 0, decltype(policy)::value);
+                    raw.u[j] = make_uint4(q.x, q.y, q.z, q.w);
+                }
+            };
+            if (!kDirect && a.chunks * a.W > kStreamedItems) units(std::integral_constant<int, kStreaming>{});
+            else units(std::integral_constant<int, 0>{});
         }
     }
     __device__ __forceinline__ void fill_signs(uint64_t p, const BucketView& bv, uint32_t which) {

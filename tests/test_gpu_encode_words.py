@@ -49,6 +49,19 @@ def _matches_the_per_worker_calls(xs, bits, scale, payloads):
         assert torch.equal(payloads[w], ref), w
 
 
+@pytest.mark.parametrize("W,chunks", [(8, 640), (8, 641), (64, 81)])
+def test_streamed_fp32_gradients_match_the_per_worker_calls(W, chunks):
+    """fp32 gradients of more than 5120 chunks in all are read as for the last time: both sides of the line, ragged."""
+    n, bits = (chunks << 14) - 4321, 4
+    xs = [torch.randn(n, generator=torch.Generator(device="cuda").manual_seed(w), device="cuda") for w in range(W)]
+    P, nb = thc.thc_num_chunks(n, 14), thc.thc_payload_bytes(n, 14, bits)
+    ws = torch.empty(thc.thc_encode_all_workspace_bytes(W, n, 14), dtype=torch.uint8, device="cuda")
+    scale = torch.full((P,), float("nan"), device="cuda")
+    payloads = [torch.full((nb,), 0xAA, dtype=torch.uint8, device="cuda") for _ in range(W)]
+    thc.thc_encode_all(xs, 14, 7, bits, payloads, scale, ws)
+    _matches_the_per_worker_calls(xs, bits, scale, payloads)
+
+
 @pytest.mark.parametrize("W,rounds,dtype,bits", [
     (20, 3, torch.bfloat16, 4), (20, 10, torch.float32, 2),     # a word per workgroup, every wave reads
     (64, 3, torch.bfloat16, 4),                                 # the same beyond 32 workers
