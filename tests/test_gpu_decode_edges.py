@@ -234,3 +234,25 @@ def test_small_chunk_decoder_in_workgroups_of_every_width(W, l, bits):
         whole = 0 if before is None else before.numel() >> l << l
         assert whole == 0 or torch.equal(out[:whole], before[:whole]), groups
         before = out
+
+
+@pytest.mark.parametrize("bits,W", [(4, 8), (4, 13), (2, 9), (8, 5), (4, 18), (4, 24), (4, 25), (4, 64), (8, 64)])
+@pytest.mark.parametrize("per_cu,more", [(1, 0), (1, 1), (2, 0), (2, 1)])
+def test_one_chunk_per_workgroup_and_more(W, bits, per_cu, more):
+    """Both sides of the lines up to which every chunk has a workgroup of its own (one or two per CU), the last chunk
+    ragged, with and without the sums: against thc_aggregate + thc_decode."""
+    l, seed = 14, 9
+    chunks = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + more
+    n = (chunks << l) - 12345
+    gen = torch.Generator(device="cuda").manual_seed(W)
+    flat = torch.randint(0, 256, (W, thc.thc_payload_bytes(n, l, bits)), dtype=torch.uint8, generator=gen, device="cuda")
+    payloads = list(flat.unbind(0))
+    scale = torch.rand(chunks, generator=gen, device="cuda") + 0.5
+    dtype = torch.uint8 if thc.thc_sum_bytes(W, bits) == 1 else torch.int16
+    want_sums, sums = (torch.empty(chunks << l, dtype=dtype, device="cuda") for _ in range(2))
+    want, out, plain = (torch.empty(n, device="cuda") for _ in range(3))
+    thc.thc_aggregate(payloads, n, l, bits, want_sums)
+    thc.thc_decode(want_sums, scale, W, n, l, seed, bits, want)
+    thc.thc_aggregate_decode(payloads, scale, n, l, seed, bits, sums, out)
+    thc.thc_aggregate_decode(payloads, scale, n, l, seed, bits, None, plain)
+    assert torch.equal(sums, want_sums) and torch.equal(out, want) and torch.equal(plain, want)
