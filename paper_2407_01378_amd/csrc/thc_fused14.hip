@@ -600,30 +600,27 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_kern
     }
 }
 
-// The same for a launch of at most one chunk per workgroup.  Bound by one chunk's chain, so the payload loads come
-// first, two to four times as many in flight as above (there is no next chunk to keep registers for; sums of many
-// workers take 239 and have a CU to themselves), and the scale and the sign table meanwhile.  A pass with
-// the encoder, 4 bits, us, kernel above -> this: 8 workers x 50257 14.35 -> 13.46, x 2^19 14.9 -> 14.0, x 2^21 25.1 -> 24.1;
-// 2 x 2^21 14.6 -> 13.8; 16 x 2^14 14.5 -> 13.3; 64 workers x 2^15 25.3 -> 20.4, x 2^18 35.5 -> 31.5 (with groups of 8 21.1
-// and 32.5); 8 bits, 8 x 2^21 28.5 -> 27.4, 64 x 2^21 162 -> 157.
+// The same for a launch of at most one chunk per workgroup: one chunk's chain.  There is no next chunk to keep registers
+// for, so the payloads are summed without a condition inside the loop (all_alone), and the scale is read in front of
+// them.  A pass with the encoder, 4 bits, us, kernel above -> this: 2 workers x 50257 13.4 -> 12.1, 8 x 50257 14.3 -> 13.4,
+// 8 x 2^19 14.9 -> 14.0, 8 x 2^21 25.1 -> 24.2, 16 x 50257 15.7 -> 14.0, 64 x 50257 26.5 -> 22.0, 64 x 2^21 132.5 -> 129.5;
+// 8 bits, 8 x 2^20 23.2 -> 22.0, 64 x 2^20 92.6 -> 85.5; 2 bits, 64 x 2^18 34.9 -> 28.5.  (All payloads of 8 or 16 workers in
+// flight, with the sign table computed meanwhile, was 2 % slower; only the sign table, no difference.)
 template <int BITS, bool RANGED, bool WIDE, bool ONCE>
-__global__ __launch_bounds__(kThreads, WIDE ? 2 : kWavesPerSimd) void aggregate_decode_one_kernel(const AggDecodeArgs a,
+__global__ __launch_bounds__(kThreads, kWavesPerSimd) void aggregate_decode_one_kernel(const AggDecodeArgs a,
                                                                            const FusedPayloadPtrs ptrs) {
     __shared__ Shared sh;
-    using Sum = PayloadSum<BITS, false, WIDE, ONCE, BITS == 8 ? 4 : WIDE ? 16 : 8>;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint32_t block = lay14::block_of_lane(lane), tp = (t & ~63u) | block;   // the thread's 32 coordinates
     const uint64_t p = blockIdx.x, g0 = p << kChunkLog2, left = a.n - g0;
     const uint32_t valid = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
-    const uint64_t base = (g0 * BITS) / 8u;
-    const uint32_t offset = tp * (4u * BITS);
-    Sum sum{ptrs, nullptr, a.W};
-    sum.burst_begin(base, offset);
     const float s = RANGED ? -a.scale[2 * p] : a.scale[p];
     const float step = (RANGED ? a.scale[2 * p + 1] + s : s + s) / (float)((1u << BITS) - 1u);
     const float qf = step / (float)a.W;
+    PayloadSum<BITS, false, WIDE, ONCE> sum{ptrs, nullptr, a.W};
+    sum.clear();
+    sum.all_alone((g0 * BITS) / 8u + tp * (4u * BITS));
     fill_sign_table<true, false>(sh.sign[0], g0, a.key0, a.key1, t);
-    sum.burst_end(base, offset);
     float v[kRegs];
     uint32_t S[kRegs];
     sum.unpack(S);
@@ -915,8 +912,8 @@ hipError_t launch_aggregate_decode_t(const AggDecodeArgs& a, const FusedPayloadP
                                         hipStream_t stream) {
     uint32_t G = resident_grid<aggregate_decode_kernel<BITS, BATCH, RANGED, WIDE, ONCE>>();
     if (G == 0) return hipErrorInvalidValue;
-    if constexpr (!BATCH) {   // every chunk has a workgroup of its own at once (two per CU, one for the sums of many workers)
-        if (a.chunks <= resident_grid<aggregate_decode_one_kernel<BITS, RANGED, WIDE, ONCE>>()) {
+    if constexpr (!BATCH) {   // every chunk has a workgroup of its own (one round)
+        if (a.chunks <= G) {
             hipLaunchKernelGGL((aggregate_decode_one_kernel<BITS, RANGED, WIDE, ONCE>), dim3((uint32_t)a.chunks),
                                dim3(kThreads), 0, stream, a, ptrs);
             return hipGetLastError();

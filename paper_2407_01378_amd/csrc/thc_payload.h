@@ -142,10 +142,10 @@ struct PayloadLoads {
 // WIDE: 16-bit accumulators for 4-bit payloads too (W * L > 255: more than 17 workers); lane q
 // then holds coordinates q (low half) and q + 4 (high half) of the dword's 8.  The workers
 // meet in 8-bit lanes first, kFlush groups of them (16 * 15 <= 255), which takes half the operations.
-template <int BITS, bool BATCH = false, bool WIDE = false, bool ONCE = BITS != 8, int GROUP = BITS == 8 ? 2 : 4>
-struct PayloadSum : PayloadLoads<BITS, BATCH, GROUP, ONCE> {
+template <int BITS, bool BATCH = false, bool WIDE = false, bool ONCE = BITS != 8>
+struct PayloadSum : PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE> {
     static_assert(!(WIDE && BITS != 4), "8-bit payloads always sum in 16-bit lanes, 2-bit ones in 8-bit lanes");
-    using Loads = PayloadLoads<BITS, BATCH, GROUP, ONCE>;
+    using Loads = PayloadLoads<BITS, BATCH, BITS == 8 ? 2 : 4, ONCE>;
     using Loads::groups;
     using Loads::kGroup;
     using Loads::kOneAhead;
@@ -249,7 +249,7 @@ struct PayloadSum : PayloadLoads<BITS, BATCH, GROUP, ONCE> {
     // first worker of a part of a group before it loads the second), and less code to fetch for few workers.
     // Small-chunk decoder, `all` | this, 2^10 coordinates per chunk, us: 64 workers x 2^20 at 8 bits 22.7 | 18.0,
     // at 4 bits 15.6 | 13.5, at 2 bits 14.4 | 9.4; 8 workers 6.9 | 6.5, 5.7 | 5.5, 5.7 | 5.4; 1 worker at 2 bits 6.2 | 6.0.
-    // (The decoder of chunks of 2^14 has no registers left for it.)
+    // (The decoder of chunks of 2^14 has no registers left for it where it prepares a next chunk.)
     __device__ __forceinline__ void all_alone(uint64_t byte0) {
         const uint32_t whole = W / kGroup, more = W % kGroup;
         PayloadWords<BITS> y[kGroup - 1u];
@@ -282,39 +282,6 @@ struct PayloadSum : PayloadLoads<BITS, BATCH, GROUP, ONCE> {
         for (uint32_t j = 0; j + 1u < kGroup; ++j)
             if (j < more) add_one(y[j]);
         flush();   // (at most three whole groups and three workers since the last time: 15 * 15 <= 255)
-    }
-
-    // For a kernel of one item: the first two groups on their way, then (burst_end) their sum and that of the others.
-    // base: the same for every lane, so that an address is a pair of scalar registers and the lane's 32-bit offset.
-    __device__ __forceinline__ void burst_begin(uint64_t base, uint32_t offset) {
-        issue_filled<0>(base, offset, 0u);
-        if (W > kGroup) issue_filled<1>(base, offset, 1u);
-    }
-    __device__ __forceinline__ void burst_end(uint64_t base, uint32_t offset) {
-        clear();
-        clear_wide();
-        const uint32_t n = groups();
-        for (uint32_t g = 0; g < n; g += 2u) {
-            add<0>(g);
-            flush(g);
-            if (g + 2u < n) issue_filled<0>(base, offset, g + 2u);
-            if (g + 1u < n) {
-                add<1>(g + 1u);
-                flush(g + 1u);
-                if (g + 3u < n) issue_filled<1>(base, offset, g + 3u);
-            }
-        }
-    }
-    // A group's loads without a condition per worker: beyond the last worker its payload is read once more (from a cache),
-    // but a group of 16 of which half is there reads only that half.
-    template <int B>
-    __device__ __forceinline__ void issue_filled(uint64_t base, uint32_t offset, uint32_t group) {
-#pragma unroll
-        for (uint32_t j = 0; j < kGroup; ++j) {
-            const uint32_t w = group * kGroup + j;
-            if (j == 8u && w >= W) break;
-            x[B][j] = load_payload_words<BITS, ONCE>(this->pointer(w < W ? w : W - 1u) + base + offset);
-        }
     }
 
     // Sub-word lanes -> one sum per coordinate.

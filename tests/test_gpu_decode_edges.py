@@ -239,7 +239,7 @@ def test_small_chunk_decoder_in_workgroups_of_every_width(W, l, bits):
 @pytest.mark.parametrize("bits,W", [(4, 8), (4, 13), (2, 9), (8, 5), (4, 18), (4, 24), (4, 25), (4, 64), (8, 64)])
 @pytest.mark.parametrize("per_cu,more", [(1, 0), (1, 1), (2, 0), (2, 1)])
 def test_one_chunk_per_workgroup_and_more(W, bits, per_cu, more):
-    """Both sides of the lines up to which every chunk has a workgroup of its own (one or two per CU), the last chunk
+    """One and two workgroups per CU and one more (two are resident): up to there every chunk has its own; the last chunk
     ragged, with and without the sums: against thc_aggregate + thc_decode."""
     l, seed = 14, 9
     chunks = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + more
