@@ -506,26 +506,36 @@ __global__ __launch_bounds__(256) void scatter_kernel(const uint16_t* values, co
 // sees them all.  `out` must be 16-byte aligned.
 constexpr int kScatterThreads = 256;
 constexpr int kTileChunks = kScatterThreads;
+// Workgroups wanted, where the output has that many pieces of one 16-byte unit per thread: 2^20 coordinates, C = 64, as 64
+// tiles 10.9 us of kernel, as 1024 pieces 4 (512 and 2048 pieces: the round 2 % slower for 2^17 .. 2^19 coordinates, the
+// same above).
+constexpr uint64_t kScatterGroups = 1024;
 __global__ __launch_bounds__(kScatterThreads) void scatter_dense_kernel(
     const uint16_t* values, const uint32_t* indices, uint32_t J, uint32_t C, uint32_t W, uint64_t n, uint64_t P,
     uint64_t chunks_per_group, float* out) {
     __shared__ int32_t rank[kTileChunks];
-    __shared__ uint32_t first;
     const uint32_t t = threadIdx.x;
     const uint64_t begin = (uint64_t)blockIdx.x * chunks_per_group;
     if (begin >= P) return;
     const uint64_t end = begin + chunks_per_group < P ? begin + chunks_per_group : P;
-    if (t == 0) {   // first j with indices[j] >= begin
-        uint32_t lo = 0, hi = J;
-        while (lo < hi) {
-            const uint32_t mid = lo + (hi - lo) / 2u;
-            if ((uint64_t)indices[mid] < begin) lo = mid + 1u;
-            else hi = mid;
+    // first j with indices[j] >= begin: 256 positions at a time cut what is left to 1/256 (a halving search is a chain of 18
+    // dependent reads for a quarter million of indices)
+    uint32_t lo = 0, hi = J;   // indices[lo - 1] < begin <= indices[hi]
+    while (lo < hi) {
+        const uint32_t step = (hi - lo + kScatterThreads - 1u) / kScatterThreads;   // (the last step ends at hi or behind it)
+        const uint32_t at = lo + t * step;
+        const bool below = at < hi && (uint64_t)indices[at] < begin;
+        const uint32_t count = (uint32_t)__syncthreads_count(below);   // the first `count` probes are below
+        if (count != 0u) {
+            const uint32_t last = lo + (count - 1u) * step;
+            const uint32_t end_at = last + step;
+            lo = last + 1u;
+            hi = end_at < hi ? end_at : hi;
+        } else {
+            hi = lo;
         }
-        first = lo;
     }
-    __syncthreads();
-    uint32_t j = first;
+    uint32_t j = lo;
     const float Wf = (float)W;
     const uint32_t units_per_chunk = C / 4u;            // 16-byte units of fp32 output per chunk
     const uint32_t shift = 31u - (uint32_t)__builtin_clz(units_per_chunk);
@@ -645,11 +655,12 @@ hipError_t launch_topkc_scatter(const uint16_t* values, const uint32_t* indices,
     const uint64_t P = (n + C - 1) / C;
     if (P == 0) return hipSuccess;
     if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
-        // one pass: contiguous ranges of whole tiles
+        // one pass: contiguous ranges of whole tiles, or of parts of one where the tiles are few
         const uint64_t tiles = (P + kTileChunks - 1) / kTileChunks;
         uint64_t groups = 16384u;   // (5.2 GB written: 2048 groups 1.37 ms, 4096 1.20, 16384 1.12, 32768 1.11)
         if (groups > tiles) groups = tiles;
-        const uint64_t chunks_per_group = (tiles + groups - 1) / groups * kTileChunks;
+        uint64_t chunks_per_group = (tiles + groups - 1) / groups * kTileChunks;
+        while (chunks_per_group > 1024u / C && P / chunks_per_group < kScatterGroups) chunks_per_group >>= 1;
         groups = (P + chunks_per_group - 1) / chunks_per_group;
         hipLaunchKernelGGL(scatter_dense_kernel, dim3((uint32_t)groups), dim3(kScatterThreads), 0, stream, values,
                            indices, J, C, W, n, P, chunks_per_group, out);

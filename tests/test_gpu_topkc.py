@@ -283,3 +283,18 @@ def test_topkc_select_on_unaligned_and_ragged_key_arrays(offset, P, J):
     torch.cuda.synchronize()
     ref = K.select(s.cpu().numpy(), J)
     assert (idx.cpu().numpy().view(np.uint32) == ref).all()
+
+
+@pytest.mark.parametrize("P,J,C", [(3, 1, 512), (70, 70, 8), (2048, 500, 64), (300_000, 66_049, 8), (300_000, 131_071, 8),
+                                   (300_000, 300_000, 8)])
+def test_topkc_scatter_finds_the_first_chunk_of_every_group(P, J, C):
+    """Outputs of less than a tile per workgroup up to many, lists of one, two and three steps of the search."""
+    n, W = P * C - 3, 3
+    rng = np.random.default_rng(J)
+    indices = np.sort(rng.choice(P, J, replace=False)).astype(np.uint32)
+    values = rng.standard_normal((J, C)).astype(np.float16)
+    out = torch.full((n + 16,), 7.0, device=DEV)
+    thc.topkc_scatter_mean(torch.from_numpy(values).to(DEV).view(-1), torch.from_numpy(indices.view(np.int32)).to(DEV), J, C, W,
+                           out[:n])
+    assert (out[:n].cpu().numpy() == K.scatter_mean(values, indices, C, W, n)).all()
+    assert bool((out[n:] == 7.0).all())
