@@ -452,6 +452,118 @@ __global__ __launch_bounds__(256) void write_indices_kernel(const uint16_t* s, u
     }
 }
 
+// All of the selection in one workgroup: thread t holds keys 8 G t .. 8 G t + 8 G - 1 in registers, both histograms and
+// the scan lie in LDS, and nothing goes through the workspace.  For few keys the selection is five launches' time, 15 us
+// and more where the host issues them one by one; for many, one CU's LDS atomics.  A round of 8 workers, C = 64 and 32, five launches |
+// this, us: 2048 and 4096 keys 60.8 | 44.4, 63.4 | 42.8, 16384 57.6 | 47.1, 32768 62.5 | 54.9 and 62.8 | 52.6, 65536 63.6 | 71.8,
+// which is where the line comes from.
+constexpr uint32_t kOneThreads = 1024;
+constexpr uint64_t kOneKeys = 32768;
+template <int G>
+__global__ __launch_bounds__(kOneThreads) void select_one_kernel(const uint16_t* s, uint32_t P, uint32_t J,
+                                                                 uint32_t* indices) {
+    __shared__ uint32_t copies[kCopies * 257u];
+    __shared__ uint32_t hist[256];
+    __shared__ uint32_t wave_tot[2][kOneThreads / 64u];
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    const uint32_t first = t * (8u * G);
+    const bool vec = (reinterpret_cast<uintptr_t>(s) & 15u) == 0;
+    uint32_t w[G][4];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const uint32_t p = first + 8u * g;
+        if (vec && p + 8u <= P) {
+            const uint4 q = *reinterpret_cast<const uint4*>(s + p);
+            w[g][0] = q.x; w[g][1] = q.y; w[g][2] = q.z; w[g][3] = q.w;
+        } else {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t lo = p + 2 * d < P ? s[p + 2 * d] : 0u;
+                const uint32_t hi = p + 2 * d + 1 < P ? s[p + 2 * d + 1] : 0u;
+                w[g][d] = lo | (hi << 16);
+            }
+        }
+    }
+    const uint32_t mine = first < P ? (P - first < 8u * G ? P - first : 8u * G) : 0u;   // keys of this thread
+    auto key_of = [&](int g, int e) { return (w[g][e >> 1] >> (16 * (e & 1))) & 0xFFFFu; };
+    uint32_t want = J, bucket = 0u, T = 0u;
+    uint32_t* h = copies + (t & (kCopies - 1u)) * 257u;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        for (uint32_t i = t; i < kCopies * 257u; i += kOneThreads) copies[i] = 0u;
+        __syncthreads();
+        int cur = -1;
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t key = key_of(g, e);
+                int b = pass == 0 ? (int)(key >> 8) : (key >> 8) == bucket ? (int)(key & 255u) : -1;
+                if (8u * g + e >= mine) b = -1;
+                if (b != cur) {
+                    if (cur >= 0) atomicAdd(&h[cur], cnt);
+                    cur = b;
+                    cnt = 1u;
+                } else {
+                    ++cnt;
+                }
+            }
+        if (cur >= 0) atomicAdd(&h[cur], cnt);
+        __syncthreads();
+        if (t < 256u) {
+            uint32_t c = 0u;
+#pragma unroll
+            for (uint32_t i = 0; i < kCopies; ++i) c += copies[i * 257u + t];
+            hist[t] = c;
+        }
+        __syncthreads();
+        const Found f = find_bin(hist, want);
+        want -= f.above;   // keys still to take in the bin (>= 1)
+        if (pass == 0) bucket = f.bin;
+        else T = (bucket << 8) | f.bin;
+    }
+    uint32_t above = 0, equal = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (8u * g + e < mine) {
+                above += key_of(g, e) > T ? 1u : 0u;
+                equal += key_of(g, e) == T ? 1u : 0u;
+            }
+    uint32_t ia = above, ie = equal;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t ya = __shfl_up(ia, o, 64), ye = __shfl_up(ie, o, 64);
+        if (lane >= (uint32_t)o) {
+            ia += ya;
+            ie += ye;
+        }
+    }
+    if (lane == 63u) {
+        wave_tot[0][wave] = ia;
+        wave_tot[1][wave] = ie;
+    }
+    __syncthreads();
+    uint32_t above_before = ia - above, equal_before = ie - equal;
+    for (uint32_t v = 0; v < wave; ++v) {
+        above_before += wave_tot[0][v];
+        equal_before += wave_tot[1][v];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (8u * g + e < mine) {
+                const uint32_t key = key_of(g, e);
+                if (key > T || (key == T && equal_before < want))
+                    indices[above_before + min(equal_before, want)] = first + 8u * g + e;
+                above_before += key > T ? 1u : 0u;
+                equal_before += key == T ? 1u : 0u;
+            }
+}
+
 // ---- selected chunks --------------------------------------------------------------------------
 // values[j * C + e] = fp16 sum over workers, in worker order, of fp16(x_w[indices[j] * C + e]).
 template <bool BF16>
@@ -630,6 +742,13 @@ static void select_kernels(const uint16_t* s, uint64_t P, uint32_t J, uint32_t* 
 
 hipError_t launch_topkc_select(const uint16_t* s, uint64_t P, uint32_t J, uint32_t* indices, uint32_t* ws,
                                hipStream_t stream) {
+    if (P <= kOneKeys) {
+        const dim3 grid(1), block(kOneThreads);
+        if (P <= 8u * kOneThreads) hipLaunchKernelGGL(select_one_kernel<1>, grid, block, 0, stream, s, (uint32_t)P, J, indices);
+        else if (P <= 16u * kOneThreads) hipLaunchKernelGGL(select_one_kernel<2>, grid, block, 0, stream, s, (uint32_t)P, J, indices);
+        else hipLaunchKernelGGL(select_one_kernel<4>, grid, block, 0, stream, s, (uint32_t)P, J, indices);
+        return hipGetLastError();
+    }
     const uint32_t segments = (uint32_t)((P + kSegment - 1) / kSegment);
     hipError_t e = launch_zero_words(ws, kHdr, stream);
     if (e != hipSuccess) return e;

@@ -285,6 +285,26 @@ def test_topkc_select_on_unaligned_and_ragged_key_arrays(offset, P, J):
     assert (idx.cpu().numpy().view(np.uint32) == ref).all()
 
 
+@pytest.mark.parametrize("P", [1, 9, 1024, 8191, 8192, 8193, 16385, 32767, 32768, 32769])
+@pytest.mark.parametrize("values", [3, 65536])   # many equal keys; nearly none
+@pytest.mark.parametrize("offset", [0, 1])
+def test_topkc_select_of_one_workgroup_and_more(P, values, offset):
+    """The edges of the key counts that one workgroup takes (8, 16 and 32 keys per thread) and the first beyond."""
+    rng = np.random.default_rng(P + values)
+    keys = (rng.integers(0, values, P) if values > 3 else rng.choice([0, 0x1234, 0x12FF], P)).astype(np.uint16)
+    whole = torch.zeros(P + 8, dtype=torch.int16, device=DEV)
+    s = whole[offset:offset + P].view(torch.float16)
+    s.view(torch.int16).copy_(torch.from_numpy(keys.view(np.int16)))
+    order = np.argsort(-keys.astype(np.int64), kind="stable")
+    for J in sorted({1, P // 3 + 1, P}):
+        idx = torch.full((J + 8,), -1, dtype=torch.int32, device=DEV)
+        ws = torch.full((thc.topkc_select_workspace_bytes(P),), 0xFF, dtype=torch.uint8, device=DEV)
+        thc.topkc_select(s, J, idx[:J], ws)
+        got = idx.cpu().numpy()
+        assert (got[J:] == -1).all()
+        assert (got[:J] == np.sort(order[:J])).all(), J
+
+
 @pytest.mark.parametrize("P,J,C", [(3, 1, 512), (70, 70, 8), (2048, 500, 64), (300_000, 66_049, 8), (300_000, 131_071, 8),
                                    (300_000, 300_000, 8)])
 def test_topkc_scatter_finds_the_first_chunk_of_every_group(P, J, C):
