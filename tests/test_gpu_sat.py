@@ -254,3 +254,41 @@ def test_sat_coordinates_beyond_2_to_32():
     a, b = results
     assert a["overflow"] == b["overflow"]
     assert torch.equal(a["aggregate"], b["aggregate"]) and torch.equal(a["out"], b["out"])
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 8, 13, 64])
+def test_sat_sums_of_any_payload_bytes(W, bits):
+    """Every index a payload can hold, the one beyond the grid's largest among them: aggregate, overflow count and estimate
+    against the definition, worker after worker (small steps, large steps of one sign, both signs)."""
+    l, seed, n = 14, 3, 2 * (1 << 14) + 77
+    M = (1 << (bits - 1)) - 1
+    P, count = thc.thc_num_chunks(n, l), thc.thc_payload_bytes(n, l, bits)
+    rng = np.random.default_rng(W * 10 + bits)
+    raw = rng.integers(0, 256, (W, count), dtype=np.uint8)
+    raw[:, : count // 8] = 0                       # the lowest index, always
+    raw[:, count // 8: count // 4] = 255           # the highest, always
+    raw[::2, count // 4: count // 2] = 0           # in turn
+    raw[1::2, count // 4: count // 2] = 255
+    per = 8 // bits
+    a = np.zeros((count, per), np.int64)
+    clipped = np.zeros((count, per), bool)
+    for r in raw:
+        for k in range(per):
+            t = a[:, k] + ((r >> (bits * k)) & ((1 << bits) - 1)).astype(np.int64) - M
+            a[:, k] = np.clip(t, -M, M)
+            clipped[:, k] |= t != a[:, k]
+    want = np.zeros(count, np.int64)
+    for k in range(per):
+        want |= (a[:, k] + M) << (bits * k)
+    payloads = [torch.from_numpy(r.copy()).to(DEV) for r in raw]
+    scale = torch.rand(P, device=DEV) + 0.5
+    aggregate = torch.empty(count, dtype=torch.uint8, device=DEV)
+    overflow = torch.zeros(1, dtype=torch.int64, device=DEV)
+    out, plain, ref = (torch.empty(n, device=DEV) for _ in range(3))
+    thc.thc_sat_aggregate_decode(payloads, scale, n, l, seed, bits, aggregate, overflow, out)
+    thc.thc_sat_aggregate_decode(payloads, scale, n, l, seed, bits, None, None, plain)
+    assert (aggregate.cpu().numpy() == want).all()
+    assert int(overflow) == int(clipped.sum())
+    thc.thc_sat_decode(aggregate, scale, W, n, l, seed, bits, ref)
+    assert torch.equal(out, ref) and torch.equal(plain, ref)
