@@ -13,9 +13,9 @@
 // operations per worker-coordinate by the counters; one workgroup of 16 waves per CU, a round of 256 items 6 us:
 // 1280 items 38.8 us, 1536 42.8, of which the operations are 35.6); a last round that is nearly empty takes as long as
 // a full one (1600 items 48.2 us, 1792 48.7), and a launch of one item per workgroup is the item's own chain of loads,
-// stages and barriers (4 workers x 2^20 fp32, chunk 2^10: 7.8 us, and 5.7 of the decoder; what the host adds is 1 us).
+// stages and barriers (4 workers x 2^20 fp32, chunk 2^10: 6.9 us, and 5.7 of the decoder).
 //   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 69 us
-//   (3.6 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 14.7 us.  Before: one range and one encode
+//   (3.6 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 13.3 us.  Before: one range and one encode
 //   launch per worker of the generic kernels, which load element by element and take a
 //   barrier per stage above 2^4.
 //
@@ -70,6 +70,10 @@ template <bool BF16, int CLASS, int BITS, SmallOp OP>
 __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const SmallArgs a, const FusedWorkerPtrs ptrs) {
     constexpr int kUnits = BF16 ? 4 : 8;
     constexpr int kElem = BF16 ? 2 : 4;
+    // bf16 input is loaded one item ahead.  fp32 (32 registers in flight) when its item starts: ahead, the kernel spills.  Pass
+    // with the decoder, us, ahead -> this: 4 workers x 2^20, chunk 2^10 14.9 -> 13.3, 8 x 2^20 20.7 -> 16.4, 8 x 2^22 44.7 -> 38.8,
+    // 2 x 2^24 53.4 -> 47.7, 8 x 2^23, chunk 2^12 91.6 -> 78.4; 8 x 2^24, chunk 2^11 166 -> 154.
+    constexpr bool kAhead = BF16;
     extern __shared__ uint4 dyn[];
     const uint32_t t = threadIdx.x, lane = t & 63u;
     // (the wave's number is the same for all lanes: kept in a scalar register, so are the
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     };
 
     uint64_t item = blockIdx.x;
-    load(item, 0u);
+    if (kAhead) load(item, 0u);
     fill_signs(item, 0u);
     __syncthreads();
     uint32_t cur = 0u, step = 0u;
@@ -203,6 +207,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             }
             units_to_l1<kUnits, true>(sx, raw.u, v);
         } else {
+            load(item, step);
 #pragma unroll
             for (int j = 0; j < kUnits; ++j) stage[lay14::stage_unit((uint32_t)j * 64u + lane)] = raw.u[j];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -215,7 +220,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
         for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));   // converted before `raw` is loaded again
         asm volatile("" ::: "memory");
         const bool item_ends = step + 1u == steps;
-        load(item_ends ? item + gridDim.x : item, item_ends ? 0u : step + 1u);
+        if (kAhead) load(item_ends ? item + gridDim.x : item, item_ends ? 0u : step + 1u);
         if (step == 0u && item + gridDim.x < a.items) fill_signs(item + gridDim.x, cur ^ 1u);
 
         butterflies<0, 5>(v);
