@@ -255,8 +255,8 @@ __device__ __forceinline__ void x3d_load(const Shared& sh, float (&v)[kRegs], ui
 
 // Two waves trade half of their registers through LDS: the upper half of the one against the
 // lower half of the other, so that register bit 4 and the bit in which the waves' numbers differ
-// change places.  `upper`: this wave has the bit set; `mine` / `theirs`: 4 KB per wave.  Ends with
-// a barrier: the buffers may be rewritten.
+// change places.  `upper`: this wave has the bit set; `mine` / `theirs`: 4 KB per wave, which are still being read on
+// return.
 __device__ __forceinline__ void trade_halves(float (&v)[kRegs], float4* mine, const float4* theirs, bool upper,
                                              uint32_t lane) {
     // (the empty assembly statements differ, so the two branches are not merged into one that picks
@@ -297,7 +297,6 @@ __device__ __forceinline__ void trade_halves(float (&v)[kRegs], float4* mine, co
         }
         asm volatile("; lower wave has" ::: "memory");
     }
-    __syncthreads();
 }
 
 // Stages 0..13 on a chunk that sits in layout L1 in v; result (unnormalised H_c x) in

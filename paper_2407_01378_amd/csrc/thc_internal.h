@@ -132,6 +132,7 @@ hipError_t launch_aggregate_decode_fused(const AggDecodeArgs& a, const FusedPayl
                                          uint32_t bits, hipStream_t stream);
 // The same two steps for chunk_log2 = 5 .. 13 (thc_small.hip).  clear_error: the kernel also
 // zeroes the workspace's first four words.
+uint32_t small_encode_parts(uint32_t W, uint32_t chunk_log2);
 bool small_encode_all_applicable(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2);
 hipError_t launch_small_encode_all(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2, float norm,
                                    bool bf16, uint32_t bits, bool clear_error, hipStream_t stream);

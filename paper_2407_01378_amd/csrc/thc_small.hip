@@ -1,11 +1,15 @@
 // Tuned kernels for chunks of 2^5 .. 2^13 coordinates, same results as the generic ones.
 //
-// Encode.  A chunk this small needs no agreement between workgroups: one workgroup holds the
-// same coordinates of ALL workers at once, a wave 2^11 coordinates of one worker (32 per
-// thread, in registers), so the shared range of a chunk is a maximum over a few words in LDS
-// behind one barrier.  Up to 16 waves' worth of workers (16 up to chunks of 2^11, 8 at 2^12, 4 at
-// 2^13) every gradient is read once; more take rounds, and all rounds but the last are loaded and
-// rotated a second time for the quantizer (8 workers at 2^13: 1.5 times the work).  The rotation
+// Encode.  A wave holds 2^11 coordinates of one worker, 32 per thread, in registers; a workgroup the same coordinates
+// of ALL workers at once where they fit 16 waves (16 workers up to chunks of 2^11, 8 at 2^12, 4 at 2^13), so the shared
+// range of a chunk is a maximum over a few words in LDS behind one barrier and no workgroup waits for another.  More
+// workers are spread over workgroups of up to 8 waves that agree on the range through the workspace (the protocol of
+// thc_fused14.hip: persistent grid, an item's workgroups side by side, bounded waits).  Every gradient is read and rotated
+// once.  Before, one workgroup took them in rounds, all but the last of which it rotated a second time, and a launch of
+// few chunks had one workgroup for each: us with the decoder, rounds -> spread: 8 workers x 50257, chunk 2^13 25.6 -> 15.0,
+// 8 x 2^20 26.6 -> 20.2, 8 x 2.4 M fp32 51.4 -> 33.8, 16 x 0.75 M fp32 52.4 -> 28.6; 32 x 0.34 M, chunk 2^12, 8 bits 45.3 -> 28.1; 64 x
+// 0.53 M fp32, chunk 2^10 82 -> 47.4, 32 x 2^17 22.2 -> 16.1; 64 x 2^15, chunk 2^8, 2 bits 34.0 -> 15.9.  (Where 16 waves do, spread over
+// two workgroups is slower: 16 x 2^23, chunk 2^10 110 and 130 us.)  The rotation
 // stays inside the wave up to chunks of 2^11: 5 stages between registers, 4 between lanes by
 // data-parallel primitives and 2 after a swap of a lane bit into the registers (thc_lanes.h).
 // Chunks of 2^12 and 2^13 span two and four waves, which trade half of their registers through LDS
@@ -40,10 +44,17 @@ constexpr uint32_t kWaveLog2 = 11;               // coordinates of a wave
 constexpr uint32_t kWaveCoords = 1u << kWaveLog2;
 constexpr uint32_t kMaxWaves = 16;
 constexpr uint32_t kPreferredWaves = 8;          // two workgroups of 8 waves fill a CU at 128 registers
+// Pauses of the wait for the peers' words, in units of 64 clocks: in front of the first read, and between reads.  Many
+// workgroups publish further apart, and their reads load the path the words travel on: encoder, us, 16 and 4 | 24 and 4 | 40
+// and 8: 64 workers x 2^22, chunk 2^12 (16 workgroups) 237 | 233 | 225, 64 x 2^21 fp32, 2^13 (32) 173 | 170 | 164, 64 x 0.4 M, 2^11 (8)
+// 30.1 | 29.4 | 28.6; 8 x 2^24, 2^13 (4) 117 | 116 | 116, 32 x 2^22, 2^8 (4) 95.6 | 95.5 | 101.
+constexpr int kFirstPollSleep = 24, kPollSleep = 4;
+constexpr int kFirstPollSleepMany = 40, kPollSleepMany = 8;   // more than kFewParts workgroups
+constexpr uint32_t kFewParts = 4;
 
-// What a launch does: encode all workers onto their common range; only the range of one
-// worker; encode one worker onto a range handed in.
-enum class SmallOp : int { EncodeAll = 0, Absmax = 1, EncodeOnto = 2 };
+// What a launch does: encode all workers of a workgroup onto their common range; only the range of one
+// worker; encode one worker onto a range handed in; encode all workers, who are spread over several workgroups.
+enum class SmallOp : int { EncodeAll = 0, Absmax = 1, EncodeOnto = 2, EncodeSpread = 3 };
 
 struct SmallArgs {
     uint64_t n, padded;
@@ -56,11 +67,16 @@ struct SmallArgs {
     float norm;               // c^(-1/2)
     float* scale_out;         // may be null
     const float* scale_in;    // EncodeOnto
-    uint32_t* error;          // may be null: four words that a good run leaves zero
+    uint32_t* error;          // EncodeAll: may be null, four words that a good run leaves zero; EncodeSpread: set if a wait expires
     // shape of a workgroup: wave = (region * groups + group) * 2^wpw_log2 + part; a unit is the
-    // 2^max(11, l) coordinates of one worker that its 2^wpw_log2 waves hold, a group takes workers
-    // group, group + groups, ... (rounds of them)
-    uint32_t wpw_log2, groups, regions, rounds;
+    // 2^max(11, l) coordinates of one worker that its 2^wpw_log2 waves hold, a group is one worker
+    uint32_t wpw_log2, groups, regions;
+    // EncodeSpread: workgroups of an item (each has `groups` of the workers), a word per chunk for each of them and one
+    // counter per chunk, all zero before and after
+    uint32_t parts;
+    uint32_t max_spins;
+    uint32_t* slots;
+    uint32_t* done;
 };
 
 // Coordinate ranges by chunk size: CLASS 0: l <= 9, 1: l = 10, 11, 2: l = 12, 13.
@@ -89,7 +105,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     const uint32_t unit_log2 = CLASS == 2 ? a.l : kWaveLog2;
 
     // LDS: staging of fp32 input / the traded registers, two sign tables, two range tables
-    constexpr uint32_t kStage = !BF16 ? 512u : (CLASS == 2 ? 256u : 0u);   // 16-byte units per wave
+    constexpr uint32_t kStage = !BF16 || CLASS == 2 ? 512u : 0u;   // 16-byte units per wave
     const uint32_t sign_words = a.regions * (1u << (unit_log2 - 5u));
     uint4* stage = dyn + kStage * wave;
     uint32_t* sign = reinterpret_cast<uint32_t*>(dyn + kStage * waves);
@@ -98,9 +114,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     const uint32_t row = (a.groups * wpw + 3u) & ~3u;
     float* red = reinterpret_cast<float*>(sign + 2u * sign_words);
     const uint32_t red_words = (a.regions << rows_log2) * row;
-    if (OP == SmallOp::EncodeAll) {
+    if (OP == SmallOp::EncodeAll || OP == SmallOp::EncodeSpread) {
         for (uint32_t i = t; i < 2u * red_words; i += blockDim.x) red[i] = 0.0f;   // (the unused end of a row stays zero)
     }
+    uint32_t* got = reinterpret_cast<uint32_t*>(red + red_words);   // EncodeSpread: the peers' words, instead of the second table
     // this lane's chunk inside its unit
     const uint32_t chunk = CLASS == 0 ? block >> (a.l - 5u) : (CLASS == 1 && a.l == 10u ? lane >> 5 : 0u);
     float* red_row = red + ((region << rows_log2) + chunk) * row;
@@ -128,17 +145,17 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     const uint32_t lane_stages = CLASS == 0 ? a.l - 5u : 4u;   // how many of i5..i8 are rotated
     const float neg = (__popc(block & ((1u << lane_stages) - 1u)) & 1) ? -1.0f : 1.0f;
 
-    // A step is one worker's unit: a round of an item.  Rounds 0 .. rounds-1 find the range; the
-    // last one is quantized where it stands, the earlier ones are rotated once more.
-    const uint32_t rounds = OP == SmallOp::EncodeAll ? a.rounds : 1u;
-    const uint32_t steps = 2u * rounds - 1u;
-    auto worker_of = [&](uint32_t step) { return group + a.groups * (step < rounds ? step : steps - 1u - step); };
+    // EncodeSpread: which of an item's workgroups this one is, and the items it takes
+    const uint32_t parts = OP == SmallOp::EncodeSpread ? a.parts : 1u;
+    const uint32_t first = OP == SmallOp::EncodeSpread ? blockIdx.x / parts : blockIdx.x;
+    const uint32_t stride = OP == SmallOp::EncodeSpread ? gridDim.x / parts : gridDim.x;
+    const uint32_t mine = OP == SmallOp::EncodeSpread ? blockIdx.x - first * parts : 0u;
+    const uint32_t w = group + a.groups * mine;   // the worker
     auto coord0_of = [&](uint64_t item) { return (item * a.regions + region) << unit_log2; };
 
     Raw<kUnits> raw;
     uint32_t odd_tail = 0u;   // BF16: the last coordinate of an odd count, in the lane that owns it
-    auto load = [&](uint64_t item, uint32_t step) {
-        const uint32_t w = worker_of(step);
+    auto load = [&](uint64_t item) {
         const uint64_t g0 = coord0_of(item) + part * kWaveCoords;
         uint64_t left = (item < a.items && w < a.W && g0 < a.n) ? a.n - g0 : 0u;
         if (left > (uint64_t)kWaveCoords) left = kWaveCoords;
@@ -164,10 +181,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 odd_tail = reinterpret_cast<const uint16_t*>(addr)[left - 1u];
         }
     };
-    // the coordinates of the step that exist (for the odd tail), as load() saw them
-    auto left_of = [&](uint64_t item, uint32_t step) -> uint32_t {
+    // the coordinates of the item that exist (for the odd tail), as load() saw them
+    auto left_of = [&](uint64_t item) -> uint32_t {
         const uint64_t g0 = coord0_of(item) + part * kWaveCoords;
-        const uint64_t left = (item < a.items && worker_of(step) < a.W && g0 < a.n) ? a.n - g0 : 0u;
+        const uint64_t left = (item < a.items && w < a.W && g0 < a.n) ? a.n - g0 : 0u;
         return left > (uint64_t)kWaveCoords ? kWaveCoords : (uint32_t)left;
     };
     auto fill_signs = [&](uint64_t item, uint32_t which) {
@@ -179,21 +196,21 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
         }
     };
 
-    uint64_t item = blockIdx.x;
-    if (kAhead) load(item, 0u);
-    fill_signs(item, 0u);
+    if (kAhead) load(first);
+    fill_signs(first, 0u);
     __syncthreads();
-    uint32_t cur = 0u, step = 0u;
-    uint32_t most = 0u;   // largest magnitude of the lane's chunk over the rounds so far, as a word
-    float s = 0.0f;
-    while (item < a.items) {
-        const uint32_t w = worker_of(step);
+    uint32_t cur = 0u;
+    // EncodeSpread: first chunk and number of chunks of this and of the previous item
+    const uint64_t chunks = a.padded >> a.l;
+    uint64_t prev0 = 0u;
+    uint32_t prev_live = 0u;
+    for (uint64_t item = first; item < a.items; item += stride) {
         const uint64_t u0 = coord0_of(item);
         const uint32_t sx = sign[cur * sign_words + (region << (unit_log2 - 5u)) + part * 64u + block];
         float v[kRegs];
         if constexpr (BF16) {
             if (a.n & 1u) {   // (uniform)
-                const uint32_t left = left_of(item, step);
+                const uint32_t left = left_of(item);
                 if ((left & 1u) && block == left >> 5) {
                     const uint32_t d = (left & 31u) >> 1;   // dword of the lane's 16 that holds it
 #pragma unroll
@@ -207,7 +224,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             }
             units_to_l1<kUnits, true>(sx, raw.u, v);
         } else {
-            load(item, step);
+            if (!kAhead) load(item);
 #pragma unroll
             for (int j = 0; j < kUnits; ++j) stage[lay14::stage_unit((uint32_t)j * 64u + lane)] = raw.u[j];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -219,9 +236,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
 #pragma unroll
         for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));   // converted before `raw` is loaded again
         asm volatile("" ::: "memory");
-        const bool item_ends = step + 1u == steps;
-        if (kAhead) load(item_ends ? item + gridDim.x : item, item_ends ? 0u : step + 1u);
-        if (step == 0u && item + gridDim.x < a.items) fill_signs(item + gridDim.x, cur ^ 1u);
+        if (kAhead) load(item + stride);
+        if (item + stride < a.items) fill_signs(item + stride, cur ^ 1u);
 
         butterflies<0, 5>(v);
         if (CLASS != 0 || a.l > 5u) lanes::lane_stage<0>(v, sg0);
@@ -237,16 +253,19 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             }
         }
         if constexpr (CLASS == 2) {
+            // (two buffers, free again behind the item's last barrier)
             float4* buf = reinterpret_cast<float4*>(dyn);
             trade_halves(v, buf + kStage * wave, buf + kStage * (wave ^ 1u), (part & 1u) != 0u, lane);
             butterflies<4, 5>(v);
             if (a.l > 12u) {
+                buf += 256;
                 trade_halves(v, buf + kStage * wave, buf + kStage * (wave ^ 2u), (part & 2u) != 0u, lane);
                 butterflies<4, 5>(v);
             }
         }
 
-        if (OP != SmallOp::EncodeOnto && step < rounds) {
+        uint32_t most = 0u;   // largest magnitude of the lane's chunk, as a word
+        if (OP != SmallOp::EncodeOnto) {
             // the chunk's largest magnitude: registers, then the lanes that share the chunk
             float m = 0.0f;
 #pragma unroll
@@ -261,26 +280,80 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 x = lanes::umax_step<16>(x);
                 if (CLASS == 2 || a.l > 10u) x = lanes::umax_step<32>(x);
             }
-            most = step == 0u ? x : (x > most ? x : most);
+            most = x;
         }
         const bool leader = CLASS == 0 ? (block & ((1u << (a.l - 5u)) - 1u)) == 0u
                                        : (CLASS == 1 && a.l == 10u ? (lane & 31u) == 0u : lane == 0u);
         const uint64_t p = (u0 >> a.l) + chunk;
         const bool exists = (p << a.l) < a.padded;
+        float s = 0.0f;
         if (OP == SmallOp::EncodeAll) {
-            if (step + 1u == rounds) {
-                // all workers' waves have published behind the barrier (which also orders the sign
-                // table of the next item); the two range tables take turns
-                float* at = red_row + cur * red_words;
-                if (leader) at[group * wpw + part] = __uint_as_float(most);
-                __syncthreads();
-                s = 0.0f;
-                for (uint32_t i = 0; i < row; i += 4u) {
-                    const float4 f = *reinterpret_cast<const float4*>(at + i);
-                    s = fmaxf(fmaxf(s, fmaxf(f.x, f.y)), fmaxf(f.z, f.w));
-                }
-                if (leader && group == 0u && part == 0u && exists && a.scale_out) a.scale_out[p] = s;
+            // all workers' waves have published behind the barrier (which also orders the sign
+            // table of the next item); the two range tables take turns
+            float* at = red_row + cur * red_words;
+            if (leader) at[group * wpw + part] = __uint_as_float(most);
+            __syncthreads();
+            for (uint32_t i = 0; i < row; i += 4u) {
+                const float4 f = *reinterpret_cast<const float4*>(at + i);
+                s = fmaxf(fmaxf(s, fmaxf(f.x, f.y)), fmaxf(f.z, f.w));
             }
+            if (leader && group == 0u && part == 0u && exists && a.scale_out) a.scale_out[p] = s;
+        } else if (OP == SmallOp::EncodeSpread) {
+            // The waves' maxima meet in LDS; the first wave publishes the workgroup's word of every chunk and waits for
+            // the peers' (see EncodeAllCtx in thc_fused14.hip, whose protocol this is, in the form with one reader).
+            if (leader) red_row[group * wpw + part] = __uint_as_float(most);
+            __syncthreads();   // (also orders the sign table of the next item)
+            if (wave == 0u) {
+                const uint64_t p0 = coord0_of(item) >> a.l;
+                const uint32_t live = chunks - p0 < (1ull << rows_log2) ? (uint32_t)(chunks - p0) : 1u << rows_log2;
+                uint32_t* words = a.slots + p0 * parts;
+                if (lane < live) {
+                    const float* at = red + lane * row;
+                    float m = 0.0f;
+                    for (uint32_t i = 0; i < row; i += 4u) {
+                        const float4 f = *reinterpret_cast<const float4*>(at + i);
+                        m = fmaxf(fmaxf(m, fmaxf(f.x, f.y)), fmaxf(f.z, f.w));
+                    }
+                    __hip_atomic_store(&words[lane * parts + mine], __float_as_uint(m) | 0x80000000u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (parts > kFewParts) __builtin_amdgcn_s_sleep(kFirstPollSleepMany);
+                else __builtin_amdgcn_s_sleep(kFirstPollSleep);
+                bool seen = false;
+                for (uint32_t spins = 0;; ++spins) {
+                    uint32_t valid = 0x80000000u;
+                    for (uint32_t base = 0; base < live * parts; base += 64u) {
+                        const uint32_t i = base + lane;
+                        if (i < live * parts) {
+                            const uint32_t val = __hip_atomic_load(&words[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            valid &= val;
+                            got[i] = val & 0x7FFFFFFFu;
+                        }
+                    }
+                    seen = __all(valid != 0u);
+                    if (seen || spins >= a.max_spins) break;
+                    if (parts > kFewParts) __builtin_amdgcn_s_sleep(kPollSleepMany);
+                    else __builtin_amdgcn_s_sleep(kPollSleep);
+                }
+                if (!seen && lane == 0u) __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                // With all of this item's words seen every peer has read the previous item's: nobody will read them
+                // again, and this workgroup clears its own.
+                if (seen && lane < prev_live)
+                    __hip_atomic_store(&a.slots[(prev0 + lane) * parts + mine], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                prev0 = p0;
+                prev_live = live;
+            }
+            __syncthreads();
+            // the next item's input has arrived in the meantime; knowing that, the compiler does not wait for it
+            // behind the stores below
+#pragma unroll
+            for (int j = 0; kAhead && j < kUnits; ++j)
+                asm volatile("" : "+v"(raw.u[j].x), "+v"(raw.u[j].y), "+v"(raw.u[j].z), "+v"(raw.u[j].w));
+            uint32_t x = 0u;
+            if (exists)
+                for (uint32_t i = 0; i < parts; ++i) x = max(x, got[chunk * parts + i]);
+            s = __uint_as_float(x);
+            if (leader && mine == 0u && group == 0u && part == 0u && exists) a.scale_out[p] = s;
         } else if (OP == SmallOp::Absmax) {
             if (CLASS == 2) {
                 float* at = red_row + cur * red_words;
@@ -299,7 +372,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             __syncthreads();       // the next item's sign table
         }
 
-        if (OP != SmallOp::Absmax && step + 1u >= rounds && w < a.W) {
+        if (OP != SmallOp::Absmax && w < a.W) {
             constexpr bool kClamp = OP == SmallOp::EncodeOnto;
             constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;
             const float two = s + s;
@@ -341,16 +414,21 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 }
             }
         }
-        if (item_ends) {
-            if (rounds > 1u) __syncthreads();   // the rounds behind the range's barrier read the sign table too
-            item += gridDim.x;
-            step = 0u;
-            cur ^= 1u;
-        } else {
-            ++step;
+        cur ^= 1u;
+    }
+    if (OP == SmallOp::EncodeAll && a.error && blockIdx.x == 0 && t < 4u) a.error[t] = 0u;
+    if (OP == SmallOp::EncodeSpread && wave == 0u && prev_live != 0u) {
+        // the last item's words: its workgroups count themselves off, the last one clears them and the counter
+        uint32_t arrived = 0u;
+        if (lane == 0u)
+            arrived = __hip_atomic_fetch_add(&a.done[prev0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
+        if (arrived == parts - 1u) {
+            for (uint32_t i = lane; i < prev_live * parts; i += 64u)
+                __hip_atomic_store(&a.slots[prev0 * parts + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0u) __hip_atomic_store(&a.done[prev0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    if (a.error && blockIdx.x == 0 && t < 4u) a.error[t] = 0u;
 }
 
 // ------------------------------------------------------------------------------ decode
@@ -449,7 +527,7 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void small_decode_kernel(const S
         hi = 2048u;
     }
     if (l > 12u) {
-        trade_halves(v, xb4 + 512u * wave, xb4 + 512u * (wave ^ 2u), (wave & 2u) != 0u, lane);
+        trade_halves(v, xb4 + 256 + 512u * wave, xb4 + 256 + 512u * (wave ^ 2u), (wave & 2u) != 0u, lane);
         butterflies<4, 5>(v);
         at = (wave << 10) + ((lane >> 5) << 9);
         hi = 4096u;
@@ -482,13 +560,16 @@ hipError_t launch_encode_t(const SmallArgs& a, const FusedWorkerPtrs& ptrs, hipS
     const uint32_t wpw = 1u << a.wpw_log2, waves = a.regions * a.groups * wpw;
     const uint32_t unit_log2 = a.l > kWaveLog2 ? a.l : kWaveLog2;
     const uint32_t rows_log2 = a.l < kWaveLog2 ? kWaveLog2 - a.l : 0u;
-    const uint32_t lds = waves * (!BF16 ? 8192u : (CLASS == 2 ? 4096u : 0u)) +
+    const uint32_t lds = waves * (!BF16 || CLASS == 2 ? 8192u : 0u) +
                          2u * 4u * (a.regions << (unit_log2 - 5u)) +
-                         2u * 4u * (a.regions << rows_log2) * ((a.groups * wpw + 3u) & ~3u);
+                         2u * 4u * (a.regions << rows_log2) * ((a.groups * wpw + 3u) & ~3u) +
+                         (OP == SmallOp::EncodeSpread ? 4u * (a.parts << rows_log2) : 0u);
     if (!allow_lds<kernel>(lds)) return hipErrorInvalidValue;
     uint64_t G = resident_grid<kernel>(64u * waves, lds);
+    if (OP == SmallOp::EncodeSpread) G /= a.parts;   // an item's workgroups wait for one another: all of them resident
     if (G == 0) return hipErrorInvalidValue;
     if (G > a.items) G = a.items;
+    if (OP == SmallOp::EncodeSpread) G *= a.parts;
     hipLaunchKernelGGL(kernel, dim3((uint32_t)G), dim3(64u * waves), lds, stream, a, ptrs);
     return hipGetLastError();
 }
@@ -503,14 +584,12 @@ hipError_t launch_encode_bits(const SmallArgs& a, const FusedWorkerPtrs& ptrs, u
 
 template <SmallOp OP>
 hipError_t launch_encode(SmallArgs& a, const FusedWorkerPtrs& ptrs, bool bf16, uint32_t bits, hipStream_t stream) {
-    // Shape of a workgroup.  All workers of a unit side by side where they fit 16 waves, and as
-    // many units as fill 8; more workers take rounds, evenly.
+    // Shape of a workgroup.  All workers of a unit side by side, and as many units as fill 8 waves; spread: the workers,
+    // evenly, over workgroups of up to 8 waves.
     a.wpw_log2 = a.l > kWaveLog2 ? a.l - kWaveLog2 : 0u;
-    const uint32_t max_groups = kMaxWaves >> a.wpw_log2;
-    a.rounds = (a.W + max_groups - 1u) / max_groups;
-    a.groups = (a.W + a.rounds - 1u) / a.rounds;
+    a.groups = OP == SmallOp::EncodeSpread ? (a.W + a.parts - 1u) / a.parts : a.W;
     const uint32_t per_region = a.groups << a.wpw_log2;
-    a.regions = per_region < kPreferredWaves ? kPreferredWaves / per_region : 1u;
+    a.regions = OP != SmallOp::EncodeSpread && per_region < kPreferredWaves ? kPreferredWaves / per_region : 1u;
     const uint32_t unit_log2 = a.l > kWaveLog2 ? a.l : kWaveLog2;
     const uint64_t units = (a.padded + (1ull << unit_log2) - 1u) >> unit_log2;
     // (a few units: spread over the CUs before they share a workgroup)
@@ -540,6 +619,13 @@ bool small_encode_all_applicable(const EncodeAllArgs& a, const FusedWorkerPtrs& 
     return true;
 }
 
+// Over how many workgroups the workers of a chunk are spread; more than one: they agree on the range through the workspace.
+uint32_t small_encode_parts(uint32_t W, uint32_t chunk_log2) {
+    const uint32_t wpw_log2 = chunk_log2 > k14::kWaveLog2 ? chunk_log2 - k14::kWaveLog2 : 0u;
+    const uint32_t waves = W << wpw_log2;
+    return waves > k14::kMaxWaves ? (waves + k14::kPreferredWaves - 1u) / k14::kPreferredWaves : 1u;
+}
+
 hipError_t launch_small_encode_all(const EncodeAllArgs& e, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2, float norm,
                                    bool bf16, uint32_t bits, bool clear_error, hipStream_t stream) {
     k14::SmallArgs a{};
@@ -552,6 +638,14 @@ hipError_t launch_small_encode_all(const EncodeAllArgs& e, const FusedWorkerPtrs
     a.levels = e.levels;
     a.norm = norm;
     a.scale_out = e.scale;
+    a.parts = small_encode_parts(e.W, chunk_log2);
+    if (a.parts > 1u) {
+        a.error = e.error;
+        a.max_spins = e.max_spins;
+        a.slots = e.slots;
+        a.done = e.slots + a.parts * e.chunks;
+        return k14::launch_encode<k14::SmallOp::EncodeSpread>(a, ptrs, bf16, bits, stream);
+    }
     a.error = clear_error ? e.error : nullptr;
     return k14::launch_encode<k14::SmallOp::EncodeAll>(a, ptrs, bf16, bits, stream);
 }

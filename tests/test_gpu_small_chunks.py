@@ -1,5 +1,5 @@
 """The tuned kernels for chunks of 2^5 .. 2^13 coordinates against the CPU oracle: every chunk
-size, worker counts around the edges of a workgroup (16 waves, rounds of workers beyond),
+size, worker counts around the edges of a workgroup (16 waves, several workgroups beyond),
 odd and ragged sizes, one-pass and per-call forms, and the signed grid's centre rule."""
 import numpy as np
 import pytest
@@ -27,7 +27,7 @@ def _grads(W, n, dtype, seed):
     return xs
 
 
-CASES = [  # (l, W, bits, n): a lone ragged chunk, edges of a wave's 2^11, rounds of workers, regions
+CASES = [  # (l, W, bits, n): a lone ragged chunk, edges of a wave's 2^11, several workgroups, regions
     (5, 8, 4, 33), (5, 3, 2, 40_001), (6, 1, 8, 70_000), (7, 16, 4, 10_243), (8, 17, 8, 5_001), (9, 2, 4, 131_072),
     (9, 33, 2, 6_145), (10, 4, 4, 100_003), (10, 8, 8, 2_047), (10, 64, 4, 4_099), (11, 1, 4, 200_001), (11, 5, 2, 40_961),
     (11, 18, 4, 8_191), (12, 8, 8, 60_001), (12, 3, 4, 4_097), (12, 9, 2, 12_289), (12, 1, 4, 300_001), (13, 4, 4, 90_003),
@@ -112,3 +112,66 @@ def test_gradients_off_the_16_byte_grid_match_the_oracle(l, W, bits, n, dtype):
     s = O.chunk_absmax(y, l)
     assert (scale.cpu().numpy() == s).all()
     assert (own.cpu().numpy() == O.pack(O.quantize(y, s, l, 0, 6, bits, dtype=np.float32), bits)).all()
+
+
+def _one_pass(xs, l, bits, ws, cleared=True):
+    W, n = len(xs), xs[0].numel()
+    scale = torch.full((thc.thc_num_chunks(n, l),), float("nan"), device=DEV)
+    pay = [torch.full((thc.thc_payload_bytes(n, l, bits),), 0xAA, dtype=torch.uint8, device=DEV) for _ in range(W)]
+    (thc.thc_encode_all_cleared if cleared else thc.thc_encode_all)(xs, l, 5, bits, pay, scale, ws)
+    return scale, pay
+
+
+def _matches_the_per_worker_calls(xs, l, bits, scale, pay):
+    W, P = len(xs), scale.numel()
+    absmax, want, own = torch.empty(W * P, device=DEV), torch.empty_like(scale), torch.empty_like(pay[0])
+    for w in range(W):
+        thc.thc_chunk_absmax(xs[w], l, 5, absmax[w * P:(w + 1) * P])
+    thc.thc_scale_reduce(absmax, W, P, want)
+    assert torch.equal(want, scale)
+    for w in range(W):
+        thc.thc_encode(xs[w], l, 5, w, bits, want, own)
+        assert torch.equal(own, pay[w]), w
+
+
+SPREAD = [  # (l, W, bits, n): the fewest and the most workers of several workgroups, more items than the chip holds
+    (5, 17, 4, 33), (5, 64, 2, 4_100), (5, 24, 8, 700_001), (8, 33, 4, 30_000), (10, 17, 2, 1_500_001), (11, 64, 4, 200_001),
+    (12, 9, 8, 4_097), (12, 64, 4, 300_001), (13, 5, 4, 8_193), (13, 8, 8, 2_000_001), (13, 64, 2, 250_001), (13, 33, 4, 1),
+]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("l,W,bits,n", SPREAD)
+def test_workers_spread_over_workgroups(l, W, bits, n, dtype):
+    """Against the one-call-per-worker route, on a workspace that has to come back clear, twice; and on one in any state."""
+    print(f"spread l={l} W={W} bits={bits} n={n} {dtype}", flush=True)
+    xs = _grads(W, n, dtype, l + W)
+    ws = torch.zeros(thc.thc_encode_all_workspace_bytes(W, n, l), dtype=torch.uint8, device=DEV)
+    for cleared in (True, True, False):
+        if not cleared:
+            ws.fill_(0xFF)
+        scale, pay = _one_pass(xs, l, bits, ws, cleared)
+        torch.cuda.synchronize()
+        assert not thc.thc_encode_all_timed_out(ws) and (not cleared or int(ws.count_nonzero()) == 0)
+        _matches_the_per_worker_calls(xs, l, bits, scale, pay)
+
+
+@pytest.mark.parametrize("l,W,n", [(8, 24, 900_001), (13, 64, 250_001)])
+def test_expired_wait_of_spread_workers(l, W, n):
+    """Failure handling forced from the host: with a poll limit of zero a wait gives up after one read.  Every wave still
+    ends, and a cleared workspace is good again."""
+    print(f"expired wait l={l} W={W} n={n}", flush=True)
+    xs = _grads(W, n, torch.bfloat16, l + W)
+    ws = torch.zeros(thc.thc_encode_all_workspace_bytes(W, n, l), dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    try:
+        thc.thc_set_spin_limit(0)
+        _one_pass(xs, l, 4, ws)
+        torch.cuda.synchronize()
+    finally:
+        thc.thc_set_spin_limit(1 << 22)
+    thc.thc_workspace_clear(ws)
+    scale, pay = _one_pass(xs, l, 4, ws)
+    torch.cuda.synchronize()
+    assert int(ws.count_nonzero()) == 0
+    _matches_the_per_worker_calls(xs, l, 4, scale, pay)

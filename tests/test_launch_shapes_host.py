@@ -82,6 +82,21 @@ def test_answers_are_kept_per_shape_and_beyond_the_table(run):
     assert sum(s[4] for s in seen[-9:]) <= 4      # (what the overflow displaced is asked for again, no more)
 
 
+def test_workers_beyond_16_waves_are_spread_over_resident_workgroups(run):
+    for l in range(5, 14):
+        wpw = 1 << max(0, l - 11)
+        for W in (1, 4, 5, 8, 9, 16, 17, 33, 64):
+            for n in (1, 5_000_000):
+                rc, grid, block, lds, _, launches = run((0, l, W, BF16, 4, n))[0]
+                parts = -(-W * wpw // 8) if W * wpw > 16 else 1
+                assert rc == 0 and launches == (2 if parts > 1 else 1)    # (with the clearing of the words)
+                items = -(-n // (1 << max(l, 11)))
+                if parts > 1:
+                    assert grid % parts == 0 and block == 64 * wpw * -(-W // parts) <= 512
+                    resident = 256 * min(2048 // block, 163840 // lds)   # as the stand-in has it
+                    assert grid == min(items, resident // parts) * parts
+
+
 @pytest.mark.parametrize("dtype,off", [(F32, 4), (BF16, 2)])
 def test_gradients_off_the_16_byte_grid_take_the_generic_kernels(run, dtype, off):
     W, n = 3, 100_003
