@@ -261,7 +261,7 @@ int thc_encode_all_static(const void* const* grads, thc_dtype dt, uint32_t W, ui
  * 2^22, about seconds).  It counts polls, not time: a poll is a read of the chunk's range words
  * and a pause of 512 clocks, or of 256 with more than 32 workers, where one wave of a workgroup
  * polls for all.  Chunks below 2^14 wait only with more workers than one workgroup holds (16 up to 2^11, 8 at
- * 2^12, 4 at 2^13): 256 clocks, or 512 where a chunk has more than four workgroups.  A tuning and test knob: with a tiny limit the waits expire, the
+ * 2^12, 4 at 2^13): 256 clocks, or 512 where a chunk has more than eight workgroups.  A tuning and test knob: with a tiny limit the waits expire, the
  * error word is set and every wave still exits.  PROCESS-GLOBAL and not thread-safe: the
  * value is read when a call is enqueued, by every thread's calls; changing it while another
  * thread encodes makes that thread's waits expire early, which only the error word of its

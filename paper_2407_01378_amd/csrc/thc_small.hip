@@ -45,12 +45,12 @@ constexpr uint32_t kWaveCoords = 1u << kWaveLog2;
 constexpr uint32_t kMaxWaves = 16;
 constexpr uint32_t kPreferredWaves = 8;          // two workgroups of 8 waves fill a CU at 128 registers
 // Pauses of the wait for the peers' words, in units of 64 clocks: in front of the first read, and between reads.  Many
-// workgroups publish further apart, and their reads load the path the words travel on: encoder, us, 16 and 4 | 24 and 4 | 40
-// and 8: 64 workers x 2^22, chunk 2^12 (16 workgroups) 237 | 233 | 225, 64 x 2^21 fp32, 2^13 (32) 173 | 170 | 164, 64 x 0.4 M, 2^11 (8)
-// 30.1 | 29.4 | 28.6; 8 x 2^24, 2^13 (4) 117 | 116 | 116, 32 x 2^22, 2^8 (4) 95.6 | 95.5 | 101.
+// workgroups publish further apart, and their reads load the path the words travel on.  Encoder, us, 16 and 4 | 24 and 4 |
+// 40 and 8: 64 workers x 2^22, chunk 2^12 (16 workgroups) 237 | 233 | 225, 64 x 2^21 fp32, 2^13 (32) 173 | 170 | 164; 64 x 4 M, 2^8 (8)
+// 24 and 4 175, 40 and 8 185, 48 x 2.5 M (6) 86.9 and 89.1; 20 x 4 M, 2^11 (3) 74.4 | 70.3, 32 x 8.4 M, 2^9 (4) 185 | 189.
 constexpr int kFirstPollSleep = 24, kPollSleep = 4;
 constexpr int kFirstPollSleepMany = 40, kPollSleepMany = 8;   // more than kFewParts workgroups
-constexpr uint32_t kFewParts = 4;
+constexpr uint32_t kFewParts = 8;
 
 // What a launch does: encode all workers of a workgroup onto their common range; only the range of one
 // worker; encode one worker onto a range handed in; encode all workers, who are spread over several workgroups.
@@ -239,6 +239,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
         if (kAhead) load(item + stride);
         if (item + stride < a.items) fill_signs(item + stride, cur ^ 1u);
 
+        // (as in the chunk-2^14 encoder: the rotation ahead of the other workgroup's quantizer.  Encoder alone, us: 8 workers
+        // x 2^24, chunk 2^13 129 -> 116, 64 x 2^22, chunk 2^12 250 -> 221; one workgroup per CU 48.7 -> 47.0)
+        set_prio<true, kPrioRotateEarly>();
         butterflies<0, 5>(v);
         if (CLASS != 0 || a.l > 5u) lanes::lane_stage<0>(v, sg0);
         if (CLASS != 0 || a.l > 6u) lanes::lane_stage<1>(v, sg1);
@@ -254,6 +257,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
         }
         if constexpr (CLASS == 2) {
             // (two buffers, free again behind the item's last barrier)
+            set_prio<OP == SmallOp::EncodeSpread, kPrioRotateLate>();
             float4* buf = reinterpret_cast<float4*>(dyn);
             trade_halves(v, buf + kStage * wave, buf + kStage * (wave ^ 1u), (part & 1u) != 0u, lane);
             butterflies<4, 5>(v);
@@ -372,6 +376,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             __syncthreads();       // the next item's sign table
         }
 
+        set_prio<true, kPrioTail>();
         if (OP != SmallOp::Absmax && w < a.W) {
             constexpr bool kClamp = OP == SmallOp::EncodeOnto;
             constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;
