@@ -555,18 +555,16 @@ __device__ __forceinline__ void cvt_into_byte(uint32_t& acc, float tt) {
     }
 }
 
-// One half of it: the 16 coordinates in registers 16 half .. 16 half + 15, which are those of
-// block `blk` of the rounding stream, into index bytes by[4 half .. 4 half + 3].
+// One half of it: the 16 coordinates in registers 16 half .. 16 half + 15, whose block of the rounding
+// stream is rb, into index bytes by[4 half .. 4 half + 3].
 //   norm     factor from v to y where it is not folded
 //   NEG      the lane holds the negated value where sgn = -1 (a lane exchange leaves it so): mul
 //            (FOLD) or norm carries the sign already, and sgn itself is used only where v meets sub
 template <int BITS, bool CLAMP, bool FOLD, bool RANGED, bool NEG = false>
-__device__ __forceinline__ void quantize_half(const float (&v)[kRegs], int half, uint64_t blk, float sub, float mul,
-                                              float base, uint32_t L, uint32_t worker, uint32_t key0, uint32_t key1,
-                                              uint32_t (&by)[8], float norm = kInvSqrtC, float sgn = 1.0f) {
+__device__ __forceinline__ void quantize_drawn(const float (&v)[kRegs], int half, const u32x4& rb, float sub, float mul,
+                                               float base, uint32_t L, uint32_t (&by)[8], float norm, float sgn) {
     constexpr int kSub = 8 / BITS;        // coordinates per payload byte: 1, 2, 4
     const float Lf = (float)L;
-    const u32x4 rb = round_block(blk, worker, key0, key1);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const int r = 16 * half + e;
@@ -589,6 +587,25 @@ __device__ __forceinline__ void quantize_half(const float (&v)[kRegs], int half,
         }
     }
 }
+// The same with the block's number: it is drawn here.
+template <int BITS, bool CLAMP, bool FOLD, bool RANGED, bool NEG = false>
+__device__ __forceinline__ void quantize_half(const float (&v)[kRegs], int half, uint64_t blk, float sub, float mul,
+                                              float base, uint32_t L, uint32_t worker, uint32_t key0, uint32_t key1,
+                                              uint32_t (&by)[8], float norm = kInvSqrtC, float sgn = 1.0f) {
+    quantize_drawn<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, round_block(blk, worker, key0, key1), sub, mul, base, L, by, norm, sgn);
+}
+// A thread's two blocks of the rounding stream, drawn where the caller puts this: in front of what it waits for.
+struct Drawn {
+    u32x4 rb[2];
+    __device__ __forceinline__ void draw(uint64_t g, uint32_t worker, uint32_t key0, uint32_t key1) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            rb[h] = round_block((g >> 4) + h, worker, key0, key1);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rb[h].w[i]));   // (not moved to where it is used)
+        }
+    }
+};
 // Index bytes -> payload words.
 template <int BITS>
 __device__ __forceinline__ void pack_bytes(const uint32_t (&by)[8], uint32_t (&pk)[BITS]) {
@@ -604,12 +621,15 @@ template <int BITS, bool CLAMP, bool FOLD, bool RANGED, bool NEG = false>
 __device__ __forceinline__ void quantize_pack(const float (&v)[kRegs], float sub, float mul, float base,
                                               uint32_t L, uint64_t g, uint32_t worker, uint32_t key0,
                                               uint32_t key1, uint32_t (&pk)[BITS], float norm = kInvSqrtC,
-                                              float sgn = 1.0f) {
+                                              float sgn = 1.0f, const Drawn* drawn = nullptr) {
     uint32_t by[8];                       // index bytes; by[m] serves payload word m / kSub
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
-        quantize_half<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, (g >> 4) + half, sub, mul, base, L, worker, key0, key1, by,
-                                                      norm, sgn);
+    for (int half = 0; half < 2; ++half) {
+        if (drawn) quantize_drawn<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, drawn->rb[half], sub, mul, base, L, by, norm, sgn);
+        else
+            quantize_half<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, (g >> 4) + half, sub, mul, base, L, worker, key0, key1, by,
+                                                          norm, sgn);
+    }
     pack_bytes<BITS>(by, pk);
 }
 
@@ -635,7 +655,8 @@ __device__ __forceinline__ void store_packed(const uint32_t (&pk)[BITS], uint8_t
 template <int BITS, bool CLAMP, bool NEG = false>
 __device__ __forceinline__ void quantize_store(const float (&v)[kRegs], float s, uint32_t L, uint64_t g0,
                                                uint32_t worker, uint32_t key0, uint32_t key1,
-                                               uint8_t* payload, uint32_t t, float sgn = 1.0f) {
+                                               uint8_t* payload, uint32_t t, float sgn = 1.0f,
+                                               const Drawn* drawn = nullptr) {
     constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;   // both grids of this width
     const float two = s + s;
     const bool ranged = two >= kMinRange;   // false: an all-zero chunk, or one too small for L / two
@@ -646,10 +667,10 @@ __device__ __forceinline__ void quantize_store(const float (&v)[kRegs], float s,
     uint32_t pk[BITS];   // 32 coordinates * BITS bits = BITS dwords
     if (s >= 0x1p-100f && s <= 0x1p100f)   // the same for every thread of the workgroup
         quantize_pack<BITS, CLAMP, true, kOffset, NEG>(v, -128.0f * s, inv * (NEG && !kOffset ? kInvSqrtC * sgn : kInvSqrtC),
-                                                       base, L, g, worker, key0, key1, pk, kInvSqrtC, sgn);
+                                                       base, L, g, worker, key0, key1, pk, kInvSqrtC, sgn, drawn);
     else
         quantize_pack<BITS, CLAMP, false, kOffset, NEG>(v, -s, inv, base, L, g, worker, key0, key1, pk,
-                                                        NEG ? kInvSqrtC * sgn : kInvSqrtC, sgn);
+                                                        NEG ? kInvSqrtC * sgn : kInvSqrtC, sgn, drawn);
     store_packed<BITS>(pk, payload + (g * BITS) / 8u);
 }
 
@@ -660,12 +681,12 @@ template <int BITS, bool ROTATED = true, bool CLAMP = true>
 __device__ __forceinline__ void quantize_store_range(const float (&v)[kRegs], float lo, float hi, uint32_t L,
                                                      uint64_t g0, uint32_t worker, uint32_t key0,
                                                      uint32_t key1, uint8_t* payload, uint32_t t,
-                                                     float norm = kInvSqrtC) {
+                                                     float norm = kInvSqrtC, const Drawn* drawn = nullptr) {
     const float width = hi - lo;
     const float inv = width >= kMinRange ? (float)L / width : 0.0f;
     const uint64_t g = g0 + (uint64_t)t * 32u;
     uint32_t pk[BITS];
-    quantize_pack<BITS, CLAMP, !ROTATED, true>(v, lo, inv, 0x1p-9f, L, g, worker, key0, key1, pk, norm);
+    quantize_pack<BITS, CLAMP, !ROTATED, true>(v, lo, inv, 0x1p-9f, L, g, worker, key0, key1, pk, norm, 1.0f, drawn);
     store_packed<BITS>(pk, payload + (g * BITS) / 8u);
 }
 

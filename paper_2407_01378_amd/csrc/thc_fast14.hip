@@ -5,6 +5,7 @@
 // everything else with identical results.
 #include "thc_core14.h"
 #include "thc_internal.h"
+#include "thc_resident.h"
 
 #pragma clang fp contract(off)
 
@@ -20,8 +21,12 @@ namespace {
 // of six up to the range.  Forward keeps the LDS maps (long calls
 // of it are bound by memory: 6 TB/s); MinMax keeps them too, the lanes have not been timed there.
 // Measured at 7 M bf16 (433 chunks): range 8.0 -> 6.5 us, 8-bit encode 11.1 -> 9.4; per-call round of
-// eight workers 177 -> 153 us.
-template <bool BF16, Mode MODE, int BITS>
+// eight workers 177 -> 153 us.  Encode also draws its rounding bytes (a tenth of its operations) and reads the given range
+// while the input is on its way: 8 bits, 433 chunks 8.8 -> 8.5 us, 512 9.3 -> 8.8, 2048 29.9 -> 26.8, fp32 2048 38.8 -> 35.5.
+//   PRIO  the rotation ahead of the other workgroup's quantizer, for launches of up to two workgroups per CU: 433 chunks
+//         8.4 -> 7.9, 512 8.7 -> 8.25.  In longer ones it would hold up the loads of the workgroups that follow: fp32 1024 chunks
+//         20.1 us, with it 20.8; 2048 33.8 and 35.4.  (The range has nothing behind the rotation to put back.)
+template <bool BF16, Mode MODE, int BITS, bool PRIO = false>
 __global__ __launch_bounds__(kThreads) void per_worker_kernel(const ChunkArgs a) {
     __shared__ Shared sh;
     constexpr int kUnits = BF16 ? 4 : 8;
@@ -32,19 +37,31 @@ __global__ __launch_bounds__(kThreads) void per_worker_kernel(const ChunkArgs a)
     const uint64_t left = a.n - g0;
     const uint32_t valid = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
 
+    // Encode: the given range is read, and the rounding stream drawn, while the input is on its way
+    float lo = 0.0f, hi = 0.0f;
+    if constexpr (MODE == Mode::Encode) {
+        if (a.range_in) {
+            lo = a.range_in[2 * p];
+            hi = a.range_in[2 * p + 1];
+        } else if (a.scale_in) {
+            hi = a.scale_in[p];
+        }
+    }
+    Drawn drawn;
     constexpr bool kLanes = MODE == Mode::Absmax || MODE == Mode::Encode;
     const uint32_t block = lay14::block_of_lane(lane), tp = kLanes ? (t & ~63u) | block : t;
     constexpr bool kDirect = kLanes && BF16;   // every thread loads its own 64 bytes
     Raw<kUnits> raw;
     load_raw<kUnits, kElem, kDirect>(raw, static_cast<const uint8_t*>(a.in) + g0 * kElem, valid, kDirect ? tp : t);
     fill_sign_table<!BF16, BF16>(sh.sign[0], g0, a.key0, a.key1, t);
+    if constexpr (MODE == Mode::Encode) drawn.draw(g0 + 32u * tp, a.worker, a.key0, a.key1);
     if (!kDirect) raw_to_lds<kUnits>(sh, raw, t);
     __syncthreads();
     float v[kRegs];
     if (kDirect) units_to_l1<kUnits, true>(sh.sign[0], raw.u, v, tp);
     else lds_to_l1<kUnits, true>(sh, sh.sign[0], v, tp);
     // (a wave reads the units of its own 8 KB of the buffer, and the first exchange stores there: no barrier)
-    if constexpr (kLanes) rotate_lanes_to_l3<false>(sh, v, lane, block, wave);
+    if constexpr (kLanes) rotate_lanes_to_l3<PRIO>(sh, v, lane, block, wave);
     else rotate_l1_to_l3<false>(sh, v, lane, wave);
     const float sgn = odd_parity4(block) ? -1.0f : 1.0f;   // Encode: the thread's values are negated
 
@@ -68,21 +85,15 @@ __global__ __launch_bounds__(kThreads) void per_worker_kernel(const ChunkArgs a)
             static_cast<float*>(a.out)[2 * p + 1] = rotated_end(r.hi);
         }
     } else if (a.range_in) {   // Encode on the min/max grid
-        const float lo = a.range_in[2 * p], hi = a.range_in[2 * p + 1];
-        l3_to_l4e_lanes<false>(sh, v, lane, block, wave);
+        l3_to_l4e_lanes<PRIO>(sh, v, lane, block, wave);
         quantize_store_range<BITS>(v, lo, hi, a.levels, g0, a.worker, a.key0, a.key1,
-                                   static_cast<uint8_t*>(a.out), tp, kInvSqrtC * sgn);
+                                   static_cast<uint8_t*>(a.out), tp, kInvSqrtC * sgn, &drawn);
     } else {
-        float s;
-        if (a.scale_in) {
-            s = a.scale_in[p];
-        } else {
-            s = chunk_absmax(sh, v, lane, wave) * kInvSqrtC;
-        }
+        const float s = a.scale_in ? hi : chunk_absmax(sh, v, lane, wave) * kInvSqrtC;
         if (a.scale_out && t == 0) a.scale_out[p] = s;
-        l3_to_l4e_lanes<false>(sh, v, lane, block, wave);
+        l3_to_l4e_lanes<PRIO>(sh, v, lane, block, wave);
         quantize_store<BITS, true, true>(v, s, a.levels, g0, a.worker, a.key0, a.key1, static_cast<uint8_t*>(a.out),
-                                         tp, sgn);
+                                         tp, sgn, &drawn);
     }
 }
 
@@ -198,12 +209,18 @@ __global__ __launch_bounds__(kThreads) void inverse_kernel(const ChunkArgs a) {
 template <bool BF16, Mode MODE>
 hipError_t launch_bits(const ChunkArgs& a, dim3 grid, hipStream_t stream) {
     if constexpr (MODE == Mode::Encode) {
-        if (a.bits == 2)
-            hipLaunchKernelGGL((per_worker_kernel<BF16, MODE, 2>), grid, dim3(kThreads), 0, stream, a);
-        else if (a.bits == 4)
-            hipLaunchKernelGGL((per_worker_kernel<BF16, MODE, 4>), grid, dim3(kThreads), 0, stream, a);
-        else
-            hipLaunchKernelGGL((per_worker_kernel<BF16, MODE, 8>), grid, dim3(kThreads), 0, stream, a);
+        const bool prio = grid.x <= 2u * (uint32_t)device_cus();
+#define THC_ENCODE(BITS)                                                                                                  \
+    if (prio) hipLaunchKernelGGL((per_worker_kernel<BF16, MODE, BITS, true>), grid, dim3(kThreads), 0, stream, a);        \
+    else hipLaunchKernelGGL((per_worker_kernel<BF16, MODE, BITS, false>), grid, dim3(kThreads), 0, stream, a)
+        if (a.bits == 2) {
+            THC_ENCODE(2);
+        } else if (a.bits == 4) {
+            THC_ENCODE(4);
+        } else {
+            THC_ENCODE(8);
+        }
+#undef THC_ENCODE
     } else {
         hipLaunchKernelGGL((per_worker_kernel<BF16, MODE, 4>), grid, dim3(kThreads), 0, stream, a);
     }

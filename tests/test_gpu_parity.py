@@ -310,3 +310,23 @@ def test_chunks_of_two_coordinates_and_a_partial_last_payload_byte(n, bits):
     assert thc.thc_payload_bytes(n, 1, bits) == (((n + 1) // 2) * 2 * bits + 7) // 8
     check_against_oracle(xs, run_path(xs, 1, 8, bits), 1, 8, bits)
     check_against_oracle(xs, run_path_fused(xs, 1, 8, bits), 1, 8, bits)
+
+
+@pytest.mark.parametrize("dtype,bits", [(torch.bfloat16, 8), (torch.float32, 2), (torch.bfloat16, 4)])
+@pytest.mark.parametrize("chunks", [1, 512, 513])
+def test_encoder_of_one_worker_around_two_workgroups_per_cu(chunks, dtype, bits):
+    """Up to and beyond the launch that the chip holds at once: onto a given range and onto the worker's own, the same
+    payload as the one-pass encoder's."""
+    from gpu_util import run_path_fused
+    n = (chunks << 14) - 99
+    print(f"one worker, {chunks} chunks {dtype} {bits} bits", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(chunks)
+    x = torch.randn(n, generator=g, device=DEV).to(dtype)
+    ref = run_path_fused([x], 14, 5, bits)
+    given, own = (torch.empty_like(ref["payloads"][0]) for _ in range(2))
+    scale = torch.empty_like(ref["scale"])
+    thc.thc_encode(x, 14, 5, 0, bits, ref["scale"], given)
+    thc.thc_encode(x, 14, 5, 0, bits, None, own, scale)
+    torch.cuda.synchronize()
+    assert torch.equal(given, ref["payloads"][0]) and torch.equal(own, given) and torch.equal(scale, ref["scale"])
