@@ -47,7 +47,8 @@ constexpr uint32_t kPerGroupMaxWorkers = 32;
 //              chunks would lose 5 %)
 //   few rounds bf16 and up to 4 bits 16: 32 workers x 48 chunks 24.1 us (32: 24.4), 64 x 16 chunks 19.6 (20.2); fp32 or 8
 //              bits, where an item is longer, 32: 32 x 64 chunks bf16 8 bits 32.1 (16: 35.5), fp32 4 bits 43.2 (46.1), 64 x 32 fp32 41.0 (44.6)
-//   Quick      4 chunks x 8 workers 14.7 -> 14.4 us with the decoder, 2 chunks x 2 workers 13.0 -> 12.4
+//   Quick      4 chunks x 8 workers 14.7 -> 14.4 us with the decoder, 2 chunks x 2 workers 13.0 -> 12.4.  (It also draws its
+//              rounding bytes while the input is on its way: 13.5 -> 13.15 with the present decoder.)
 constexpr int kFirstPollSleep = 32;
 constexpr int kFirstPollSleepPerGroup = 40;
 constexpr int kFirstPollSleepLate = 48;
@@ -120,6 +121,7 @@ struct EncodeAllCtx {
     uint32_t bidx;          // BATCH: bucket of the most recent look-up (chunks only move forward)
     uint64_t boundary;      // BATCH: first chunk of the bucket after that one
     BucketView cur, nxt;    // of the item being processed / of the item whose input is in flight
+    Drawn drawn;            // Quick: the item's rounding bytes
     static constexpr uint32_t kNone = 0xFFFFFFFFu;
 
     // MINMAX: the chunk's words as 8-byte pairs (the slots start 16-byte aligned and a chunk
@@ -365,7 +367,8 @@ struct EncodeAllCtx {
         // the look-up's register barrier as plain addresses)
         if (w == 0 && t == 0) global_ptr<float>(reinterpret_cast<uint64_t>(cur.scale))[pl] = s;
         quantize_store<BITS, false, true>(v, s, a.levels, pl << kChunkLog2, w, cur.key0, cur.key1,
-                                          global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), tp, sgn);
+                                          global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), tp, sgn,
+                                          kQuick ? &drawn : nullptr);
     }
 
     // After the workgroup's last item: its words have no later chunk to vouch for them, so
@@ -416,6 +419,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     c.cur = c.nxt = c.view_of(p0);
     if (Ctx::kDirect) c.load(p0, c.cur);
     c.fill_signs(p0, c.cur, 0u);
+    if (Ctx::kQuick) c.drawn.draw(((uint64_t)p0 << kChunkLog2) + 32u * c.tp, c.w, a.key0, a.key1);   // while the input is on its way
     __syncthreads();
     // the first chunk's input has arrived before the loop is entered, as every later
     // chunk's has by the time its item starts (see the end of the wait in back())
