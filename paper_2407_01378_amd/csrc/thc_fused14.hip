@@ -31,8 +31,7 @@ constexpr int kWavesPerSimd = 4;
 enum class Words : int {
     PerWave = 0,    // every wave publishes a word and reads all words: up to 16 workers
     PerGroup = 1,   // one word per workgroup (the waves' maxima meet in LDS), read by every wave: up to 32, and see one_reader
-    OneReader = 2,  // the same, read by one wave for all: beyond
-    Quick = 3       // PerWave for a launch of at most one workgroup per CU and one item each: nothing to overlap
+    OneReader = 2   // the same, read by one wave for all: beyond
 };
 constexpr uint32_t kPerWaveMaxWorkers = 16;
 constexpr uint32_t kPerGroupMaxWorkers = 32;
@@ -47,15 +46,16 @@ constexpr uint32_t kPerGroupMaxWorkers = 32;
 //              chunks would lose 5 %)
 //   few rounds bf16 and up to 4 bits 16: 32 workers x 48 chunks 24.1 us (32: 24.4), 64 x 16 chunks 19.6 (20.2); fp32 or 8
 //              bits, where an item is longer, 32: 32 x 64 chunks bf16 8 bits 32.1 (16: 35.5), fp32 4 bits 43.2 (46.1), 64 x 32 fp32 41.0 (44.6)
-//   Quick      4 chunks x 8 workers 14.7 -> 14.4 us with the decoder, 2 chunks x 2 workers 13.0 -> 12.4.  (It also draws its
-//              rounding bytes while the input is on its way: 13.5 -> 13.15 with the present decoder.)
+//   one item   (PerWave) 4 chunks x 8 workers 14.7 -> 14.4 us with the decoder, 2 chunks x 2 workers 13.0 -> 12.4; where more than
+//              three quarters of the places are taken 24: with the decoder, fp32 4 bits, 8 | 24, 15 x 34 chunks 23.9 | 21.0, 14 x 36
+//              23.5 | 21.3, 16 x 32 25.3 | 22.4, bf16 9 x 50 19.5 | 17.9; fewer, 12 x 30 17.4 | 18.5, 8 x 33 15.6 | 16.6
 constexpr int kFirstPollSleep = 32;
 constexpr int kFirstPollSleepPerGroup = 40;
 constexpr int kFirstPollSleepLate = 48;
 constexpr uint32_t kLateRound = 8;
 constexpr int kFirstPollSleepFewRounds = 16;   // PerGroup, OneReader
 constexpr uint32_t kFewRounds = 4;
-constexpr int kFirstPollSleepQuick = 8;
+constexpr int kFirstPollSleepOne = 8, kFirstPollSleepOneCrowded = 24;   // PerWave
 constexpr int kPollSleep = 8;
 constexpr int kPollSleepOneReader = 4;
 // fp32 gradients of all workers that do not fit the last-level cache (256 MB, and a quarter more, because part of them is
@@ -95,11 +95,13 @@ struct BucketView {
 // For many workers: with W = 64 a chunk would otherwise have 512 words, every polling wave
 // would read 2 KB per poll, and that traffic delays the words it waits for.  At W = 8 the
 // later publication costs more than the lighter polls save, so the per-wave form stays.
-template <bool BF16, bool ODD, bool BATCH, bool MINMAX = false, Words WORDS = Words::PerWave>
+// ONE: a launch of one item per workgroup.  There is no next item to load for, and the rounding bytes are drawn while
+// the input is on its way.  With the decoder, us: 8 workers x 50257 13.5 -> 13.15, 8 x 50 chunks 17.5 -> 16.4, fp32 19.7 -> 18.1, 16 x 23
+// chunks at 8 bits 25.5 -> 20.8, 2 x 200 17.2 -> 16.2, 32 x 9 at 8 bits 23.6 -> 23.0, 64 x 8 26.5 -> 26.0.
+template <bool BF16, bool ODD, bool BATCH, bool MINMAX = false, Words WORDS = Words::PerWave, bool ONE = false>
 struct EncodeAllCtx {
     static constexpr bool WGWORD = WORDS == Words::PerGroup || WORDS == Words::OneReader;
-    static constexpr bool kQuick = WORDS == Words::Quick;
-    static_assert(!MINMAX || WORDS == Words::PerWave, "the other forms exist for the symmetric grid only");
+    static_assert(!MINMAX || (WORDS == Words::PerWave && !ONE), "the other forms exist for the symmetric grid only");
     static constexpr uint32_t kWordsPerWorker = WGWORD ? 1u : kWaves;
     static constexpr int kUnits = BF16 ? 4 : 8;
     static constexpr int kElem = BF16 ? 2 : 4;
@@ -121,7 +123,7 @@ struct EncodeAllCtx {
     uint32_t bidx;          // BATCH: bucket of the most recent look-up (chunks only move forward)
     uint64_t boundary;      // BATCH: first chunk of the bucket after that one
     BucketView cur, nxt;    // of the item being processed / of the item whose input is in flight
-    Drawn drawn;            // Quick: the item's rounding bytes
+    Drawn drawn;            // ONE: the item's rounding bytes
     static constexpr uint32_t kNone = 0xFFFFFFFFu;
 
     // MINMAX: the chunk's words as 8-byte pairs (the slots start 16-byte aligned and a chunk
@@ -192,7 +194,7 @@ struct EncodeAllCtx {
     // layout.  The direct form also fills the sign table of the workgroup's next item,
     // which is read only after the barriers of this item's exchanges.
     __device__ __forceinline__ void front(float (&v)[kRegs], uint64_t p) {
-        const bool more = !kQuick && p + dp < a.chunks;
+        const bool more = !ONE && p + dp < a.chunks;
         if constexpr (kDirect) {
             units_to_l1<kUnits, true>(sh.sign[parity], raw.u, v, tp);
         } else {
@@ -212,7 +214,7 @@ struct EncodeAllCtx {
         for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));
         asm volatile("" ::: "memory");
         if (BATCH && more && p + dp >= boundary) nxt = view_of(p + dp);   // rarely: a new bucket
-        if (kDirect && !kQuick) load(p + dp, nxt);
+        if (kDirect && !ONE) load(p + dp, nxt);
         if (more) fill_signs(p + dp, nxt, parity ^ 1u);
         parity ^= 1u;
         rotate_lanes_to_l3<true>(sh, v, lane, block, wave);
@@ -277,7 +279,8 @@ struct EncodeAllCtx {
                 else __builtin_amdgcn_s_sleep(kFirstPollSleepLate);
             }
         } else {
-            __builtin_amdgcn_s_sleep(kQuick ? kFirstPollSleepQuick : kFirstPollSleep);
+            if (ONE && a.crowded) __builtin_amdgcn_s_sleep(kFirstPollSleepOneCrowded);
+            else __builtin_amdgcn_s_sleep(ONE ? kFirstPollSleepOne : kFirstPollSleep);
         }
         for (uint32_t spins = 0; polls; ++spins) {
             if constexpr (MINMAX) {
@@ -318,7 +321,7 @@ struct EncodeAllCtx {
         // registers through an empty asm tells the compiler so: the next item then starts
         // without a wait on them, which would also wait for the stores issued below.
         // (OneReader: a wave that has not polled waits for them here.)
-        if (kDirect && !kQuick) {
+        if (kDirect && !ONE) {
 #pragma unroll
             for (int j = 0; j < kUnits; ++j)
                 asm volatile("" : "+v"(raw.u[j].x), "+v"(raw.u[j].y), "+v"(raw.u[j].z), "+v"(raw.u[j].w));
@@ -368,7 +371,7 @@ struct EncodeAllCtx {
         if (w == 0 && t == 0) global_ptr<float>(reinterpret_cast<uint64_t>(cur.scale))[pl] = s;
         quantize_store<BITS, false, true>(v, s, a.levels, pl << kChunkLog2, w, cur.key0, cur.key1,
                                           global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), tp, sgn,
-                                          kQuick ? &drawn : nullptr);
+                                          ONE ? &drawn : nullptr);
     }
 
     // After the workgroup's last item: its words have no later chunk to vouch for them, so
@@ -397,12 +400,12 @@ constexpr int kStaggerSleeps = 6;   // late start of half the grid, in units of 
 // Items are (chunk, worker) pairs; workgroup g of a grid of G (a multiple of W) takes worker
 // g mod W of chunks g / W, g / W + G / W, ...  The peers of an item are therefore items of
 // the same round of other workgroups, and with every workgroup resident no wait is circular.
-template <bool BF16, int BITS, bool ODD, bool BATCH, bool MINMAX = false, Words WORDS = Words::PerWave>
+template <bool BF16, int BITS, bool ODD, bool BATCH, bool MINMAX = false, Words WORDS = Words::PerWave, bool ONE = false>
 __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(const EncodeAllArgs a,
                                                                  const FusedWorkerPtrs ptrs,
                                                                  const BatchArgs batch) {
     __shared__ Shared sh;
-    using Ctx = EncodeAllCtx<BF16, ODD, BATCH, MINMAX, WORDS>;
+    using Ctx = EncodeAllCtx<BF16, ODD, BATCH, MINMAX, WORDS, ONE>;
     const uint32_t t = threadIdx.x;
     const uint32_t p0 = blockIdx.x / a.W;
     const uint32_t block = lanes::block_of_lane(t & 63u);
@@ -414,12 +417,12 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     // the same half and nobody waits longer for a peer).  Measured, 50 buckets of 1600 chunks with a decode launch in between: 4 to 7
     // such units shorten the step by 1.3 to 3 %, 9 and more lengthen it, quarters or eighths
     // of the grid in steps do no better.
-    if (!Ctx::kQuick && a.chunks > c.dp && p0 >= (c.dp >> 1))
+    if (!ONE && a.chunks > c.dp && p0 >= (c.dp >> 1))
         for (int i = 0; i < kStaggerSleeps; ++i) __builtin_amdgcn_s_sleep(16);
     c.cur = c.nxt = c.view_of(p0);
     if (Ctx::kDirect) c.load(p0, c.cur);
     c.fill_signs(p0, c.cur, 0u);
-    if (Ctx::kQuick) c.drawn.draw(((uint64_t)p0 << kChunkLog2) + 32u * c.tp, c.w, a.key0, a.key1);   // while the input is on its way
+    if (ONE) c.drawn.draw(((uint64_t)p0 << kChunkLog2) + 32u * c.tp, c.w, a.key0, a.key1);   // while the input is on its way
     __syncthreads();
     // the first chunk's input has arrived before the loop is entered, as every later
     // chunk's has by the time its item starts (see the end of the wait in back())
@@ -433,7 +436,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
         c.front(v, p);
         c.template back<BITS>(v, p);
         if (BATCH) c.cur = c.nxt;
-        if (Ctx::kQuick) break;
+        if (ONE) break;
     }
     c.finish();
 }
@@ -969,7 +972,7 @@ inline bool one_reader(const EncodeAllArgs& a, uint64_t dp, bool short_item) {
 }
 
 template <bool BF16, int BITS, bool ODD, bool BATCH>
-hipError_t launch_encode_all_t(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch,
+hipError_t launch_encode_all_t(EncodeAllArgs a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch,
                                hipStream_t stream) {
     const uint32_t resident = resident_grid<encode_all_kernel<BF16, BITS, ODD, BATCH>>();
     uint32_t G = resident;
@@ -980,17 +983,24 @@ hipError_t launch_encode_all_t(const EncodeAllArgs& a, const FusedWorkerPtrs& pt
     // fewer resident workgroups than workers would leave peers that never run
     if (G < a.W) return hipErrorInvalidConfiguration;
     G -= G % a.W;
-#define THC_ENCODE_ALL(WORDS)                                                                                          \
+    a.crowded = 4u * G > 3u * resident;
+#define THC_ENCODE_ALL(...)                                                                                            \
     do {                                                                                                              \
-        hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, false, false, WORDS>), dim3(G), dim3(kThreads), 0,      \
-                           stream, a, ptrs, batch);                                                                   \
+        hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, false, false, __VA_ARGS__>), dim3(G), dim3(kThreads),   \
+                           0, stream, a, ptrs, batch);                                                                \
         return hipGetLastError();                                                                                     \
     } while (0)
     if constexpr (!BATCH) {
-        if (a.W > kPerGroupMaxWorkers && one_reader(a, G / a.W, BF16 && BITS <= 4)) THC_ENCODE_ALL(Words::OneReader);
-        if (a.W > kPerWaveMaxWorkers) THC_ENCODE_ALL(Words::PerGroup);
-        // every workgroup has one item, and a CU (each holds two) to itself
-        if (G == total && 2u * G <= resident) THC_ENCODE_ALL(Words::Quick);
+        const bool one = G == total;   // every workgroup has one item
+        if (a.W > kPerGroupMaxWorkers && one_reader(a, G / a.W, BF16 && BITS <= 4)) {
+            if (one) THC_ENCODE_ALL(Words::OneReader, true);
+            THC_ENCODE_ALL(Words::OneReader);
+        }
+        if (a.W > kPerWaveMaxWorkers) {
+            if (one) THC_ENCODE_ALL(Words::PerGroup, true);
+            THC_ENCODE_ALL(Words::PerGroup);
+        }
+        if (one) THC_ENCODE_ALL(Words::PerWave, true);
     }
 #undef THC_ENCODE_ALL
     hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, BATCH>), dim3(G), dim3(kThreads), 0, stream, a, ptrs,

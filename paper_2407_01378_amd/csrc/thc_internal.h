@@ -78,6 +78,7 @@ struct EncodeAllArgs {
     uint32_t* slots;     // zero on entry and on exit: chunks x encode_all_slot_words(W) words
     uint32_t* done;      // zero on entry and on exit: one arrival counter per chunk
     uint32_t* error;     // zeroed: set to 1 if a wait timed out
+    uint32_t crowded;    // set by the launch: its workgroups take more than three quarters of the places
 };
 // ---- batched forms: several buckets in one launch ---------------------------------------
 // One record per bucket in device memory, followed by the bucket's W gradient pointers and
