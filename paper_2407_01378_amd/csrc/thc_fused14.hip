@@ -82,8 +82,11 @@ struct BucketView {
 };
 
 // ODD: bf16 input with an odd number of coordinates.  Its last coordinate shares a dword
-// with nothing, which the range check of a buffer load (done per dword) would cut off, so
-// that shape keeps the element-wise loader; every other shape loads through a descriptor.
+// with nothing, which the range check of a buffer load (done per dword) would cut off: its owner
+// fetches it by itself and puts it in when the item starts.  (An element-wise loader for the last chunk, which
+// merged its registers with the whole chunks' on every item, left it to the compiler whether an item waited for the loads
+// that it had just issued: 8 workers x 8.2 M, 4 bits 66.3 us, 72.8 in a build with the registers allocated otherwise, 65.5 so; 8 x 4.2 M
+// 41.6 -> 40.4, 64 x 1 M 77.5 -> 69.4.)
 // BATCH: the launch covers several buckets (a.chunks is their total, chunks are numbered
 // through all of them); everything per bucket comes from the records in device memory.
 // MINMAX: the grid runs from the chunk's smallest to its largest value instead of
@@ -114,6 +117,7 @@ struct EncodeAllCtx {
     const BatchArgs& batch;
     Shared& sh;
     Raw<kUnits> raw;        // input of the next item to enter the pipeline, in flight
+    uint32_t odd_tail;      // ODD: the last coordinate of an odd count, in the thread that owns it, with that input
     uint32_t t, lane, wave, nwords;
     uint32_t block, tp;     // the lane's block of 32 coordinates in the wave (thc_lanes.h), in the chunk
     uint32_t w;             // worker of every item of this workgroup (the grid is a multiple of W)
@@ -162,27 +166,40 @@ struct EncodeAllCtx {
         uint64_t left = p < a.chunks ? bv.n - g0 : 0u;
         if (left > (uint64_t)kChunk) left = kChunk;
         uint64_t addr = reinterpret_cast<uint64_t>(bv.grad) + (p < a.chunks ? g0 * kElem : 0u);
-        if constexpr (ODD) {
-            if (left != 0u) load_raw<kUnits, kElem, kDirect>(raw, reinterpret_cast<const void*>(addr), (uint32_t)left, tp);
-        } else {
-            // the descriptor is the same for every lane: it belongs in scalar registers
-            addr = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32) |
-                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)addr);
-            const uint32_t bytes = (uint32_t)left * kElem;   // a multiple of 4: the count is even
-            __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                reinterpret_cast<void*>(addr), 0, bytes, 0x00020000);
-            auto units = [&](auto policy) {
-                typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+        // the descriptor is the same for every lane: it belongs in scalar registers
+        addr = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)addr);
+        const uint32_t bytes = (ODD ? (uint32_t)left & ~1u : (uint32_t)left) * kElem;   // a multiple of 4
+        __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<void*>(addr), 0, bytes, 0x00020000);
+        auto units = [&](auto policy) {
+            typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 #pragma unroll
-                for (int j = 0; j < kUnits; ++j) {
-                    // fp32: the wave's own 8 KB in coalesced order, dealt out through its part of the buffer
-                    const uint32_t unit = kDirect ? kUnits * tp + j : wave * 512u + j * 64u + lane;
-                    const u4v q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, unit * 16u, 0, decltype(policy)::value);
-                    raw.u[j] = make_uint4(q.x, q.y, q.z, q.w);
-                }
-            };
-            if (!kDirect && a.chunks * a.W > kStreamedItems) units(std::integral_constant<int, kStreaming>{});
-            else units(std::integral_constant<int, 0>{});
+            for (int j = 0; j < kUnits; ++j) {
+                // fp32: the wave's own 8 KB in coalesced order, dealt out through its part of the buffer
+                const uint32_t unit = kDirect ? kUnits * tp + j : wave * 512u + j * 64u + lane;
+                const u4v q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, unit * 16u, 0, decltype(policy)::value);
+                raw.u[j] = make_uint4(q.x, q.y, q.z, q.w);
+            }
+        };
+        if (!kDirect && a.chunks * a.W > kStreamedItems) units(std::integral_constant<int, kStreaming>{});
+        else units(std::integral_constant<int, 0>{});
+        if (ODD && (left & 1u)) {   // (the bucket's last chunk)
+            odd_tail = 0u;
+            if (tp == (uint32_t)left >> 5) odd_tail = reinterpret_cast<const uint16_t*>(addr)[left - 1u];
+        }
+    }
+    // ODD: odd_tail into the input of chunk p, whose bucket is cur.
+    __device__ __forceinline__ void put_odd_tail(uint64_t p) {
+        const uint64_t left = cur.n - ((p - cur.chunk0) << kChunkLog2);
+        if (left >= (uint64_t)kChunk || !(left & 1u) || tp != (uint32_t)left >> 5) return;
+        const uint32_t d = ((uint32_t)left & 31u) >> 1;   // dword of the thread's 16 that holds it
+#pragma unroll
+        for (int k = 0; k < kUnits; ++k) {
+            raw.u[k].x = d == 4u * k ? odd_tail : raw.u[k].x;
+            raw.u[k].y = d == 4u * k + 1u ? odd_tail : raw.u[k].y;
+            raw.u[k].z = d == 4u * k + 2u ? odd_tail : raw.u[k].z;
+            raw.u[k].w = d == 4u * k + 3u ? odd_tail : raw.u[k].w;
         }
     }
     __device__ __forceinline__ void fill_signs(uint64_t p, const BucketView& bv, uint32_t which) {
@@ -196,6 +213,7 @@ struct EncodeAllCtx {
     __device__ __forceinline__ void front(float (&v)[kRegs], uint64_t p) {
         const bool more = !ONE && p + dp < a.chunks;
         if constexpr (kDirect) {
+            if (ODD) put_odd_tail(p);
             units_to_l1<kUnits, true>(sh.sign[parity], raw.u, v, tp);
         } else {
             load(p, cur);
@@ -409,7 +427,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     const uint32_t t = threadIdx.x;
     const uint32_t p0 = blockIdx.x / a.W;
     const uint32_t block = lanes::block_of_lane(t & 63u);
-    Ctx c{a, ptrs, batch, sh, {}, t, t & 63u, t >> 6, (MINMAX ? 2u : 1u) * Ctx::kWordsPerWorker * a.W, block,
+    Ctx c{a, ptrs, batch, sh, {}, 0u, t, t & 63u, t >> 6, (MINMAX ? 2u : 1u) * Ctx::kWordsPerWorker * a.W, block,
           (t & ~63u) | block, blockIdx.x - p0 * a.W, gridDim.x / a.W, 0u, Ctx::kNone, 0u, 0u, {}, {}};
     if (p0 >= a.chunks) return;
     // With more than one round of items, the second half of the grid starts about 2.6 us late

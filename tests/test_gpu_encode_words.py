@@ -95,3 +95,24 @@ def test_expired_wait_of_every_form_of_agreement(W, rounds, dtype, bits):
     torch.cuda.synchronize()
     assert int(ws.count_nonzero()) == 0
     _matches_the_per_worker_calls(xs, bits, scale, payloads)
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("W,chunks,rest", [(3, 1, 1), (3, 2, 31), (8, 4, 33), (8, 3, 16383), (24, 2, 8191), (40, 1, 16351),   # one round
+                                           (2, 300, 1), (8, 70, 65), (24, 25, 16383), (40, 14, 32769 - 16384)])
+def test_odd_counts_of_bf16(W, chunks, rest, bits):
+    """The last coordinate of an odd count, by the thread of the last chunk that owns it; in launches of one round and of
+    several, for every form of agreement."""
+    n = ((chunks - 1) << 14) + rest
+    print(f"odd W={W} n={n} {bits} bits", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(W + rest)
+    xs = [torch.randn(n, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(W)]
+    for w in range(W):
+        xs[w][-1] = 40.0 + w          # it decides the range of its chunk
+    P, nb = thc.thc_num_chunks(n, 14), thc.thc_payload_bytes(n, 14, bits)
+    ws = torch.empty(thc.thc_encode_all_workspace_bytes(W, n, 14), dtype=torch.uint8, device="cuda")
+    scale = torch.full((P,), float("nan"), device="cuda")
+    payloads = [torch.full((nb,), 0xAA, dtype=torch.uint8, device="cuda") for _ in range(W)]
+    thc.thc_encode_all(xs, 14, 7, bits, payloads, scale, ws)
+    _matches_the_per_worker_calls(xs, bits, scale, payloads)
