@@ -74,11 +74,11 @@ struct EncodeAllArgs {
     uint32_t key0, key1;
     uint32_t max_spins;  // bound on the polls of one wait
     uint32_t levels;     // largest grid index L
+    uint32_t crowded;    // set by the launch: its workgroups take more than three quarters of the places
     float* scale;        // out: chunks shared scales
     uint32_t* slots;     // zero on entry and on exit: chunks x encode_all_slot_words(W) words
     uint32_t* done;      // zero on entry and on exit: one arrival counter per chunk
     uint32_t* error;     // zeroed: set to 1 if a wait timed out
-    uint32_t crowded;    // set by the launch: its workgroups take more than three quarters of the places
 };
 // ---- batched forms: several buckets in one launch ---------------------------------------
 // One record per bucket in device memory, followed by the bucket's W gradient pointers and

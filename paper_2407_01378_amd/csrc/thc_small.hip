@@ -198,14 +198,25 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
 
     if (kAhead) load(first);
     fill_signs(first, 0u);
+    // What the items need of the arguments later, read while the input is on its way: left to the compiler, some of these
+    // scalar reads stand where their values are used, behind the barriers, and the wave waits for them there.
+    uint64_t payload_at = OP != SmallOp::Absmax ? reinterpret_cast<uint64_t>(ptrs.payload[w < a.W ? w : 0u]) : 0u;
+    uint64_t out_at = reinterpret_cast<uint64_t>(a.scale_out), in_at = reinterpret_cast<uint64_t>(a.scale_in);
+    uint32_t step = stride;
+    asm volatile("" : "+s"(payload_at), "+s"(out_at), "+s"(in_at), "+s"(step));
+    uint8_t* payload = global_ptr<uint8_t>(payload_at);
+    float* scale_out = global_ptr<float>(out_at);
+    const float* scale_in = global_ptr<const float>(in_at);
     __syncthreads();
     uint32_t cur = 0u;
     // EncodeSpread: first chunk and number of chunks of this and of the previous item
     const uint64_t chunks = a.padded >> a.l;
     uint64_t prev0 = 0u;
     uint32_t prev_live = 0u;
-    for (uint64_t item = first; item < a.items; item += stride) {
+    for (uint64_t item = first; item < a.items; item += step) {
         const uint64_t u0 = coord0_of(item);
+        const uint64_t p = (u0 >> a.l) + chunk;
+        const bool exists = (p << a.l) < a.padded;
         const uint32_t sx = sign[cur * sign_words + (region << (unit_log2 - 5u)) + part * 64u + block];
         float v[kRegs];
         if constexpr (BF16) {
@@ -236,8 +247,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
 #pragma unroll
         for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));   // converted before `raw` is loaded again
         asm volatile("" ::: "memory");
-        if (kAhead) load(item + stride);
-        if (item + stride < a.items) fill_signs(item + stride, cur ^ 1u);
+        if (kAhead) load(item + step);
+        if (item + step < a.items) fill_signs(item + step, cur ^ 1u);
 
         // (as in the chunk-2^14 encoder: the rotation ahead of the other workgroup's quantizer.  Encoder alone, us: 8 workers
         // x 2^24, chunk 2^13 129 -> 116, 64 x 2^22, chunk 2^12 250 -> 221; one workgroup per CU 48.7 -> 47.0)
@@ -288,8 +299,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
         }
         const bool leader = CLASS == 0 ? (block & ((1u << (a.l - 5u)) - 1u)) == 0u
                                        : (CLASS == 1 && a.l == 10u ? (lane & 31u) == 0u : lane == 0u);
-        const uint64_t p = (u0 >> a.l) + chunk;
-        const bool exists = (p << a.l) < a.padded;
         float s = 0.0f;
         if (OP == SmallOp::EncodeAll) {
             // all workers' waves have published behind the barrier (which also orders the sign
@@ -301,7 +310,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 const float4 f = *reinterpret_cast<const float4*>(at + i);
                 s = fmaxf(fmaxf(s, fmaxf(f.x, f.y)), fmaxf(f.z, f.w));
             }
-            if (leader && group == 0u && part == 0u && exists && a.scale_out) a.scale_out[p] = s;
+            if (leader && group == 0u && part == 0u && exists && out_at) scale_out[p] = s;
         } else if (OP == SmallOp::EncodeSpread) {
             // The waves' maxima meet in LDS; the first wave publishes the workgroup's word of every chunk and waits for
             // the peers' (see EncodeAllCtx in thc_fused14.hip, whose protocol this is, in the form with one reader).
@@ -357,7 +366,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             if (exists)
                 for (uint32_t i = 0; i < parts; ++i) x = max(x, got[chunk * parts + i]);
             s = __uint_as_float(x);
-            if (leader && mine == 0u && group == 0u && part == 0u && exists) a.scale_out[p] = s;
+            if (leader && mine == 0u && group == 0u && part == 0u && exists) scale_out[p] = s;
         } else if (OP == SmallOp::Absmax) {
             if (CLASS == 2) {
                 float* at = red_row + cur * red_words;
@@ -365,14 +374,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 __syncthreads();
                 s = 0.0f;
                 for (uint32_t i = 0; i < wpw; ++i) s = fmaxf(s, at[i]);
-                if (leader && part == 0u && exists) a.scale_out[p] = s;
+                if (leader && part == 0u && exists) scale_out[p] = s;
             } else {
-                if (leader && exists) a.scale_out[p] = __uint_as_float(most);
+                if (leader && exists) scale_out[p] = __uint_as_float(most);
                 __syncthreads();   // the next item's sign table
             }
         } else {
-            s = exists ? a.scale_in[p] : 0.0f;
-            if (leader && part == 0u && exists && a.scale_out) a.scale_out[p] = s;
+            s = exists ? scale_in[p] : 0.0f;
+            if (leader && part == 0u && exists && out_at) scale_out[p] = s;
             __syncthreads();       // the next item's sign table
         }
 
@@ -401,7 +410,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 quantize_half<BITS, kClamp, false, kOffset, true>(v, 1, b1, -s, inv, base, a.levels, worker, a.key0, a.key1, by, norm, neg);
             }
             pack_bytes<BITS>(by, pk);
-            uint8_t* dst = ptrs.payload[w];
+            uint8_t* dst = payload;
             if constexpr (CLASS == 0) {   // 32 consecutive coordinates
                 if (exists) store_packed<BITS>(pk, dst + b0 * (2u * BITS));
             } else if (exists) {
