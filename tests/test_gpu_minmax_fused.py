@@ -245,3 +245,15 @@ def test_one_pass_minmax_expired_wait_sets_the_error_word_and_every_wave_exits(r
     assert torch.equal(got["range"], ref["range"])
     for w in range(W):
         assert torch.equal(got["payloads"][w], ref["payloads"][w])
+
+
+@pytest.mark.parametrize("dtype,bits", [(torch.bfloat16, 4), (torch.float32, 8), (torch.bfloat16, 2)])
+@pytest.mark.parametrize("W,chunks", [(8, 48), (8, 49), (8, 64), (8, 65), (17, 30), (17, 31)])   # 384 and 512 places, and beyond
+def test_one_pass_minmax_around_one_round_of_workgroups(W, chunks, dtype, bits):
+    n = (chunks << 14) - 4097
+    print(f"minmax one round W={W} chunks={chunks} {dtype} {bits} bits", flush=True)
+    xs = [_rand(n, dtype, 7 * w + chunks, scale=10.0 ** (-2 - (w % 3)), shift=3e-3) for w in range(W)]
+    got, ref = run_fused(xs, 23, bits, True), run_minmax(xs, L14, 23, bits, True, torch.float32)
+    assert torch.equal(got["range"], ref["range"])
+    assert all(torch.equal(got["payloads"][w], ref["payloads"][w]) for w in range(W))
+    assert torch.equal(got["out"], ref["out"])
