@@ -8,6 +8,8 @@
 // for coalesced fp32 stores).
 #pragma once
 
+#include <type_traits>
+
 #include "thc_device.h"
 #include "thc_lanes.h"
 #include "thc_layout14.h"
@@ -617,15 +619,18 @@ __device__ __forceinline__ void pack_bytes(const uint32_t (&by)[8], uint32_t (&p
             pk[d] = by[4 * d] | (by[4 * d + 1] << 2) | (by[4 * d + 2] << 4) | (by[4 * d + 3] << 6);
     }
 }
-template <int BITS, bool CLAMP, bool FOLD, bool RANGED, bool NEG = false>
+// drawn: a pointer to a Drawn, or nullptr: the bytes are drawn here.  (A question of the type: asked of the value, it
+// changed the registers of the persistent kernels too, and cost the batched one at 8 bits 19 operations.)
+template <int BITS, bool CLAMP, bool FOLD, bool RANGED, bool NEG = false, class D = decltype(nullptr)>
 __device__ __forceinline__ void quantize_pack(const float (&v)[kRegs], float sub, float mul, float base,
                                               uint32_t L, uint64_t g, uint32_t worker, uint32_t key0,
                                               uint32_t key1, uint32_t (&pk)[BITS], float norm = kInvSqrtC,
-                                              float sgn = 1.0f, const Drawn* drawn = nullptr) {
+                                              float sgn = 1.0f, D drawn = nullptr) {
     uint32_t by[8];                       // index bytes; by[m] serves payload word m / kSub
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-        if (drawn) quantize_drawn<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, drawn->rb[half], sub, mul, base, L, by, norm, sgn);
+        if constexpr (!std::is_same_v<D, decltype(nullptr)>)
+            quantize_drawn<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, drawn->rb[half], sub, mul, base, L, by, norm, sgn);
         else
             quantize_half<BITS, CLAMP, FOLD, RANGED, NEG>(v, half, (g >> 4) + half, sub, mul, base, L, worker, key0, key1, by,
                                                           norm, sgn);
@@ -652,11 +657,11 @@ __device__ __forceinline__ void store_packed(const uint32_t (&pk)[BITS], uint8_t
 // dead there too when s is the chunk's largest magnitude: 0 <= y + s <= 2 s, and
 // 2 s * inv <= L (1 + 2^-24), so t < L + 255.5/256 + L 2^-24 < L + 1.
 // NEG: the thread's values are negated where sgn = -1 (see rotate_lanes_to_l3); t: its block of 32.
-template <int BITS, bool CLAMP, bool NEG = false>
+template <int BITS, bool CLAMP, bool NEG = false, class D = decltype(nullptr)>
 __device__ __forceinline__ void quantize_store(const float (&v)[kRegs], float s, uint32_t L, uint64_t g0,
                                                uint32_t worker, uint32_t key0, uint32_t key1,
                                                uint8_t* payload, uint32_t t, float sgn = 1.0f,
-                                               const Drawn* drawn = nullptr) {
+                                               D drawn = nullptr) {
     constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;   // both grids of this width
     const float two = s + s;
     const bool ranged = two >= kMinRange;   // false: an all-zero chunk, or one too small for L / two
@@ -677,11 +682,11 @@ __device__ __forceinline__ void quantize_store(const float (&v)[kRegs], float s,
 // Min/max grid: idx = floor((y - lo) * inv + u), inv = L / (hi - lo) (0 for a constant chunk
 // and for one narrower than kMinRange).
 // ROTATED false: v holds y itself (the unrotated, zero-padded gradient), not 2^7 y.
-template <int BITS, bool ROTATED = true, bool CLAMP = true>
+template <int BITS, bool ROTATED = true, bool CLAMP = true, class D = decltype(nullptr)>
 __device__ __forceinline__ void quantize_store_range(const float (&v)[kRegs], float lo, float hi, uint32_t L,
                                                      uint64_t g0, uint32_t worker, uint32_t key0,
                                                      uint32_t key1, uint8_t* payload, uint32_t t,
-                                                     float norm = kInvSqrtC, const Drawn* drawn = nullptr) {
+                                                     float norm = kInvSqrtC, D drawn = nullptr) {
     const float width = hi - lo;
     const float inv = width >= kMinRange ? (float)L / width : 0.0f;
     const uint64_t g = g0 + (uint64_t)t * 32u;

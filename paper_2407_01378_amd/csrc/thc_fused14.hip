@@ -117,7 +117,8 @@ struct EncodeAllCtx {
     const BatchArgs& batch;
     Shared& sh;
     Raw<kUnits> raw;        // input of the next item to enter the pipeline, in flight
-    uint32_t odd_tail;      // ODD: the last coordinate of an odd count, in the thread that owns it, with that input
+    struct Nothing {};      // (members that a form does not have take no part in its register allocation)
+    std::conditional_t<ODD, uint32_t, Nothing> odd_tail;   // the last coordinate of an odd count, in the thread that owns it, with that input
     uint32_t t, lane, wave, nwords;
     uint32_t block, tp;     // the lane's block of 32 coordinates in the wave (thc_lanes.h), in the chunk
     uint32_t w;             // worker of every item of this workgroup (the grid is a multiple of W)
@@ -127,7 +128,7 @@ struct EncodeAllCtx {
     uint32_t bidx;          // BATCH: bucket of the most recent look-up (chunks only move forward)
     uint64_t boundary;      // BATCH: first chunk of the bucket after that one
     BucketView cur, nxt;    // of the item being processed / of the item whose input is in flight
-    Drawn drawn;            // ONE: the item's rounding bytes
+    std::conditional_t<ONE, Drawn, Nothing> drawn;         // the item's rounding bytes
     static constexpr uint32_t kNone = 0xFFFFFFFFu;
 
     // MINMAX: the chunk's words as 8-byte pairs (the slots start 16-byte aligned and a chunk
@@ -184,10 +185,16 @@ struct EncodeAllCtx {
         };
         if (!kDirect && a.chunks * a.W > kStreamedItems) units(std::integral_constant<int, kStreaming>{});
         else units(std::integral_constant<int, 0>{});
-        if (ODD && (left & 1u)) {   // (the bucket's last chunk)
-            odd_tail = 0u;
-            if (tp == (uint32_t)left >> 5) odd_tail = reinterpret_cast<const uint16_t*>(addr)[left - 1u];
+        if constexpr (ODD) {
+            if (left & 1u) {   // (the bucket's last chunk)
+                odd_tail = 0u;
+                if (tp == (uint32_t)left >> 5) odd_tail = reinterpret_cast<const uint16_t*>(addr)[left - 1u];
+            }
         }
+    }
+    __device__ __forceinline__ auto drawn_bytes() const {
+        if constexpr (ONE) return static_cast<const Drawn*>(&drawn);
+        else return nullptr;
     }
     // ODD: odd_tail into the input of chunk p, whose bucket is cur.
     __device__ __forceinline__ void put_odd_tail(uint64_t p) {
@@ -213,7 +220,7 @@ struct EncodeAllCtx {
     __device__ __forceinline__ void front(float (&v)[kRegs], uint64_t p) {
         const bool more = !ONE && p + dp < a.chunks;
         if constexpr (kDirect) {
-            if (ODD) put_odd_tail(p);
+            if constexpr (ODD) put_odd_tail(p);
             units_to_l1<kUnits, true>(sh.sign[parity], raw.u, v, tp);
         } else {
             load(p, cur);
@@ -380,7 +387,7 @@ struct EncodeAllCtx {
             // (no clamp: lo and hi are the chunk's own extremes, see quantize_pack)
             quantize_store_range<BITS, true, false>(v, lo, hi, a.levels, pl << kChunkLog2, w, cur.key0, cur.key1,
                                              global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), tp,
-                                             kInvSqrtC * sgn, ONE ? &drawn : nullptr);
+                                             kInvSqrtC * sgn, drawn_bytes());
             return;
         }
         const float s = __uint_as_float(sbits);
@@ -389,7 +396,7 @@ struct EncodeAllCtx {
         if (w == 0 && t == 0) global_ptr<float>(reinterpret_cast<uint64_t>(cur.scale))[pl] = s;
         quantize_store<BITS, false, true>(v, s, a.levels, pl << kChunkLog2, w, cur.key0, cur.key1,
                                           global_ptr<uint8_t>(reinterpret_cast<uint64_t>(cur.payload)), tp, sgn,
-                                          ONE ? &drawn : nullptr);
+                                          drawn_bytes());
     }
 
     // After the workgroup's last item: its words have no later chunk to vouch for them, so
@@ -427,7 +434,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     const uint32_t t = threadIdx.x;
     const uint32_t p0 = blockIdx.x / a.W;
     const uint32_t block = lanes::block_of_lane(t & 63u);
-    Ctx c{a, ptrs, batch, sh, {}, 0u, t, t & 63u, t >> 6, (MINMAX ? 2u : 1u) * Ctx::kWordsPerWorker * a.W, block,
+    Ctx c{a, ptrs, batch, sh, {}, {}, t, t & 63u, t >> 6, (MINMAX ? 2u : 1u) * Ctx::kWordsPerWorker * a.W, block,
           (t & ~63u) | block, blockIdx.x - p0 * a.W, gridDim.x / a.W, 0u, Ctx::kNone, 0u, 0u, {}, {}};
     if (p0 >= a.chunks) return;
     // With more than one round of items, the second half of the grid starts about 2.6 us late
@@ -440,7 +447,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void encode_all_kernel(con
     c.cur = c.nxt = c.view_of(p0);
     if (Ctx::kDirect) c.load(p0, c.cur);
     c.fill_signs(p0, c.cur, 0u);
-    if (ONE) c.drawn.draw(((uint64_t)p0 << kChunkLog2) + 32u * c.tp, c.w, a.key0, a.key1);   // while the input is on its way
+    if constexpr (ONE) c.drawn.draw(((uint64_t)p0 << kChunkLog2) + 32u * c.tp, c.w, a.key0, a.key1);   // while the input is on its way
     __syncthreads();
     // the first chunk's input has arrived before the loop is entered, as every later
     // chunk's has by the time its item starts (see the end of the wait in back())
