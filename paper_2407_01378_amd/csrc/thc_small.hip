@@ -16,10 +16,10 @@
 // before each further stage.  Bound by vector-ALU issue while its rounds are full (8 workers, chunk 2^12, 8 bits: 27.8
 // operations per worker-coordinate by the counters; one workgroup of 16 waves per CU, a round of 256 items 6 us:
 // 1280 items 38.8 us, 1536 42.8, of which the operations are 35.6); a last round that is nearly empty takes as long as
-// a full one (1600 items 48.2 us, 1792 48.7), and a launch of one item per workgroup is the item's own chain of loads,
-// stages and barriers (4 workers x 2^20 fp32, chunk 2^10: 6.9 us, and 5.7 of the decoder).
-//   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 69 us
-//   (3.6 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 13.3 us.  Before: one range and one encode
+// a full one (1600 items 48.2 us, 1792 48.7; with wave priorities 1600 47.0), and a launch of one item per workgroup is the item's own chain of loads,
+// stages and barriers (4 workers x 2^20 fp32, chunk 2^10: 6.4 us, and 5.7 of the decoder).
+//   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 67 us
+//   (3.7 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 12.8 us.  Before: one range and one encode
 //   launch per worker of the generic kernels, which load element by element and take a
 //   barrier per stage above 2^4.
 //
