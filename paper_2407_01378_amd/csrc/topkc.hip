@@ -7,6 +7,7 @@
 
 #include "thc_device.h"
 #include "thc_internal.h"
+#include "topkc_search.h"
 
 #pragma clang fp contract(off)
 
@@ -611,8 +612,8 @@ __global__ __launch_bounds__(256) void scatter_kernel(const uint16_t* values, co
 
 // The dense estimate in ONE pass over the output: every coordinate is written exactly once,
 // float(value) / W inside the selected chunks and 0 elsewhere.  `indices` is ascending, so a
-// workgroup that owns a contiguous range of chunks finds its first selected chunk by one
-// binary search and then walks the list: per tile of kTileChunks chunks, thread t looks at
+// workgroup that owns a contiguous range of chunks searches for its first selected chunk
+// (topkc_search.h) and then walks the list: per tile of kTileChunks chunks, thread t looks at
 // indices[j + t] and, if that chunk lies in the tile, records its rank j + t for the
 // chunk; no more than kTileChunks selected chunks can lie in a tile, so one look per thread
 // sees them all.  `out` must be 16-byte aligned.
@@ -630,24 +631,14 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_dense_kernel(
     const uint64_t begin = (uint64_t)blockIdx.x * chunks_per_group;
     if (begin >= P) return;
     const uint64_t end = begin + chunks_per_group < P ? begin + chunks_per_group : P;
-    // first j with indices[j] >= begin: 256 positions at a time cut what is left to 1/256 (a halving search is a chain of 18
-    // dependent reads for a quarter million of indices)
-    uint32_t lo = 0, hi = J;   // indices[lo - 1] < begin <= indices[hi]
-    while (lo < hi) {
-        const uint32_t step = (hi - lo + kScatterThreads - 1u) / kScatterThreads;   // (the last step ends at hi or behind it)
-        const uint32_t at = lo + t * step;
-        const bool below = at < hi && (uint64_t)indices[at] < begin;
-        const uint32_t count = (uint32_t)__syncthreads_count(below);   // the first `count` probes are below
-        if (count != 0u) {
-            const uint32_t last = lo + (count - 1u) * step;
-            const uint32_t end_at = last + step;
-            lo = last + 1u;
-            hi = end_at < hi ? end_at : hi;
-        } else {
-            hi = lo;
-        }
+    SearchRange r = {0u, J};   // -> the first j with indices[j] >= begin
+    while (r.lo < r.hi) {
+        const uint32_t step = r.step(kScatterThreads);
+        const uint64_t at = r.at(t, step);
+        const bool below = at < r.hi && (uint64_t)indices[at] < begin;
+        r.cut((uint32_t)__syncthreads_count(below), step);
     }
-    uint32_t j = lo;
+    uint32_t j = r.lo;
     const float Wf = (float)W;
     const uint32_t units_per_chunk = C / 4u;            // 16-byte units of fp32 output per chunk
     const uint32_t shift = 31u - (uint32_t)__builtin_clz(units_per_chunk);
