@@ -626,7 +626,7 @@ constexpr uint64_t kScatterGroups = 1024;
 __global__ __launch_bounds__(kScatterThreads) void scatter_dense_kernel(
     const uint16_t* values, const uint32_t* indices, uint32_t J, uint32_t C, uint32_t W, uint64_t n, uint64_t P,
     uint64_t chunks_per_group, float* out) {
-    __shared__ int32_t rank[kTileChunks];
+    __shared__ uint32_t rank[kTileChunks];
     const uint32_t t = threadIdx.x;
     const uint64_t begin = (uint64_t)blockIdx.x * chunks_per_group;
     if (begin >= P) return;
@@ -644,21 +644,21 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_dense_kernel(
     const uint32_t shift = 31u - (uint32_t)__builtin_clz(units_per_chunk);
     for (uint64_t c0 = begin; c0 < end; c0 += kTileChunks) {
         const uint64_t c1 = c0 + kTileChunks < end ? c0 + kTileChunks : end;
-        rank[t] = -1;
+        rank[t] = kNotSelected;
         __syncthreads();
         const uint64_t cand = (uint64_t)j + t < (uint64_t)J ? (uint64_t)indices[j + t] : ~0ull;
         const bool inside = cand >= c0 && cand < c1;    // cand >= c0 whenever the list is ascending
-        if (inside) rank[cand - c0] = (int32_t)(j + t);
+        if (inside) rank[cand - c0] = j + t;
         j += (uint32_t)__syncthreads_count(inside);     // also orders the writes of rank before its reads
         const uint64_t unit0 = c0 * units_per_chunk;
         const uint64_t units = (c1 - c0) * units_per_chunk;
         for (uint64_t u = t; u < units; u += kScatterThreads) {
             const uint32_t lc = (uint32_t)(u >> shift);
             const uint32_t e0 = ((uint32_t)u & (units_per_chunk - 1u)) * 4u;
-            const int32_t r = rank[lc];
+            const uint32_t place = rank[lc];
             float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (r >= 0) {
-                const uint2 q = *reinterpret_cast<const uint2*>(values + (uint64_t)(uint32_t)r * C + e0);
+            if (is_selected(place)) {
+                const uint2 q = *reinterpret_cast<const uint2*>(values + (uint64_t)place * C + e0);
                 x[0] = f16_bits_to_f32(q.x & 0xFFFFu) / Wf;
                 x[1] = f16_bits_to_f32(q.x >> 16) / Wf;
                 x[2] = f16_bits_to_f32(q.y & 0xFFFFu) / Wf;

@@ -13,6 +13,10 @@
 
 namespace thc {
 
+// A chunk's place in the list, or that it has none: a list of up to 2^32 - 1 entries has no such place.
+constexpr uint32_t kNotSelected = 0xFFFFFFFFu;
+THC_SEARCH_HD bool is_selected(uint32_t place) { return place != kNotSelected; }
+
 // Entries in front of lo are below the bound that is looked for, entry hi (or the end of the list) is not.
 struct SearchRange {
     uint32_t lo, hi;

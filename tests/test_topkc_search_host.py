@@ -1,6 +1,6 @@
 """The dense estimate's search in the list of selected chunks (topkc_search.h) against the position it has by
 construction, for lists of every length up to the largest that the entry points take (2^32 - 1 entries, where 32-bit
-sums of positions come round).  The check is a small C++ program (tests/topkc_search_check.cpp) compiled with g++."""
+sums of positions come round), and the mark of a chunk that is not in it.  The check is a small C++ program (tests/topkc_search_check.cpp) compiled with g++."""
 import os
 import shutil
 import subprocess

@@ -39,6 +39,9 @@ int main() {
             for (uint64_t part = 0; part <= 64; ++part)
                 for (uint64_t off : {0ull, 1ull, 2ull, 300ull})
                     search(J, stride, (J * stride / 64) * part + off, 256u);
+    for (uint32_t place : {0u, 1u, 0x7FFFFFFFu, 0x80000000u, 0xFFFFFFFEu})   // every place that a list has
+        if (!thc::is_selected(place)) ++bad;
+    if (thc::is_selected(thc::kNotSelected)) ++bad;
     printf("%d problems\n", bad);
     return bad != 0;
 }
