@@ -996,47 +996,53 @@ inline bool one_reader(const EncodeAllArgs& a, uint64_t dp, bool short_item) {
     return !(short_item && (dp & 1u) == 0u && a.chunks > kFewRounds * dp && a.chunks < kLateRound * dp);
 }
 
-template <bool BF16, int BITS, bool ODD, bool BATCH>
-hipError_t launch_encode_all_t(EncodeAllArgs a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch,
-                               hipStream_t stream) {
-    const uint32_t resident = resident_grid<encode_all_kernel<BF16, BITS, ODD, BATCH>>();
-    uint32_t G = resident;
-    if (G == 0) return hipErrorInvalidValue;
+// Grid of an encoder, whose workgroups wait for one another and have to be resident all at once: what the device keeps of
+// the very kernel that is launched (its forms differ in registers), and, as every workgroup keeps one worker, a whole
+// number of chunks per round.  0: not even the workgroups of one chunk.
+template <auto kernel>
+uint32_t agreeing_grid(const EncodeAllArgs& a) {
     const uint64_t total = a.chunks * a.W;
-    if (G > total) G = (uint32_t)total;
-    // every workgroup keeps one worker, so the grid is a whole number of chunks per round;
-    // fewer resident workgroups than workers would leave peers that never run
-    if (G < a.W) return hipErrorInvalidConfiguration;
-    G -= G % a.W;
-    a.crowded = 4u * G > 3u * resident;
-#define THC_ENCODE_ALL(...)                                                                                            \
-    do {                                                                                                              \
-        hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, false, false, __VA_ARGS__>), dim3(G), dim3(kThreads),   \
-                           0, stream, a, ptrs, batch);                                                                \
-        return hipGetLastError();                                                                                     \
-    } while (0)
-    if constexpr (!BATCH) {
-        const bool one = G == total;   // every workgroup has one item
-        if (a.W > kPerGroupMaxWorkers && one_reader(a, G / a.W, BF16 && BITS <= 4)) {
-            if (one) THC_ENCODE_ALL(Words::OneReader, true);
-            THC_ENCODE_ALL(Words::OneReader);
-        }
-        if (a.W > kPerWaveMaxWorkers) {
-            if (one) THC_ENCODE_ALL(Words::PerGroup, true);
-            THC_ENCODE_ALL(Words::PerGroup);
-        }
-        if (one) THC_ENCODE_ALL(Words::PerWave, true);
-    }
-#undef THC_ENCODE_ALL
-    hipLaunchKernelGGL((encode_all_kernel<BF16, BITS, ODD, BATCH>), dim3(G), dim3(kThreads), 0, stream, a, ptrs,
-                       batch);
+    uint64_t G = resident_grid<kernel>();
+    if (G > total) G = total;
+    return (uint32_t)(G - G % a.W);
+}
+template <auto kernel>
+hipError_t launch_agreeing(EncodeAllArgs a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch, hipStream_t stream) {
+    const uint32_t G = agreeing_grid<kernel>(a);
+    if (G == 0) return hipErrorInvalidConfiguration;
+    a.crowded = 4ull * G > 3ull * resident_grid<kernel>();
+    hipLaunchKernelGGL(kernel, dim3(G), dim3(kThreads), 0, stream, a, ptrs, batch);
     return hipGetLastError();
+}
+// The form of one item per workgroup where that is a launch of it, the persistent one otherwise.
+template <bool BF16, int BITS, bool ODD, bool MINMAX, Words WORDS>
+hipError_t launch_one_or_persistent(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, hipStream_t stream) {
+    constexpr auto one = encode_all_kernel<BF16, BITS, ODD, false, MINMAX, WORDS, true>;
+    if (agreeing_grid<one>(a) == a.chunks * a.W) return launch_agreeing<one>(a, ptrs, BatchArgs{}, stream);
+    return launch_agreeing<encode_all_kernel<BF16, BITS, ODD, false, MINMAX, WORDS>>(a, ptrs, BatchArgs{}, stream);
+}
+
+template <bool BF16, int BITS, bool ODD, bool BATCH>
+hipError_t launch_encode_all_t(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch,
+                               hipStream_t stream) {
+    if constexpr (BATCH) {
+        return launch_agreeing<encode_all_kernel<BF16, BITS, ODD, true>>(a, ptrs, batch, stream);
+    } else {
+        if (a.W > kPerGroupMaxWorkers) {
+            const uint64_t dp = agreeing_grid<encode_all_kernel<BF16, BITS, ODD, false, false, Words::OneReader>>(a) / a.W;
+            if (one_reader(a, dp, BF16 && BITS <= 4))
+                return launch_one_or_persistent<BF16, BITS, ODD, false, Words::OneReader>(a, ptrs, stream);
+        }
+        if (a.W > kPerWaveMaxWorkers)
+            return launch_one_or_persistent<BF16, BITS, ODD, false, Words::PerGroup>(a, ptrs, stream);
+        return launch_one_or_persistent<BF16, BITS, ODD, false, Words::PerWave>(a, ptrs, stream);
+    }
 }
 
 template <bool BATCH>
 hipError_t launch_encode_all_pick(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, const BatchArgs& batch,
                                   bool bf16, bool odd, uint32_t bits, hipStream_t stream) {
-    if (bf16 && odd) {   // an odd count of bf16 somewhere: element-wise loader for the last coordinate
+    if (bf16 && odd) {   // an odd count of bf16 somewhere: the last coordinate comes by itself
         if (bits == 2) return launch_encode_all_t<true, 2, true, BATCH>(a, ptrs, batch, stream);
         if (bits == 4) return launch_encode_all_t<true, 4, true, BATCH>(a, ptrs, batch, stream);
         return launch_encode_all_t<true, 8, true, BATCH>(a, ptrs, batch, stream);
@@ -1132,29 +1138,11 @@ hipError_t launch_encode_all_fused(const EncodeAllArgs& a, const FusedWorkerPtrs
 // The min/max grid through the same kernel: a.scale receives (lo, hi) pairs and a.slots has
 // twice the words per chunk.  Launches of one round take the form without a next item here too (with the decoder and the
 // clearing launch, us: 8 workers x 100000 16.7 -> 14.8, 8 x 2^20 23.7 -> 22.3, 16 x 0.5 M fp32 30.2 -> 26.0, 32 x 2^18 33.8 -> 30.9).
-hipError_t launch_encode_all_ranged(const EncodeAllArgs& args, const FusedWorkerPtrs& ptrs, bool bf16,
+hipError_t launch_encode_all_ranged(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, bool bf16,
                                     uint32_t bits, hipStream_t stream) {
     using namespace k14;
-    EncodeAllArgs a = args;
-    const BatchArgs none{};
     const bool odd = (a.n & 1u) != 0u;
-#define THC_RANGED(BF, B, O)                                                                       \
-    do {                                                                                           \
-        uint32_t G = resident_grid<encode_all_kernel<BF, B, O, false, true>>();                    \
-        if (G == 0) return hipErrorInvalidValue;                                                   \
-        const uint64_t total = a.chunks * a.W;                                                     \
-        a.crowded = 4ull * total > 3ull * G;                                                       \
-        if (G > total) G = (uint32_t)total;                                                        \
-        if (G < a.W) return hipErrorInvalidConfiguration;                                          \
-        G -= G % a.W;                                                                              \
-        if (G == total)                                                                            \
-            hipLaunchKernelGGL((encode_all_kernel<BF, B, O, false, true, Words::PerWave, true>),   \
-                               dim3(G), dim3(kThreads), 0, stream, a, ptrs, none);                 \
-        else                                                                                       \
-            hipLaunchKernelGGL((encode_all_kernel<BF, B, O, false, true>), dim3(G), dim3(kThreads), \
-                               0, stream, a, ptrs, none);                                          \
-        return hipGetLastError();                                                                  \
-    } while (0)
+#define THC_RANGED(BF, B, O) return launch_one_or_persistent<BF, B, O, true, Words::PerWave>(a, ptrs, stream)
     if (a.chunks == 0) return hipSuccess;
     if (bf16 && odd) {
         if (bits == 2) THC_RANGED(true, 2, true);

@@ -108,6 +108,46 @@ def test_gradients_off_the_16_byte_grid_take_the_generic_kernels(run, dtype, off
         assert generic[5] == 2 * W + 2 and generic[1:4] == [(n + (1 << 14) - 1) >> 14, 1024, 0]
 
 
+AGREEING_CHILD = """
+import ctypes, json, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+fake.fake_scarce(int(sys.argv[3]))
+u64, vp = ctypes.c_uint64, ctypes.c_void_p
+lib.thc_encode_all_workspace_bytes.restype = lib.thc_encode_all_minmax_workspace_bytes.restype = u64
+seen = []
+for W in (1, 2, 8, 16, 17, 32, 33, 48, 64):
+    at = (vp * W)(*[0x10000 * (w + 1) for w in range(W)])   # (addresses that only a launch would use)
+    for chunks in (1, 255 // W + 1, 512 // W, 512 // W + 1, 1024 // W, 1024 // W + 1, 6 * (1024 // W), 700):
+        for n in ((chunks << 14), (chunks << 14) - 3):
+            for dtype in (0, 1):
+                for bits in (2, 4, 8):
+                    need = lib.thc_encode_all_workspace_bytes(W, u64(n), 14)
+                    rc = lib.thc_encode_all(at, dtype, W, u64(n), 14, u64(1), bits, at, vp(0x1000), vp(0x2000), u64(need), None)
+                    seen.append(["one-pass", W, n, dtype, bits, rc, fake.fake_grid(), fake.fake_resident()])
+                    need = lib.thc_encode_all_minmax_workspace_bytes(W, u64(n), 14)
+                    for rotate in (0, 1):
+                        rc = lib.thc_encode_all_minmax(at, dtype, W, u64(n), 14, u64(1), bits, rotate, at, vp(0x1000),
+                                                       vp(0x2000), u64(need), None)
+                        seen.append([f"min/max {rotate}", W, n, dtype, bits, rc, fake.fake_grid(), fake.fake_resident()])
+print(json.dumps(seen))
+"""
+
+
+@pytest.mark.parametrize("scarce", [0, 2, 3])
+def test_workgroups_that_wait_for_one_another_are_resident_in_the_kernel_launched(run, scarce):
+    """A grid of them is at most what the device keeps of that very kernel, also where it keeps fewer of some
+    instantiations than of others, and whole chunks per round."""
+    res = subprocess.run([sys.executable, "-c", AGREEING_CHILD, run.fake, binding.LIB_PATH, str(scarce)],
+                         stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+    assert res.returncode == 0, res.stderr[-3000:]
+    seen = json.loads(res.stdout.splitlines()[-1])
+    for call in seen:
+        what, W, n, dtype, bits, rc, grid, resident = call
+        assert rc == 0, call
+        assert 0 < grid <= resident and grid % W == 0, call
+
+
 FULL_CHILD = """
 import ctypes, json, sys
 fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
