@@ -1,5 +1,5 @@
-"""The one-pass encoder's forms of agreement (a word per wave, per workgroup, one reader per workgroup, and the
-launch of at most one workgroup per CU), on both sides of the worker counts where they change, with one item
+"""The one-pass encoder's forms of agreement (a word per wave, per workgroup, one reader per workgroup, each also
+for launches of one item per workgroup), on both sides of the worker counts where they change, with one item
 per workgroup, a few and more than eight rounds: scales and payloads are those of the per-worker calls, and
 the workspace comes back clear."""
 import pytest
@@ -66,7 +66,9 @@ def test_streamed_fp32_gradients_match_the_per_worker_calls(W, chunks):
     (20, 3, torch.bfloat16, 4), (20, 10, torch.float32, 2),     # a word per workgroup, every wave reads
     (64, 3, torch.bfloat16, 4),                                 # the same beyond 32 workers
     (64, 3, torch.float32, 4), (64, 10, torch.bfloat16, 8),     # one reader, few rounds and the late pause
-    (2, 0, torch.bfloat16, 4), (8, 0, torch.float32, 8),        # one item per workgroup and CU
+    (2, 0, torch.bfloat16, 4), (8, 0, torch.float32, 8),        # one item per workgroup: a word per wave
+    (20, 0, torch.bfloat16, 4), (32, 0, torch.float32, 8),      # a word per workgroup
+    (33, 0, torch.float32, 2), (64, 0, torch.bfloat16, 4),      # one reader
 ])
 def test_expired_wait_of_every_form_of_agreement(W, rounds, dtype, bits):
     """Failure handling forced from the host: with a poll limit of zero a wait gives up after one read.  Every wave

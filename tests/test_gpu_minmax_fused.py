@@ -257,3 +257,27 @@ def test_one_pass_minmax_around_one_round_of_workgroups(W, chunks, dtype, bits):
     assert torch.equal(got["range"], ref["range"])
     assert all(torch.equal(got["payloads"][w], ref["payloads"][w]) for w in range(W))
     assert torch.equal(got["out"], ref["out"])
+
+
+@pytest.mark.parametrize("W,chunks,dtype", [(8, 3, torch.bfloat16), (8, 60, torch.float32), (17, 30, torch.bfloat16)])
+def test_expired_wait_in_one_round_leaves_a_workspace_that_can_be_cleared(W, chunks, dtype):
+    """The form of one item per workgroup with a poll limit of zero: the launch ends, whether or not a wait had to be
+    given up, and the same call on the same workspace is right again with the limit restored."""
+    bits, n = 4, (chunks << 14) - 4097
+    print(f"minmax one round, expired wait W={W} chunks={chunks} {dtype}", flush=True)
+    xs = [_rand(n, dtype, 5 * w + chunks, scale=1e-2, shift=1e-3) for w in range(W)]
+    pay = [torch.empty(thc.thc_payload_bytes(n, L14, bits), dtype=torch.uint8, device=DEV) for _ in range(W)]
+    rng = torch.empty(2 * thc.thc_num_chunks(n, L14), device=DEV)
+    ws = torch.empty(thc.thc_encode_all_minmax_workspace_bytes(W, n, L14), dtype=torch.uint8, device=DEV)
+    try:
+        thc.thc_set_spin_limit(0)
+        thc.thc_encode_all_minmax(xs, L14, 9, bits, True, pay, rng, ws)
+        torch.cuda.synchronize()            # returns: nothing hangs
+    finally:
+        thc.thc_set_spin_limit(1 << 22)
+    thc.thc_encode_all_minmax(xs, L14, 9, bits, True, pay, rng, ws)
+    torch.cuda.synchronize()
+    assert not thc.thc_encode_all_timed_out(ws)
+    ref = run_minmax(xs, L14, 9, bits, True, torch.float32)
+    assert torch.equal(rng.view(-1, 2), ref["range"])
+    assert all(torch.equal(pay[w], ref["payloads"][w]) for w in range(W))

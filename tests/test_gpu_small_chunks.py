@@ -159,7 +159,8 @@ def test_workers_spread_over_workgroups(l, W, bits, n, dtype):
 @pytest.mark.parametrize("l,W,n", [(8, 24, 900_001), (13, 64, 250_001)])
 def test_expired_wait_of_spread_workers(l, W, n):
     """Failure handling forced from the host: with a poll limit of zero a wait gives up after one read.  Every wave still
-    ends, and a cleared workspace is good again."""
+    ends, the error word is set (several rounds: a word takes longer from one workgroup to another than the pause in front
+    of that read), and a cleared workspace is good again."""
     print(f"expired wait l={l} W={W} n={n}", flush=True)
     xs = _grads(W, n, torch.bfloat16, l + W)
     ws = torch.zeros(thc.thc_encode_all_workspace_bytes(W, n, l), dtype=torch.uint8, device=DEV)
@@ -170,6 +171,7 @@ def test_expired_wait_of_spread_workers(l, W, n):
         torch.cuda.synchronize()
     finally:
         thc.thc_set_spin_limit(1 << 22)
+    assert thc.thc_encode_all_timed_out(ws)
     thc.thc_workspace_clear(ws)
     scale, pay = _one_pass(xs, l, 4, ws)
     torch.cuda.synchronize()

@@ -12,12 +12,16 @@ The model restates the protocol, it shares nothing with the kernels:
   one word per workgroup (more than 16 workers): wave 0 publishes behind the barrier and clears
   one reader (more than 32 workers): the same, and wave 0 alone polls; it hands the result to the other
                     waves through the cell in which it gathered the workgroup's own maximum
+  spread workers    (small chunks of more workers than a workgroup holds) one reader, and an item has several chunks: a
+                    word per workgroup and chunk, published, waited for and cleared together, fewer in the last item;
+                    the words that were read are handed over in a table of their own
   pipelined kernel  (unrotated bf16) no barriers: publish item k + 1, wait for item k,
                     clear the own word of item k - 2
   both              the workgroups of a chunk count themselves off for a workgroup's last
                     chunk(s); the last one clears all of the chunk's words and the counter
 and deliberately wrong variants (the pipelined kernel clearing item k - 1, the one reader without a barrier
-in front of the hand-over or in front of the cell's next use) must be caught.  With a bound on the polls of a
+in front of the hand-over or in front of the cell's next use, the spread workers without one of their two barriers,
+clearing the words of the current item, or as many of the last item as of the one before it) must be caught.  With a bound on the polls of a
 wait every wave still ends, and the waves of a workgroup go on with one and the same result.
 """
 import random
@@ -158,6 +162,60 @@ def one_reader_wave(world, bar, w, v, items, limit=None, handover_barrier=True, 
         yield from _count_off(world, prev)
 
 
+def spread_wave(world, bar, w, v, items, per_item=1, limit=None, gather_barrier=True, handover_barrier=True,
+                clear_current=False, clear_as_before=False):
+    """An item is per_item consecutive chunks, the last one what is left of them.  bar.cell: a place per wave for its
+    maximum; bar.got: the words that wave 0 has read."""
+    if not hasattr(bar, "cell"):
+        bar.cell, bar.got, bar.results = [0] * bar.parties, None, {}
+    prev = []
+    for c in items:
+        chunks = [p for p in range(c * per_item, (c + 1) * per_item) if p < len(world.done)]
+        yield "maximum"
+        bar.cell[v] = 100 + c
+        if gather_barrier:
+            yield from _barrier(bar)
+        if v == 0:
+            for p in chunks:
+                assert bar.cell == [100 + c] * bar.parties, "a maximum is missing or was overwritten"
+                yield "publish"
+                world.word[(p, w, 0)] = 100 + c
+            polls, done = 0, False
+            while not done and (limit is None or polls <= limit):
+                yield "poll"
+                words = []
+                for p in chunks:
+                    words += world.all_words(p)
+                    yield "read"                      # (the words are read one after the other)
+                done = all(x != 0 for x in words)
+                polls += 1
+            bar.got = (c, tuple(words))
+            if not done:
+                world.expired = True
+            else:
+                for p in chunks if clear_current else prev[:len(chunks)] if clear_as_before else prev:
+                    yield "clear"
+                    world.word[(p, w, 0)] = 0
+        if handover_barrier:
+            yield from _barrier(bar)
+        yield "take over"
+        assert bar.got is not None and bar.got[0] == c, "a wave took something else over"
+        assert bar.results.setdefault(c, bar.got) == bar.got
+        for k, p in enumerate(chunks):
+            world.seen[(w, v, p)] = [x - c + p if x else 0 for x in bar.got[1][k * world.W:(k + 1) * world.W]]
+        prev = chunks
+    if v == 0 and prev:
+        yield "atomic"
+        arrived = world.done[prev[0]]
+        world.done[prev[0]] += 1
+        if arrived == world.W - 1:
+            for p in prev:
+                for u in range(world.W):
+                    yield "clear"
+                    world.word[(p, u, 0)] = 0
+            world.done[prev[0]] = 0
+
+
 def pipelined_wave(world, bar, w, v, items, clear_lag=2):
     """No barrier between items: the range of item k + 1 is published before the wait for item k."""
     if not items:
@@ -178,14 +236,16 @@ def pipelined_wave(world, bar, w, v, items, clear_lag=2):
             yield from _count_off(world, c)
 
 
-def run(kind, W, V, groups, rounds, seed, words_per_workgroup=None, **kw):
-    """groups peer groups of W workgroups; group q handles chunks q, q + groups, ..."""
+def run(kind, W, V, groups, rounds, seed, words_per_workgroup=None, missing=0, **kw):
+    """groups peer groups of W workgroups; group q handles items q, q + groups, ...  An item is a chunk, or
+    per_item of them (missing: fewer in the last item)."""
     rng = random.Random(seed)
-    chunks = groups * rounds
+    items_in_all = groups * rounds
+    chunks = items_in_all * kw.get("per_item", 1) - missing
     world = World(W, V, chunks, words_per_workgroup)
     waves = []
     for q in range(groups):
-        items = list(range(q, chunks, groups))
+        items = list(range(q, items_in_all, groups))
         for w in range(W):
             bar = Barrier(V)
             for v in range(V):
@@ -200,7 +260,7 @@ def run(kind, W, V, groups, rounds, seed, words_per_workgroup=None, **kw):
             waves.pop(i)
             idle = 0
             continue
-        if step in ("poll", "barrier") and before == (world.word, world.done):
+        if step in ("poll", "read", "barrier") and before == (world.word, world.done):
             idle += 1
             if idle > 2000 * len(waves):
                 raise Hang(f"no progress: {len(waves)} waves stuck")
@@ -241,6 +301,33 @@ def test_one_reader_that_gives_up_ends_with_one_result_per_workgroup(W, V, group
     expired = sum(run(one_reader_wave, W, V, groups, rounds, seed, words_per_workgroup=1, limit=limit).expired
                   for seed in range(300))
     assert expired > 0
+
+
+@pytest.mark.parametrize("parts,V,groups,rounds,per_item,missing", [
+    (2, 2, 1, 1, 1, 0), (2, 2, 1, 4, 3, 2), (3, 2, 2, 3, 2, 1), (3, 1, 1, 5, 4, 0), (2, 3, 2, 2, 3, 1)])
+def test_spread_protocol_clears_itself_and_never_hangs(parts, V, groups, rounds, per_item, missing):
+    for seed in range(300):
+        assert not run(spread_wave, parts, V, groups, rounds, seed, words_per_workgroup=1, per_item=per_item,
+                       missing=missing).expired
+
+
+@pytest.mark.parametrize("limit", [0, 2])
+def test_spread_reader_that_gives_up_ends_with_one_result_per_workgroup(limit):
+    expired = sum(run(spread_wave, 2, 3, 1, 4, seed, words_per_workgroup=1, per_item=3, missing=1, limit=limit).expired
+                  for seed in range(300))
+    assert expired > 0
+
+
+@pytest.mark.parametrize("wrong", [dict(gather_barrier=False), dict(handover_barrier=False), dict(clear_current=True),
+                                   dict(clear_as_before=True)])
+def test_the_model_catches_a_wrong_spread_protocol(wrong):
+    def catches(seed):
+        try:
+            run(spread_wave, 2, 3, 1, 4, seed, words_per_workgroup=1, per_item=3, missing=2, **wrong)
+        except (Hang, AssertionError):
+            return True
+        return False
+    assert any(catches(seed) for seed in range(300))
 
 
 @pytest.mark.parametrize("without", ["handover_barrier", "rotation_barrier"])
