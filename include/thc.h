@@ -174,12 +174,19 @@ uint64_t thc_encode_all_workspace_bytes(uint32_t W, uint64_t n, uint32_t chunk_l
  *              aligned.  Its first 32-bit word is 0 after a good run and 1 if a bounded
  *              wait between workgroups expired (the payloads are then invalid); check it
  *              after synchronising the stream.
- * Calls that share a workspace must not overlap in time.  The workgroups of a chunk wait
- * for one another, so the launch is sized to be resident on the device all at once; other
- * kernels running at the same time only delay it (their workgroups finish and free their
- * place), but two thc_encode_all / thc_sat_encode_all calls must not run concurrently on
- * one device (issue them on one stream), and a device kept busy by other work for longer
- * than the spin limit makes the call report a time-out. */
+ * Calls that share a workspace must not overlap in time.  In some shapes the workgroups of a chunk wait
+ * for one another through the workspace:
+ *   - chunks of 2^14 with up to 64 workers;
+ *   - chunks of 2^5 .. 2^13 with more workers than one workgroup holds, up to 64: more than 16 workers for chunks
+ *     of up to 2^11, more than 8 for 2^12, more than 4 for 2^13;
+ * both with gradients and payloads on the 16-byte grid.  Such a launch is sized to be resident on the device
+ * all at once; other kernels running at the same time only delay it (their workgroups finish and free their
+ * place), but two calls of these shapes (thc_encode_all, thc_sat_encode_all and the _cleared, _batch, _static and
+ * _minmax forms) must not run concurrently on one device, whatever streams, threads or processes issue them and
+ * also with a workspace each: the workgroups that one waits for may then find no place beside the other's.  Issue
+ * them on one stream.  A device kept busy by other work for longer than the spin limit makes the
+ * call report a time-out as well.  All other shapes wait for nobody: they never report a time-out and,
+ * each with a workspace of its own, may run beside any other call. */
 int thc_encode_all(const void* const* grads, thc_dtype dt, uint32_t W, uint64_t n,
                    uint32_t chunk_log2, uint64_t seed, uint32_t bits, uint8_t* const* payloads,
                    float* scale, void* workspace, uint64_t workspace_bytes, void* stream);
@@ -192,7 +199,8 @@ int thc_encode_all(const void* const* grads, thc_dtype dt, uint32_t W, uint64_t 
  * every workgroup of the chunk has read them.  Same arguments, results and rules as
  * thc_encode_all otherwise.  Exception: after a time-out the first word is 1 (it is how
  * the time-out is reported) and other words may be left set; clear the workspace again
- * before the next call.  A workspace that is not
+ * before the next call.  In a shape whose workgroups wait for one another (see
+ * thc_encode_all: small chunks of many workers are among them) a workspace that is not
  * all zero gives wrong payloads without any error: when in doubt use thc_encode_all,
  * which clears what it uses itself and accepts a workspace in any state. */
 int thc_workspace_clear(void* workspace, uint64_t workspace_bytes, void* stream);
@@ -260,8 +268,8 @@ int thc_encode_all_static(const void* const* grads, thc_dtype dt, uint32_t W, ui
 /* Upper bound on the polls of one inter-workgroup wait inside thc_encode_all (default
  * 2^22, about seconds).  It counts polls, not time: a poll is a read of the chunk's range words
  * and a pause of 512 clocks, or of 256 with more than 32 workers, where one wave of a workgroup
- * polls for all.  Chunks below 2^14 wait only with more workers than one workgroup holds (16 up to 2^11, 8 at
- * 2^12, 4 at 2^13): 256 clocks, or 512 where a chunk has more than eight workgroups.  A tuning and test knob: with a tiny limit the waits expire, the
+ * polls for all.  Chunks below 2^14 (those that wait at all, see thc_encode_all): 256 clocks, or 512 where a
+ * chunk has more than eight workgroups.  A tuning and test knob: with a tiny limit the waits expire, the
  * error word is set and every wave still exits.  PROCESS-GLOBAL and not thread-safe: the
  * value is read when a call is enqueued, by every thread's calls; changing it while another
  * thread encodes makes that thread's waits expire early, which only the error word of its

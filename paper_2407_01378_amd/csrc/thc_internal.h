@@ -76,8 +76,8 @@ struct EncodeAllArgs {
     uint32_t levels;     // largest grid index L
     uint32_t crowded;    // set by the launch: its workgroups take more than three quarters of the places
     float* scale;        // out: chunks shared scales
-    uint32_t* slots;     // zero on entry and on exit: chunks x encode_all_slot_words(W) words
-    uint32_t* done;      // zero on entry and on exit: one arrival counter per chunk
+    uint32_t* slots;     // zero on entry and on exit: chunks x encode_all_slot_words(W) words (small chunks: see small_encode_parts)
+    uint32_t* done;      // zero on entry and on exit: one arrival counter per chunk (small chunks: not read)
     uint32_t* error;     // zeroed: set to 1 if a wait timed out
 };
 // ---- batched forms: several buckets in one launch ---------------------------------------
@@ -131,8 +131,11 @@ struct AggDecodeArgs {
 bool aggregate_decode_fused_applicable(uint32_t W, uint32_t chunk_log2, uint32_t bits);
 hipError_t launch_aggregate_decode_fused(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs,
                                          uint32_t bits, hipStream_t stream);
-// The same two steps for chunk_log2 = 5 .. 13 (thc_small.hip).  clear_error: the kernel also
-// zeroes the workspace's first four words.
+// The same two steps for chunk_log2 = 5 .. 13 (thc_small.hip).
+// Workgroups over which the workers of a chunk are spread.  One: the workspace is not used; clear_error: the kernel
+// also zeroes its first four words.  More: the first 4 + (parts + 1) x chunks words, which the kernel takes for
+// the error word, its range words (parts to a chunk) and a counter per chunk, have to be zero on entry and are zero on
+// exit; clear_error has no effect.
 uint32_t small_encode_parts(uint32_t W, uint32_t chunk_log2);
 bool small_encode_all_applicable(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2);
 hipError_t launch_small_encode_all(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2, float norm,
