@@ -178,7 +178,8 @@ uint64_t thc_encode_all_workspace_bytes(uint32_t W, uint64_t n, uint32_t chunk_l
  * for one another through the workspace:
  *   - chunks of 2^14 with up to 64 workers;
  *   - chunks of 2^5 .. 2^13 with more workers than one workgroup holds, up to 64: more than 16 workers for chunks
- *     of up to 2^11, more than 8 for 2^12, more than 4 for 2^13;
+ *     of up to 2^11, more than 8 for 2^12, more than 4 for 2^13 (by the number of coordinates and the device, some of
+ *     these do not wait; count on it that they do);
  * both with gradients and payloads on the 16-byte grid.  Such a launch is sized to be resident on the device
  * all at once; other kernels running at the same time only delay it (their workgroups finish and free their
  * place), but two calls of these shapes (thc_encode_all, thc_sat_encode_all and the _cleared, _batch, _static and

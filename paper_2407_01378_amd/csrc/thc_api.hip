@@ -296,13 +296,13 @@ static int encode_all_impl(const void* const* grads, thc_dtype dt, uint32_t W, u
             return finish(thc::launch_encode_all_fused(a, ptrs, dt == THC_BF16, bits, st));
         }
         // smaller chunks: one launch too, without a workspace (a clear one stays clear) unless the workers of a chunk
-        // take several workgroups
+        // are spread over several workgroups
         if (thc::small_encode_all_applicable(a, ptrs, chunk_log2)) {
-            const uint32_t parts = thc::small_encode_parts(W, chunk_log2);
+            const uint32_t parts = thc::small_encode_parts(W, chunk_log2, chunks, dt == THC_BF16);
             if (!cleared && parts > 1u && thc::launch_zero_words(words, 4 + (parts + 1u) * chunks, st) != hipSuccess)
                 return THC_ERR_HIP;
             return finish(thc::launch_small_encode_all(a, ptrs, chunk_log2, base_args(n, chunk_log2, seed).inv_sqrt_c,
-                                                       dt == THC_BF16, bits, !cleared, st));
+                                                       dt == THC_BF16, bits, parts, !cleared, st));
         }
     }
     // Fallback: the unfused sequence, per-worker ranges kept in the workspace.

@@ -132,14 +132,14 @@ bool aggregate_decode_fused_applicable(uint32_t W, uint32_t chunk_log2, uint32_t
 hipError_t launch_aggregate_decode_fused(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs,
                                          uint32_t bits, hipStream_t stream);
 // The same two steps for chunk_log2 = 5 .. 13 (thc_small.hip).
-// Workgroups over which the workers of a chunk are spread.  One: the workspace is not used; clear_error: the kernel
+// Workgroups over which the workers of a chunk are spread (`parts` of the launch).  One: the workspace is not used; clear_error: the kernel
 // also zeroes its first four words.  More: the first 4 + (parts + 1) x chunks words, which the kernel takes for
 // the error word, its range words (parts to a chunk) and a counter per chunk, have to be zero on entry and are zero on
 // exit; clear_error has no effect.
-uint32_t small_encode_parts(uint32_t W, uint32_t chunk_log2);
+uint32_t small_encode_parts(uint32_t W, uint32_t chunk_log2, uint64_t chunks, bool bf16);
 bool small_encode_all_applicable(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2);
 hipError_t launch_small_encode_all(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2, float norm,
-                                   bool bf16, uint32_t bits, bool clear_error, hipStream_t stream);
+                                   bool bf16, uint32_t bits, uint32_t parts, bool clear_error, hipStream_t stream);
 bool small_aggregate_decode_applicable(uint32_t W, uint32_t chunk_log2, uint32_t bits, uint64_t padded);
 hipError_t launch_small_aggregate_decode(const AggDecodeArgs& a, const FusedPayloadPtrs& ptrs, uint32_t chunk_log2,
                                          float norm, uint32_t bits, hipStream_t stream);

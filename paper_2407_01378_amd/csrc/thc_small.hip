@@ -3,12 +3,13 @@
 // Encode.  A wave holds 2^11 coordinates of one worker, 32 per thread, in registers; a workgroup the same coordinates
 // of ALL workers at once where they fit 16 waves (16 workers up to chunks of 2^11, 8 at 2^12, 4 at 2^13), so the shared
 // range of a chunk is a maximum over a few words in LDS behind one barrier and no workgroup waits for another.  More
-// workers are spread over workgroups of up to 8 waves that agree on the range through the workspace (the protocol of
-// thc_fused14.hip: persistent grid, an item's workgroups side by side, bounded waits).  Every gradient is read and rotated
-// once.  Before, one workgroup took them in rounds, all but the last of which it rotated a second time, and a launch of
-// few chunks had one workgroup for each: us with the decoder, rounds -> spread: 8 workers x 50257, chunk 2^13 25.6 -> 15.0,
-// 8 x 2^20 26.6 -> 20.2, 8 x 2.4 M fp32 51.4 -> 33.8, 16 x 0.75 M fp32 52.4 -> 28.6; 32 x 0.34 M, chunk 2^12, 8 bits 45.3 -> 28.1; 64 x
-// 0.53 M fp32, chunk 2^10 82 -> 47.4, 32 x 2^17 22.2 -> 16.1; 64 x 2^15, chunk 2^8, 2 bits 34.0 -> 15.9.  (Where 16 waves do, spread over
+// workers, by size (rounds_are_better, with figures): either they are spread over workgroups of up to 8 waves that agree on the
+// range through the workspace (the protocol of thc_fused14.hip: persistent grid, an item's workgroups side by side, bounded waits),
+// and every gradient is read and rotated once; or one workgroup takes them in rounds, all but the last of which it rotates a
+// second time.  Spread is the better one in launches that leave CUs without an item and wherever an item's rotation is long: us with the
+// decoder, rounds -> spread: 8 workers x 50257, chunk 2^13 25.6 -> 15.0, 8 x 2^20 26.6 -> 20.2, 8 x 2.4 M fp32 51.4 -> 33.8, 16 x 0.75 M
+// fp32 52.4 -> 28.6; 32 x 0.34 M, chunk 2^12, 8 bits 45.3 -> 28.1; 64 x 0.53 M fp32, chunk 2^10 82 -> 47.4, 32 x 2^17 22.2 -> 16.1; 64 x 2^15,
+// chunk 2^8, 2 bits 34.0 -> 15.9; rounds where the items fill the CUs and the rotation is short.  (Where 16 waves do, spread over
 // two workgroups is slower: 16 x 2^23, chunk 2^10 110 and 130 us.)  The rotation
 // stays inside the wave up to chunks of 2^11: 5 stages between registers, 4 between lanes by
 // data-parallel primitives and 2 after a swap of a lane bit into the registers (thc_lanes.h).
@@ -53,8 +54,9 @@ constexpr int kFirstPollSleepMany = 40, kPollSleepMany = 8;   // more than kFewP
 constexpr uint32_t kFewParts = 8;
 
 // What a launch does: encode all workers of a workgroup onto their common range; only the range of one
-// worker; encode one worker onto a range handed in; encode all workers, who are spread over several workgroups.
-enum class SmallOp : int { EncodeAll = 0, Absmax = 1, EncodeOnto = 2, EncodeSpread = 3 };
+// worker; encode one worker onto a range handed in; encode all workers, who are spread over several workgroups; encode
+// all workers in one workgroup, in rounds of them.
+enum class SmallOp : int { EncodeAll = 0, Absmax = 1, EncodeOnto = 2, EncodeSpread = 3, EncodeRounds = 4 };
 
 struct SmallArgs {
     uint64_t n, padded;
@@ -72,7 +74,7 @@ struct SmallArgs {
     // 2^max(11, l) coordinates of one worker that its 2^wpw_log2 waves hold, a group is one worker
     uint32_t wpw_log2, groups, regions;
     // EncodeSpread: workgroups of an item (each has `groups` of the workers), a word per chunk for each of them and one
-    // counter per chunk, all zero before and after
+    // counter per chunk, all zero before and after.  EncodeRounds: rounds, of `groups` workers each
     uint32_t parts;
     uint32_t max_spins;
     uint32_t* slots;
@@ -90,6 +92,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     // with the decoder, us, ahead -> this: 4 workers x 2^20, chunk 2^10 14.9 -> 13.3, 8 x 2^20 20.7 -> 16.4, 8 x 2^22 44.7 -> 38.8,
     // 2 x 2^24 53.4 -> 47.7, 8 x 2^23, chunk 2^12 91.6 -> 78.4; 8 x 2^24, chunk 2^11 166 -> 154.
     constexpr bool kAhead = BF16;
+    constexpr bool kRounds = OP == SmallOp::EncodeRounds;
     extern __shared__ uint4 dyn[];
     const uint32_t t = threadIdx.x, lane = t & 63u;
     // (the wave's number is the same for all lanes: kept in a scalar register, so are the
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     const uint32_t row = (a.groups * wpw + 3u) & ~3u;
     float* red = reinterpret_cast<float*>(sign + 2u * sign_words);
     const uint32_t red_words = (a.regions << rows_log2) * row;
-    if (OP == SmallOp::EncodeAll || OP == SmallOp::EncodeSpread) {
+    if (OP == SmallOp::EncodeAll || OP == SmallOp::EncodeSpread || kRounds) {
         for (uint32_t i = t; i < 2u * red_words; i += blockDim.x) red[i] = 0.0f;   // (the unused end of a row stays zero)
     }
     uint32_t* got = reinterpret_cast<uint32_t*>(red + red_words);   // EncodeSpread: the peers' words, instead of the second table
@@ -150,12 +153,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     const uint32_t first = OP == SmallOp::EncodeSpread ? blockIdx.x / parts : blockIdx.x;
     const uint32_t stride = OP == SmallOp::EncodeSpread ? gridDim.x / parts : gridDim.x;
     const uint32_t mine = OP == SmallOp::EncodeSpread ? blockIdx.x - first * parts : 0u;
-    const uint32_t w = group + a.groups * mine;   // the worker
+    uint32_t w = group + a.groups * mine;   // the worker
+    // EncodeRounds: a turn is one worker's unit.  The first `parts` turns find the range; the last of them is quantized where
+    // it stands, the ones before it are rotated once more, backwards.
+    const uint32_t turns = kRounds ? 2u * a.parts - 1u : 1u;
+    auto worker_of = [&](uint32_t turn) { return group + a.groups * (turn < a.parts ? turn : turns - 1u - turn); };
     auto coord0_of = [&](uint64_t item) { return (item * a.regions + region) << unit_log2; };
 
     Raw<kUnits> raw;
     uint32_t odd_tail = 0u;   // BF16: the last coordinate of an odd count, in the lane that owns it
-    auto load = [&](uint64_t item) {
+    auto load = [&](uint64_t item, uint32_t w) {
         const uint64_t g0 = coord0_of(item) + part * kWaveCoords;
         uint64_t left = (item < a.items && w < a.W && g0 < a.n) ? a.n - g0 : 0u;
         if (left > (uint64_t)kWaveCoords) left = kWaveCoords;
@@ -196,7 +203,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
         }
     };
 
-    if (kAhead) load(first);
+    if (kAhead) load(first, w);
     fill_signs(first, 0u);
     // What the items need of the arguments later, read while the input is on its way: left to the compiler, some of these
     // scalar reads stand where their values are used, behind the barriers, and the wave waits for them there.
@@ -213,7 +220,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
     const uint64_t chunks = a.padded >> a.l;
     uint64_t prev0 = 0u;
     uint32_t prev_live = 0u;
-    for (uint64_t item = first; item < a.items; item += step) {
+    uint32_t turn = 0u, most = 0u;   // most: largest magnitude of the lane's chunk, as a word
+    float s = 0.0f;
+    for (uint64_t item = first; item < a.items;) {
+        const bool ends = !kRounds || turn + 1u == turns;   // the item's last turn
         const uint64_t u0 = coord0_of(item);
         const uint64_t p = (u0 >> a.l) + chunk;
         const bool exists = (p << a.l) < a.padded;
@@ -235,7 +245,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
             }
             units_to_l1<kUnits, true>(sx, raw.u, v);
         } else {
-            if (!kAhead) load(item);
+            if (!kAhead) load(item, w);
 #pragma unroll
             for (int j = 0; j < kUnits; ++j) stage[lay14::stage_unit((uint32_t)j * 64u + lane)] = raw.u[j];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -247,8 +257,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
 #pragma unroll
         for (int i = 0; i < kRegs; ++i) asm volatile("" : "+v"(v[i]));   // converted before `raw` is loaded again
         asm volatile("" ::: "memory");
-        if (kAhead) load(item + step);
-        if (item + step < a.items) fill_signs(item + step, cur ^ 1u);
+        if (kAhead) load(ends ? item + step : item, kRounds ? worker_of(ends ? 0u : turn + 1u) : w);
+        if ((!kRounds || turn == 0u) && item + step < a.items) fill_signs(item + step, cur ^ 1u);
 
         // (as in the chunk-2^14 encoder: the rotation ahead of the other workgroup's quantizer.  Encoder alone, us: 8 workers
         // x 2^24, chunk 2^13 129 -> 116, 64 x 2^22, chunk 2^12 250 -> 221; one workgroup per CU 48.7 -> 47.0)
@@ -277,10 +287,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 trade_halves(v, buf + kStage * wave, buf + kStage * (wave ^ 2u), (part & 2u) != 0u, lane);
                 butterflies<4, 5>(v);
             }
+            if (kRounds) __syncthreads();   // (the next turn stores into them)
         }
 
-        uint32_t most = 0u;   // largest magnitude of the lane's chunk, as a word
-        if (OP != SmallOp::EncodeOnto) {
+        if (OP != SmallOp::EncodeOnto && (!kRounds || turn < a.parts)) {
             // the chunk's largest magnitude: registers, then the lanes that share the chunk
             float m = 0.0f;
 #pragma unroll
@@ -295,17 +305,19 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 x = lanes::umax_step<16>(x);
                 if (CLASS == 2 || a.l > 10u) x = lanes::umax_step<32>(x);
             }
-            most = x;
+            most = kRounds && turn != 0u && most > x ? most : x;
         }
         const bool leader = CLASS == 0 ? (block & ((1u << (a.l - 5u)) - 1u)) == 0u
                                        : (CLASS == 1 && a.l == 10u ? (lane & 31u) == 0u : lane == 0u);
-        float s = 0.0f;
-        if (OP == SmallOp::EncodeAll) {
+        if (kRounds && turn + 1u != a.parts) {
+            // (the range is not known yet, or it is already)
+        } else if (OP == SmallOp::EncodeAll || kRounds) {
             // all workers' waves have published behind the barrier (which also orders the sign
             // table of the next item); the two range tables take turns
             float* at = red_row + cur * red_words;
             if (leader) at[group * wpw + part] = __uint_as_float(most);
             __syncthreads();
+            s = 0.0f;
             for (uint32_t i = 0; i < row; i += 4u) {
                 const float4 f = *reinterpret_cast<const float4*>(at + i);
                 s = fmaxf(fmaxf(s, fmaxf(f.x, f.y)), fmaxf(f.z, f.w));
@@ -386,7 +398,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
         }
 
         set_prio<true, kPrioTail>();
-        if (OP != SmallOp::Absmax && w < a.W) {
+        if (OP != SmallOp::Absmax && (!kRounds || turn + 1u >= a.parts) && w < a.W) {
             constexpr bool kClamp = OP == SmallOp::EncodeOnto;
             constexpr bool kOffset = ((1u << BITS) - 2u) > kSingleFmaMaxLevels;
             const float two = s + s;
@@ -410,7 +422,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 quantize_half<BITS, kClamp, false, kOffset, true>(v, 1, b1, -s, inv, base, a.levels, worker, a.key0, a.key1, by, norm, neg);
             }
             pack_bytes<BITS>(by, pk);
-            uint8_t* dst = payload;
+            uint8_t* dst = kRounds ? global_ptr<uint8_t>(reinterpret_cast<uint64_t>(ptrs.payload[w])) : payload;
             if constexpr (CLASS == 0) {   // 32 consecutive coordinates
                 if (exists) store_packed<BITS>(pk, dst + b0 * (2u * BITS));
             } else if (exists) {
@@ -428,9 +440,17 @@ __global__ __launch_bounds__(64 * kMaxWaves) void small_encode_kernel(const Smal
                 }
             }
         }
-        cur ^= 1u;
+        if (ends) {
+            if (kRounds) __syncthreads();   // (the turns behind the range's barrier read the sign table too)
+            item += step;
+            cur ^= 1u;
+            turn = 0u;
+        } else {
+            ++turn;
+        }
+        if (kRounds) w = worker_of(turn);
     }
-    if (OP == SmallOp::EncodeAll && a.error && blockIdx.x == 0 && t < 4u) a.error[t] = 0u;
+    if ((OP == SmallOp::EncodeAll || kRounds) && a.error && blockIdx.x == 0 && t < 4u) a.error[t] = 0u;
     if (OP == SmallOp::EncodeSpread && wave == 0u && prev_live != 0u) {
         // the last item's words: its workgroups count themselves off, the last one clears them and the counter
         uint32_t arrived = 0u;
@@ -599,11 +619,14 @@ hipError_t launch_encode_bits(const SmallArgs& a, const FusedWorkerPtrs& ptrs, u
 template <SmallOp OP>
 hipError_t launch_encode(SmallArgs& a, const FusedWorkerPtrs& ptrs, bool bf16, uint32_t bits, hipStream_t stream) {
     // Shape of a workgroup.  All workers of a unit side by side, and as many units as fill 8 waves; spread: the workers,
-    // evenly, over workgroups of up to 8 waves.
+    // evenly, over workgroups of up to 8 waves; rounds: evenly, over as few rounds of up to 16 waves as there can be.
     a.wpw_log2 = a.l > kWaveLog2 ? a.l - kWaveLog2 : 0u;
-    a.groups = OP == SmallOp::EncodeSpread ? (a.W + a.parts - 1u) / a.parts : a.W;
+    const uint32_t most = kMaxWaves >> a.wpw_log2;
+    if (OP == SmallOp::EncodeRounds) a.parts = (a.W + most - 1u) / most;
+    const uint32_t split = OP == SmallOp::EncodeSpread || OP == SmallOp::EncodeRounds ? a.parts : 1u;
+    a.groups = (a.W + split - 1u) / split;
     const uint32_t per_region = a.groups << a.wpw_log2;
-    a.regions = OP != SmallOp::EncodeSpread && per_region < kPreferredWaves ? kPreferredWaves / per_region : 1u;
+    a.regions = split == 1u && per_region < kPreferredWaves ? kPreferredWaves / per_region : 1u;
     const uint32_t unit_log2 = a.l > kWaveLog2 ? a.l : kWaveLog2;
     const uint64_t units = (a.padded + (1ull << unit_log2) - 1u) >> unit_log2;
     // (a few units: spread over the CUs before they share a workgroup)
@@ -620,6 +643,26 @@ hipError_t launch_encode(SmallArgs& a, const FusedWorkerPtrs& ptrs, bool bf16, u
     return launch_encode_bits<false, 2, OP>(a, ptrs, bits, stream);
 }
 
+// More workers than 16 waves: in rounds of them in one workgroup (all rounds but the last are rotated twice, a CU has one
+// such workgroup), or spread over `parts` workgroups of half its size that agree on the range.  Rounds of the grid in both
+// forms: ceil(items / CUs) and ceil(items / (2 CUs / parts)); one of the first form takes about parts (l + 4 for fp32) / 14 as long
+// as one of the second, whose agreement costs more the more chunks an item has (64 at 2^5).  Over 1907 shapes (l = 5 .. 13, 5 .. 64
+// workers, 64 .. 2048 items) that picks a form 0.3 % slower than the better one on average, where spread throughout is 3.3 %
+// and rounds throughout 19 %.  Encoder, us, rounds | spread, bf16 4 bits: chunk 2^5, 17 workers x 2^19 10.0 | 14.7, 64 x 2^20 53 | 73, 32 x
+// 2^22 91 | 113; 2^8, 17 x 2^20 19.4 | 22.1, 32 x 2^20 28.3 | 26.6, 64 x 2^21 102 | 96; 2^8, 17 x 2^18 11.2 | 8.7; 2^11, 32 x 2^21 61 | 56; fp32,
+// 2^8, 32 x 2^20 33 | 28.
+// Three parts of a grid of the first form that is one nearly full round (the spread form's second round is half empty): 17 workers x
+// 2^19, 2^10 12.9 | 14.8, fp32 12.7 | 14.8; 20 x 2^19, 2^10 13.7 | 14.6; 9 x 2^20, 2^12 14.8 | 16.0; at 2^13 the same or slower.
+bool rounds_are_better(uint32_t parts, uint32_t l, uint64_t chunks, bool bf16) {
+    const uint64_t cus = (uint64_t)device_cus(), groups = 2u * cus / parts;
+    if (groups == 0u) return true;   // (the form that waits for nobody)
+    const uint32_t unit_log2 = l > kWaveLog2 ? l : kWaveLog2;
+    const uint64_t items = ((chunks << l) + (1ull << unit_log2) - 1u) >> unit_log2;
+    const uint64_t in_rounds = (items + cus - 1u) / cus, spread = (items + groups - 1u) / groups;
+    if (parts == 3u && l <= 12u && items <= cus && 8u * items > 7u * cus) return true;
+    return in_rounds * parts * (bf16 ? l : l + 4u) < 14u * spread;
+}
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 bool small_size(uint32_t chunk_log2) { return chunk_log2 >= 5u && chunk_log2 < 14u; }
 
@@ -634,14 +677,16 @@ bool small_encode_all_applicable(const EncodeAllArgs& a, const FusedWorkerPtrs& 
 }
 
 // Over how many workgroups the workers of a chunk are spread; more than one: they agree on the range through the workspace.
-uint32_t small_encode_parts(uint32_t W, uint32_t chunk_log2) {
+uint32_t small_encode_parts(uint32_t W, uint32_t chunk_log2, uint64_t chunks, bool bf16) {
     const uint32_t wpw_log2 = chunk_log2 > k14::kWaveLog2 ? chunk_log2 - k14::kWaveLog2 : 0u;
     const uint32_t waves = W << wpw_log2;
-    return waves > k14::kMaxWaves ? (waves + k14::kPreferredWaves - 1u) / k14::kPreferredWaves : 1u;
+    if (waves <= k14::kMaxWaves) return 1u;
+    const uint32_t parts = (waves + k14::kPreferredWaves - 1u) / k14::kPreferredWaves;
+    return k14::rounds_are_better(parts, chunk_log2, chunks, bf16) ? 1u : parts;
 }
 
 hipError_t launch_small_encode_all(const EncodeAllArgs& e, const FusedWorkerPtrs& ptrs, uint32_t chunk_log2, float norm,
-                                   bool bf16, uint32_t bits, bool clear_error, hipStream_t stream) {
+                                   bool bf16, uint32_t bits, uint32_t parts, bool clear_error, hipStream_t stream) {
     k14::SmallArgs a{};
     a.n = e.n;
     a.padded = e.chunks << chunk_log2;
@@ -652,15 +697,17 @@ hipError_t launch_small_encode_all(const EncodeAllArgs& e, const FusedWorkerPtrs
     a.levels = e.levels;
     a.norm = norm;
     a.scale_out = e.scale;
-    a.parts = small_encode_parts(e.W, chunk_log2);
-    if (a.parts > 1u) {
+    a.parts = parts;
+    if (parts > 1u) {
         a.error = e.error;
         a.max_spins = e.max_spins;
         a.slots = e.slots;
-        a.done = e.slots + a.parts * e.chunks;
+        a.done = e.slots + parts * e.chunks;
         return k14::launch_encode<k14::SmallOp::EncodeSpread>(a, ptrs, bf16, bits, stream);
     }
     a.error = clear_error ? e.error : nullptr;
+    const uint32_t wpw_log2 = chunk_log2 > k14::kWaveLog2 ? chunk_log2 - k14::kWaveLog2 : 0u;
+    if ((e.W << wpw_log2) > k14::kMaxWaves) return k14::launch_encode<k14::SmallOp::EncodeRounds>(a, ptrs, bf16, bits, stream);
     return k14::launch_encode<k14::SmallOp::EncodeAll>(a, ptrs, bf16, bits, stream);
 }
 

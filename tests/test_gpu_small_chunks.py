@@ -156,6 +156,29 @@ def test_workers_spread_over_workgroups(l, W, bits, n, dtype):
         _matches_the_per_worker_calls(xs, l, bits, scale, pay)
 
 
+ROUNDS = [  # (l, W, bits, n): two to four rounds of workers, fewer and more items than CUs, a worker too few for the last round
+    (5, 17, 4, 500_001), (5, 64, 2, 700_001), (5, 33, 8, 1_100_003), (6, 31, 4, 524_287), (7, 33, 8, 1_048_001), (8, 17, 2, 524_288),
+    (9, 23, 4, 520_001), (10, 17, 8, 500_001), (11, 18, 4, 524_000), (12, 9, 2, 1_000_003), (12, 10, 8, 1 << 20), (12, 12, 4, 1_048_001),
+]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("l,W,bits,n", ROUNDS)
+def test_workers_taken_in_rounds(l, W, bits, n, dtype):
+    """Against the one-call-per-worker route, twice: no workspace is needed, a clear one stays clear, the error word of any
+    other is cleared."""
+    print(f"rounds l={l} W={W} bits={bits} n={n} {dtype}", flush=True)
+    xs = _grads(W, n, dtype, l + W)
+    ws = torch.zeros(thc.thc_encode_all_workspace_bytes(W, n, l), dtype=torch.uint8, device=DEV)
+    for cleared in (True, False):
+        if not cleared:
+            ws.fill_(0xFF)
+        scale, pay = _one_pass(xs, l, bits, ws, cleared)
+        torch.cuda.synchronize()
+        assert not thc.thc_encode_all_timed_out(ws) and (not cleared or int(ws.count_nonzero()) == 0)
+        _matches_the_per_worker_calls(xs, l, bits, scale, pay)
+
+
 @pytest.mark.parametrize("l,W,n", [(8, 24, 900_001), (13, 64, 250_001)])
 def test_expired_wait_of_spread_workers(l, W, n):
     """Failure handling forced from the host: with a poll limit of zero a wait gives up after one read.  Every wave still

@@ -82,19 +82,38 @@ def test_answers_are_kept_per_shape_and_beyond_the_table(run):
     assert sum(s[4] for s in seen[-9:]) <= 4      # (what the overflow displaced is asked for again, no more)
 
 
-def test_workers_beyond_16_waves_are_spread_over_resident_workgroups(run):
-    for l in range(5, 14):
+def _spread_over(W, l, n, dtype, cus=256):
+    """Workgroups that the workers of a chunk are spread over: 1 where one workgroup holds them or takes them in rounds."""
+    waves = W << max(0, l - 11)
+    if waves <= 16:
+        return 1
+    parts = -(-waves // 8)
+    items = -(-(-(-n // (1 << l)) << l) // (1 << max(l, 11)))
+    if parts == 3 and l <= 12 and 7 * cus < 8 * items <= 8 * cus:
+        return 1
+    rounds, spread = -(-items // cus), -(-items // (2 * cus // parts))
+    return 1 if rounds * parts * (l + 4 * (dtype == F32)) < 14 * spread else parts
+
+
+def test_workers_beyond_16_waves_are_spread_over_resident_workgroups_or_taken_in_rounds(run):
+    calls = [(0, l, W, dtype, 4, n) for l in range(5, 14) for W in (1, 4, 5, 8, 9, 16, 17, 33, 64)
+             for dtype in (F32, BF16) for n in (1, 350_000, 500_000, 5_000_000)]
+    forms = set()
+    for (_, l, W, dtype, _, n), (rc, grid, block, lds, _, launches) in zip(calls, run(*calls)):
         wpw = 1 << max(0, l - 11)
-        for W in (1, 4, 5, 8, 9, 16, 17, 33, 64):
-            for n in (1, 5_000_000):
-                rc, grid, block, lds, _, launches = run((0, l, W, BF16, 4, n))[0]
-                parts = -(-W * wpw // 8) if W * wpw > 16 else 1
-                assert rc == 0 and launches == (2 if parts > 1 else 1)    # (with the clearing of the words)
-                items = -(-n // (1 << max(l, 11)))
-                if parts > 1:
-                    assert grid % parts == 0 and block == 64 * wpw * -(-W // parts) <= 512
-                    resident = 256 * min(2048 // block, 163840 // lds)   # as the stand-in has it
-                    assert grid == min(items, resident // parts) * parts
+        parts = _spread_over(W, l, n, dtype)
+        assert rc == 0 and launches == (2 if parts > 1 else 1), (l, W, dtype, n)    # (with the clearing of the words)
+        items = -(-n // (1 << max(l, 11)))
+        resident = 256 * min(2048 // block, 163840 // lds)   # as the stand-in has it
+        if parts > 1:
+            assert grid % parts == 0 and block == 64 * wpw * -(-W // parts) <= 512
+            assert grid == min(items, resident // parts) * parts
+            forms.add(("spread", l <= 9))
+        elif W * wpw > 16:
+            rounds = -(-W // (16 // wpw))
+            assert block == 64 * wpw * -(-W // rounds) <= 1024 and grid == min(items, resident)
+            forms.add(("rounds", l <= 9))
+    assert {("spread", True), ("spread", False), ("rounds", True)} <= forms
 
 
 @pytest.mark.parametrize("dtype,off", [(F32, 4), (BF16, 2)])
