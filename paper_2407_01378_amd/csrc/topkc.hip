@@ -622,23 +622,31 @@ constexpr int kTileChunks = kScatterThreads;
 // Workgroups wanted, where the output has that many pieces of one 16-byte unit per thread: 2^20 coordinates, C = 64, as 64
 // tiles 10.9 us of kernel, as 1024 pieces 4 (512 and 2048 pieces: the round 2 % slower for 2^17 .. 2^19 coordinates, the
 // same above).
+// The search by one wave, 64 entries at a time: with all 256 threads every workgroup read up to 1024 scattered entries, which
+// costs launches of many small workgroups more than one round of reads fewer gains them; 8 coordinates to a chunk, halving by one
+// thread | 256 | 64, us: 20 M outputs, a tenth selected 22.2 | 25.1 | 18.7, 7.1 M 11.0 | 12.0 | 9.7; all four waves, 64 each 21.0.
 constexpr uint64_t kScatterGroups = 1024;
 __global__ __launch_bounds__(kScatterThreads) void scatter_dense_kernel(
     const uint16_t* values, const uint32_t* indices, uint32_t J, uint32_t C, uint32_t W, uint64_t n, uint64_t P,
     uint64_t chunks_per_group, float* out) {
     __shared__ uint32_t rank[kTileChunks];
+    __shared__ uint32_t first;
     const uint32_t t = threadIdx.x;
     const uint64_t begin = (uint64_t)blockIdx.x * chunks_per_group;
     if (begin >= P) return;
     const uint64_t end = begin + chunks_per_group < P ? begin + chunks_per_group : P;
-    SearchRange r = {0u, J};   // -> the first j with indices[j] >= begin
-    while (r.lo < r.hi) {
-        const uint32_t step = r.step(kScatterThreads);
-        const uint64_t at = r.at(t, step);
-        const bool below = at < r.hi && (uint64_t)indices[at] < begin;
-        r.cut((uint32_t)__syncthreads_count(below), step);
+    if (t < 64u) {   // the first wave searches for the first j with indices[j] >= begin
+        SearchRange r = {0u, J};
+        while (r.lo < r.hi) {
+            const uint32_t step = r.step(64u);
+            const uint64_t at = r.at(t, step);
+            const bool below = at < r.hi && (uint64_t)indices[at] < begin;
+            r.cut((uint32_t)__popcll(__ballot(below)), step);
+        }
+        if (t == 0u) first = r.lo;
     }
-    uint32_t j = r.lo;
+    __syncthreads();
+    uint32_t j = first;
     const float Wf = (float)W;
     const uint32_t units_per_chunk = C / 4u;            // 16-byte units of fp32 output per chunk
     const uint32_t shift = 31u - (uint32_t)__builtin_clz(units_per_chunk);

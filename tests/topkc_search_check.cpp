@@ -24,7 +24,7 @@ static void search(uint32_t J, uint64_t stride, uint64_t bound, uint32_t probes)
     }
     const uint64_t first = (bound + stride - 1) / stride;
     const uint64_t want = first < J ? first : J;
-    if (r.lo != want || r.lo != r.hi || rounds > 5) {
+    if (r.lo != want || r.lo != r.hi || rounds > 7) {
         if (bad < 20) printf("J %u stride %llu bound %llu: found %u, is %llu, %d rounds\n", J, (unsigned long long)stride,
                              (unsigned long long)bound, r.lo, (unsigned long long)want, rounds);
         ++bad;
@@ -38,7 +38,7 @@ int main() {
         for (uint64_t stride : {1ull, 3ull})
             for (uint64_t part = 0; part <= 64; ++part)
                 for (uint64_t off : {0ull, 1ull, 2ull, 300ull})
-                    search(J, stride, (J * stride / 64) * part + off, 256u);
+                    for (uint32_t probes : {64u, 256u}) search(J, stride, (J * stride / 64) * part + off, probes);
     for (uint32_t place : {0u, 1u, 0x7FFFFFFFu, 0x80000000u, 0xFFFFFFFEu})   // every place that a list has
         if (!thc::is_selected(place)) ++bad;
     if (thc::is_selected(thc::kNotSelected)) ++bad;
