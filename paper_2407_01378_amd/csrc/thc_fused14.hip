@@ -99,8 +99,9 @@ struct BucketView {
 // would read 2 KB per poll, and that traffic delays the words it waits for.  At W = 8 the
 // later publication costs more than the lighter polls save, so the per-wave form stays.
 // ONE: a launch of one item per workgroup.  There is no next item to load for, and the rounding bytes are drawn while
-// the input is on its way.  With the decoder, us: 8 workers x 50257 13.5 -> 13.15, 8 x 50 chunks 17.5 -> 16.4, fp32 19.7 -> 18.1, 16 x 23
-// chunks at 8 bits 25.5 -> 20.8, 2 x 200 17.2 -> 16.2, 32 x 9 at 8 bits 23.6 -> 23.0, 64 x 8 26.5 -> 26.0.
+// the input is on its way.  With the decoder and the pauses above, us: 8 workers x 50257 14.2 -> 13.0, 8 x 50 chunks 18.1 -> 17.3, fp32
+// 19.4 -> 17.2, 16 x 23 chunks at 8 bits 26.2 -> 20.9, 2 x 200 17.5 -> 16.5, 20 x 20 19.6 -> 18.9, 32 x 9 at 8 bits 23.6 -> 22.9, 48 x 8 at 8
+// bits 27.6 -> 26.8, 64 x 8 26.5 -> 25.9.
 template <bool BF16, bool ODD, bool BATCH, bool MINMAX = false, Words WORDS = Words::PerWave, bool ONE = false>
 struct EncodeAllCtx {
     static constexpr bool WGWORD = WORDS == Words::PerGroup || WORDS == Words::OneReader;
@@ -1138,6 +1139,9 @@ hipError_t launch_encode_all_fused(const EncodeAllArgs& a, const FusedWorkerPtrs
 // The min/max grid through the same kernel: a.scale receives (lo, hi) pairs and a.slots has
 // twice the words per chunk.  Launches of one round take the form without a next item here too (with the decoder and the
 // clearing launch, us: 8 workers x 100000 16.7 -> 14.8, 8 x 2^20 23.7 -> 22.3, 16 x 0.5 M fp32 30.2 -> 26.0, 32 x 2^18 33.8 -> 30.9).
+// Its pauses, 8 | 24, with the decoder: 8 workers x 40 chunks bf16 19.8 | 19.4, fp32 19.6 | 20.5, x 50 21.2 | 20.0, 20.7 | 20.9, x 64 23.0 | 20.4,
+// 23.9 | 21.8; 16 x 24 fp32 24.0 | 25.0, x 28 25.5 | 26.2, x 32 29.5 | 26.3: the line of the symmetric grid serves.  (By itself, with no
+// decoder between, the fp32 encoder of a full launch takes 16.7 us with the longer pause and 14.5 with the shorter one, 8 x 64.)
 hipError_t launch_encode_all_ranged(const EncodeAllArgs& a, const FusedWorkerPtrs& ptrs, bool bf16,
                                     uint32_t bits, hipStream_t stream) {
     using namespace k14;

@@ -14,11 +14,11 @@
 // stays inside the wave up to chunks of 2^11: 5 stages between registers, 4 between lanes by
 // data-parallel primitives and 2 after a swap of a lane bit into the registers (thc_lanes.h).
 // Chunks of 2^12 and 2^13 span two and four waves, which trade half of their registers through LDS
-// before each further stage.  Bound by vector-ALU issue while its rounds are full (8 workers, chunk 2^12, 8 bits: 27.8
+// before each further stage.  Bound by vector-ALU issue while its rounds are full (8 workers, chunk 2^12, 8 bits: 27.3
 // operations per worker-coordinate by the counters; one workgroup of 16 waves per CU, a round of 256 items 6 us:
-// 1280 items 38.8 us, 1536 42.8, of which the operations are 35.6); a last round that is nearly empty takes as long as
+// 1280 items 38.8 us, 1536 42.8, of which the operations are 35.0); a last round that is nearly empty takes as long as
 // a full one (1600 items 48.2 us, 1792 48.7; with wave priorities 1600 47.0), and a launch of one item per workgroup is the item's own chain of loads,
-// stages and barriers (4 workers x 2^20 fp32, chunk 2^10: 6.4 us, and 5.7 of the decoder).
+// stages and barriers (4 workers x 2^20 fp32, chunk 2^10: 6.5 us, and 5.9 of the decoder, in a loop of each and in a trace).
 //   Measured, encode + aggregate + decode: 8 workers x 6.5 M bf16, chunk 2^12, 8 bits: 762 -> 67 us
 //   (3.7 TB/s); 4 workers x 1 M fp32, chunk 2^10: 178 -> 12.8 us.  Before: one range and one encode
 //   launch per worker of the generic kernels, which load element by element and take a
